@@ -246,3 +246,39 @@ def tolerance(case):
     if _out_dtype(case) == "bf16":
         return {"rel": 7e-3}
     return {"rel": 4e-6}
+
+
+# ------------------------------------------------------------------ the same results in 64 bits
+def exact(case, seed):
+    """What `run` returns, as plain torch gives it in 64 bits: one product or one elementwise pass per filter tap.  The sums of
+    the int8 cases stay below 2^53, so they are exact too."""
+    c = case
+    ins = [t.double() for t in _inputs(c, seed)]
+    if c["kind"] == "matmul":
+        a = ins[0].t().contiguous() if c["layout"] == "tn" else ins[0]
+        b = ins[1].t().contiguous() if c["layout"] == "nt" else ins[1]
+        y = a @ b
+        return torch.relu(y + ins[2]) if c["fused"] else y
+    N, H, R, Ho = c["N"], c["H"], c["R"], _out(c)
+    x = ins[0]
+    if c["kind"] == "upconv":
+        y = x.new_zeros((N, Ho, Ho, c["Co"]))
+        for i in range(R):
+            for j in range(R):
+                y[:, i:i + 2 * H - 1:2, j:j + 2 * H - 1:2] += x @ ins[1][i, j]
+        return y
+    p, s = _pad(c), c["stride"]
+    lowest = c["kind"] == "window" and c["op"] == "max"
+    x = torch.nn.functional.pad(x, (0, 0, p, p, p, p), value=float("-inf") if lowest else 0.0)
+    y = None
+    for i in range(R):
+        for j in range(R):
+            v = x[:, i:i + s * (Ho - 1) + 1:s, j:j + s * (Ho - 1) + 1:s]
+            if c["kind"] == "conv":
+                v = v.contiguous() @ ins[1][i, j].t().contiguous()
+            elif c["op"] == "depthwise":
+                v = v * ins[1][i, j]
+            elif c["op"] == "avg":
+                v = v * ins[1]
+            y = v if y is None else torch.maximum(y, v) if lowest else y + v
+    return torch.relu(y + ins[2]) if c.get("fused") else y
