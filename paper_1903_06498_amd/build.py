@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libstripe_hip.so")
-SOURCES = ["api.cpp", "plan.cpp", "tiling.cpp", "generic.hip", "generic_tiled.hip", "pool.hip", "gemm.hip", "conv.hip", "conv_i8.hip", "conv_igemm.hip"]
+SOURCES = ["api.cpp", "plan.cpp", "tiling.cpp", "generic.hip", "generic_tiled.hip", "contract.hip:4", "contract.hip:2", "contract.hip:1", "pool.hip", "gemm.hip", "conv.hip", "conv_i8.hip", "conv_igemm.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
          # the LDS-direct load helpers name M0 in their clobber lists on purpose (see their comments); the compiler
@@ -31,8 +31,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
     procs = []
     os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
     for src in SOURCES:
-        obj = os.path.join(HERE, "_build", src + ".o")
-        cmd = ["hipcc"] + [f for f in FLAGS if f != "-shared"] + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+        # "file:n": the file compiled with CONTRACT_T = n (element size of the kernels in that object)
+        src, _, elem = src.partition(":")
+        obj = os.path.join(HERE, "_build", src + elem + ".o")
+        cmd = ["hipcc"] + [f for f in FLAGS if f != "-shared"] + ([f"-DCONTRACT_T={elem}"] if elem else []) + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd))
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))

@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "contract.hpp"
 #include "kernels.hpp"
 #include "plan.hpp"
 
@@ -29,6 +30,7 @@ struct stripe_block {
   GemmLaunch gemm;
   ConvLaunch conv;
   PoolLaunch pool;
+  ContractLaunch contract;   // blocks of the generic path that the general matrix-core contraction takes
   int n_inputs = 0;
   // statement lists (empty for a single block): stages in order, and per root refinement either the caller's
   // input number, or the size of a temporary the handle owns (allocated on the first run, per device)
@@ -46,7 +48,7 @@ struct stripe_block {
   void* owned_ws = nullptr;
   int owned_ws_dev = -1;
   // 1, 2: the two statements run as one convolution kernel with a bias+relu epilogue (fp32 / bf16 output);
-  // 3, 4: the same with the dense-contraction kernel
+  // 3, 4: the same with the dense-contraction kernel; 5, 6: with the general matrix-core contraction
   int fused = 0;
   int64_t fuse_bias_off = 0, fuse_o_m = 0, fuse_o_base = 0;
   ~stripe_block() {
@@ -296,6 +298,43 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
       }
     }
   }
+  // And for the general matrix-core contraction: the second statement reads T and writes O through one map, over the
+  // product's output and nothing else, with a bias along the product's single column index.
+  if (!prog->fused && prog->stages.size() == 2 && tune_int("fuse", 1)) {
+    const Stage &s0 = prog->stages[0], &s1 = prog->stages[1];
+    const Plan& c = s0.blk->plan;
+    const ContractLaunch& ct = s0.blk->contract;
+    const FlatBlock& e = s1.blk->plan.flat;
+    bool ok = c.info.path == STRIPE_PATH_GENERIC && ct.use && c.in_dtype == STRIPE_BF16 && ct.p.epilogue == 0 && !ct.p.n_ob_used && ct.batch == 1 &&
+              ct.p.n.n == 1 && ct.p.n_out[0] == 1 && root->refs[s0.dst].dir == STRIPE_TEMP && s1.n_in == 2 && s1.src[0] == s0.dst && !e.empty &&
+              e.intrinsic == STRIPE_INTR_ADD_RELU && e.cons.empty() && e.n_refs == 3 && e.n_idx >= 2 && e.ref[0].dtype == STRIPE_F32 &&
+              e.ref[1].dtype == STRIPE_F32;
+    if (ok) {
+      std::vector<int64_t> rng, ct_, cbias, co;
+      address_form(e, 2, &rng, &ct_, &cbias, &co);
+      ok = rng.size() == 2 && ct_ == co && e.ref[0].addr.k == e.ref[2].addr.k && e.ref[0].addr.k == ct.p.o_base;
+      if (ok) {
+        const int n = (cbias[0] == 1 && ct_[0] == 1) ? 0 : 1, m = 1 - n;
+        ok = rng[n] == (int64_t)ct.p.N && rng[m] == (int64_t)ct.p.M && ct_[n] == 1 && cbias[n] == 1 && cbias[m] == 0 && ct_[m] >= (int64_t)ct.p.N;
+        // the rows of the product are the same addresses: evenly spaced by ct_[m] from innermost to outermost
+        std::vector<std::pair<int64_t, int64_t>> rows;
+        for (int j = 0; j < ct.p.m.n; ++j) rows.push_back({ct.p.m_out[j], (int64_t)ct.p.m.range[j]});
+        std::sort(rows.begin(), rows.end());
+        int64_t next = ct_[m];
+        for (const auto& r : rows) {
+          ok = ok && r.first == next;
+          next *= r.second;
+        }
+      }
+      if (ok) {
+        prog->fused = e.out_bf16 ? 6 : 5;
+        prog->contract = ct;
+        prog->plan.in_dtype = c.in_dtype;
+        prog->fuse_bias_off = e.ref[1].addr.k;
+        prog->temp_bytes[s0.dst] = 0;
+      }
+    }
+  }
   // what the program as a whole looks like from outside
   stripe_block_info_t& info = prog->plan.info;
   info = prog->stages[0].blk->plan.info;
@@ -315,7 +354,7 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
       for (int d = 0; d < root->refs[r].ndim; ++d) n *= root->refs[r].sizes[d];
       info.algorithmic_bytes += n * (root->refs[r].dtype == STRIPE_I8 ? 1 : root->refs[r].dtype == STRIPE_BF16 ? 2 : 4);
     }
-  if (prog->fused) names = std::string(prog->stages[0].blk->plan.info.kernel) + (prog->fused == 2 ? "+bias_relu_bf16" : "+bias_relu");
+  if (prog->fused) names = std::string(prog->stages[0].blk->plan.info.kernel) + (prog->fused == 2 || prog->fused == 6 ? "+bias_relu_bf16" : "+bias_relu");
   std::snprintf(info.kernel, sizeof info.kernel, "%s", names.c_str());
   // workspace layout: temporaries that were not scalarised away, then what each stage's own launches need
   prog->temp_off.assign(R, 0);
@@ -398,6 +437,12 @@ stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void*
   if (prog->fused) {
     const Stage &s0 = prog->stages[0], &s1 = prog->stages[1];
     const float* bias = (const float*)inputs[prog->input_slot[s1.src[1]]] + prog->fuse_bias_off;
+    if (prog->fused >= 5) {
+      e = launch_contract(prog->contract, prog->plan.in_dtype, inputs[prog->input_slot[s0.src[0]]], inputs[prog->input_slot[s0.src[1]]], output, bias,
+                          prog->fused == 6, (hipStream_t)hip_stream);
+      if (e != hipSuccess) return fail(STRIPE_ERR_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
+      return STRIPE_OK;
+    }
     const bool conv = prog->fused < 3, out_bf16 = prog->fused == 2 || prog->fused == 4;
     if (((uintptr_t)inputs[prog->input_slot[s0.src[0]]] % 16) || ((uintptr_t)inputs[prog->input_slot[s0.src[1]]] % 16) ||
         ((uintptr_t)bias % (conv ? 16 : 4)) || ((uintptr_t)output % (conv ? 16 : out_bf16 ? 2 : 4)))
@@ -440,7 +485,10 @@ stripe_status_t run_single(stripe_block* blk, const void* const* inputs, void* o
     case STRIPE_PATH_MFMA_GEMM: e = launch_gemm(p.gemm, blk->gemm, in0, in1, output, ws, s); break;
     case STRIPE_PATH_MFMA_CONV: e = launch_conv(p.conv, blk->conv, in0, in1, output, s); break;
     case STRIPE_PATH_POOL: e = launch_pool(p.pool, blk->pool, in0, in1, output, s); break;
-    default: e = launch_generic(p, in0, in1, output, s); break;
+    default:
+      if (blk->contract.use) e = launch_contract(blk->contract, p.in_dtype, in0, in1, output, nullptr, false, s);
+      else e = launch_generic(p, in0, in1, output, s);
+      break;
   }
   if (e != hipSuccess) return fail(STRIPE_ERR_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
   return STRIPE_OK;
@@ -504,6 +552,8 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
         return fail(STRIPE_ERR_UNSUPPORTED, "no kernel family covers this block");
       }
       generic_info(p, &p.info);
+      // without a forced path, sum-of-products blocks of the generic path run on the matrix cores
+      if (!forced) contract_select(p.flat, &blk->contract, &p.info);
     }
     if (p.info.path == STRIPE_PATH_MFMA_GEMM && picked) blk->ws_bytes = blk->gemm.ws_bytes;
   }

@@ -1,0 +1,1011 @@
+// General matrix-core contraction (gfx950): sum-of-products blocks whose sizes, layouts or element types none of the
+// specialised families take -- fp32 products, odd or unaligned extents, A stored [k][m], three input channels,
+// transposed convolutions.
+//
+// The planner splits the block's indexes by the operands that use them (Section 3.2: every access is affine): indexes of
+// A and the output form the rows m, indexes of B and the output the columns n, reduction indexes k, indexes of all three
+// a batch.  An index of a shared output element (O[2y + i]: y of A, i of B) is rewritten first: with i = 2*i1 + i0 and
+// y' = y + i1 the output is O[2y' + i0], one owner per element, and i1 is a reduction index; 0 <= y' - i1 < Y and
+// 2*i1 + i0 < R become range tests.  What the atomic form did in 117 us (stride-2 transposed 3x3, 8 x 28 x 28 x 32) then
+// is a product like any other.
+//
+// A workgroup of four wavefronts owns a BM x BN tile.  Operands are fetched through buffer loads: a point outside the
+// polyhedron or the tile's remainder gets an offset beyond the buffer's range and the load returns zero, so no select
+// follows.  Three ways to fetch, chosen per operand by the planner: 16 bytes along k; vectors along the row index, turned
+// to k order in registers; or element by element with neighbouring lanes on neighbouring k.  Tiles go registers -> LDS
+// (two buffers, one barrier per K tile) in rows of BKB bytes + 16, which spreads the 16 rows of a fragment read over all
+// banks; the loads of the next K tile are in flight during the matrix instructions.  A 16-byte fragment is one
+// 16x16x32 bf16 / 16x16x64 int8 instruction or four 16x16x4 fp32 ones; sums are fp32 / int32 throughout.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdio>
+#include <type_traits>
+#include <vector>
+
+#include "contract.hpp"
+#include "kernels.hpp"
+
+namespace stripe {
+namespace {
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kFar = -0x40000000;          // a range-test value no other part can bring back into range
+[[maybe_unused]] constexpr uint32_t kTop = 0x3fffffffu;     // "no upper end"
+constexpr uint32_t kOutside = 0x80000000u; // byte offset beyond every buffer's range: the load returns zero
+constexpr uint32_t kRecords = 0x7fffffffu;
+
+__device__ __forceinline__ uint32_t fast_div(uint32_t v, uint32_t mul, int shift) { return __umulhi(v, mul) >> shift; }
+
+// calls f(index number, value) for the indexes of a flat position; unused slots (range, mul 0) get 0.  Without branches, so
+// that the parameters stay in scalar registers.
+template <typename F>
+__device__ __forceinline__ void decode(const CtIndex& ix, uint32_t v, F f) {
+#pragma unroll
+  for (int j = 0; j < kCtIdx; ++j) {
+    const uint32_t q = fast_div(v, ix.mul[j], ix.shift[j]);
+    f(j, (int)(v - q * ix.range[j]));
+    v = q;
+  }
+}
+
+struct KPart {
+  int off, t0, t1;
+  int run;        // elements from here to the end of the innermost index's real range
+};
+
+template <bool SIDE_A>
+__device__ __forceinline__ KPart k_part(const ContractParams& p, uint32_t k) {
+  KPart r = {0, 0, 0, 0};
+  auto add = [&](int j, int v) {
+    if (j == 0) r.run = p.k_run - v;
+    r.off += (SIDE_A ? p.k_a[j] : p.k_b[j]) * v;
+    r.t0 += (SIDE_A ? p.ka_t[0][j] : p.kb_t[0][j]) * v;
+    r.t1 += (SIDE_A ? p.ka_t[1][j] : p.kb_t[1][j]) * v;
+  };
+  if (p.k.n == 1) add(0, (int)k);
+  else decode(p.k, k, add);
+  if (k >= p.K || r.run <= 0) r.t0 = kFar;
+  return r;
+}
+
+template <typename T>
+struct Ct;
+template <>
+struct Ct<uint16_t> {
+  using Acc = f32x4;
+  using S = float;
+  [[maybe_unused]] static constexpr int KP = 2, V = 8;      // elements per dword; rows per vector of the row-wise fetch
+  static __device__ __forceinline__ Acc mma(u32x4 a, u32x4 b, Acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ S widen(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
+  static __device__ __forceinline__ bool finite(uint32_t w) { return ((w & 0x7f80u) != 0x7f80u) & ((w & 0x7f800000u) != 0x7f800000u); }
+};
+template <>
+struct Ct<int8_t> {
+  using Acc = i32x4;
+  using S = int32_t;
+  [[maybe_unused]] static constexpr int KP = 4, V = 8;
+  static __device__ __forceinline__ Acc mma(u32x4 a, u32x4 b, Acc c) {
+    return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ S widen(int8_t v) { return v; }
+  static __device__ __forceinline__ bool finite(uint32_t) { return true; }
+};
+template <>
+struct Ct<float> {
+  using Acc = f32x4;
+  using S = float;
+  [[maybe_unused]] static constexpr int KP = 1, V = 4;
+  static __device__ __forceinline__ Acc mma(u32x4 a, u32x4 b, Acc c) {
+    const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[i], c, 0, 0, 0);
+    return c;
+  }
+  static __device__ __forceinline__ S widen(float v) { return v; }
+  static __device__ __forceinline__ bool finite(uint32_t w) { return (w & 0x7f800000u) != 0x7f800000u; }
+};
+
+template <typename T>
+__device__ __forceinline__ uint32_t load_elem(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  if constexpr (sizeof(T) == 4) return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+  else if constexpr (sizeof(T) == 2) return __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0);
+  else return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0);
+}
+
+// One operand's share of a K tile: ROWS x BKB bytes over 256 lanes, DW dwords each.  MODE: how it is fetched (see
+// ContractParams::mode_a); a template parameter, so that the loads of a K tile are straight-line code: with the three forms
+// behind branches the compiler waited for each load at the join (fp32 1000^3: 87 us, bf16 [k][m] x [k][n] 1000 x 1000 x 3000: 127 us).
+template <typename T, int ROWS, int BKB, bool SIDE_A, int MODE>
+struct Stager {
+  static constexpr int E = sizeof(T), KP = Ct<T>::KP, V = Ct<T>::V;
+  static constexpr int DW = ROWS * BKB / 4 / 256;
+  static constexpr int PITCH = BKB + 16;
+  static_assert(MODE != 2 || DW % V == 0, "whole units of V rows per lane");
+  static constexpr int CH = BKB / 16, STEP1 = 256 / CH, VE = 16 / E;         // mode 1: vectors of VE along k
+  static constexpr int KD = BKB / 4, STEP0 = 256 / KD;                       // mode 0: dwords of KP along k
+  static constexpr int G = ROWS / V, GL = G < 8 ? G : 8;                     // mode 2: groups of V rows, GL on neighbouring lanes
+  static constexpr int CH3 = BKB / 8, STEP3 = 256 / CH3, VE3 = 8 / E;         // mode 3: vectors of 8 bytes along k
+  uint32_t r[DW];
+  uint32_t back[MODE == 3 ? DW / 2 : 1];     // mode 3: bits a vector was fetched early (it would end behind the operand)
+  uint64_t mask = 0;                         // mode 3: the vector's elements inside the innermost index's range
+
+  static __device__ __forceinline__ uint32_t place(const ContractParams& p, const i32x4 row, const i32x4 k) {
+    const bool ok = ((uint32_t)(row[1] + k[1]) <= (SIDE_A ? p.top_a[0] : p.top_b[0])) & ((uint32_t)(row[2] + k[2]) <= (SIDE_A ? p.top_a[1] : p.top_b[1]));
+    return ok ? (uint32_t)(row[0] + k[0]) * E : kOutside;
+  }
+
+  __device__ __forceinline__ void load(const ContractParams& p, __amdgpu_buffer_rsrc_t buf, const i32x4* rows, const i32x4* ks, uint32_t k0) {
+    const int tid = threadIdx.x;
+    if constexpr (MODE == 1) {
+      const uint32_t k = k0 + (tid % CH) * VE;
+      i32x4 kp = ks[(tid % CH) * VE];
+      if (k < p.K && k + VE > p.K) kp[0] -= (int)(k + VE - p.K);    // a row's last, partial vector is fetched from earlier on; store() shifts it down
+#pragma unroll
+      for (int i = 0; i < DW / 4; ++i) {
+        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(buf, place(p, rows[tid / CH + i * STEP1], kp), 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[4 * i + e] = x[e];
+      }
+    } else if constexpr (MODE == 3) {
+      const i32x4 kp = ks[(tid % CH3) * VE3];
+      const uint32_t last = SIDE_A ? p.last_a : p.last_b;
+      mask = kp[3] >= VE3 ? ~0ull : kp[3] <= 0 ? 0ull : (1ull << (8 * E * kp[3])) - 1;
+#pragma unroll
+      for (int i = 0; i < DW / 2; ++i) {
+        const uint32_t off = place(p, rows[tid / CH3 + i * STEP3], kp);
+        const bool late = off > last && off != kOutside;
+        back[i] = late ? (off - last) * 8 : 0;
+        const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(buf, late ? last : off, 0, 0);
+        r[2 * i] = x[0];
+        r[2 * i + 1] = x[1];
+      }
+    } else if constexpr (MODE == 2) {
+      // V rows x KP steps of k per unit; lanes: GL row groups, then k, then the other row groups
+#pragma unroll
+      for (int i = 0; i < DW / V; ++i) {
+        const int u = tid + i * 256;
+        const int g = u % GL + u / (GL * KD) * GL, kd = u / GL % KD;
+        const i32x4 row = rows[g * V];
+#pragma unroll
+        for (int q = 0; q < KP; ++q) {
+          const uint32_t off = place(p, row, ks[kd * KP + q]);
+          if constexpr (V * E == 16) {
+            const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(buf, off, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[V * i + 4 * q + e] = x[e];
+          } else {
+            const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(buf, off, 0, 0);
+            r[V * i + 2 * q] = x[0];
+            r[V * i + 2 * q + 1] = x[1];
+          }
+        }
+      }
+    } else {
+      i32x4 kp[KP];
+#pragma unroll
+      for (int q = 0; q < KP; ++q) kp[q] = ks[(tid % KD) * KP + q];
+#pragma unroll
+      for (int i = 0; i < DW; ++i) {
+        const i32x4 row = rows[tid / KD + i * STEP0];
+        uint32_t w = 0;
+#pragma unroll
+        for (int q = 0; q < KP; ++q) w |= load_elem<T>(buf, place(p, row, kp[q])) << (8 * E * q % 32);
+        r[i] = w;
+      }
+    }
+  }
+
+  // -> LDS rows of k; returns whether every value is finite
+  __device__ __forceinline__ bool store(const ContractParams& p, unsigned char* lds, uint32_t k0, bool look) {
+    const int tid = threadIdx.x;
+    bool fin = true;
+    if constexpr (MODE == 3) {
+#pragma unroll
+      for (int i = 0; i < DW / 2; ++i) {
+        const uint64_t x = ((r[2 * i] | (uint64_t)r[2 * i + 1] << 32) >> back[i]) & mask;
+        r[2 * i] = (uint32_t)x;
+        r[2 * i + 1] = (uint32_t)(x >> 32);
+      }
+    }
+    if (look) {
+#pragma unroll
+      for (int i = 0; i < DW; ++i) fin &= Ct<T>::finite(r[i]);
+    }
+    if constexpr (MODE == 1) {
+      if (p.K % VE && k0 + CH * VE > p.K) {      // uniform: the last K tile
+        const uint32_t k = k0 + (tid % CH) * VE;
+        const uint32_t drop = k < p.K && k + VE > p.K ? (k + VE - p.K) * E : 0;   // bytes that belong to the vector before
+#pragma unroll
+        for (int i = 0; i < DW / 4; ++i) {
+          uint64_t lo = r[4 * i] | (uint64_t)r[4 * i + 1] << 32, hi = r[4 * i + 2] | (uint64_t)r[4 * i + 3] << 32;
+          if (drop & 8) { lo = hi; hi = 0; }
+          const uint32_t bits = (drop & 7) * 8;
+          if (bits) { lo = lo >> bits | hi << (64 - bits); hi >>= bits; }
+          r[4 * i] = (uint32_t)lo; r[4 * i + 1] = (uint32_t)(lo >> 32);
+          r[4 * i + 2] = (uint32_t)hi; r[4 * i + 3] = (uint32_t)(hi >> 32);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < DW / 4; ++i)
+        *(u32x4*)(lds + (tid / CH + i * STEP1) * PITCH + tid % CH * 16) = (u32x4){r[4 * i], r[4 * i + 1], r[4 * i + 2], r[4 * i + 3]};
+    } else if constexpr (MODE == 3) {
+#pragma unroll
+      for (int i = 0; i < DW / 2; ++i) *(u32x2*)(lds + (tid / CH3 + i * STEP3) * PITCH + tid % CH3 * 8) = (u32x2){r[2 * i], r[2 * i + 1]};
+    } else if constexpr (MODE == 2) {
+#pragma unroll
+      for (int i = 0; i < DW / V; ++i) {
+        const int u = tid + i * 256;
+        const int g = u % GL + u / (GL * KD) * GL, kd = u / GL % KD;
+        unsigned char* at = lds + g * V * PITCH + kd * 4;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          uint32_t w;
+          if constexpr (KP == 1) {
+            w = r[V * i + v];
+          } else if constexpr (KP == 2) {   // row v: half v % 2 of dword v / 2 of the two k steps
+            const uint32_t x = r[V * i + v / 2], y = r[V * i + 4 + v / 2];
+            w = v % 2 ? (x >> 16) | (y & 0xffff0000u) : (x & 0xffffu) | (y << 16);
+          } else {
+            w = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w |= ((r[V * i + 2 * q + v / 4] >> (8 * (v % 4))) & 0xffu) << (8 * q);
+          }
+          *(uint32_t*)(at + v * PITCH) = w;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < DW; ++i) *(uint32_t*)(lds + (tid / KD + i * STEP0) * PITCH + tid % KD * 4) = r[i];
+    }
+    return fin;
+  }
+};
+
+// one output element, through the launch's epilogue
+template <typename S>
+__device__ __forceinline__ void put(const ContractParams& p, void* O, const float* bias, int off, uint32_t n, S v) {
+  if constexpr (std::is_same<S, float>::value) {
+    if (p.epilogue >= 2) v = v + bias[n] > 0.f ? v + bias[n] : 0.f;
+    if (p.epilogue & 1) {
+      ((__bf16*)O)[off] = (__bf16)v;
+      return;
+    }
+  }
+  ((S*)O)[off] = v;
+}
+
+// BM x BN tile, K tiles of BKB bytes per row; WM x WN wavefronts over the tile, the remaining factor WK of the four
+// wavefronts takes every WK-th 64-byte step of a K tile (small tiles) and their sums are added through LDS at the end.
+template <typename T, int BM, int BN, int BKB, int WM, int WN, int MA, int MB>
+__global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, const T* __restrict__ A, const T* __restrict__ B,
+                                                       void* __restrict__ O, const float* __restrict__ bias) {
+  using Acc = typename Ct<T>::Acc;
+  using S = typename Ct<T>::S;
+  constexpr int WK = 4 / (WM * WN), STEPS = BKB / 64, FM = BM / WM / 16, FN = BN / WN / 16;
+  constexpr int PITCH = BKB + 16, BUF = (BM + BN) * PITCH;
+  static_assert(STEPS % WK == 0, "K steps are shared out evenly");
+  static_assert(WK == 1 || (WK - 1) * BM * BN * 4 <= 2 * BUF, "partial sums fit the staging buffers");
+  __shared__ __align__(16) unsigned char lds[2 * BUF];
+  __shared__ i32x4 rows_a[BM], rows_b[BN];   // {input offset, range-test values, output offset}
+  __shared__ int2 ob_m[BM], ob_n[BN];
+  constexpr uint32_t BK = BKB / sizeof(T);
+  // k's share of the addresses and range tests, for both operands: a K tile's entries are worked out once, one iteration
+  // before its loads, in a ring of three (decoded at each load, they were most of the kernel's time: bf16 [k][m] x [k][n] 1000 x 1000 x 3000 87 us)
+  __shared__ i32x4 ks_a[3][BK], ks_b[3][BK];
+  static_assert(BK <= 256, "one entry per lane");
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t m0 = blockIdx.x / (uint32_t)p.tiles_n * BM, n0 = blockIdx.x % (uint32_t)p.tiles_n * BN;
+  int a_base = p.a_base, b_base = p.b_base, o_base = p.o_base;
+  {
+    uint32_t t = blockIdx.y;     // unused batch indexes: range 1
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int v = (int)(t % p.batch_range[j]);
+      t /= p.batch_range[j];
+      a_base += p.batch_a[j] * v;
+      b_base += p.batch_b[j] * v;
+      o_base += p.batch_o[j] * v;
+    }
+  }
+  auto fill_ks = [&](uint32_t t, uint32_t slot) {       // A's entries on the first BK lanes, B's on the next (all lanes both where BK is 256)
+    const uint32_t at = (uint32_t)tid % BK;
+    if (2 * BK > 256 || (uint32_t)tid < BK) {
+      const KPart a = k_part<true>(p, t * BK + at);
+      ks_a[slot][at] = (i32x4){a.off, a.t0, a.t1, a.run};
+    }
+    if (2 * BK > 256 || ((uint32_t)tid >= BK && (uint32_t)tid < 2 * BK)) {
+      const KPart b = k_part<false>(p, t * BK + at);
+      ks_b[slot][at] = (i32x4){b.off, b.t0, b.t1, b.run};
+    }
+  };
+  for (uint32_t t = 0; t < 3; ++t) fill_ks(t, t);
+  for (int i = tid; i < BM + BN; i += 256) {
+    const bool am = i < BM;
+    uint32_t at = am ? m0 + i : n0 + i - BM;
+    // Vectors along the row index: the operand's last, partial group of V rows starts V rows before its end instead.  The
+    // rows it shares with the group before are computed and stored twice, with the same bits.
+    constexpr uint32_t V = Ct<T>::V;
+    const uint32_t end = am ? p.M : p.N;
+    if ((am ? MA : MB) == 2 && at / V * V < end && at / V * V + V > end) at = end - V + at % V;
+    i32x4 e = {am ? a_base : b_base, am ? p.c_a[0] : p.c_b[0], am ? p.c_a[1] : p.c_b[1], 0};
+    int2 ob = {0, 0};
+    if (am) {
+      decode(p.m, at, [&](int j, int v) {
+        e[0] += p.m_in[j] * v; e[1] += p.m_t[0][j] * v; e[2] += p.m_t[1][j] * v; e[3] += p.m_out[j] * v;
+        ob.x += p.m_ob[0][j] * v; ob.y += p.m_ob[1][j] * v;
+      });
+      if (at >= p.M) e[1] = kFar;
+      rows_a[i] = e;
+      ob_m[i] = ob;
+    } else {
+      decode(p.n, at, [&](int j, int v) {
+        e[0] += p.n_in[j] * v; e[1] += p.n_t[0][j] * v; e[2] += p.n_t[1][j] * v; e[3] += p.n_out[j] * v;
+        ob.x += p.n_ob[0][j] * v; ob.y += p.n_ob[1][j] * v;
+      });
+      if (at >= p.N) e[1] = kFar;
+      rows_b[i - BM] = e;
+      ob_n[i - BM] = ob;
+    }
+  }
+  __syncthreads();
+
+  const __amdgpu_buffer_rsrc_t buf_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, kRecords, 0x00020000);
+  const __amdgpu_buffer_rsrc_t buf_b = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, kRecords, 0x00020000);
+  Stager<T, BM, BKB, true, MA> sa[2];      // K tiles t and t + 1 on their way
+  Stager<T, BN, BKB, false, MB> sb[2];
+  const uint32_t n_kt = (p.K + BK - 1) / BK;
+  const bool look = p.tested && std::is_same<S, float>::value;
+  bool fin = true;
+
+  const int wk = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+  const int frag_row = lane & 15, frag_k = lane >> 4;
+  Acc acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = (Acc){0, 0, 0, 0};
+
+  // bf16 / fp32: partial sums over FLUSH K tiles start from zero and are added to the total, short chains of roundings
+  // instead of one long one (not on the largest tile, whose registers hold one set of sums at two wavefronts per SIMD)
+  constexpr uint32_t FLUSH = BM * BN > 8192 ? 0xffffffffu : std::is_same<T, float>::value ? 1 : std::is_same<T, uint16_t>::value ? 4 : 0xffffffffu;
+  Acc sum[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) sum[i][j] = (Acc){0, 0, 0, 0};
+  auto flush = [&]() {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        acc[i][j] += sum[i][j];
+        sum[i][j] = (Acc){0, 0, 0, 0};
+      }
+  };
+
+  // Two K tiles are in flight in registers (set t & 1 holds tile t): with one, few workgroups and long reductions spent an
+  // iteration waiting for memory.  The loop's loads are unconditional (a tile past the last one loads zeros); the last two tiles
+  // are peeled off without loads.
+  sa[0].load(p, buf_a, rows_a, ks_a[0], 0);
+  sb[0].load(p, buf_b, rows_b, ks_b[0], 0);
+  if (n_kt > 1) {
+    sa[1].load(p, buf_a, rows_a, ks_a[1], BK);
+    sb[1].load(p, buf_b, rows_b, ks_b[1], BK);
+  }
+  fin &= sa[0].store(p, lds, 0, look);
+  fin &= sb[0].store(p, lds + BM * PITCH, 0, look);
+  uint32_t slot = 2;             // of tile t + 2 in the ring
+  auto step = [&](uint32_t t, auto set, auto loads, auto stores) {
+    constexpr int S0 = decltype(set)::value;
+    __syncthreads();
+    if constexpr (decltype(loads)::value) {
+      sa[S0].load(p, buf_a, rows_a, ks_a[slot], (t + 2) * BK);
+      sb[S0].load(p, buf_b, rows_b, ks_b[slot], (t + 2) * BK);
+      slot = slot == 2 ? 0 : slot + 1;
+      fill_ks(t + 3, slot);        // over the entries of tile t, read two iterations ago
+    }
+    const unsigned char* base = lds + S0 * BUF + frag_k * 16;
+#pragma unroll
+    for (int s = 0; s < STEPS / WK; ++s) {
+      const unsigned char* at = base + (s * WK + wk) * 64;
+      u32x4 fa[FM], fb[FN];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) fa[i] = *(const u32x4*)(at + (wm * (BM / WM) + i * 16 + frag_row) * PITCH);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) fb[j] = *(const u32x4*)(at + (BM + wn * (BN / WN) + j * 16 + frag_row) * PITCH);
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) sum[i][j] = Ct<T>::mma(fb[j], fa[i], sum[i][j]);   // rows of the result: n
+    }
+    if ((t + 1) % FLUSH == 0) flush();
+    if constexpr (decltype(stores)::value) {
+      unsigned char* next = lds + (1 - S0) * BUF;
+      fin &= sa[1 - S0].store(p, next, (t + 1) * BK, look);
+      fin &= sb[1 - S0].store(p, next + BM * PITCH, (t + 1) * BK, look);
+    }
+  };
+  constexpr std::integral_constant<int, 0> even;
+  constexpr std::integral_constant<int, 1> odd;
+  constexpr std::true_type yes;
+  constexpr std::false_type no;
+  uint32_t t = 0;
+  for (; t + 2 < n_kt; t += 2) {
+    step(t, even, yes, yes);
+    step(t + 1, odd, yes, yes);
+  }
+  if (t + 1 < n_kt) {
+    step(t, even, no, yes);
+    step(t + 1, odd, no, no);
+  } else {
+    step(t, even, no, no);
+  }
+  flush();
+
+  if constexpr (WK > 1) {
+    __syncthreads();
+    Acc* part = (Acc*)lds;
+    if (wk > 0)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) part[((((wk - 1) * WM * WN + wave % (WM * WN)) * FM + i) * FN + j) * 64 + lane] = acc[i][j];
+    __syncthreads();
+    if (wk == 0)
+#pragma unroll
+      for (int w = 0; w < WK - 1; ++w)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j) acc[i][j] += part[(((w * WM * WN + wave % (WM * WN)) * FM + i) * FN + j) * 64 + lane];
+  }
+
+  // A removed point contributes 0 * x, which is not 0 where x is an infinity or NaN: a tile that met one is summed again
+  // point by point (Definition 2: a removed point contributes nothing).
+  if (look && __syncthreads_or(!fin)) {
+    for (int at = tid; at < BM * BN; at += 256) {
+      const int mi = at / BN, ni = at % BN;
+      const i32x4 rm = rows_a[mi], rn = rows_b[ni];
+      if (rm[1] == kFar || rn[1] == kFar || ob_m[mi].x + ob_n[ni].x > p.ob[0] || ob_m[mi].y + ob_n[ni].y > p.ob[1]) continue;
+      S sum = 0;
+      for (uint32_t k = 0; k < p.K; ++k) {
+        const KPart ka = k_part<true>(p, k), kb = k_part<false>(p, k);
+        if ((uint32_t)(rm[1] + ka.t0) <= p.top_a[0] && (uint32_t)(rm[2] + ka.t1) <= p.top_a[1] && (uint32_t)(rn[1] + kb.t0) <= p.top_b[0] &&
+            (uint32_t)(rn[2] + kb.t1) <= p.top_b[1])
+          sum += Ct<T>::widen(A[rm[0] + ka.off]) * Ct<T>::widen(B[rn[0] + kb.off]);
+      }
+      put<S>(p, O, bias, o_base + rm[3] + rn[3], rn[3], sum);
+    }
+    return;
+  }
+  if (WK > 1 && wk > 0) return;
+
+#pragma unroll
+  for (int j = 0; j < FN; ++j) {
+    const int ni = wn * (BN / WN) + j * 16 + frag_k * 4;
+    int n_off[4];
+    bool n_in[4];
+    int2 on[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const i32x4 rn = rows_b[ni + e];
+      n_off[e] = rn[3];
+      n_in[e] = rn[1] != kFar;
+      on[e] = ob_n[ni + e];
+    }
+    float bs[4] = {0.f, 0.f, 0.f, 0.f};
+    if (p.epilogue >= 2) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (n_in[e]) bs[e] = bias[n_off[e]];      // one column index of unit output stride
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int mi = wm * (BM / WM) + i * 16 + frag_row;
+      const i32x4 rm = rows_a[mi];
+      if (rm[1] == kFar) continue;
+      const int off = o_base + rm[3];
+      const int2 om = ob_m[mi];
+      S v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = acc[i][j][e];
+        if constexpr (std::is_same<S, float>::value) {
+          if (p.epilogue >= 2) v[e] = v[e] + bs[e] > 0.f ? v[e] + bs[e] : 0.f;
+        }
+      }
+      const bool half = std::is_same<S, float>::value && (p.epilogue & 1);
+      // the planner: four columns from a multiple of four are neighbours and share the bound
+      if (p.vec_out && n_in[0]) {
+        if (om.x + on[0].x <= p.ob[0] && om.y + on[0].y <= p.ob[1]) {
+          typedef S s4 __attribute__((ext_vector_type(4)));
+          if (half) *(bf16x4*)((uint16_t*)O + off + n_off[0]) = __builtin_convertvector((f32x4){(float)v[0], (float)v[1], (float)v[2], (float)v[3]}, bf16x4);
+          else *(s4*)((S*)O + off + n_off[0]) = (s4){v[0], v[1], v[2], v[3]};
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n_in[e] && om.x + on[e].x <= p.ob[0] && om.y + on[e].y <= p.ob[1]) {
+            if (half) ((__bf16*)O)[off + n_off[e]] = (__bf16)(float)v[e];
+            else ((S*)O)[off + n_off[e]] = v[e];
+          }
+      }
+    }
+  }
+}
+
+}  // namespace
+
+// one translation unit per element type compiles the kernels (CONTRACT_T); the planner is compiled with the last of them
+hipError_t launch_contract_f32(const ContractLaunch&, const ContractParams&, const void*, const void*, void*, const float*, hipStream_t);
+hipError_t launch_contract_bf16(const ContractLaunch&, const ContractParams&, const void*, const void*, void*, const float*, hipStream_t);
+hipError_t launch_contract_i8(const ContractLaunch&, const ContractParams&, const void*, const void*, void*, const float*, hipStream_t);
+
+namespace {
+
+template <typename T, int MA, int MB>
+hipError_t launch_modes(const ContractLaunch& l, const ContractParams& p, const void* a, const void* b, void* o, const float* bias, hipStream_t s) {
+  const dim3 g((unsigned)l.grid, (unsigned)l.batch), w(256);
+  switch (l.tile) {
+    case 0: hipLaunchKernelGGL((contract_kernel<T, 128, 128, 64, 2, 2, MA, MB>), g, w, 0, s, p, (const T*)a, (const T*)b, o, bias); break;
+    case 1: hipLaunchKernelGGL((contract_kernel<T, 64, 64, 128, 2, 2, MA, MB>), g, w, 0, s, p, (const T*)a, (const T*)b, o, bias); break;
+    case 3:
+      if constexpr (MB == 2 && sizeof(T) < 4) return hipErrorInvalidValue;   // 64 rows of 64 bytes are less than a unit per lane: the planner takes tile 1
+      else hipLaunchKernelGGL((contract_kernel<T, 128, 64, 64, 2, 2, MA, MB>), g, w, 0, s, p, (const T*)a, (const T*)b, o, bias);
+      break;
+    default: hipLaunchKernelGGL((contract_kernel<T, 32, 32, 256, 1, 1, MA, MB>), g, w, 0, s, p, (const T*)a, (const T*)b, o, bias); break;
+  }
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_t(const ContractLaunch& l, const ContractParams& p, const void* a, const void* b, void* o, const float* bias, hipStream_t s) {
+  switch (p.mode_a * 4 + p.mode_b) {
+    case 0: return launch_modes<T, 0, 0>(l, p, a, b, o, bias, s);
+    case 1: return launch_modes<T, 0, 1>(l, p, a, b, o, bias, s);
+    case 2: return launch_modes<T, 0, 2>(l, p, a, b, o, bias, s);
+    case 3: return launch_modes<T, 0, 3>(l, p, a, b, o, bias, s);
+    case 4: return launch_modes<T, 1, 0>(l, p, a, b, o, bias, s);
+    case 5: return launch_modes<T, 1, 1>(l, p, a, b, o, bias, s);
+    case 6: return launch_modes<T, 1, 2>(l, p, a, b, o, bias, s);
+    case 7: return launch_modes<T, 1, 3>(l, p, a, b, o, bias, s);
+    case 8: return launch_modes<T, 2, 0>(l, p, a, b, o, bias, s);
+    case 9: return launch_modes<T, 2, 1>(l, p, a, b, o, bias, s);
+    case 10: return launch_modes<T, 2, 2>(l, p, a, b, o, bias, s);
+    case 11: return launch_modes<T, 2, 3>(l, p, a, b, o, bias, s);
+    case 12: return launch_modes<T, 3, 0>(l, p, a, b, o, bias, s);
+    case 13: return launch_modes<T, 3, 1>(l, p, a, b, o, bias, s);
+    case 14: return launch_modes<T, 3, 2>(l, p, a, b, o, bias, s);
+    default: return launch_modes<T, 3, 3>(l, p, a, b, o, bias, s);
+  }
+}
+
+}  // namespace
+
+
+#if CONTRACT_T == 4
+hipError_t launch_contract_f32(const ContractLaunch& l, const ContractParams& p, const void* a, const void* b, void* o, const float* bias, hipStream_t s) {
+  return launch_t<float>(l, p, a, b, o, bias, s);
+}
+#elif CONTRACT_T == 2
+hipError_t launch_contract_bf16(const ContractLaunch& l, const ContractParams& p, const void* a, const void* b, void* o, const float* bias, hipStream_t s) {
+  return launch_t<uint16_t>(l, p, a, b, o, bias, s);
+}
+#else
+hipError_t launch_contract_i8(const ContractLaunch& l, const ContractParams& p, const void* a, const void* b, void* o, const float* bias, hipStream_t s) {
+  return launch_t<int8_t>(l, p, a, b, o, bias, s);
+}
+
+namespace {
+
+typedef __int128 i128;
+
+struct Tile {
+  int bm, bn, bkb;
+};
+constexpr Tile kTiles[] = {{128, 128, 64}, {64, 64, 128}, {32, 32, 256}, {128, 64, 64}};
+
+struct Ix {                      // one index: range, address coefficients, constraint coefficients, output-bound coefficients
+  int64_t range = 1, a = 0, b = 0, o = 0;
+  std::vector<int64_t> con;
+  int64_t ob[kCtTests] = {0, 0};
+};
+
+bool fill_side(const std::vector<Ix>& v, CtIndex* c) {
+  if ((int)v.size() > kCtIdx) return false;
+  c->n = (int)v.size();
+  for (int j = 0; j < kCtIdx; ++j) {
+    c->range[j] = 0;
+    c->mul[j] = 0;
+    c->shift[j] = 0;
+  }
+  for (size_t j = 0; j < v.size(); ++j) {
+    const uint64_t d = (uint64_t)v[j].range;
+    if (d < 2 || d > 0x3fffffff) return false;
+    int s = 0;
+    while (((uint64_t)1 << s) < d) ++s;
+    // floor(v * mul / 2^(31+s)) = v / d for v < 2^31: mul exceeds 2^(31+s)/d by at most 1, and 2^s >= d
+    c->range[j] = (uint32_t)d;
+    c->mul[j] = (uint32_t)((((uint64_t)1 << (31 + s)) / d) + 1);
+    c->shift[j] = s - 1;
+  }
+  return true;
+}
+
+}  // namespace
+
+bool contract_select(const FlatBlock& fb, ContractLaunch* l, stripe_block_info_t* info) {
+  l->use = false;
+  if (!tune_int("contract", 1)) return false;
+  if (fb.empty || fb.n_refs != 3 || fb.intrinsic != STRIPE_INTR_MUL || fb.agg != STRIPE_AGG_ADD) return false;
+  const int dt = fb.ref[0].dtype;
+  if (fb.ref[1].dtype != dt || (dt != STRIPE_F32 && dt != STRIPE_BF16 && dt != STRIPE_I8)) return false;
+  const int esize = dt == STRIPE_F32 ? 4 : dt == STRIPE_BF16 ? 2 : 1;
+
+  // the block's indexes and constraints
+  std::vector<Ix> ix;
+  std::vector<int64_t> con_k;
+  size_t n_con = fb.cons.size();
+  for (const Affine& q : fb.cons) con_k.push_back(q.k);
+  for (int j = 0; j < fb.n_idx; ++j) {
+    Ix x;
+    x.range = fb.range[j];
+    x.a = fb.ref[0].addr.c[j];
+    x.b = fb.ref[1].addr.c[j];
+    x.o = fb.ref[2].addr.c[j];
+    for (const Affine& q : fb.cons) x.con.push_back(q.c[j]);
+    ix.push_back(x);
+  }
+  // all values the kernel forms stay far inside 32 bits (bytes for the operands)
+  auto small = [&](int64_t k, auto coef, i128 lim) {
+    i128 m = k < 0 ? -(i128)k : (i128)k;
+    for (const Ix& x : ix) {
+      const int64_t c = coef(x);
+      m += (c < 0 ? -(i128)c : (i128)c) * (x.range + 1);
+    }
+    return m < lim;
+  };
+
+  // Every output element one owner: pairs p (of A), i (of B) with o_p = s * o_i and overlapping spans are rewritten as in
+  // the file's head comment.
+  const size_t first_new = n_con;      // constraints from here on come from the rewriting
+  int n_ob = 0;
+  int64_t ob[kCtTests] = {0, 0};
+  std::vector<std::pair<int64_t, int64_t>> combined;    // (output stride, extent) of the rewritten pairs
+  std::vector<char> in_pair(ix.size(), 0);
+  for (size_t pi = 0; pi < in_pair.size(); ++pi)
+    for (size_t ii = 0; ii < in_pair.size(); ++ii) {
+      if (pi == ii || in_pair[pi] || in_pair[ii]) continue;
+      const Ix p = ix[pi], i = ix[ii];
+      if (!p.a || p.b || !i.b || i.a || p.o <= 0 || i.o <= 0 || p.o % i.o) continue;
+      const int64_t s = p.o / i.o;
+      if (i.range <= s) continue;                        // no overlap
+      bool free = n_ob < kCtTests;
+      for (size_t q = 0; q < n_con && free; ++q) free = !p.con[q] && !i.con[q];
+      if (!free) return false;
+      const int64_t i1n = (i.range + s - 1) / s;
+      Ix pp = p, i1, i0 = i;
+      pp.range = p.range + i1n - 1;
+      i1.range = i1n; i1.a = -p.a; i1.b = s * i.b; i1.o = 0;
+      i0.range = s;
+      pp.ob[n_ob] = s;
+      i0.ob[n_ob] = 1;
+      ob[n_ob] = s * (p.range - 1) + i.range - 1;
+      combined.push_back({i.o, ob[n_ob] + 1});
+      ++n_ob;
+      i1.con.assign(con_k.size(), 0);
+      ix[pi] = pp;
+      ix[ii] = i0;
+      ix.push_back(i1);
+      in_pair[pi] = in_pair[ii] = 1;
+      auto add_con = [&](int64_t k, int64_t cp, int64_t c1, int64_t c0) {
+        con_k.push_back(k);
+        for (Ix& x : ix) x.con.push_back(0);
+        ix[pi].con.back() = cp;
+        ix[ii].con.back() = c0;
+        ix.back().con.back() = c1;
+      };
+      add_con(0, 1, -1, 0);                              // p' - i1 >= 0
+      add_con(p.range - 1, -1, 1, 0);                    // p' - i1 <= P - 1
+      if (i.range % s) add_con(i.range - 1, 0, -s, -1);  // s*i1 + i0 <= R - 1
+    }
+  n_con = con_k.size();
+  // one owner per element now?  strides by magnitude, each beyond the span of the smaller ones
+  {
+    std::vector<std::pair<int64_t, int64_t>> t = combined;
+    for (const Ix& x : ix)
+      if (x.o && !x.ob[0] && !x.ob[1]) t.push_back({x.o < 0 ? -x.o : x.o, x.range});
+    std::sort(t.begin(), t.end());
+    i128 span = 0;
+    for (const auto& e : t) {
+      if ((i128)e.first <= span) return false;
+      span += (i128)e.first * (e.second - 1);
+    }
+    if (n_ob && fb.out_bf16) return false;
+  }
+  // ranges of 1 (a stride-1 transposed convolution's i0) carry nothing
+  for (size_t j = 0; j < ix.size();) {
+    if (ix[j].range == 1) ix.erase(ix.begin() + j);
+    else ++j;
+  }
+  const i128 lim = 0x3fffffff;
+  if (!small(fb.ref[0].addr.k, [](const Ix& x) { return x.a; }, lim / esize) || !small(fb.ref[1].addr.k, [](const Ix& x) { return x.b; }, lim / esize) ||
+      !small(fb.ref[2].addr.k, [](const Ix& x) { return x.o; }, lim))
+    return false;
+  for (size_t q = 0; q < n_con; ++q)
+    if (!small(con_k[q], [q](const Ix& x) { return x.con[q]; }, lim / 4)) return false;
+
+  // Every owner has a point (constraints that share no index are independent): else an element would have to stay
+  // unwritten.  The rewritten pairs' own constraints are covered by the output bounds.
+  {
+    std::vector<char> done(first_new, 0);
+    for (size_t q0 = 0; q0 < first_new; ++q0) {
+      if (done[q0]) continue;
+      std::vector<size_t> group{q0};
+      done[q0] = 1;
+      std::vector<char> uses(ix.size(), 0);
+      for (bool grown = true; grown;) {
+        grown = false;
+        for (size_t g : group)
+          for (size_t j = 0; j < ix.size(); ++j)
+            if (ix[j].con[g]) uses[j] = 1;
+        for (size_t q = 0; q < first_new; ++q) {
+          bool shares = false;
+          for (size_t j = 0; j < ix.size(); ++j) shares = shares || (uses[j] && ix[j].con[q]);
+          if (!done[q] && shares) {
+            done[q] = 1;
+            group.push_back(q);
+            grown = true;
+          }
+        }
+      }
+      std::vector<size_t> outs, reds;
+      i128 pts = 1;
+      for (size_t j = 0; j < ix.size(); ++j)
+        if (uses[j]) {
+          pts *= ix[j].range;
+          (ix[j].o ? outs : reds).push_back(j);
+        }
+      if (pts > ((i128)1 << 20)) return false;
+      i128 n_outs = 1, n_reds = 1;
+      for (size_t j : outs) n_outs *= ix[j].range;
+      for (size_t j : reds) n_reds *= ix[j].range;
+      for (int64_t o = 0; o < (int64_t)n_outs; ++o) {
+        bool any = false;
+        for (int64_t r = 0; r < (int64_t)n_reds && !any; ++r) {
+          bool ok = true;
+          for (size_t g : group) {
+            int64_t v = con_k[g], to = o, tr = r;
+            for (size_t j : outs) { v += ix[j].con[g] * (to % ix[j].range); to /= ix[j].range; }
+            for (size_t j : reds) { v += ix[j].con[g] * (tr % ix[j].range); tr /= ix[j].range; }
+            ok = ok && v >= 0;
+          }
+          any = ok;
+        }
+        if (!any) return false;
+      }
+    }
+  }
+
+  // the second operand plays A where it owns the output's unit stride (columns are stored four at a time)
+  l->swap = false;
+  for (const Ix& x : ix)
+    if (x.o == 1 && x.a && !x.b) l->swap = true;
+  if (l->swap)
+    for (Ix& x : ix) std::swap(x.a, x.b);
+  const int64_t base_a = fb.ref[l->swap ? 1 : 0].addr.k, base_b = fb.ref[l->swap ? 0 : 1].addr.k;
+
+  std::vector<Ix> m, n, k, bat;
+  for (const Ix& x : ix) {
+    if (!x.o) k.push_back(x);
+    else if (x.a && x.b) bat.push_back(x);
+    else if (x.b) n.push_back(x);
+    else m.push_back(x);
+  }
+  if (m.empty() || n.empty() || k.empty() || bat.size() > 2) return false;
+  auto mag = [](int64_t v) { return v < 0 ? -v : v; };
+  // rows: the index A holds contiguously first (vector fetches), else by output stride
+  std::sort(m.begin(), m.end(), [&](const Ix& x, const Ix& y) { return (x.a == 1) != (y.a == 1) ? x.a == 1 : mag(x.o) < mag(y.o); });
+  std::sort(n.begin(), n.end(), [&](const Ix& x, const Ix& y) {
+    const int rx = x.o == 1 ? 0 : x.b == 1 ? 1 : 2, ry = y.o == 1 ? 0 : y.b == 1 ? 1 : 2;
+    return rx != ry ? rx < ry : mag(x.o) < mag(y.o);
+  });
+  // reduction: the index that is contiguous in most operands first
+  std::sort(k.begin(), k.end(), [&](const Ix& x, const Ix& y) {
+    const int rx = (x.a == 1) + (x.b == 1), ry = (y.a == 1) + (y.b == 1);
+    return rx != ry ? rx > ry : mag(x.a) + mag(x.b) < mag(y.a) + mag(y.b);
+  });
+
+  ContractParams& p = l->p;
+  std::memset(&p, 0, sizeof p);
+  // Byte offset of the last 8 bytes an operand holds (its declared buffer's end, or the last address the block can form if
+  // that comes first); false if it holds fewer.
+  auto last_byte = [&](bool a, ContractParams& q) {
+    const FlatRef& r = fb.ref[(a != l->swap) ? 0 : 1];
+    i128 first = r.addr.k, end = 0, hull = r.addr.k;
+    for (int d = 0; d < r.ndim; ++d) {
+      first -= (i128)r.coord[d].k * r.strides[d];
+      end += (i128)(r.sizes[d] - 1) * r.strides[d];
+    }
+    for (int j = 0; j < fb.n_idx; ++j)
+      if (r.addr.c[j] > 0) hull += (i128)r.addr.c[j] * (fb.range[j] - 1);
+    end = std::min(first + end, hull) + 1;
+    if (first < 0 || (end - first) * esize < 8) return false;
+    (a ? q.last_a : q.last_b) = (uint32_t)(end * esize - 8);
+    return true;
+  };
+  if (!fill_side(m, &p.m) || !fill_side(n, &p.n) || !fill_side(k, &p.k)) return false;
+  i128 M = 1, N = 1, K = 1;
+  for (const Ix& x : m) M *= x.range;
+  for (const Ix& x : n) N *= x.range;
+  for (const Ix& x : k) K *= x.range;
+  if (M > lim || N > lim || K > lim) return false;
+  p.M = (uint32_t)M; p.N = (uint32_t)N; p.K = (uint32_t)K;
+  for (size_t j = 0; j < m.size(); ++j) {
+    p.m_in[j] = (int32_t)m[j].a;
+    p.m_out[j] = (int32_t)m[j].o;
+    for (int t = 0; t < kCtTests; ++t) p.m_ob[t][j] = (int32_t)m[j].ob[t];
+  }
+  for (size_t j = 0; j < n.size(); ++j) {
+    p.n_in[j] = (int32_t)n[j].b;
+    p.n_out[j] = (int32_t)n[j].o;
+    for (int t = 0; t < kCtTests; ++t) p.n_ob[t][j] = (int32_t)n[j].ob[t];
+  }
+  for (size_t j = 0; j < k.size(); ++j) {
+    p.k_a[j] = (int32_t)k[j].a;
+    p.k_b[j] = (int32_t)k[j].b;
+  }
+  p.a_base = (int32_t)base_a; p.b_base = (int32_t)base_b; p.o_base = (int32_t)fb.ref[2].addr.k;
+  p.batch_range[0] = p.batch_range[1] = 1;
+  l->batch = 1;
+  for (size_t j = 0; j < bat.size(); ++j) {
+    p.batch_range[j] = (uint32_t)bat[j].range;
+    p.batch_a[j] = (int32_t)bat[j].a; p.batch_b[j] = (int32_t)bat[j].b; p.batch_o[j] = (int32_t)bat[j].o;
+    l->batch *= bat[j].range;
+    if (l->batch > 65535) return false;
+  }
+  p.n_ob_used = n_ob;     // unused bounds: 0 <= 0
+  for (int t = 0; t < kCtTests; ++t) p.ob[t] = (int32_t)ob[t];
+
+  // constraints -> range tests of one operand; a pair f + c >= 0, -f + d >= 0 is one test
+  for (int t = 0; t < kCtTests; ++t) p.top_a[t] = p.top_b[t] = kTop;
+  int used_a = 0, used_b = 0;
+  std::vector<char> done(n_con, 0);
+  for (size_t q = 0; q < n_con; ++q) {
+    if (done[q]) continue;
+    bool in_m = false, in_n = false;
+    for (const Ix& x : m) in_m = in_m || x.con[q];
+    for (const Ix& x : n) in_n = in_n || x.con[q];
+    for (const Ix& x : bat)
+      if (x.con[q]) return false;
+    if (in_m && in_n) return false;
+    int64_t top = kTop;
+    for (size_t r = q + 1; r < n_con; ++r) {
+      bool opposite = !done[r];
+      for (const Ix& x : ix) opposite = opposite && x.con[r] == -x.con[q];
+      if (opposite) {
+        done[r] = 1;
+        top = std::min(top, con_k[q] + con_k[r]);
+      }
+    }
+    if (top < 0) return false;
+    int& used = in_n ? used_b : used_a;
+    if (used >= kCtTests) return false;
+    if (in_n) {
+      p.c_b[used] = (int32_t)con_k[q];
+      p.top_b[used] = (uint32_t)top;
+      for (size_t j = 0; j < n.size(); ++j) p.n_t[used][j] = (int32_t)n[j].con[q];
+      for (size_t j = 0; j < k.size(); ++j) p.kb_t[used][j] = (int32_t)k[j].con[q];
+    } else {
+      p.c_a[used] = (int32_t)con_k[q];
+      p.top_a[used] = (uint32_t)top;
+      for (size_t j = 0; j < m.size(); ++j) p.m_t[used][j] = (int32_t)m[j].con[q];
+      for (size_t j = 0; j < k.size(); ++j) p.ka_t[used][j] = (int32_t)k[j].con[q];
+    }
+    ++used;
+  }
+  p.tested = used_a + used_b > 0;
+
+  // How each operand is fetched.  A vector needs its elements neighbours and under the same tests, and stays inside one
+  // run of its innermost index: the run is a multiple of the vector, or the side has one index only of at least a vector,
+  // whose end is fetched as an overlapping vector.  (Buffer loads take any element alignment.)  Where no 16-byte vector fits
+  // the innermost reduction index (three or 24 channels), 8-byte vectors do, with that index's range padded to whole
+  // vectors: the padding is zero in both operands.  For three bf16 channels that is one load and one set of range tests for
+  // four elements of k.
+  const int ve = 16 / esize, ve3 = 8 / esize, vr = dt == STRIPE_F32 ? 4 : 8;
+  auto fetch = [&](bool a) {
+    const Ix& k0 = k[0];
+    const std::vector<Ix>& row = a ? m : n;
+    bool k_tests = false, row_tests = false;
+    for (int t = 0; t < kCtTests; ++t) {
+      k_tests = k_tests || (a ? p.ka_t[t][0] : p.kb_t[t][0]) != 0;
+      row_tests = row_tests || (a ? p.m_t[t][0] : p.n_t[t][0]) != 0;
+    }
+    const bool k_unit = (a ? k0.a : k0.b) == 1 && !k_tests;
+    if (k_unit && ((k.size() == 1 && k0.range >= ve) || k0.range % ve == 0)) return 1;
+    if ((a ? row[0].a : row[0].b) == 1 && !row_tests && ((row.size() == 1 && row[0].range >= vr) || row[0].range % vr == 0)) return 2;
+    if (k_unit && last_byte(a, p) && k0.range > 1) return 3;
+    return 0;
+  };
+  p.mode_a = fetch(true);
+  p.mode_b = fetch(false);
+  p.k_run = (int32_t)k[0].range;
+  if ((p.mode_a == 3 || p.mode_b == 3) && k[0].range % ve3) {
+    const int64_t padded = (k[0].range + ve3 - 1) / ve3 * ve3;
+    const i128 padded_K = K / k[0].range * padded;
+    if (padded_K > lim / 4) return false;
+    k[0].range = padded;
+    if (!fill_side(k, &p.k)) return false;
+    p.K = (uint32_t)padded_K;
+    // the other operand's 16-byte vectors would cross the padding: they need a run of whole vectors, or none was padded
+    if (p.mode_a == 1) p.mode_a = 0;
+    if (p.mode_b == 1) p.mode_b = 0;
+  }
+  bool vec = n[0].o == 1 && n[0].range % 4 == 0 && p.o_base % 4 == 0 && !n[0].ob[0] && !n[0].ob[1];
+  for (size_t j = 1; j < n.size(); ++j) vec = vec && n[j].o % 4 == 0;
+  for (const Ix& x : m) vec = vec && x.o % 4 == 0;
+  for (const Ix& x : bat) vec = vec && x.o % 4 == 0;
+  p.vec_out = vec;
+  p.epilogue = fb.out_bf16 ? 1 : 0;
+
+  // Fewer than 65536 points stay on the literal kernels: there a launch is all the time there is.
+  i128 points = 1;
+  for (int j = 0; j < fb.n_idx; ++j) points *= fb.range[j];
+  if (points < tune_int("contract_min", 65536)) return false;
+  auto tiles = [&](int t) { return ((M + kTiles[t].bm - 1) / kTiles[t].bm) * ((N + kTiles[t].bn - 1) / kTiles[t].bn) * l->batch; };
+  // The largest tile that still gives every CU a workgroup; 64 x 64 also for somewhat fewer, and for half as many where the
+  // reduction is a few K tiles and the small tile's sharing of k has nothing to share.  Measured, us: 2000 x 2000 x 1000 bf16
+  // [k][m] 42 on 128 x 128, 54 on 64 x 64, 78 on 32 x 32; 3569 x 256 x 3264 bf16 (224 tiles of 64 x 64) 57 against 61 on 32 x 32;
+  // 500 x 1000 x 777 (128 tiles) 17 against 14; 596 x 715 x 64 (120 tiles) 8.6 against 9.3; a 3 -> 64-channel 5 x 5
+  // convolution at 135 x 135 (428 tiles of 128 x 64) 16 on those, 20 on 64 x 64.
+  int tile = tiles(0) >= 256 && M > 64 && N > 64               ? 0
+             : tiles(3) >= 256                                  ? 3
+             : tiles(1) >= 192 || (tiles(1) >= 96 && (int64_t)p.K * esize <= 512) ? 1
+                                                                : 2;
+  const int forced = tune_int("contract_tile", -1);
+  if (forced >= 0 && forced <= 3) tile = forced;
+  if (tile == 3 && p.mode_b == 2 && esize < 4) tile = 1;
+  l->tile = tile;
+  const i128 grid = tiles(tile) / l->batch;
+  if (grid > 0x7fffffff) return false;
+  p.tiles_n = (int32_t)((N + kTiles[tile].bn - 1) / kTiles[tile].bn);
+  l->grid = (int64_t)grid;
+  l->use = true;
+  info->path = STRIPE_PATH_GENERIC;
+  info->tile_m = kTiles[tile].bm; info->tile_n = kTiles[tile].bn; info->tile_k = kTiles[tile].bkb / esize;
+  info->frag_m = info->frag_n = 16;
+  info->frag_k = dt == STRIPE_F32 ? 4 : 64 / esize;
+  info->lds_bytes = (kTiles[tile].bm + kTiles[tile].bn) * (2 * (kTiles[tile].bkb + 16) + 24) + 96 * kTiles[tile].bkb / esize;
+  info->workgroup_size = 256;
+  info->grid = l->grid * l->batch;
+  std::snprintf(info->kernel, sizeof info->kernel, "contract_%s_%dx%dx%d_fetch%d%d", dt == STRIPE_F32 ? "f32" : dt == STRIPE_BF16 ? "bf16" : "i8",
+                kTiles[tile].bm, kTiles[tile].bn, (int)info->tile_k, p.mode_a, p.mode_b);
+  return true;
+}
+
+hipError_t launch_contract(const ContractLaunch& l, int in_dtype, const void* in0, const void* in1, void* out, const float* bias, bool out_bf16,
+                           hipStream_t stream) {
+  if (!l.use || l.grid <= 0) return hipErrorInvalidValue;
+  ContractParams p = l.p;
+  if (bias) p.epilogue = out_bf16 ? 3 : 2;
+  if ((uintptr_t)out % ((p.epilogue & 1) ? 8 : 16)) p.vec_out = 0;
+  const void *a = l.swap ? in1 : in0, *b = l.swap ? in0 : in1;
+  switch (in_dtype) {
+    case STRIPE_I8: return launch_contract_i8(l, p, a, b, out, bias, stream);
+    case STRIPE_BF16: return launch_contract_bf16(l, p, a, b, out, bias, stream);
+    default: return launch_contract_f32(l, p, a, b, out, bias, stream);
+  }
+}
+#endif
+
+}  // namespace stripe

@@ -1,0 +1,115 @@
+"""The general matrix-core contraction against the oracle, at the edges of their tiles and fetch
+forms.  Tolerances as in tests/util.py; integers bit-exact, elements no iteration writes untouched."""
+import math
+import random
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import stripe_oracle as O
+from paper_1903_06498_amd import binding as B
+from paper_1903_06498_amd import workloads as W
+from tests import brute
+from tests.util import SENTINEL_I, parity, run_gpu
+
+pytestmark = pytest.mark.gpu
+TAKEN = []
+
+
+@pytest.mark.parametrize("seed", range(64))
+def test_random_blocks(seed, monkeypatch):
+    """Random small (nested) int8 sum-of-products blocks: negative strides, constraints over several indexes, passed values,
+    shared output elements; every tile."""
+    monkeypatch.setenv("STRIPE_TUNE", f"contract_min=1,contract_tile={seed % 4}")
+    rng = random.Random(9100 + seed)
+    inj = seed % 5 != 4
+    blk = brute.random_block(rng, seed % 3 == 2, "i8", "i32", "add", "mul", injective_out=inj, max_range=9, contraction_roles=inj)
+    nrng = np.random.default_rng(seed)
+    ins = [torch.from_numpy(nrng.integers(-3, 4, size=int(np.prod(r.sizes)), dtype=np.int8)) for r in blk.refs[:-1]]
+    try:
+        gpu, sb = run_gpu(blk, ins, return_block=True)
+    except B.StripeError as e:
+        assert e.status == 5, str(e)
+        pytest.skip(f"rejected at create: {e}")
+    TAKEN.append(sb.info["kernel"].startswith("contract_"))
+    res = O.evaluate(blk, [W.to_numpy(t) for t in ins], out=np.full(W.output_extent(blk), SENTINEL_I, np.int64))
+    assert np.array_equal(gpu.astype(np.int64), res.out), sb.info["kernel"]
+
+
+def test_random_blocks_reached_the_kernel():
+    assert sum(TAKEN) >= 12, (len(TAKEN), sum(TAKEN))
+
+
+def matmul(M, N, K, dt, layout):
+    bufs = [W.Buffer("A", "in", dt, (K, M) if layout == "tn" else (M, K)), W.Buffer("B", "in", dt, (N, K) if layout == "nt" else (K, N)),
+            W.Buffer("C", "out", "i32" if dt == "i8" else "f32", (M, N))]
+    return W.flat_block(bufs, dict(m=M, n=N, k=K), [(["k", "m"] if layout == "tn" else ["m", "k"], "assign"),
+                                                    (["n", "k"] if layout == "nt" else ["k", "n"], "assign"), (["m", "n"], "add")])
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "i8"])
+@pytest.mark.parametrize("layout", ["nn", "nt", "tn"])
+@pytest.mark.parametrize("M,N,K,tile", [(1, 1, 1, 2), (33, 31, 17, 2), (7, 130, 1025, 2), (65, 63, 129, 1), (129, 127, 67, 0), (130, 65, 193, 3),
+                                        (64, 64, 256, 1), (40, 36, 15, 2), (72, 8, 16, 1)])
+def test_products(M, N, K, tile, layout, dt, monkeypatch):
+    """Edges of tiles, K remainders inside one vector, operands with fewer rows than a vector, unaligned rows."""
+    monkeypatch.setenv("STRIPE_TUNE", f"contract_min=1,contract_tile={tile}")
+    blk = matmul(M, N, K, dt, layout)
+    ins = [W.seeded_tensor(blk.refs[0].sizes, dt, 0), W.seeded_tensor(blk.refs[1].sizes, dt, 1)]
+    parity(blk, ins, what=f"{layout} {M}x{N}x{K} {dt}")
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "i8"])
+@pytest.mark.parametrize("shape", [(2, 19, 13, 3, 20, 5, 2, 2), (1, 9, 11, 8, 70, 3, 1, 1), (3, 7, 8, 13, 5, 1, 2, 0), (1, 14, 30, 24, 33, 7, 1, 3), (1, 6, 7, 9, 12, 3, 1, 1)])
+@pytest.mark.parametrize("tile", [1, 2, 3])
+def test_convolutions(shape, dt, tile, monkeypatch):
+    monkeypatch.setenv("STRIPE_TUNE", f"contract_min=1,contract_tile={tile},conv_igemm=0")
+    N, H, Wd, Ci, Co, R, s, p = shape
+    blk = W.conv2d_block(N, H, Wd, Ci, Co, R, R, s, p, dt, "i32" if dt == "i8" else "f32")
+    info, _ = parity(blk, [W.seeded_tensor((N, H, Wd, Ci), dt, 0), W.seeded_tensor((R, R, Co, Ci), dt, 1)], what=f"conv {shape} {dt}")
+    assert info["kernel"].startswith(("contract_", "gemm_")), info
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "i8"])
+@pytest.mark.parametrize("R,s,Co", [(3, 2, 6), (2, 2, 8), (4, 2, 5), (3, 1, 8), (5, 3, 16), (2, 3, 4)])
+def test_transposed_convolutions(R, s, Co, dt, monkeypatch):
+    """Shared output elements (R > s), none (R <= s), gaps that stay unwritten (R < s) and rows beyond the last tap."""
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1")
+    N, H, Wd, Ci = 2, 6, 9, 8
+    bufs = [W.Buffer("I", "in", dt, (N, H, Wd, Ci)), W.Buffer("F", "in", dt, (R, R, Ci, Co)),
+            W.Buffer("O", "out", "i32" if dt == "i8" else "f32", (N, s * (H - 1) + R + 1, s * (Wd - 1) + R + 1, Co))]
+    blk = W.flat_block(bufs, dict(n=N, y=H, x=Wd, i=R, j=R, c=Ci, k=Co),
+                       [(["n", "y", "x", "c"], "assign"), (["i", "j", "c", "k"], "assign"), (["n", f"{s}*y + i", f"{s}*x + j", "k"], "add")])
+    info, _ = parity(blk, [W.seeded_tensor((N, H, Wd, Ci), dt, 0), W.seeded_tensor((R, R, Ci, Co), dt, 1)], what=f"transposed {R} {s} {dt}")
+    assert info["kernel"].startswith("contract_"), info
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_infinities_at_removed_points(dt, monkeypatch):
+    """A removed point contributes nothing, also where the other operand is infinite: equal to the literal kernel."""
+    blk = W.conv2d_block(1, 9, 8, 6, 10, 3, 3, 1, 1, dt, "f32")
+    ins = [W.seeded_tensor((1, 9, 8, 6), dt, 0), W.seeded_tensor((3, 3, 10, 6), dt, 1)]
+    ins[0] = ins[0].abs() + 0.5
+    ins[1][0, 1, 3, 2] = math.inf
+    ins[1][2, 2, 7, 0] = math.nan
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1")
+    got, sb = run_gpu(blk, ins, return_block=True)
+    assert sb.info["kernel"].startswith("contract_")
+    want = run_gpu(blk, ins, "generic")
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want)) and np.isinf(want).any()
+    fin = np.isfinite(want)
+    assert 0 < fin.sum() and np.allclose(got[fin], want[fin], rtol=1e-5, atol=1e-4)     # 54 products of order 1 in fp32: 54 * 2^-24 * sum |a b|
+
+
+@pytest.mark.parametrize("out_dt", ["bf16", "f32"])
+def test_fused_bias_relu(out_dt):
+    """The 3-channel convolution and its pointwise statement as one launch."""
+    N, H, Ci, Co, R = 2, 30, 3, 20, 5
+    prog = W.conv_bias_relu_program(N, H, H, Ci, Co, R, R, 2, 2, "bf16", out_dt)
+    ins = [W.seeded_tensor((N, H, H, Ci), "bf16", 0), W.seeded_tensor((R, R, Co, Ci), "bf16", 1), W.seeded_tensor((Co,), "f32", 2)]
+    got, sb = run_gpu(prog, ins, return_block=True)
+    assert sb.info["kernel"].startswith("contract_") and "+bias_relu" in sb.info["kernel"] and sb.info["workspace_bytes"] == 0, sb.info
+    res = O.evaluate_program(prog, [W.to_numpy(t).ravel() for t in ins], threads=8)
+    tol = 75 * 2.0 ** -24 * 75 * float(ins[0].abs().max()) * float(ins[1].abs().max()) + (2.0 ** -8 * np.abs(res.out) if out_dt == "bf16" else 0)
+    assert res.touched.all() and np.all(np.abs(got - res.out) <= tol)
