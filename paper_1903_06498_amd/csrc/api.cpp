@@ -30,6 +30,7 @@ struct stripe_block {
   GemmLaunch gemm;
   ConvLaunch conv;
   PoolLaunch pool;
+  RowsLaunch rows;           // products with few rows (the GEMM or the generic path's pointer contract)
   ContractLaunch contract;   // blocks of the generic path that the general matrix-core contraction takes
   int n_inputs = 0;
   // statement lists (empty for a single block): stages in order, and per root refinement either the caller's
@@ -275,7 +276,8 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
     const Stage &s0 = prog->stages[0], &s1 = prog->stages[1];
     const Plan& c = s0.blk->plan;
     const FlatBlock& e = s1.blk->plan.flat;
-    bool ok = c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && gemm_can_fuse_bias_relu(c.gemm, s0.blk->gemm) &&
+    const bool few_rows = s0.blk->rows.use && c.in_dtype == STRIPE_BF16;
+    bool ok = (few_rows || (c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && gemm_can_fuse_bias_relu(c.gemm, s0.blk->gemm))) &&
               root->refs[s0.dst].dir == STRIPE_TEMP && s1.n_in == 2 && s1.src[0] == s0.dst && !e.empty && e.intrinsic == STRIPE_INTR_ADD_RELU &&
               e.cons.empty() && e.n_refs == 3 && e.n_idx >= 2 && e.ref[0].dtype == STRIPE_F32 && e.ref[1].dtype == STRIPE_F32;
     if (ok) {
@@ -290,6 +292,9 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
           prog->fused = e.out_bf16 ? 4 : 3;
           prog->plan.gemm = c.gemm;
           prog->gemm = s0.blk->gemm;
+          prog->rows = s0.blk->rows;
+          prog->plan.in_dtype = c.in_dtype;
+          prog->plan.info.path = c.info.path;
           prog->fuse_bias_off = e.ref[1].addr.k;
           prog->fuse_o_m = co[m];
           prog->fuse_o_base = e.ref[2].addr.k;
@@ -444,10 +449,15 @@ stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void*
       return STRIPE_OK;
     }
     const bool conv = prog->fused < 3, out_bf16 = prog->fused == 2 || prog->fused == 4;
-    if (((uintptr_t)inputs[prog->input_slot[s0.src[0]]] % 16) || ((uintptr_t)inputs[prog->input_slot[s0.src[1]]] % 16) ||
+    const bool any_align = prog->rows.use && prog->plan.info.path == STRIPE_PATH_GENERIC;    // generic path: any element alignment
+    if (any_align) {
+    } else if (((uintptr_t)inputs[prog->input_slot[s0.src[0]]] % 16) || ((uintptr_t)inputs[prog->input_slot[s0.src[1]]] % 16) ||
         ((uintptr_t)bias % (conv ? 16 : 4)) || ((uintptr_t)output % (conv ? 16 : out_bf16 ? 2 : 4)))
       return fail(STRIPE_ERR_MISALIGNED, "the fused matrix-core kernel needs 16-byte aligned operands (convolution: also bias and output)");
-    if (prog->fused >= 3)
+    if (prog->rows.use)
+      e = launch_gemm_rows(prog->plan.gemm, prog->plan.in_dtype, inputs[prog->input_slot[s0.src[0]]], inputs[prog->input_slot[s0.src[1]]], output,
+                           prog->fuse_o_m, prog->fuse_o_base, bias, prog->fused == 4, (hipStream_t)hip_stream);
+    else if (prog->fused >= 3)
       e = launch_gemm_bias_relu(prog->plan.gemm, prog->gemm, inputs[prog->input_slot[s0.src[0]]], inputs[prog->input_slot[s0.src[1]]], bias,
                                 output, prog->fuse_o_m, prog->fuse_o_base, prog->fused == 4, (hipStream_t)hip_stream);
     else
@@ -482,11 +492,15 @@ stripe_status_t run_single(stripe_block* blk, const void* const* inputs, void* o
     return fail(STRIPE_ERR_MISALIGNED, "this handle was planned for a kernel family that moves 16 bytes per lane: input pointers (and, except for "
                                        "dense contractions and the general convolution kernel, the output pointer) must be 16-byte aligned");
   switch (p.info.path) {
-    case STRIPE_PATH_MFMA_GEMM: e = launch_gemm(p.gemm, blk->gemm, in0, in1, output, ws, s); break;
+    case STRIPE_PATH_MFMA_GEMM:
+      if (blk->rows.use) e = launch_gemm_rows(p.gemm, p.in_dtype, in0, in1, output, p.gemm.c_m, p.gemm.c_base, nullptr, false, s);
+      else e = launch_gemm(p.gemm, blk->gemm, in0, in1, output, ws, s);
+      break;
     case STRIPE_PATH_MFMA_CONV: e = launch_conv(p.conv, blk->conv, in0, in1, output, s); break;
     case STRIPE_PATH_POOL: e = launch_pool(p.pool, blk->pool, in0, in1, output, s); break;
     default:
-      if (blk->contract.use) e = launch_contract(blk->contract, p.in_dtype, in0, in1, output, nullptr, false, s);
+      if (blk->rows.use) e = launch_gemm_rows(p.gemm, p.in_dtype, in0, in1, output, p.gemm.c_m, p.gemm.c_base, nullptr, false, s);
+      else if (blk->contract.use) e = launch_contract(blk->contract, p.in_dtype, in0, in1, output, nullptr, false, s);
       else e = launch_generic(p, in0, in1, output, s);
       break;
   }
@@ -553,7 +567,9 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
       }
       generic_info(p, &p.info);
       // without a forced path, sum-of-products blocks of the generic path run on the matrix cores
-      if (!forced) contract_select(p.flat, &blk->contract, &p.info);
+      if (!forced && !(p.is_gemm && gemm_rows_select(p.gemm, p.in_dtype, &blk->rows, &p.info))) contract_select(p.flat, &blk->contract, &p.info);
+    } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM && gemm_rows_select(p.gemm, p.in_dtype, &blk->rows, &p.info)) {
+      blk->gemm.ws_bytes = 0;    // no partial sums of a split reduction
     }
     if (p.info.path == STRIPE_PATH_MFMA_GEMM && picked) blk->ws_bytes = blk->gemm.ws_bytes;
   }

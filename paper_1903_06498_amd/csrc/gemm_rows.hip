@@ -1,0 +1,175 @@
+// Products with few rows (gfx950): C[m, n] = sum over k of A[m, k] * B[n, k] with at most 32 rows, both operands
+// k-contiguous -- a Linear layer at a small batch.  What bounds it is reading B once; a 256-wide tile leaves most CUs
+// idle (4096 x 4096 weights: 16 workgroups) and computes padding rows.
+//
+// A workgroup owns 16 columns; its eight wavefronts share the reduction out in 128-byte pieces (together 1 KB of every
+// row per step) and add their sums through LDS, so 4096 columns are 256 workgroups with up to 16 16-byte loads of B per lane
+// in flight.  Nothing is staged: a lane's 16 bytes along k are a matrix instruction's fragment as they are, for
+// both operands; A (a few rows) comes from L2.  Rows, columns and k beyond the operand load zeros (buffer range).
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <type_traits>
+
+#include "kernels.hpp"
+
+namespace stripe {
+namespace {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+constexpr uint32_t kOutside = 0x80000000u, kRecords = 0x7fffffffu;
+constexpr int kWaves = 8, kCols = 16, kMaxRows = 32;
+
+template <typename T>
+__device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c) {
+  if constexpr (sizeof(T) == 2) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  } else {
+    const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[i], c, 0, 0, 0);
+    return c;
+  }
+}
+template <typename T>
+__device__ __forceinline__ i32x4 mma(u32x4 a, u32x4 b, i32x4 c) {
+  return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0, 0);
+}
+
+// epilogue: 0 sums; 2 relu(sum + bias[n]) in fp32; 3 the same in bf16
+template <typename T, int FM, int UNROLL>
+__global__ __launch_bounds__(64 * kWaves) void rows_kernel(const T* __restrict__ A, const T* __restrict__ B, void* __restrict__ C, const float* __restrict__ bias,
+                                                           uint32_t M, uint32_t N, uint32_t k_bytes, uint32_t a_row, uint32_t b_row, int64_t c_row,
+                                                           int epilogue, int vec_out) {
+  using Acc = typename std::conditional<sizeof(T) == 1, i32x4, f32x4>::type;
+  using S = typename std::conditional<sizeof(T) == 1, int32_t, float>::type;
+  __shared__ Acc part[kWaves][FM][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = lane & 15;
+  const uint32_t n0 = blockIdx.x * kCols;
+  const __amdgpu_buffer_rsrc_t buf_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, kRecords, 0x00020000);
+  const __amdgpu_buffer_rsrc_t buf_b = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, kRecords, 0x00020000);
+  const bool b_in = n0 + row < N;
+  const uint32_t b_off = (n0 + row) * b_row;
+  uint32_t a_off[FM];
+  bool a_in[FM];
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    a_in[i] = (uint32_t)(i * 16 + row) < M;
+    a_off[i] = (i * 16 + row) * a_row;
+  }
+  Acc acc[FM];
+#pragma unroll
+  for (int i = 0; i < FM; ++i) acc[i] = (Acc){0, 0, 0, 0};
+  uint32_t at = wave * 128 + (lane >> 4) * 16;
+  const uint32_t steps = (k_bytes + kWaves * 128 - 1) / (kWaves * 128);
+  for (uint32_t s = 0; s < steps; s += UNROLL) {
+    u32x4 b[2 * UNROLL], a[2 * UNROLL][FM];
+#pragma unroll
+    for (int u = 0; u < 2 * UNROLL; ++u) {      // piece u / 2 of the unrolled steps, its lower or upper 64 bytes
+      const uint32_t k = at + u / 2 * (kWaves * 128) + u % 2 * 64;
+      b[u] = __builtin_amdgcn_raw_buffer_load_b128(buf_b, b_in && k < k_bytes ? b_off + k : kOutside, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 2 * UNROLL; ++u) {
+      const uint32_t k = at + u / 2 * (kWaves * 128) + u % 2 * 64;
+#pragma unroll
+      for (int i = 0; i < FM; ++i) a[u][i] = __builtin_amdgcn_raw_buffer_load_b128(buf_a, a_in[i] && k < k_bytes ? a_off[i] + k : kOutside, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);          // all loads of the unrolled steps are issued before the first is waited for
+#pragma unroll
+    for (int u = 0; u < 2 * UNROLL; ++u)
+#pragma unroll
+      for (int i = 0; i < FM; ++i) acc[i] = mma<T>(b[u], a[u][i], acc[i]);     // rows of the result: n
+    at += UNROLL * kWaves * 128;
+  }
+#pragma unroll
+  for (int i = 0; i < FM; ++i) part[wave][i][lane] = acc[i];
+  __syncthreads();
+  if (wave >= FM) return;
+  Acc sum = part[0][wave][lane];
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) sum += part[w][wave][lane];
+  const uint32_t m = wave * 16 + row, n = n0 + (lane >> 4) * 4;
+  if (m >= M) return;
+  S v[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    v[e] = sum[e];
+    if constexpr (std::is_same<S, float>::value) {
+      if (epilogue && n + e < N) {
+        const float y = v[e] + bias[n + e];
+        v[e] = y > 0.f ? y : 0.f;
+      }
+    }
+  }
+  const int64_t off = (int64_t)m * c_row + n;
+  if (vec_out && n + 4 <= N) {
+    typedef S s4 __attribute__((ext_vector_type(4)));
+    if (epilogue == 3) *(bf16x4*)((uint16_t*)C + off) = __builtin_convertvector((f32x4){(float)v[0], (float)v[1], (float)v[2], (float)v[3]}, bf16x4);
+    else *(s4*)((S*)C + off) = (s4){v[0], v[1], v[2], v[3]};
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < N) {
+        if (epilogue == 3) ((__bf16*)C)[off + e] = (__bf16)(float)v[e];
+        else ((S*)C)[off + e] = v[e];
+      }
+  }
+}
+
+template <typename T>
+hipError_t launch_t(const GemmShape& g, const void* a, const void* b, void* c, const float* bias, int epi, int64_t c_row, int vec, hipStream_t s) {
+  const dim3 grid((unsigned)((g.N + kCols - 1) / kCols)), wg(64 * kWaves);
+  const T *pa = (const T*)a + g.a_base, *pb = (const T*)b + g.b_base;
+  const uint32_t e = sizeof(T);
+  if (g.M <= 16)
+    hipLaunchKernelGGL((rows_kernel<T, 1, 8>), grid, wg, 0, s, pa, pb, c, bias, (uint32_t)g.M, (uint32_t)g.N, (uint32_t)g.K * e, (uint32_t)g.a_m * e,
+                       (uint32_t)g.b_n * e, c_row, epi, vec);
+  else
+    hipLaunchKernelGGL((rows_kernel<T, 2, 4>), grid, wg, 0, s, pa, pb, c, bias, (uint32_t)g.M, (uint32_t)g.N, (uint32_t)g.K * e, (uint32_t)g.a_m * e,
+                       (uint32_t)g.b_n * e, c_row, epi, vec);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool gemm_rows_select(const GemmShape& g, int in_dtype, RowsLaunch* l, stripe_block_info_t* info) {
+  l->use = false;
+  if (!tune_int("gemm_rows", 1)) return false;
+  if (in_dtype != STRIPE_BF16 && in_dtype != STRIPE_I8 && in_dtype != STRIPE_F32) return false;
+  const int64_t e = in_dtype == STRIPE_F32 ? 4 : in_dtype == STRIPE_BF16 ? 2 : 1;
+  // both operands k-contiguous, whole 16-byte pieces of k (rows at any element: buffer loads need no more), one product
+  if (g.a_k != 1 || g.b_k != 1 || g.c_n != 1 || g.batch != 1 || g.M > kMaxRows || g.K * e % 16) return false;
+  // at least one piece for each wavefront; operands within a buffer's range
+  if (g.K * e < 1024 || g.N > 0x3fffffff || g.a_m > (1 << 24) || g.b_n > (1 << 26)) return false;
+  const __int128 a_end = ((__int128)(g.M - 1) * g.a_m + g.K) * e, b_end = ((__int128)(g.N - 1) * g.b_n + g.K) * e;
+  if (a_end > 0x7fffff00 || b_end > 0x7fffff00) return false;
+  l->use = true;
+  info->tile_m = g.M <= 16 ? 16 : 32; info->tile_n = kCols; info->tile_k = (int)(kWaves * 128 / e);
+  info->frag_m = info->frag_n = 16; info->frag_k = in_dtype == STRIPE_F32 ? 4 : (int)(64 / e);
+  info->lds_bytes = kWaves * (g.M <= 16 ? 1 : 2) * 1024;
+  info->workgroup_size = 64 * kWaves;
+  info->grid = (g.N + kCols - 1) / kCols;
+  std::snprintf(info->kernel, sizeof info->kernel, "gemm_rows_%s_%dx16_w8", in_dtype == STRIPE_F32 ? "f32" : in_dtype == STRIPE_BF16 ? "bf16" : "i8",
+                g.M <= 16 ? 16 : 32);
+  return true;
+}
+
+hipError_t launch_gemm_rows(const GemmShape& g, int in_dtype, const void* a, const void* b, void* c, int64_t c_row, int64_t c_base, const float* bias,
+                            bool out_bf16, hipStream_t stream) {
+  const int epi = bias ? (out_bf16 ? 3 : 2) : 0;
+  void* out = (char*)c + c_base * (out_bf16 ? 2 : 4);
+  const int vec = c_row % 4 == 0 && (uintptr_t)out % (out_bf16 ? 8 : 16) == 0;
+  switch (in_dtype) {
+    case STRIPE_I8: return launch_t<int8_t>(g, a, b, out, bias, epi, c_row, vec, stream);
+    case STRIPE_BF16: return launch_t<uint16_t>(g, a, b, out, bias, epi, c_row, vec, stream);
+    default: return launch_t<float>(g, a, b, out, bias, epi, c_row, vec, stream);
+  }
+}
+
+}  // namespace stripe

@@ -47,6 +47,14 @@ bool gemm_can_fuse_bias_relu(const GemmShape& g, const GemmLaunch& l);
 hipError_t launch_gemm_bias_relu(const GemmShape& g, const GemmLaunch& l, const void* a, const void* b, const void* bias, void* out,
                                  int64_t o_m, int64_t o_base, bool out_bf16, hipStream_t stream);
 
+// products with at most 32 rows and k-contiguous operands (gemm_rows.hip); bias != nullptr: O = relu(C + bias[n])
+struct RowsLaunch {
+  bool use = false;
+};
+bool gemm_rows_select(const GemmShape& g, int in_dtype, RowsLaunch* l, stripe_block_info_t* info);
+hipError_t launch_gemm_rows(const GemmShape& g, int in_dtype, const void* a, const void* b, void* c, int64_t c_row, int64_t c_base, const float* bias,
+                            bool out_bf16, hipStream_t stream);
+
 // ---- nested-tile convolution-shaped contraction on matrix cores -----------
 constexpr int kConvIgemmVariant = 300;   // general convolution kernel; 300: 128 x 128 tiles, 301: 256 x 64, 302: 256 x 128
 constexpr int kConvGemmVariant = 400;    // large convolutions on the 256 x 256-tile contraction kernel's convolution mode

@@ -1,4 +1,4 @@
-"""The general matrix-core contraction against the oracle, at the edges of their tiles and fetch
+"""The general matrix-core contraction and the few-rows product against the oracle, at the edges of their tiles and fetch
 forms.  Tolerances as in tests/util.py; integers bit-exact, elements no iteration writes untouched."""
 import math
 import random
@@ -54,7 +54,7 @@ def matmul(M, N, K, dt, layout):
                                         (64, 64, 256, 1), (40, 36, 15, 2), (72, 8, 16, 1)])
 def test_products(M, N, K, tile, layout, dt, monkeypatch):
     """Edges of tiles, K remainders inside one vector, operands with fewer rows than a vector, unaligned rows."""
-    monkeypatch.setenv("STRIPE_TUNE", f"contract_min=1,contract_tile={tile}")
+    monkeypatch.setenv("STRIPE_TUNE", f"contract_min=1,contract_tile={tile},gemm_rows=0")
     blk = matmul(M, N, K, dt, layout)
     ins = [W.seeded_tensor(blk.refs[0].sizes, dt, 0), W.seeded_tensor(blk.refs[1].sizes, dt, 1)]
     parity(blk, ins, what=f"{layout} {M}x{N}x{K} {dt}")
@@ -100,6 +100,33 @@ def test_infinities_at_removed_points(dt, monkeypatch):
     assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want)) and np.isinf(want).any()
     fin = np.isfinite(want)
     assert 0 < fin.sum() and np.allclose(got[fin], want[fin], rtol=1e-5, atol=1e-4)     # 54 products of order 1 in fp32: 54 * 2^-24 * sum |a b|
+
+
+@pytest.mark.parametrize("in_dt,out_dt", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32"), ("f32", "bf16")])
+@pytest.mark.parametrize("M,N,K", [(5, 33, 1024), (16, 16, 520), (17, 40, 512), (32, 130, 2064), (8, 1, 1040)])
+def test_few_rows(M, N, K, in_dt, out_dt):
+    """Both row counts of the kernel, columns beyond the tile, a reduction that ends inside a step; with bias + relu."""
+    if K * (2 if in_dt == "bf16" else 4) < 1024:
+        K *= 2
+    prog = W.linear_bias_relu_program(M, N, K, out_dt, b_transposed=True) if in_dt == "bf16" else None
+    blk = matmul(M, N, K, in_dt, "nt")
+    ins = [W.seeded_tensor((M, K), in_dt, 0), W.seeded_tensor((N, K), in_dt, 1)]
+    info, _ = parity(blk, ins, what="few rows")
+    assert N == 1 or info["kernel"].startswith("gemm_rows_"), info
+    if prog is not None:
+        bias = W.seeded_tensor((N,), "f32", 2)
+        got, sb = run_gpu(prog, ins + [bias], return_block=True)
+        want = torch.relu(ins[0].double() @ ins[1].double().t() + bias.double()).numpy().ravel()
+        # fp32 sums of K products, one rounding to bf16 on a bf16 store
+        tol = K * 2.0 ** -24 * (ins[0].double().abs() @ ins[1].double().abs().t()).numpy().ravel() + 1e-5 + (2.0 ** -8 * want if out_dt == "bf16" else 0)
+        assert np.all(np.abs(got - want) <= tol), sb.info["kernel"]
+        assert N == 1 or sb.info["kernel"].endswith("+bias_relu"), sb.info
+
+
+def test_few_rows_int8():
+    blk = matmul(9, 50, 2048, "i8", "nt")
+    info, _ = parity(blk, [W.seeded_tensor((9, 2048), "i8", 0), W.seeded_tensor((50, 2048), "i8", 1)], what="few rows int8")
+    assert info["kernel"].startswith("gemm_rows_i8"), info
 
 
 @pytest.mark.parametrize("out_dt", ["bf16", "f32"])
