@@ -567,7 +567,11 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
       }
       generic_info(p, &p.info);
       // without a forced path, sum-of-products blocks of the generic path run on the matrix cores
-      if (!forced && !(p.is_gemm && gemm_rows_select(p.gemm, p.in_dtype, &blk->rows, &p.info))) contract_select(p.flat, &blk->contract, &p.info);
+      // -- but where a wavefront per output walks its reduction in two steps and the block is small, the literal kernel's short
+      // prologue wins (3x3, 8 -> 16 channels at 16 x 16, fp32: 7.0 us against 7.2 to 8.0)
+      const bool literal = !p.tiled.use && p.gen.lanes == 64 && p.gen.red_total <= 128 && p.info.hull_points < (1 << 19) && tune_int("contract_min", 65536) == 65536;
+      if (!forced && !(p.is_gemm && gemm_rows_select(p.gemm, p.in_dtype, &blk->rows, &p.info)) && !literal)
+        contract_select(p.flat, &blk->contract, &p.info);
     } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM && gemm_rows_select(p.gemm, p.in_dtype, &blk->rows, &p.info)) {
       blk->gemm.ws_bytes = 0;    // no partial sums of a split reduction
     }
