@@ -654,6 +654,14 @@ const char* stripe_status_string(stripe_status_t status) {
 
 const char* stripe_last_error(void) { return g_last_error.c_str(); }
 
+// For the host tests, which follow the general contraction's fetches on the CPU: its launch parameters for a planned block.
+// Returns their size (0: the block runs on another kernel) and copies them if `size` is that large.  Not part of the API.
+size_t stripe_test_contract_params(const stripe_block_t* blk, void* out, size_t size) {
+  if (!blk || !blk->contract.use) return 0;
+  if (out && size >= sizeof(ContractParams)) std::memcpy(out, &blk->contract.p, sizeof(ContractParams));
+  return sizeof(ContractParams);
+}
+
 stripe_status_t stripe_device_copy(const void* src, void* dst, size_t n_bytes, void* hip_stream) {
   if (!src || !dst) return fail(STRIPE_ERR_NULL, "src or dst is NULL");
   if (n_bytes % 16 || ((uintptr_t)src % 16) || ((uintptr_t)dst % 16))

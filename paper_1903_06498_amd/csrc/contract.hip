@@ -11,7 +11,9 @@
 //
 // A workgroup of four wavefronts owns a BM x BN tile.  Operands are fetched through buffer loads: a point outside the
 // polyhedron or the tile's remainder gets an offset beyond the buffer's range and the load returns zero, so no select
-// follows.  Three ways to fetch, chosen per operand by the planner: 16 bytes along k; vectors along the row index, turned
+// follows.  The range is the operand's declared buffer: a constraint is tested for one operand (that suffices for the
+// sum, one factor is zero), so the other one may be fetched at a removed point, where its address is not the block's to
+// read.  It is then fetched element by element, and an element outside the buffer loads as zero.  Three ways to fetch, chosen per operand by the planner: 16 bytes along k; vectors along the row index, turned
 // to k order in registers; or element by element with neighbouring lanes on neighbouring k.  Tiles go registers -> LDS
 // (two buffers, one barrier per K tile) in rows of BKB bytes + 16, which spreads the 16 rows of a fragment read over all
 // banks; the loads of the next K tile are in flight during the matrix instructions.  A 16-byte fragment is one
@@ -39,7 +41,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 constexpr int kFar = -0x40000000;          // a range-test value no other part can bring back into range
 [[maybe_unused]] constexpr uint32_t kTop = 0x3fffffffu;     // "no upper end"
 constexpr uint32_t kOutside = 0x80000000u; // byte offset beyond every buffer's range: the load returns zero
-constexpr uint32_t kRecords = 0x7fffffffu;
+[[maybe_unused]] constexpr uint32_t kRecords = 0x7fffffffu; // largest range of a buffer
 
 __device__ __forceinline__ uint32_t fast_div(uint32_t v, uint32_t mul, int shift) { return __umulhi(v, mul) >> shift; }
 
@@ -157,7 +159,7 @@ struct Stager {
       }
     } else if constexpr (MODE == 3) {
       const i32x4 kp = ks[(tid % CH3) * VE3];
-      const uint32_t last = SIDE_A ? p.last_a : p.last_b;
+      const uint32_t last = (SIDE_A ? p.bytes_a : p.bytes_b) - 8;
       mask = kp[3] >= VE3 ? ~0ull : kp[3] <= 0 ? 0ull : (1ull << (8 * E * kp[3])) - 1;
 #pragma unroll
       for (int i = 0; i < DW / 2; ++i) {
@@ -359,8 +361,8 @@ __global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, c
   }
   __syncthreads();
 
-  const __amdgpu_buffer_rsrc_t buf_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, kRecords, 0x00020000);
-  const __amdgpu_buffer_rsrc_t buf_b = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, kRecords, 0x00020000);
+  const __amdgpu_buffer_rsrc_t buf_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)p.bytes_a, 0x00020000);
+  const __amdgpu_buffer_rsrc_t buf_b = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, (int)p.bytes_b, 0x00020000);
   Stager<T, BM, BKB, true, MA> sa[2];      // K tiles t and t + 1 on their way
   Stager<T, BN, BKB, false, MB> sb[2];
   const uint32_t n_kt = (p.K + BK - 1) / BK;
@@ -828,22 +830,24 @@ bool contract_select(const FlatBlock& fb, ContractLaunch* l, stripe_block_info_t
 
   ContractParams& p = l->p;
   std::memset(&p, 0, sizeof p);
-  // Byte offset of the last 8 bytes an operand holds (its declared buffer's end, or the last address the block can form if
-  // that comes first); false if it holds fewer.
-  auto last_byte = [&](bool a, ContractParams& q) {
-    const FlatRef& r = fb.ref[(a != l->swap) ? 0 : 1];
-    i128 first = r.addr.k, end = 0, hull = r.addr.k;
+  // The range of each operand's fetches: its declared buffer, or the hull's last address if that comes first.
+  int64_t first[2];
+  for (int side = 0; side < 2; ++side) {
+    const FlatRef& r = fb.ref[(side == 0) != l->swap ? 0 : 1];
+    i128 origin = r.addr.k, end = 0, hull = r.addr.k;
     for (int d = 0; d < r.ndim; ++d) {
-      first -= (i128)r.coord[d].k * r.strides[d];
+      origin -= (i128)r.coord[d].k * r.strides[d];
       end += (i128)(r.sizes[d] - 1) * r.strides[d];
     }
     for (int j = 0; j < fb.n_idx; ++j)
       if (r.addr.c[j] > 0) hull += (i128)r.addr.c[j] * (fb.range[j] - 1);
-    end = std::min(first + end, hull) + 1;
-    if (first < 0 || (end - first) * esize < 8) return false;
-    (a ? q.last_a : q.last_b) = (uint32_t)(end * esize - 8);
-    return true;
-  };
+    end = std::min(end, hull - origin) + 1;
+    if (origin < 0 || origin > lim / esize || end < 1) return false;
+    first[side] = (int64_t)origin;
+    (side == 0 ? p.bytes_a : p.bytes_b) = (uint32_t)std::min(end * esize, (i128)kRecords);
+  }
+  l->first_a = first[0];
+  l->first_b = first[1];
   if (!fill_side(m, &p.m) || !fill_side(n, &p.n) || !fill_side(k, &p.k)) return false;
   i128 M = 1, N = 1, K = 1;
   for (const Ix& x : m) M *= x.range;
@@ -865,7 +869,7 @@ bool contract_select(const FlatBlock& fb, ContractLaunch* l, stripe_block_info_t
     p.k_a[j] = (int32_t)k[j].a;
     p.k_b[j] = (int32_t)k[j].b;
   }
-  p.a_base = (int32_t)base_a; p.b_base = (int32_t)base_b; p.o_base = (int32_t)fb.ref[2].addr.k;
+  p.a_base = (int32_t)(base_a - first[0]); p.b_base = (int32_t)(base_b - first[1]); p.o_base = (int32_t)fb.ref[2].addr.k;
   p.batch_range[0] = p.batch_range[1] = 1;
   l->batch = 1;
   for (size_t j = 0; j < bat.size(); ++j) {
@@ -877,10 +881,36 @@ bool contract_select(const FlatBlock& fb, ContractLaunch* l, stripe_block_info_t
   p.n_ob_used = n_ob;     // unused bounds: 0 <= 0
   for (int t = 0; t < kCtTests; ++t) p.ob[t] = (int32_t)ob[t];
 
-  // constraints -> range tests of one operand; a pair f + c >= 0, -f + d >= 0 is one test
+  // constraints -> range tests; a pair f + c >= 0, -f + d >= 0 is one test.  A test with a column index goes to B, any
+  // other to A; one over reduction indexes alone can guard both.
   for (int t = 0; t < kCtTests; ++t) p.top_a[t] = p.top_b[t] = kTop;
   int used_a = 0, used_b = 0;
   std::vector<char> done(n_con, 0);
+  std::vector<Affine> guards_a, guards_b;                   // the block's own constraints that an operand is tested for
+  struct KTest {
+    size_t q;
+    int64_t top;
+    std::vector<size_t> members;
+  };
+  std::vector<KTest> k_only;
+  auto add_a = [&](size_t q, int64_t top) {
+    if (used_a >= kCtTests) return false;
+    p.c_a[used_a] = (int32_t)con_k[q];
+    p.top_a[used_a] = (uint32_t)top;
+    for (size_t j = 0; j < m.size(); ++j) p.m_t[used_a][j] = (int32_t)m[j].con[q];
+    for (size_t j = 0; j < k.size(); ++j) p.ka_t[used_a][j] = (int32_t)k[j].con[q];
+    ++used_a;
+    return true;
+  };
+  auto add_b = [&](size_t q, int64_t top) {
+    if (used_b >= kCtTests) return false;
+    p.c_b[used_b] = (int32_t)con_k[q];
+    p.top_b[used_b] = (uint32_t)top;
+    for (size_t j = 0; j < n.size(); ++j) p.n_t[used_b][j] = (int32_t)n[j].con[q];
+    for (size_t j = 0; j < k.size(); ++j) p.kb_t[used_b][j] = (int32_t)k[j].con[q];
+    ++used_b;
+    return true;
+  };
   for (size_t q = 0; q < n_con; ++q) {
     if (done[q]) continue;
     bool in_m = false, in_n = false;
@@ -890,33 +920,36 @@ bool contract_select(const FlatBlock& fb, ContractLaunch* l, stripe_block_info_t
       if (x.con[q]) return false;
     if (in_m && in_n) return false;
     int64_t top = kTop;
+    std::vector<size_t> members{q};
     for (size_t r = q + 1; r < n_con; ++r) {
       bool opposite = !done[r];
       for (const Ix& x : ix) opposite = opposite && x.con[r] == -x.con[q];
       if (opposite) {
         done[r] = 1;
         top = std::min(top, con_k[q] + con_k[r]);
+        members.push_back(r);
       }
     }
     if (top < 0) return false;
-    int& used = in_n ? used_b : used_a;
-    if (used >= kCtTests) return false;
-    if (in_n) {
-      p.c_b[used] = (int32_t)con_k[q];
-      p.top_b[used] = (uint32_t)top;
-      for (size_t j = 0; j < n.size(); ++j) p.n_t[used][j] = (int32_t)n[j].con[q];
-      for (size_t j = 0; j < k.size(); ++j) p.kb_t[used][j] = (int32_t)k[j].con[q];
-    } else {
-      p.c_a[used] = (int32_t)con_k[q];
-      p.top_a[used] = (uint32_t)top;
-      for (size_t j = 0; j < m.size(); ++j) p.m_t[used][j] = (int32_t)m[j].con[q];
-      for (size_t j = 0; j < k.size(); ++j) p.ka_t[used][j] = (int32_t)k[j].con[q];
-    }
-    ++used;
+    if (!(in_n ? add_b(q, top) : add_a(q, top))) return false;
+    for (size_t r : members)
+      if (r < first_new) (in_n ? guards_b : guards_a).push_back(fb.cons[r]);
+    if (!in_m && !in_n) k_only.push_back({q, top, members});
+  }
+  // Does an operand stay inside its buffer under its own tests?  (The rewritten pairs' tests restore the block's own ranges.)
+  const int ref_a = l->swap ? 1 : 0, ref_b = 1 - ref_a;
+  const bool inside_a = access_inside(fb, ref_a, guards_a);
+  bool inside_b = access_inside(fb, ref_b, guards_b);
+  for (size_t t = 0; t < k_only.size() && !inside_b; ++t) {
+    if (!add_b(k_only[t].q, k_only[t].top)) break;
+    for (size_t r : k_only[t].members)
+      if (r < first_new) guards_b.push_back(fb.cons[r]);
+    inside_b = access_inside(fb, ref_b, guards_b);
   }
   p.tested = used_a + used_b > 0;
 
-  // How each operand is fetched.  A vector needs its elements neighbours and under the same tests, and stays inside one
+  // How each operand is fetched.  An operand that may leave its buffer at a removed point is fetched element by element
+  // (an element is inside the buffer's range or it is not; a vector could straddle its end).  A vector needs its elements neighbours and under the same tests, and stays inside one
   // run of its innermost index: the run is a multiple of the vector, or the side has one index only of at least a vector,
   // whose end is fetched as an overlapping vector.  (Buffer loads take any element alignment.)  Where no 16-byte vector fits
   // the innermost reduction index (three or 24 channels), 8-byte vectors do, with that index's range padded to whole
@@ -924,6 +957,7 @@ bool contract_select(const FlatBlock& fb, ContractLaunch* l, stripe_block_info_t
   // four elements of k.
   const int ve = 16 / esize, ve3 = 8 / esize, vr = dt == STRIPE_F32 ? 4 : 8;
   auto fetch = [&](bool a) {
+    if (!(a ? inside_a : inside_b)) return 0;
     const Ix& k0 = k[0];
     const std::vector<Ix>& row = a ? m : n;
     bool k_tests = false, row_tests = false;
@@ -934,7 +968,7 @@ bool contract_select(const FlatBlock& fb, ContractLaunch* l, stripe_block_info_t
     const bool k_unit = (a ? k0.a : k0.b) == 1 && !k_tests;
     if (k_unit && ((k.size() == 1 && k0.range >= ve) || k0.range % ve == 0)) return 1;
     if ((a ? row[0].a : row[0].b) == 1 && !row_tests && ((row.size() == 1 && row[0].range >= vr) || row[0].range % vr == 0)) return 2;
-    if (k_unit && last_byte(a, p) && k0.range > 1) return 3;
+    if (k_unit && (a ? p.bytes_a : p.bytes_b) >= 8 && k0.range > 1) return 3;
     return 0;
   };
   p.mode_a = fetch(true);
@@ -999,7 +1033,8 @@ hipError_t launch_contract(const ContractLaunch& l, int in_dtype, const void* in
   ContractParams p = l.p;
   if (bias) p.epilogue = out_bf16 ? 3 : 2;
   if ((uintptr_t)out % ((p.epilogue & 1) ? 8 : 16)) p.vec_out = 0;
-  const void *a = l.swap ? in1 : in0, *b = l.swap ? in0 : in1;
+  const int64_t esize = in_dtype == STRIPE_F32 ? 4 : in_dtype == STRIPE_BF16 ? 2 : 1;
+  const void *a = (const char*)(l.swap ? in1 : in0) + l.first_a * esize, *b = (const char*)(l.swap ? in0 : in1) + l.first_b * esize;
   switch (in_dtype) {
     case STRIPE_I8: return launch_contract_i8(l, p, a, b, out, bias, stream);
     case STRIPE_BF16: return launch_contract_bf16(l, p, a, b, out, bias, stream);

@@ -33,7 +33,7 @@ struct ContractParams {
   int32_t mode_a, mode_b;       // how an operand is fetched: 0 element by element, 1 16 bytes along k, 2 vectors along its row index,
                                 // 3 8 bytes along k, the innermost reduction index padded to whole vectors
   int32_t k_run;                // the innermost reduction index's range without that padding
-  uint32_t last_a, last_b;      // mode 3: byte offset of an operand's last 8 bytes
+  uint32_t bytes_a, bytes_b;    // an operand's declared buffer (from its origin) in bytes: no fetch goes beyond it
   int32_t vec_out;              // 1: four neighbouring outputs of a lane are one 16-byte (8-byte) store
   uint32_t batch_range[2];
   int32_t batch_a[2], batch_b[2], batch_o[2];
@@ -46,6 +46,7 @@ struct ContractLaunch {
   bool swap = false;            // the block's second operand plays A
   int tile = 0;                 // index into the kernel's tile table
   int64_t grid = 0, batch = 1;
+  int64_t first_a = 0, first_b = 0;   // an operand's buffer origin, in elements from the caller's pointer (a_base, b_base count from it)
   ContractParams p;
 };
 

@@ -87,7 +87,7 @@ bool for_each_point(const FlatBlock& fb, const std::vector<int>& sel, F f) {
 // Is `a >= 0` at every point of the polyhedron?  Interval bound first, then the
 // bound relative to one constraint (a = cons + (a - cons) with cons >= 0), then
 // enumeration of the indexes involved when that is small.
-bool prove_nonneg(const FlatBlock& fb, const Affine& a) {
+bool prove_nonneg(const FlatBlock& fb, const Affine& a, int64_t cap = (int64_t)1 << 24) {
   if (lo_of(fb, a) >= 0) return true;
   for (const Affine& q : fb.cons) {
     Affine d = a;
@@ -106,7 +106,7 @@ bool prove_nonneg(const FlatBlock& fb, const Affine& a) {
     if (used[j]) {
       sel.push_back(j);
       pts *= fb.range[j];
-      if (pts > ((i128)1 << 24)) return false;
+      if (pts > cap) return false;
     }
   return for_each_point(fb, sel, [&](const int64_t* idx) {
     for (const Affine& q : fb.cons)
@@ -297,6 +297,19 @@ stripe_status_t prove_checks(const FlatBlock& fb, std::string* err) {
                  fmt("refinement %lld dim %lld: cannot prove the access stays inside the view of level %lld", ck.ref, ck.dim, ck.level));
   }
   return STRIPE_OK;
+}
+
+bool access_inside(const FlatBlock& fb, int ref, const std::vector<Affine>& cons) {
+  FlatBlock box = fb;
+  box.cons = cons;
+  const FlatRef& r = fb.ref[ref];
+  for (int d = 0; d < r.ndim; ++d) {
+    Affine up = zero_affine();
+    add_scaled(&up, r.coord[d], -1);
+    up.k += r.sizes[d] - 1;
+    if (!prove_nonneg(box, r.coord[d], (int64_t)1 << 16) || !prove_nonneg(box, up, (int64_t)1 << 16)) return false;
+  }
+  return true;
 }
 
 // A level whose output aggregation is 'assign' promises that its iterations

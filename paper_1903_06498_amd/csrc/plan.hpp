@@ -151,6 +151,9 @@ bool match_conv2d(const FlatBlock& fb, Conv2dShape* c);
 bool match_pool2d(const FlatBlock& fb, Pool2dShape* p);
 
 int64_t count_points(const FlatBlock& fb, int64_t enumeration_cap);
+// Does refinement `ref` stay inside its declared buffer at every point of the ranges' box that meets `cons`?  (Proof by
+// intervals, by one constraint, or by enumerating up to 2^16 points; false where none of them decides.)
+bool access_inside(const FlatBlock& fb, int ref, const std::vector<Affine>& cons);
 void address_form(const FlatBlock& fb, size_t target, std::vector<int64_t>* rng, std::vector<int64_t>* ca, std::vector<int64_t>* cb,
                   std::vector<int64_t>* cc);
 

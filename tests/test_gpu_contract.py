@@ -11,6 +11,7 @@ from oracle import stripe_oracle as O
 from paper_1903_06498_amd import binding as B
 from paper_1903_06498_amd import workloads as W
 from tests import brute
+from tests.test_contract_fetch import PARTNERS
 from tests.util import SENTINEL_I, parity, run_gpu
 
 pytestmark = pytest.mark.gpu
@@ -100,6 +101,30 @@ def test_infinities_at_removed_points(dt, monkeypatch):
     assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want)) and np.isinf(want).any()
     fin = np.isfinite(want)
     assert 0 < fin.sum() and np.allclose(got[fin], want[fin], rtol=1e-5, atol=1e-4)     # 54 products of order 1 in fp32: 54 * 2^-24 * sum |a b|
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("make", PARTNERS)
+def test_partner_operand_ends_with_the_polyhedron(make, dt, monkeypatch):
+    """Nothing behind an operand enters the result: the operands lie at the front of larger tensors, whose rest is once zero
+    and once NaN; the results are the same bits, and the oracle's."""
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1")
+    blk = make(dt)
+    ins = [W.seeded_tensor(r.sizes, dt, i) for i, r in enumerate(blk.refs[:2])]
+    info, _ = parity(blk, ins, what=make.__name__)
+    assert info["kernel"].startswith("contract_"), info
+    sb, images = B.StripeBlock(blk), []
+    for rest in (0.0, math.nan):
+        held = []
+        for t in ins:
+            big = torch.full((t.numel() + (1 << 20),), rest, dtype=t.dtype, device="cuda")
+            big[:t.numel()] = t.reshape(-1).cuda()
+            held.append(big)
+        out = torch.zeros(W.output_extent(blk), dtype=torch.float32, device="cuda")
+        sb.run(held, out)
+        images.append(out.view(torch.int32).cpu().numpy())
+    sb.close()
+    assert np.array_equal(images[0], images[1])
 
 
 @pytest.mark.parametrize("in_dt,out_dt", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32"), ("f32", "bf16")])
