@@ -40,6 +40,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFar = -0x40000000;          // a range-test value no other part can bring back into range
 [[maybe_unused]] constexpr uint32_t kTop = 0x3fffffffu;     // "no upper end"
+constexpr int kNoStore = 0x3fffffff;       // a part of an output bound that no bound reaches, alone or twice
 constexpr uint32_t kOutside = 0x80000000u; // byte offset beyond every buffer's range: the load returns zero
 [[maybe_unused]] constexpr uint32_t kRecords = 0x7fffffffu; // largest range of a buffer
 
@@ -335,12 +336,13 @@ __global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, c
     const bool am = i < BM;
     uint32_t at = am ? m0 + i : n0 + i - BM;
     // Vectors along the row index: the operand's last, partial group of V rows starts V rows before its end instead.  The
-    // rows it shares with the group before are computed and stored twice, with the same bits.
+    // rows it shares with the group before are computed twice.  Where that group is another workgroup's, only that one
+    // stores them (the two may differ in rounding: one of them may have summed its tile again, see below).
     constexpr uint32_t V = Ct<T>::V;
     const uint32_t end = am ? p.M : p.N;
     if ((am ? MA : MB) == 2 && at / V * V < end && at / V * V + V > end) at = end - V + at % V;
     i32x4 e = {am ? a_base : b_base, am ? p.c_a[0] : p.c_b[0], am ? p.c_a[1] : p.c_b[1], 0};
-    int2 ob = {0, 0};
+    int2 ob = {at < (am ? m0 : n0) ? kNoStore : 0, 0};
     if (am) {
       decode(p.m, at, [&](int j, int v) {
         e[0] += p.m_in[j] * v; e[1] += p.m_t[0][j] * v; e[2] += p.m_t[1][j] * v; e[3] += p.m_out[j] * v;

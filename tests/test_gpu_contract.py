@@ -127,6 +127,25 @@ def test_partner_operand_ends_with_the_polyhedron(make, dt, monkeypatch):
     assert np.array_equal(images[0], images[1])
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_rows_of_two_tiles_have_one_owner(dt, monkeypatch):
+    """66 rows fetched in vectors along the rows: the last vector starts two (bf16: six) rows before the third tile of 32.  An
+    infinity in row 65 has that tile summed again; the rows of the tile before keep the bits they have without it."""
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1,contract_tile=2")
+    m, n, k = 66, 40, 200
+    bufs = [W.Buffer("A", "in", dt, (k, m)), W.Buffer("B", "in", dt, (k, n)), W.Buffer("C", "out", "f32", (m, n))]
+    blk = W.flat_block(bufs, dict(m=m, n=n, k=k), [(["k", "m"], "assign"), (["k", "n"], "assign"), (["m", "n"], "add")],
+                       constraints=[f"{k + n - 21} - n - k >= 0"])
+    ins = [W.seeded_tensor((k, m), dt, 0), W.seeded_tensor((k, n), dt, 1)]
+    clean, sb = run_gpu(blk, ins, return_block=True)
+    assert sb.info["kernel"].startswith("contract_") and "_fetch2" in sb.info["kernel"], sb.info
+    ins[0][3, 65] = math.inf
+    for _ in range(3):
+        got = run_gpu(blk, ins)
+        assert np.isinf(got.reshape(m, n)[65]).all()
+        assert np.array_equal(got.reshape(m, n)[:64].view(np.int32), clean.reshape(m, n)[:64].view(np.int32))
+
+
 @pytest.mark.parametrize("in_dt,out_dt", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32"), ("f32", "bf16")])
 @pytest.mark.parametrize("M,N,K", [(5, 33, 1024), (16, 16, 520), (17, 40, 512), (32, 130, 2064), (8, 1, 1040)])
 def test_few_rows(M, N, K, in_dt, out_dt):
