@@ -167,6 +167,24 @@ def test_few_rows(M, N, K, in_dt, out_dt):
         assert N == 1 or sb.info["kernel"].endswith("+bias_relu"), sb.info
 
 
+def error_against_64_bits(blk, ins, want, path="auto"):
+    """2-norm of the difference over 2-norm of the result, and the kernel's name."""
+    got, sb = run_gpu(blk, ins, path, return_block=True)
+    return float(np.linalg.norm(got - want) / np.linalg.norm(want)), sb.info["kernel"]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N,K", [(16, 1000, 576), (17, 300, 1040), (3, 500, 4000)])
+def test_few_rows_error(M, N, K, dt):
+    """The sums are no less exact than on the literal kernel, whose lanes hold 64 partial sums (both against 64 bits)."""
+    blk = matmul(M, N, K, dt, "nt")
+    ins = [W.seeded_tensor((M, K), dt, 0), W.seeded_tensor((N, K), dt, 1)]
+    want = (ins[0].double() @ ins[1].double().t()).numpy().ravel()
+    err, kernel = error_against_64_bits(blk, ins, want)
+    before, _ = error_against_64_bits(blk, ins, want, "generic")
+    assert kernel.startswith("gemm_rows_") and err <= before, (kernel, err, before)
+
+
 def test_few_rows_int8():
     blk = matmul(9, 50, 2048, "i8", "nt")
     info, _ = parity(blk, [W.seeded_tensor((9, 2048), "i8", 0), W.seeded_tensor((50, 2048), "i8", 1)], what="few rows int8")
