@@ -218,8 +218,9 @@ stripe_status_t stripe_block_run(stripe_block_t* blk, const void* const* inputs,
  * stripe_block_set_workspace is not used by this call.
  * The call makes no hipMalloc / hipFree and calls no allocating library routine; the caller still passes inputs
  * and output.  If stripe_block_workspace_size() exceeds STRIPE_STATIC_SCRATCH_BYTES the call returns
- * STRIPE_ERR_NOMEM and launches nothing (use stripe_block_run then).  Handles that need no workspace use no
- * scratch at all.
+ * STRIPE_ERR_NOMEM and launches nothing (use stripe_block_run then), unless the part beyond it is the partial sums of
+ * products with at most 32 rows, which this call then runs on a kernel that needs none.  Handles that need no workspace
+ * use no scratch at all.
  * Every call on a GPU shares that GPU's array, which keeps the previous call's contents; nothing in it needs to
  * start at zero (every element of a temporary or of a partial-sum image is written before it is read).  Two
  * calls that overlap on one GPU (different streams, or different host threads) and both need a workspace RACE

@@ -44,6 +44,9 @@ struct stripe_block {
   // run on a device), else the library's static scratch array (run_static).
   std::vector<int64_t> temp_off, stage_ws_off;
   int64_t ws_bytes = 0;
+  // Where that is more than the static scratch holds, run_static takes the few-rows kernel for the split products it can run.
+  RowsLaunch static_rows;
+  int64_t static_ws_bytes = 0;
   void* caller_ws = nullptr;
   size_t caller_ws_bytes = 0;
   void* owned_ws = nullptr;
@@ -276,7 +279,12 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
     const Stage &s0 = prog->stages[0], &s1 = prog->stages[1];
     const Plan& c = s0.blk->plan;
     const FlatBlock& e = s1.blk->plan.flat;
-    const bool few_rows = s0.blk->rows.use && c.in_dtype == STRIPE_BF16;
+    // a split product is followed by a launch of its own for the second statement (about 3 us), the few-rows kernel stores through it
+    bool few_rows = s0.blk->rows.use && c.in_dtype == STRIPE_BF16;
+    RowsLaunch rows = s0.blk->rows;
+    stripe_block_info_t rows_info = c.info;
+    if (!few_rows && path == STRIPE_PATH_AUTO && c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && s0.blk->gemm.split_k > 1)
+      few_rows = gemm_rows_select(c.gemm, c.in_dtype, gemm_few_rows_us(c.gemm, c.in_dtype, s0.blk->gemm) + 3.0, &rows, &rows_info);
     bool ok = (few_rows || (c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && gemm_can_fuse_bias_relu(c.gemm, s0.blk->gemm))) &&
               root->refs[s0.dst].dir == STRIPE_TEMP && s1.n_in == 2 && s1.src[0] == s0.dst && !e.empty && e.intrinsic == STRIPE_INTR_ADD_RELU &&
               e.cons.empty() && e.n_refs == 3 && e.n_idx >= 2 && e.ref[0].dtype == STRIPE_F32 && e.ref[1].dtype == STRIPE_F32;
@@ -292,7 +300,8 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
           prog->fused = e.out_bf16 ? 4 : 3;
           prog->plan.gemm = c.gemm;
           prog->gemm = s0.blk->gemm;
-          prog->rows = s0.blk->rows;
+          prog->rows = rows;
+          s0.blk->plan.info = rows_info;
           prog->plan.in_dtype = c.in_dtype;
           prog->plan.info.path = c.info.path;
           prog->fuse_bias_off = e.ref[1].addr.k;
@@ -370,10 +379,12 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
       prog->ws_bytes += round_up_256(prog->temp_bytes[r]);
     }
   prog->stage_ws_off.assign(prog->stages.size(), 0);
+  prog->static_ws_bytes = prog->ws_bytes;
   if (!prog->fused)
     for (size_t i = 0; i < prog->stages.size(); ++i) {
       prog->stage_ws_off[i] = prog->ws_bytes;
       prog->ws_bytes += round_up_256(prog->stages[i].blk->ws_bytes);
+      if (prog->stages[i].blk->static_ws_bytes) prog->static_ws_bytes = prog->ws_bytes;    // offsets are the full layout's
     }
   info.workspace_bytes = prog->ws_bytes;
   *out = prog;
@@ -409,8 +420,8 @@ stripe_status_t static_scratch_of(int dev, unsigned char** out) {
 stripe_status_t resolve_workspace(stripe_block* blk, bool use_static, unsigned char** ws) {
   *ws = nullptr;
   if (blk->ws_bytes == 0) return STRIPE_OK;
-  if (use_static && blk->ws_bytes > (int64_t)STRIPE_STATIC_SCRATCH_BYTES)
-    return fail(STRIPE_ERR_NOMEM, "the block's workspace needs " + std::to_string((long long)blk->ws_bytes) + " bytes, the static scratch holds " +
+  if (use_static && blk->static_ws_bytes > (int64_t)STRIPE_STATIC_SCRATCH_BYTES)
+    return fail(STRIPE_ERR_NOMEM, "the block's workspace needs " + std::to_string((long long)blk->static_ws_bytes) + " bytes, the static scratch holds " +
                                       std::to_string((long long)STRIPE_STATIC_SCRATCH_BYTES));
   if (!use_static && blk->caller_ws) {
     *ws = (unsigned char*)blk->caller_ws;
@@ -434,9 +445,9 @@ stripe_status_t resolve_workspace(stripe_block* blk, bool use_static, unsigned c
   return STRIPE_OK;
 }
 
-stripe_status_t run_single(stripe_block* blk, const void* const* inputs, void* output, void* hip_stream, unsigned char* ws);
+stripe_status_t run_single(stripe_block* blk, const void* const* inputs, void* output, void* hip_stream, unsigned char* ws, bool static_rows);
 
-stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void* output, void* hip_stream, unsigned char* ws) {
+stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void* output, void* hip_stream, unsigned char* ws, bool static_rows) {
   hipError_t e = hipSuccess;
   const int R = (int)prog->input_slot.size();
   if (prog->fused) {
@@ -474,13 +485,13 @@ stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void*
   for (size_t i = 0; i < prog->stages.size(); ++i) {
     const Stage& st = prog->stages[i];
     const void* ins[2] = {where(st.src[0]), st.n_in > 1 ? where(st.src[1]) : nullptr};
-    const stripe_status_t rc = run_single(st.blk, ins, const_cast<void*>(where(st.dst)), hip_stream, ws ? ws + prog->stage_ws_off[i] : nullptr);
+    const stripe_status_t rc = run_single(st.blk, ins, const_cast<void*>(where(st.dst)), hip_stream, ws ? ws + prog->stage_ws_off[i] : nullptr, static_rows);
     if (rc != STRIPE_OK) return rc;
   }
   return STRIPE_OK;
 }
 
-stripe_status_t run_single(stripe_block* blk, const void* const* inputs, void* output, void* hip_stream, unsigned char* ws) {
+stripe_status_t run_single(stripe_block* blk, const void* const* inputs, void* output, void* hip_stream, unsigned char* ws, bool static_rows) {
   const Plan& p = blk->plan;
   if (p.noop) return STRIPE_OK;
   hipStream_t s = (hipStream_t)hip_stream;
@@ -493,7 +504,8 @@ stripe_status_t run_single(stripe_block* blk, const void* const* inputs, void* o
                                        "dense contractions and the general convolution kernel, the output pointer) must be 16-byte aligned");
   switch (p.info.path) {
     case STRIPE_PATH_MFMA_GEMM:
-      if (blk->rows.use) e = launch_gemm_rows(p.gemm, p.in_dtype, in0, in1, output, p.gemm.c_m, p.gemm.c_base, nullptr, false, s);
+      if (blk->rows.use || (static_rows && blk->static_rows.use))
+        e = launch_gemm_rows(p.gemm, p.in_dtype, in0, in1, output, p.gemm.c_m, p.gemm.c_base, nullptr, false, s);
       else e = launch_gemm(p.gemm, blk->gemm, in0, in1, output, ws, s);
       break;
     case STRIPE_PATH_MFMA_CONV: e = launch_conv(p.conv, blk->conv, in0, in1, output, s); break;
@@ -515,8 +527,9 @@ stripe_status_t run_any(stripe_block* blk, const void* const* inputs, void* outp
   unsigned char* ws = nullptr;
   const stripe_status_t rc = resolve_workspace(blk, use_static, &ws);
   if (rc != STRIPE_OK) return rc;
-  if (!blk->stages.empty()) return run_program(blk, inputs, output, hip_stream, ws);
-  return run_single(blk, inputs, output, hip_stream, ws);
+  const bool static_rows = use_static && blk->ws_bytes > (int64_t)STRIPE_STATIC_SCRATCH_BYTES;
+  if (!blk->stages.empty()) return run_program(blk, inputs, output, hip_stream, ws, static_rows);
+  return run_single(blk, inputs, output, hip_stream, ws, static_rows);
 }
 
 stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t path, stripe_block_t** out) {
@@ -570,12 +583,15 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
       // -- but where a wavefront per output walks its reduction in two steps and the block is small, the literal kernel's short
       // prologue wins (3x3, 8 -> 16 channels at 16 x 16, fp32: 7.0 us against 7.2 to 8.0)
       const bool literal = !p.tiled.use && p.gen.lanes == 64 && p.gen.red_total <= 128 && p.info.hull_points < (1 << 19) && tune_int("contract_min", 65536) == 65536;
-      if (!forced && !(p.is_gemm && gemm_rows_select(p.gemm, p.in_dtype, &blk->rows, &p.info)) && !literal)
+      if (!forced && !(p.is_gemm && gemm_rows_select(p.gemm, p.in_dtype, __builtin_huge_val(), &blk->rows, &p.info)) && !literal)
         contract_select(p.flat, &blk->contract, &p.info);
-    } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM && gemm_rows_select(p.gemm, p.in_dtype, &blk->rows, &p.info)) {
+    } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM &&
+               gemm_rows_select(p.gemm, p.in_dtype, gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm), &blk->rows, &p.info)) {
       blk->gemm.ws_bytes = 0;    // no partial sums of a split reduction
     }
-    if (p.info.path == STRIPE_PATH_MFMA_GEMM && picked) blk->ws_bytes = blk->gemm.ws_bytes;
+    if (p.info.path == STRIPE_PATH_MFMA_GEMM && picked) blk->ws_bytes = blk->static_ws_bytes = blk->gemm.ws_bytes;
+    stripe_block_info_t unused = p.info;
+    if (!forced && blk->ws_bytes && gemm_rows_select(p.gemm, p.in_dtype, __builtin_huge_val(), &blk->static_rows, &unused)) blk->static_ws_bytes = 0;
   }
   p.info.workspace_bytes = blk->ws_bytes;
   *out = blk;

@@ -16,6 +16,7 @@
 // reads (16 bytes per lane) spread over all banks.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 
 #include "kernels.hpp"
@@ -1204,6 +1205,16 @@ static int choose_split_k(const GemmShape& g, int in_dtype, const GemmLaunch& l)
       best_t = model_us(s);
     }
   return (int)best;
+}
+
+// A product with few rows on these kernels, fitted to 250 products of 2 to 32 rows, 16 to 120000 columns, K of 512 to 32768 (13 to
+// 150 us, bf16 and int8).  Split: two launches, the K tiles of one workgroup, partial sums out and back, the operands once.
+// Not split: rounds of workgroups, or the operands from memory.
+double gemm_few_rows_us(const GemmShape& g, int in_dtype, const GemmLaunch& l) {
+  const double row_bytes = (double)g.K * (in_dtype == STRIPE_I8 ? 1 : 2), bytes = (double)g.N * row_bytes, k_tiles = row_bytes / 64, s = (double)l.split_k;
+  const double rounds = (double)((l.grid + 255) / 256);
+  if (l.split_k > 1) return 12.5 + 0.42 * rounds * k_tiles / s + s * (double)g.M * (double)g.N * 8 / 7.2e6 + bytes / 9e6;
+  return std::max(4.0 + rounds * (6.0 + 0.6 * k_tiles), bytes / 3.4e6);
 }
 
 bool gemm_select(const GemmShape& g, int in_dtype, GemmLaunch* l, stripe_block_info_t* info) {

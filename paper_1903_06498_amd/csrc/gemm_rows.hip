@@ -8,6 +8,7 @@
 // both operands; A (a few rows) comes from L2.  Rows, columns and k beyond the operand load zeros (buffer range).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <type_traits>
 
@@ -142,18 +143,36 @@ hipError_t launch_t(const GemmShape& g, const void* a, const void* b, void* c, c
   const dim3 grid((unsigned)((g.N + kCols - 1) / kCols)), wg(64 * kWaves);
   const T *pa = (const T*)a + g.a_base, *pb = (const T*)b + g.b_base;
   const uint32_t e = sizeof(T);
-  if (g.M <= 16)
-    hipLaunchKernelGGL((rows_kernel<T, 1, 8>), grid, wg, 0, s, pa, pb, c, bias, (uint32_t)g.M, (uint32_t)g.N, (uint32_t)g.K * e, (uint32_t)g.a_m * e,
+  // a step beyond the reduction costs its loads and matrix instructions all the same: no more steps at once than there are
+  // (2 x 120000 x 512 bf16, one step: 80 us with eight at once, 27 us with two)
+  const uint32_t steps = ((uint32_t)g.K * e + kWaves * 128 - 1) / (kWaves * 128);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, wg, 0, s, pa, pb, c, bias, (uint32_t)g.M, (uint32_t)g.N, (uint32_t)g.K * e, (uint32_t)g.a_m * e,
                        (uint32_t)g.b_n * e, c_row, epi, vec);
-  else
-    hipLaunchKernelGGL((rows_kernel<T, 2, 4>), grid, wg, 0, s, pa, pb, c, bias, (uint32_t)g.M, (uint32_t)g.N, (uint32_t)g.K * e, (uint32_t)g.a_m * e,
-                       (uint32_t)g.b_n * e, c_row, epi, vec);
+  };
+  if (g.M <= 16) {
+    if (steps <= 2) go(rows_kernel<T, 1, 2>);
+    else if (steps <= 4) go(rows_kernel<T, 1, 4>);
+    else go(rows_kernel<T, 1, 8>);
+  } else {
+    if (steps <= 2) go(rows_kernel<T, 2, 2>);
+    else go(rows_kernel<T, 2, 4>);
+  }
   return hipGetLastError();
 }
 
 }  // namespace
 
-bool gemm_rows_select(const GemmShape& g, int in_dtype, RowsLaunch* l, stripe_block_info_t* info) {
+// What this kernel takes: every workgroup walks the whole reduction in steps of 1 KB per row, whose time grows with the rows of
+// A fetched beside B (2 rows 0.52, 8 0.66, 16 0.80, 32 1.19 us), 256 workgroups at a time, and the operands come from memory
+// once.  Few columns and long reductions are the split product's (8 x 256 x 32768 bf16: 47 us here, 16 split; 32 x 1024 x 16384:
+// 44 and 23), ten thousands of columns the 256-wide tiles' with more than 16 rows (32 x 120000 x 2048: 164 and 147).
+static double rows_us(const GemmShape& g, int64_t e) {
+  const double steps = (double)((g.K * e + kWaves * 128 - 1) / (kWaves * 128)), rounds = std::max(1.0, (double)((g.N + kCols - 1) / kCols) / 256);
+  return 4.0 + steps * rounds * (0.5 + 0.0186 * (double)g.M + (g.M > 16 ? 0.09 : 0.0)) + (double)g.N * (double)g.K * (double)e * 0.02e-6;
+}
+
+bool gemm_rows_select(const GemmShape& g, int in_dtype, double other_us, RowsLaunch* l, stripe_block_info_t* info) {
   l->use = false;
   if (!tune_int("gemm_rows", 1)) return false;
   if (in_dtype != STRIPE_BF16 && in_dtype != STRIPE_I8 && in_dtype != STRIPE_F32) return false;
@@ -164,6 +183,7 @@ bool gemm_rows_select(const GemmShape& g, int in_dtype, RowsLaunch* l, stripe_bl
   if (g.K * e < 1024 || g.N > 0x3fffffff || g.a_m > (1 << 24) || g.b_n > (1 << 26)) return false;
   const __int128 a_end = ((__int128)(g.M - 1) * g.a_m + g.K) * e, b_end = ((__int128)(g.N - 1) * g.b_n + g.K) * e;
   if (a_end > 0x7fffff00 || b_end > 0x7fffff00) return false;
+  if (rows_us(g, e) > other_us && tune_int("gemm_rows", 1) != 2) return false;    // STRIPE_TUNE gemm_rows = 2: wherever it can
   l->use = true;
   info->tile_m = g.M <= 16 ? 16 : 32; info->tile_n = kCols; info->tile_k = (int)(kWaves * 128 / e);
   info->frag_m = info->frag_n = 16; info->frag_k = in_dtype == STRIPE_F32 ? 4 : (int)(64 / e);

@@ -47,11 +47,14 @@ bool gemm_can_fuse_bias_relu(const GemmShape& g, const GemmLaunch& l);
 hipError_t launch_gemm_bias_relu(const GemmShape& g, const GemmLaunch& l, const void* a, const void* b, const void* bias, void* out,
                                  int64_t o_m, int64_t o_base, bool out_bf16, hipStream_t stream);
 
-// products with at most 32 rows and k-contiguous operands (gemm_rows.hip); bias != nullptr: O = relu(C + bias[n])
+// Estimated time, in us, of a product with few rows on the kernels gemm_select chose.
+double gemm_few_rows_us(const GemmShape& g, int in_dtype, const GemmLaunch& l);
+// products with at most 32 rows and k-contiguous operands (gemm_rows.hip); bias != nullptr: O = relu(C + bias[n]).
+// other_us: what the product takes otherwise (infinite: unknown, slower).
 struct RowsLaunch {
   bool use = false;
 };
-bool gemm_rows_select(const GemmShape& g, int in_dtype, RowsLaunch* l, stripe_block_info_t* info);
+bool gemm_rows_select(const GemmShape& g, int in_dtype, double other_us, RowsLaunch* l, stripe_block_info_t* info);
 hipError_t launch_gemm_rows(const GemmShape& g, int in_dtype, const void* a, const void* b, void* c, int64_t c_row, int64_t c_base, const float* bias,
                             bool out_bf16, hipStream_t stream);
 

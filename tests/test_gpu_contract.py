@@ -167,6 +167,34 @@ def test_few_rows(M, N, K, in_dt, out_dt):
         assert N == 1 or sb.info["kernel"].endswith("+bias_relu"), sb.info
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16", "i8"])
+@pytest.mark.parametrize("M,pieces", [(7, 64), (7, 129), (7, 257), (16, 1025), (20, 65), (17, 129), (32, 515)])
+def test_few_rows_steps(M, pieces, dt, monkeypatch):
+    """Reductions of 1 to 17 steps of 64 pieces of 16 bytes, whole and ending inside a step: each number of steps at once."""
+    monkeypatch.setenv("STRIPE_TUNE", "gemm_rows=2")
+    K = pieces * 16 // {"f32": 4, "bf16": 2, "i8": 1}[dt]
+    blk = matmul(M, 37, K, dt, "nt")
+    info, _ = parity(blk, [W.seeded_tensor((M, K), dt, 0), W.seeded_tensor((37, K), dt, 1)], what=f"{M} rows, {pieces} pieces")
+    assert info["kernel"].startswith("gemm_rows_"), info
+
+
+def test_few_rows_program_in_static_scratch():
+    """Temporary and partial sums of this program are more than the static scratch: run_static takes the kernel that needs none."""
+    M, N, K = 32, 1024, 32768
+    prog = W.linear_bias_relu_program(M, N, K, "bf16", b_transposed=True)
+    ins = [W.seeded_tensor((M, K), "bf16", 0), W.seeded_tensor((N, K), "bf16", 1) / 16, W.seeded_tensor((N,), "f32", 2)]
+    sb = B.StripeBlock(prog)
+    assert sb.info["workspace_bytes"] > 8 << 20 and "splitk" in sb.info["kernel"], sb.info
+    dins = [t.cuda() for t in ins]
+    want = torch.relu(ins[0].double() @ ins[1].double().t() + ins[2].double())
+    tol = K * 2.0 ** -24 * (ins[0].double().abs() @ ins[1].double().abs().t()) + 2.0 ** -8 * want + 1e-5    # fp32 sums, one rounding to bf16
+    for run in (sb.run_static, sb.run):
+        out = torch.zeros((M, N), dtype=torch.bfloat16, device="cuda")
+        run(dins, out)
+        assert ((out.cpu().double() - want).abs() <= tol).all()
+    sb.close()
+
+
 def error_against_64_bits(blk, ins, want, path="auto"):
     """2-norm of the difference over 2-norm of the result, and the kernel's name."""
     got, sb = run_gpu(blk, ins, path, return_block=True)

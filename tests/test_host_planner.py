@@ -280,3 +280,13 @@ def test_fusion_keeps_apart_what_the_general_kernel_leaves_unwritten():
     prog = W.conv_bias_relu_program(1, 8, 8, 32, 32, 3, 3, 1, 3, "bf16", "f32")
     with pytest.raises(B.StripeError):
         B.StripeBlock(prog)
+
+
+@pytest.mark.parametrize("M,N,K,rows", [(8, 4096, 4096, True), (32, 1024, 4096, True), (8, 256, 32768, False), (16, 128, 32768, False),
+                                        (32, 1024, 16384, False), (2, 120000, 512, True), (32, 120000, 2048, False), (8, 4096, 8192, True)])
+def test_few_row_products_go_to_the_faster_kernel(M, N, K, rows):
+    """Few columns with a long reduction keep the split product (8 x 256 x 32768: 16 us split, 47 us on the few-rows kernel),
+    very many columns with more than 16 rows the 256-wide tiles."""
+    b = B.StripeBlock(W.matmul_block(M, N, K, "bf16", "f32", b_transposed=True))
+    assert b.info["kernel"].startswith("gemm_rows_") == rows, b.info["kernel"]
+    b.close()
