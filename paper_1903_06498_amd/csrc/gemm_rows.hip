@@ -73,6 +73,14 @@ __global__ __launch_bounds__(64 * kWaves) void rows_kernel(const T* __restrict__
   Total total[FM];
 #pragma unroll
   for (int i = 0; i < FM; ++i) total[i] = (Total){0, 0, 0, 0};
+  // the bias of the columns this lane stores, asked for before the reduction
+  const uint32_t n = n0 + (lane >> 4) * 4;
+  float bs[4] = {0.f, 0.f, 0.f, 0.f};
+  if (epilogue && wave < FM) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < N) bs[e] = bias[n + e];
+  }
   uint32_t at = wave * 128 + (lane >> 4) * 16;
   const uint32_t steps = (k_bytes + kWaves * 128 - 1) / (kWaves * 128);
   for (uint32_t s = 0; s < steps; s += UNROLL) {
@@ -110,15 +118,15 @@ __global__ __launch_bounds__(64 * kWaves) void rows_kernel(const T* __restrict__
   Total sum = part[0][wave][lane];
 #pragma unroll
   for (int w = 1; w < kWaves; ++w) sum += part[w][wave][lane];
-  const uint32_t m = wave * 16 + row, n = n0 + (lane >> 4) * 4;
+  const uint32_t m = wave * 16 + row;
   if (m >= M) return;
   S v[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     v[e] = (S)sum[e];
     if constexpr (std::is_same<S, float>::value) {
-      if (epilogue && n + e < N) {
-        const float y = v[e] + bias[n + e];
+      if (epilogue) {
+        const float y = v[e] + bs[e];
         v[e] = y > 0.f ? y : 0.f;
       }
     }
