@@ -584,7 +584,7 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
       // prologue wins (3x3, 8 -> 16 channels at 16 x 16, fp32: 7.0 us against 7.2 to 8.0)
       const bool literal = !p.tiled.use && p.gen.lanes == 64 && p.gen.red_total <= 128 && p.info.hull_points < (1 << 19) && tune_int("contract_min", 65536) == 65536;
       if (!forced && !(p.is_gemm && gemm_rows_select(p.gemm, p.in_dtype, __builtin_huge_val(), &blk->rows, &p.info)) && !literal)
-        contract_select(p.flat, &blk->contract, &p.info);
+        contract_select(p.flat, LiteralSums{p.tiled.use ? 1 : p.gen.lanes, p.gen.red_total, p.gen.atomic != 0}, &blk->contract, &p.info);
     } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM &&
                gemm_rows_select(p.gemm, p.in_dtype, gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm), &blk->rows, &p.info)) {
       blk->gemm.ws_bytes = 0;    // no partial sums of a split reduction

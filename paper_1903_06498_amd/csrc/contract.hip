@@ -35,6 +35,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
@@ -56,6 +57,14 @@ __device__ __forceinline__ void decode(const CtIndex& ix, uint32_t v, F f) {
     f(j, (int)(v - q * ix.range[j]));
     v = q;
   }
+}
+
+// The launch parameters, read again: what only the end of the kernel needs is not kept in scalar registers through the main
+// loop (the kernel spilled up to 170 of them there).
+__device__ __forceinline__ const ContractParams& reread() {
+  auto at = __builtin_amdgcn_kernarg_segment_ptr();       // the first argument
+  asm volatile("" : "+s"(at));
+  return *(const ContractParams*)at;
 }
 
 struct KPart {
@@ -88,6 +97,8 @@ struct Ct<uint16_t> {
   static __device__ __forceinline__ Acc mma(u32x4 a, u32x4 b, Acc c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   }
+  // a 64-byte step's products, summed from zero
+  static __device__ __forceinline__ Acc step(u32x4 a, u32x4 b) { return mma(a, b, (Acc){0.f, 0.f, 0.f, 0.f}); }
   static __device__ __forceinline__ S widen(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
   static __device__ __forceinline__ bool finite(uint32_t w) { return ((w & 0x7f80u) != 0x7f80u) & ((w & 0x7f800000u) != 0x7f800000u); }
 };
@@ -112,6 +123,15 @@ struct Ct<float> {
 #pragma unroll
     for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[i], c, 0, 0, 0);
     return c;
+  }
+  static __device__ __forceinline__ Acc step(u32x4 a, u32x4 b) {     // as two chains of eight products
+    const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+    Acc t[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[2 * i], y[2 * i], (Acc){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[2 * i + 1], y[2 * i + 1], t[i], 0, 0, 0);
+    return t[0] + t[1];
   }
   static __device__ __forceinline__ S widen(float v) { return v; }
   static __device__ __forceinline__ bool finite(uint32_t w) { return (w & 0x7f800000u) != 0x7f800000u; }
@@ -288,15 +308,21 @@ __device__ __forceinline__ void put(const ContractParams& p, void* O, const floa
 
 // BM x BN tile, K tiles of BKB bytes per row; WM x WN wavefronts over the tile, the remaining factor WK of the four
 // wavefronts takes every WK-th 64-byte step of a K tile (small tiles) and their sums are added through LDS at the end.
-template <typename T, int BM, int BN, int BKB, int WM, int WN, int MA, int MB>
-__global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, const T* __restrict__ A, const T* __restrict__ B,
+// PRECISE (float types): the products of one 64-byte step are summed from zero and join a total in double precision.  For blocks
+// whose literal kernel holds several sums per output (see wants_double): against it, fp32 totals had 1.1 to 1.5 times the error
+// in 64 bits (K of 64 to 33000), totals in double 0.7 to 0.99 times.  They cost up to 15 % (250 x 250 x 1001 nt fp32 20.1 -> 23.3
+// us, 1000 x 1000 x 3000 [k][m] bf16 50 -> 55), so other blocks, already more exact than before (1000^3 fp32: 5.6e-7 literal,
+// 1.5e-7 here), keep fp32 totals.
+template <typename T, int BM, int BN, int BKB, int WM, int WN, int MA, int MB, bool PRECISE>
+__global__ __launch_bounds__(256, 2) void contract_kernel(const ContractParams p, const T* __restrict__ A, const T* __restrict__ B,
                                                        void* __restrict__ O, const float* __restrict__ bias) {
   using Acc = typename Ct<T>::Acc;
   using S = typename Ct<T>::S;
   constexpr int WK = 4 / (WM * WN), STEPS = BKB / 64, FM = BM / WM / 16, FN = BN / WN / 16;
   constexpr int PITCH = BKB + 16, BUF = (BM + BN) * PITCH;
   static_assert(STEPS % WK == 0, "K steps are shared out evenly");
-  static_assert(WK == 1 || (WK - 1) * BM * BN * 4 <= 2 * BUF, "partial sums fit the staging buffers");
+  using Total = typename std::conditional<PRECISE, f64x4, Acc>::type;
+  static_assert(WK == 1 || (WK - 1) * BM * BN * (int)sizeof(Total) / 4 <= 2 * BUF, "partial sums fit the staging buffers");
   __shared__ __align__(16) unsigned char lds[2 * BUF];
   __shared__ i32x4 rows_a[BM], rows_b[BN];   // {input offset, range-test values, output offset}
   __shared__ int2 ob_m[BM], ob_n[BN];
@@ -373,11 +399,11 @@ __global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, c
 
   const int wk = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
   const int frag_row = lane & 15, frag_k = lane >> 4;
-  Acc acc[FM][FN];
+  Total acc[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = (Acc){0, 0, 0, 0};
+    for (int j = 0; j < FN; ++j) acc[i][j] = (Total){0, 0, 0, 0};
 
   // bf16 / fp32: partial sums over FLUSH K tiles start from zero and are added to the total, short chains of roundings
   // instead of one long one (not on the largest tile, whose registers hold one set of sums at two wavefronts per SIMD)
@@ -388,13 +414,15 @@ __global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, c
 #pragma unroll
     for (int j = 0; j < FN; ++j) sum[i][j] = (Acc){0, 0, 0, 0};
   auto flush = [&]() {
+    if constexpr (!PRECISE) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+      for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        acc[i][j] += sum[i][j];
-        sum[i][j] = (Acc){0, 0, 0, 0};
-      }
+        for (int j = 0; j < FN; ++j) {
+          acc[i][j] += sum[i][j];
+          sum[i][j] = (Acc){0, 0, 0, 0};
+        }
+    }
   };
 
   // Two K tiles are in flight in registers (set t & 1 holds tile t): with one, few workgroups and long reductions spent an
@@ -430,7 +458,10 @@ __global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, c
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) sum[i][j] = Ct<T>::mma(fb[j], fa[i], sum[i][j]);   // rows of the result: n
+        for (int j = 0; j < FN; ++j) {   // rows of the result: n
+          if constexpr (PRECISE) acc[i][j] += __builtin_convertvector(Ct<T>::step(fb[j], fa[i]), f64x4);
+          else sum[i][j] = Ct<T>::mma(fb[j], fa[i], sum[i][j]);
+        }
     }
     if ((t + 1) % FLUSH == 0) flush();
     if constexpr (decltype(stores)::value) {
@@ -458,7 +489,7 @@ __global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, c
 
   if constexpr (WK > 1) {
     __syncthreads();
-    Acc* part = (Acc*)lds;
+    Total* part = (Total*)lds;
     if (wk > 0)
 #pragma unroll
       for (int i = 0; i < FM; ++i)
@@ -474,21 +505,22 @@ __global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, c
           for (int j = 0; j < FN; ++j) acc[i][j] += part[(((w * WM * WN + wave % (WM * WN)) * FM + i) * FN + j) * 64 + lane];
   }
 
+  const ContractParams& q = reread();
   // A removed point contributes 0 * x, which is not 0 where x is an infinity or NaN: a tile that met one is summed again
   // point by point (Definition 2: a removed point contributes nothing).
   if (look && __syncthreads_or(!fin)) {
     for (int at = tid; at < BM * BN; at += 256) {
       const int mi = at / BN, ni = at % BN;
       const i32x4 rm = rows_a[mi], rn = rows_b[ni];
-      if (rm[1] == kFar || rn[1] == kFar || ob_m[mi].x + ob_n[ni].x > p.ob[0] || ob_m[mi].y + ob_n[ni].y > p.ob[1]) continue;
-      S sum = 0;
-      for (uint32_t k = 0; k < p.K; ++k) {
-        const KPart ka = k_part<true>(p, k), kb = k_part<false>(p, k);
-        if ((uint32_t)(rm[1] + ka.t0) <= p.top_a[0] && (uint32_t)(rm[2] + ka.t1) <= p.top_a[1] && (uint32_t)(rn[1] + kb.t0) <= p.top_b[0] &&
-            (uint32_t)(rn[2] + kb.t1) <= p.top_b[1])
+      if (rm[1] == kFar || rn[1] == kFar || ob_m[mi].x + ob_n[ni].x > q.ob[0] || ob_m[mi].y + ob_n[ni].y > q.ob[1]) continue;
+      typename std::conditional<std::is_same<S, float>::value, double, S>::type sum = 0;
+      for (uint32_t k = 0; k < q.K; ++k) {
+        const KPart ka = k_part<true>(q, k), kb = k_part<false>(q, k);
+        if ((uint32_t)(rm[1] + ka.t0) <= q.top_a[0] && (uint32_t)(rm[2] + ka.t1) <= q.top_a[1] && (uint32_t)(rn[1] + kb.t0) <= q.top_b[0] &&
+            (uint32_t)(rn[2] + kb.t1) <= q.top_b[1])
           sum += Ct<T>::widen(A[rm[0] + ka.off]) * Ct<T>::widen(B[rn[0] + kb.off]);
       }
-      put<S>(p, O, bias, o_base + rm[3] + rn[3], rn[3], sum);
+      put<S>(q, O, bias, o_base + rm[3] + rn[3], rn[3], (S)sum);
     }
     return;
   }
@@ -508,7 +540,7 @@ __global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, c
       on[e] = ob_n[ni + e];
     }
     float bs[4] = {0.f, 0.f, 0.f, 0.f};
-    if (p.epilogue >= 2) {
+    if (q.epilogue >= 2) {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (n_in[e]) bs[e] = bias[n_off[e]];      // one column index of unit output stride
@@ -523,15 +555,15 @@ __global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, c
       S v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        v[e] = acc[i][j][e];
+        v[e] = (S)acc[i][j][e];
         if constexpr (std::is_same<S, float>::value) {
-          if (p.epilogue >= 2) v[e] = v[e] + bs[e] > 0.f ? v[e] + bs[e] : 0.f;
+          if (q.epilogue >= 2) v[e] = v[e] + bs[e] > 0.f ? v[e] + bs[e] : 0.f;
         }
       }
-      const bool half = std::is_same<S, float>::value && (p.epilogue & 1);
+      const bool half = std::is_same<S, float>::value && (q.epilogue & 1);
       // the planner: four columns from a multiple of four are neighbours and share the bound
-      if (p.vec_out && n_in[0]) {
-        if (om.x + on[0].x <= p.ob[0] && om.y + on[0].y <= p.ob[1]) {
+      if (q.vec_out && n_in[0]) {
+        if (om.x + on[0].x <= q.ob[0] && om.y + on[0].y <= q.ob[1]) {
           typedef S s4 __attribute__((ext_vector_type(4)));
           if (half) *(bf16x4*)((uint16_t*)O + off + n_off[0]) = __builtin_convertvector((f32x4){(float)v[0], (float)v[1], (float)v[2], (float)v[3]}, bf16x4);
           else *(s4*)((S*)O + off + n_off[0]) = (s4){v[0], v[1], v[2], v[3]};
@@ -539,7 +571,7 @@ __global__ __launch_bounds__(256) void contract_kernel(const ContractParams p, c
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (n_in[e] && om.x + on[e].x <= p.ob[0] && om.y + on[e].y <= p.ob[1]) {
+          if (n_in[e] && om.x + on[e].x <= q.ob[0] && om.y + on[e].y <= q.ob[1]) {
             if (half) ((__bf16*)O)[off + n_off[e]] = (__bf16)(float)v[e];
             else ((S*)O)[off + n_off[e]] = v[e];
           }
@@ -560,16 +592,23 @@ namespace {
 template <typename T, int MA, int MB>
 hipError_t launch_modes(const ContractLaunch& l, const ContractParams& p, const void* a, const void* b, void* o, const float* bias, hipStream_t s) {
   const dim3 g((unsigned)l.grid, (unsigned)l.batch), w(256);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, g, w, 0, s, p, (const T*)a, (const T*)b, o, bias);
+    return hipGetLastError();
+  };
+  constexpr bool real = sizeof(T) > 1;
   switch (l.tile) {
-    case 0: hipLaunchKernelGGL((contract_kernel<T, 128, 128, 64, 2, 2, MA, MB>), g, w, 0, s, p, (const T*)a, (const T*)b, o, bias); break;
-    case 1: hipLaunchKernelGGL((contract_kernel<T, 64, 64, 128, 2, 2, MA, MB>), g, w, 0, s, p, (const T*)a, (const T*)b, o, bias); break;
+    case 0: return go(contract_kernel<T, 128, 128, 64, 2, 2, MA, MB, false>);
+    case 1:
+      if constexpr (real) if (l.precise) return go(contract_kernel<T, 64, 64, 128, 2, 2, MA, MB, true>);
+      return go(contract_kernel<T, 64, 64, 128, 2, 2, MA, MB, false>);
     case 3:
       if constexpr (MB == 2 && sizeof(T) < 4) return hipErrorInvalidValue;   // 64 rows of 64 bytes are less than a unit per lane: the planner takes tile 1
-      else hipLaunchKernelGGL((contract_kernel<T, 128, 64, 64, 2, 2, MA, MB>), g, w, 0, s, p, (const T*)a, (const T*)b, o, bias);
-      break;
-    default: hipLaunchKernelGGL((contract_kernel<T, 32, 32, 256, 1, 1, MA, MB>), g, w, 0, s, p, (const T*)a, (const T*)b, o, bias); break;
+      else return go(contract_kernel<T, 128, 64, 64, 2, 2, MA, MB, false>);
+    default:
+      if constexpr (real) if (l.precise) return go(contract_kernel<T, 32, 32, 256, 1, 1, MA, MB, true>);
+      return go(contract_kernel<T, 32, 32, 256, 1, 1, MA, MB, false>);
   }
-  return hipGetLastError();
 }
 
 template <typename T>
@@ -648,7 +687,19 @@ bool fill_side(const std::vector<Ix>& v, CtIndex* c) {
 
 }  // namespace
 
-bool contract_select(const FlatBlock& fb, ContractLaunch* l, stripe_block_info_t* info) {
+// Whether totals in double precision are needed for an error no larger than the literal kernel's.  It is not larger anyway
+// where that kernel sums an output's points in one chain (here chains of at most 32 fp32 products, 17 on the 32 x 32 tile, and
+// fp32 totals), also where such chains meet in atomic additions, if they are as long as this kernel's (transposed 3x3, 32
+// channels, fp32: 1.08e-7 both; 8 channels: 6.6e-8 and 1.0e-7).  bf16 sums run through chains of up to 256 products.
+static bool wants_double(int dtype, int tile, const LiteralSums& lit) {
+  if (dtype == STRIPE_I8) return false;
+  if (lit.lanes == 64) return true;
+  if (dtype == STRIPE_BF16) return lit.atomic;
+  if (lit.atomic) return tile == 0 || tile == 3 || lit.chain < (tile == 1 ? 32 : 17);
+  return tile == 2 && lit.chain > 8 && lit.chain < 17;
+}
+
+bool contract_select(const FlatBlock& fb, const LiteralSums& lit, ContractLaunch* l, stripe_block_info_t* info) {
   l->use = false;
   if (!tune_int("contract", 1)) return false;
   if (fb.empty || fb.n_refs != 3 || fb.intrinsic != STRIPE_INTR_MUL || fb.agg != STRIPE_AGG_ADD) return false;
@@ -1011,6 +1062,8 @@ bool contract_select(const FlatBlock& fb, ContractLaunch* l, stripe_block_info_t
   const int forced = tune_int("contract_tile", -1);
   if (forced >= 0 && forced <= 3) tile = forced;
   if (tile == 3 && p.mode_b == 2 && esize < 4) tile = 1;
+  l->precise = !fb.out_bf16 && wants_double(dt, tile, lit);      // a bf16 output's own rounding hides the sums'
+  if (l->precise && forced < 0 && (tile == 0 || tile == 3)) tile = 1;
   l->tile = tile;
   const i128 grid = tiles(tile) / l->batch;
   if (grid > 0x7fffffff) return false;

@@ -45,13 +45,21 @@ struct ContractLaunch {
   bool use = false;
   bool swap = false;            // the block's second operand plays A
   int tile = 0;                 // index into the kernel's tile table
+  bool precise = false;         // totals in double precision (tiles of 64 x 64 and 32 x 32)
   int64_t grid = 0, batch = 1;
   int64_t first_a = 0, first_b = 0;   // an operand's buffer origin, in elements from the caller's pointer (a_base, b_base count from it)
   ContractParams p;
 };
 
+// How the literal kernels would sum an output's points: lanes that share it, points one of them sums in a row, whether such sums
+// meet in atomic additions.
+struct LiteralSums {
+  int lanes;
+  int64_t chain;
+  bool atomic;
+};
 // Fills l if the kernel covers the block and is expected to be the faster one; info: kernel name, tile, grid.
-bool contract_select(const FlatBlock& fb, ContractLaunch* l, stripe_block_info_t* info);
+bool contract_select(const FlatBlock& fb, const LiteralSums& lit, ContractLaunch* l, stripe_block_info_t* info);
 // bias != nullptr: fused with a following O = relu(T + bias[n]) of the same output map (out_bf16: its element type)
 hipError_t launch_contract(const ContractLaunch& l, int in_dtype, const void* in0, const void* in1, void* out, const float* bias, bool out_bf16,
                            hipStream_t stream);

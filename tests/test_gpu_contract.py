@@ -213,6 +213,36 @@ def test_few_rows_error(M, N, K, dt):
     assert kernel.startswith("gemm_rows_") and err <= before, (kernel, err, before)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N,K", [(100, 100, 1001), (250, 250, 333), (13000, 5, 301), (40, 200, 4001)])
+def test_products_error(M, N, K, dt, monkeypatch):
+    """As test_few_rows_error, for the general contraction in place of the wavefront-per-output kernel."""
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1")
+    blk = matmul(M, N, K, dt, "nt")
+    ins = [W.seeded_tensor((M, K), dt, 0), W.seeded_tensor((N, K), dt, 1)]
+    want = (ins[0].double() @ ins[1].double().t()).numpy().ravel()
+    err, kernel = error_against_64_bits(blk, ins, want)
+    before, literal = error_against_64_bits(blk, ins, want, "generic")
+    assert kernel.startswith("contract_") and "wave_per_output" in literal and err <= before, (kernel, err, before)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_transposed_convolution_error(dt):
+    """The same where the literal kernels add up an output's tuples with atomics (64 input channels, 8 x 13 x 13, 3x3, stride 2)."""
+    N, H, C, R = 8, 13, 64, 3
+    bufs = [W.Buffer("I", "in", dt, (N, H, H, C)), W.Buffer("F", "in", dt, (R, R, C, C)), W.Buffer("O", "out", "f32", (N, 2 * H + 1, 2 * H + 1, C))]
+    blk = W.flat_block(bufs, dict(n=N, y=H, x=H, i=R, j=R, c=C, k=C),
+                       [(["n", "y", "x", "c"], "assign"), (["i", "j", "c", "k"], "assign"), (["n", "2*y + i", "2*x + j", "k"], "add")])
+    ins = [W.seeded_tensor((N, H, H, C), dt, 0), W.seeded_tensor((R, R, C, C), dt, 1)]
+    want = np.zeros((N, 2 * H + 1, 2 * H + 1, C))
+    for i in range(R):
+        for j in range(R):
+            want[:, i:i + 2 * H - 1:2, j:j + 2 * H - 1:2] += (ins[0].double().reshape(-1, C) @ ins[1][i, j].double()).reshape(N, H, H, C).numpy()
+    err, kernel = error_against_64_bits(blk, ins, want.ravel())
+    before, literal = error_against_64_bits(blk, ins, want.ravel(), "generic")
+    assert kernel.startswith("contract_") and "atomic" in literal and err <= before, (kernel, err, before)
+
+
 def test_few_rows_int8():
     blk = matmul(9, 50, 2048, "i8", "nt")
     info, _ = parity(blk, [W.seeded_tensor((9, 2048), "i8", 0), W.seeded_tensor((50, 2048), "i8", 1)], what="few rows int8")
