@@ -87,6 +87,10 @@ int64_t round_up_256(int64_t v) { return (v + 255) / 256 * 256; }
 
 stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t path, stripe_block_t** out);
 
+LiteralSums literal_sums(const Plan& p) {
+  return {p.tiled.use ? 1 : p.gen.lanes, p.gen.red_total, p.gen.n_red, p.gen.n_outputs, p.gen.atomic != 0, p.tiled.use != 0};
+}
+
 // A root block with a statement list (Section 3.2: statements execute as if in serial): every statement is planned
 // as a block of its own over the root buffers it names; temporaries of the root live in memory the handle owns.
 stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t path, stripe_block_t** out) {
@@ -317,7 +321,10 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
   if (!prog->fused && prog->stages.size() == 2 && tune_int("fuse", 1)) {
     const Stage &s0 = prog->stages[0], &s1 = prog->stages[1];
     const Plan& c = s0.blk->plan;
-    const ContractLaunch& ct = s0.blk->contract;
+    ContractLaunch ct = s0.blk->contract;
+    stripe_block_info_t ct_info = c.info;
+    if (!ct.use && path == STRIPE_PATH_AUTO && c.info.path == STRIPE_PATH_GENERIC && !c.noop && !s0.blk->rows.use && c.in_dtype == STRIPE_BF16)
+      contract_select(c.flat, literal_sums(c), true, &ct, &ct_info);
     const FlatBlock& e = s1.blk->plan.flat;
     bool ok = c.info.path == STRIPE_PATH_GENERIC && ct.use && c.in_dtype == STRIPE_BF16 && ct.p.epilogue == 0 && !ct.p.n_ob_used && ct.batch == 1 &&
               ct.p.n.n == 1 && ct.p.n_out[0] == 1 && root->refs[s0.dst].dir == STRIPE_TEMP && s1.n_in == 2 && s1.src[0] == s0.dst && !e.empty &&
@@ -343,6 +350,7 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
       if (ok) {
         prog->fused = e.out_bf16 ? 6 : 5;
         prog->contract = ct;
+        s0.blk->plan.info = ct_info;
         prog->plan.in_dtype = c.in_dtype;
         prog->fuse_bias_off = e.ref[1].addr.k;
         prog->temp_bytes[s0.dst] = 0;
@@ -579,12 +587,10 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
         return fail(STRIPE_ERR_UNSUPPORTED, "no kernel family covers this block");
       }
       generic_info(p, &p.info);
-      // without a forced path, sum-of-products blocks of the generic path run on the matrix cores
-      // -- but where a wavefront per output walks its reduction in two steps and the block is small, the literal kernel's short
-      // prologue wins (3x3, 8 -> 16 channels at 16 x 16, fp32: 7.0 us against 7.2 to 8.0)
-      const bool literal = !p.tiled.use && p.gen.lanes == 64 && p.gen.red_total <= 128 && p.info.hull_points < (1 << 19) && tune_int("contract_min", 65536) == 65536;
-      if (!forced && !(p.is_gemm && gemm_rows_select(p.gemm, p.in_dtype, __builtin_huge_val(), &blk->rows, &p.info)) && !literal)
-        contract_select(p.flat, LiteralSums{p.tiled.use ? 1 : p.gen.lanes, p.gen.red_total, p.gen.atomic != 0}, &blk->contract, &p.info);
+      // without a forced path, sum-of-products blocks of the generic path run on the matrix cores where that is faster
+      if (!forced && !(p.is_gemm && gemm_rows_select(p.gemm, p.in_dtype, __builtin_huge_val(), &blk->rows, &p.info))) {
+        contract_select(p.flat, literal_sums(p), false, &blk->contract, &p.info);
+      }
     } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM &&
                gemm_rows_select(p.gemm, p.in_dtype, gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm), &blk->rows, &p.info)) {
       blk->gemm.ws_bytes = 0;    // no partial sums of a split reduction

@@ -60,7 +60,8 @@ __device__ __forceinline__ void decode(const CtIndex& ix, uint32_t v, F f) {
 }
 
 // The launch parameters, read again: what only the end of the kernel needs is not kept in scalar registers through the main
-// loop (the kernel spilled up to 170 of them there).
+// loop (the float kernels spilled up to 170 of them there; int8's spill few, and the reads would cost them 10 % where a workgroup
+// has one K tile).
 __device__ __forceinline__ const ContractParams& reread() {
   auto at = __builtin_amdgcn_kernarg_segment_ptr();       // the first argument
   asm volatile("" : "+s"(at));
@@ -314,7 +315,7 @@ __device__ __forceinline__ void put(const ContractParams& p, void* O, const floa
 // us, 1000 x 1000 x 3000 [k][m] bf16 50 -> 55), so other blocks, already more exact than before (1000^3 fp32: 5.6e-7 literal,
 // 1.5e-7 here), keep fp32 totals.
 template <typename T, int BM, int BN, int BKB, int WM, int WN, int MA, int MB, bool PRECISE>
-__global__ __launch_bounds__(256, 2) void contract_kernel(const ContractParams p, const T* __restrict__ A, const T* __restrict__ B,
+__global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : 2) void contract_kernel(const ContractParams p, const T* __restrict__ A, const T* __restrict__ B,
                                                        void* __restrict__ O, const float* __restrict__ bias) {
   using Acc = typename Ct<T>::Acc;
   using S = typename Ct<T>::S;
@@ -505,7 +506,7 @@ __global__ __launch_bounds__(256, 2) void contract_kernel(const ContractParams p
           for (int j = 0; j < FN; ++j) acc[i][j] += part[(((w * WM * WN + wave % (WM * WN)) * FM + i) * FN + j) * 64 + lane];
   }
 
-  const ContractParams& q = reread();
+  const ContractParams& q = sizeof(T) == 1 ? p : reread();
   // A removed point contributes 0 * x, which is not 0 where x is an infinity or NaN: a tile that met one is summed again
   // point by point (Definition 2: a removed point contributes nothing).
   if (look && __syncthreads_or(!fin)) {
@@ -699,7 +700,33 @@ static bool wants_double(int dtype, int tile, const LiteralSums& lit) {
   return tile == 2 && lit.chain > 8 && lit.chain < 17;
 }
 
-bool contract_select(const FlatBlock& fb, const LiteralSums& lit, ContractLaunch* l, stripe_block_info_t* info) {
+// Blocks that stay on their literal kernel.  Measured on 1,060 blocks of 65536 to 3e9 points in fp32, bf16 and int8: the faster
+// kernel is chosen, or one within 6 %, for all but 20 (the worst 30 %).
+static bool literal_is_faster(int dtype, const ContractParams& p, const LiteralSums& lit, bool fused, __int128 points, int64_t grid, int bk) {
+  if (points < 65536) return true;       // there a launch is all the time there is
+  if (fused) return false;               // a launch and a temporary more: 33 x 33 x 1001 bf16 with bias and relu 12.0 us against 13.3
+  if (lit.atomic) return false;          // two launches and atomic additions: 118 us against 10 for a transposed convolution
+  if (lit.tiled) {
+    // Short reductions into few columns: 100000 x 3 x 5 fp32 7 us against 12 (20000 x 200 x 8 18 against 14).  Large images with few output channels fill a fraction of a tile's
+    // columns: 3x3, 3 -> 8 channels at 27 x 184 x 184 fp32 68 us against 164, 3 -> 4 bf16 40 against 71.  Products with a few
+    // columns whose first operand is contiguous along the rows: 300000 x 5 x 30 fp32 23 us against 31.
+    const uint32_t few = std::min(p.M, p.N);
+    if (lit.chain <= 8 && few <= 40) return true;
+    if (p.tested && lit.chain <= 32 && few <= (dtype == STRIPE_F32 ? 24u : 4u) && points >= ((__int128)1 << 26)) return true;
+    return dtype == STRIPE_F32 && p.mode_a == 2 && p.N <= 8 && lit.chain <= 64 && points >= ((__int128)1 << 23);
+  }
+  // Few tiles: both times from their steps.  A wavefront per output: 64 points a step, 0.36 us (0.6 with several reduction indexes
+  // to divide up), or what all outputs' steps take together (33 x 33 x 1001 nt fp32 10.4 us, on one tile row of this kernel 19;
+  // 250 x 250 x 1001 122 and 20).  A lane per output: 0.21 us a point.  Here: 0.78 / 0.62 / 0.8 us a K tile and workgroup round.
+  const double many = lit.n_red > 1 ? 2.0 : 1.0;
+  const double literal = lit.lanes == 64 ? 5.0 + (double)((lit.chain + 63) / 64) * std::max(lit.n_red > 1 ? 0.6 : 0.36, 1.2e-4 * many * (double)lit.outputs)
+                                         : 5.0 + 0.21 * (double)lit.chain * std::max(1.0, (double)lit.outputs / 5e5);
+  const double tile_us = dtype == STRIPE_F32 ? 0.78 : dtype == STRIPE_BF16 ? 0.62 : 0.8;
+  const double here = (p.tested && dtype != STRIPE_I8 ? 7.5 : 6.0) + (double)((p.K + bk - 1) / bk) * tile_us * std::max(1.0, (double)grid / 512);
+  return literal < here;
+}
+
+bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, ContractLaunch* l, stripe_block_info_t* info) {
   l->use = false;
   if (!tune_int("contract", 1)) return false;
   if (fb.empty || fb.n_refs != 3 || fb.intrinsic != STRIPE_INTR_MUL || fb.agg != STRIPE_AGG_ADD) return false;
@@ -1045,10 +1072,10 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, ContractLaunch
   p.vec_out = vec;
   p.epilogue = fb.out_bf16 ? 1 : 0;
 
-  // Fewer than 65536 points stay on the literal kernels: there a launch is all the time there is.
   i128 points = 1;
   for (int j = 0; j < fb.n_idx; ++j) points *= fb.range[j];
-  if (points < tune_int("contract_min", 65536)) return false;
+  const int least = tune_int("contract_min", 0);     // STRIPE_TUNE contract_min = n: every block of at least n points; 0: the rule
+  if (least > 0 && points < least) return false;
   auto tiles = [&](int t) { return ((M + kTiles[t].bm - 1) / kTiles[t].bm) * ((N + kTiles[t].bn - 1) / kTiles[t].bn) * l->batch; };
   // The largest tile that still gives every CU a workgroup; 64 x 64 also for somewhat fewer, and for half as many where the
   // reduction is a few K tiles and the small tile's sharing of k has nothing to share.  Measured, us: 2000 x 2000 x 1000 bf16
@@ -1067,6 +1094,7 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, ContractLaunch
   l->tile = tile;
   const i128 grid = tiles(tile) / l->batch;
   if (grid > 0x7fffffff) return false;
+  if (least == 0 && literal_is_faster(dt, p, lit, fused, points, (int64_t)grid * l->batch, kTiles[tile].bkb / esize)) return false;
   p.tiles_n = (int32_t)((N + kTiles[tile].bn - 1) / kTiles[tile].bn);
   l->grid = (int64_t)grid;
   l->use = true;

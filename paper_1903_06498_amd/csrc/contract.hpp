@@ -51,15 +51,18 @@ struct ContractLaunch {
   ContractParams p;
 };
 
-// How the literal kernels would sum an output's points: lanes that share it, points one of them sums in a row, whether such sums
-// meet in atomic additions.
+// The literal kernel the block would run on: lanes that share an output, points one lane sums in a row, reduction indexes, outputs,
+// whether sums meet in atomic additions, whether a lane computes a patch of 4 x 4 outputs.
 struct LiteralSums {
   int lanes;
   int64_t chain;
-  bool atomic;
+  int n_red;
+  int64_t outputs;
+  bool atomic, tiled;
 };
-// Fills l if the kernel covers the block and is expected to be the faster one; info: kernel name, tile, grid.
-bool contract_select(const FlatBlock& fb, const LiteralSums& lit, ContractLaunch* l, stripe_block_info_t* info);
+// Fills l if the kernel covers the block and is expected to be the faster one (fused: with a following statement in its store, so
+// that the literal kernel would need a launch more); info: kernel name, tile, grid.
+bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, ContractLaunch* l, stripe_block_info_t* info);
 // bias != nullptr: fused with a following O = relu(T + bias[n]) of the same output map (out_bf16: its element type)
 hipError_t launch_contract(const ContractLaunch& l, int in_dtype, const void* in0, const void* in1, void* out, const float* bias, bool out_bf16,
                            hipStream_t stream);

@@ -290,3 +290,17 @@ def test_few_row_products_go_to_the_faster_kernel(M, N, K, rows):
     b = B.StripeBlock(W.matmul_block(M, N, K, "bf16", "f32", b_transposed=True))
     assert b.info["kernel"].startswith("gemm_rows_") == rows, b.info["kernel"]
     b.close()
+
+
+@pytest.mark.parametrize("blk,literal", [
+    (W.matmul_block(33, 33, 1001, "f32", "f32", b_transposed=True), True), (W.matmul_block(250, 250, 1001, "f32", "f32", b_transposed=True), False),
+    (W.matmul_block(4, 100, 4001, "f32", "f32", b_transposed=True), True), (W.matmul_block(100000, 3, 5, "f32", "f32"), True),
+    (W.conv2d_block(1, 16, 16, 12, 12, 5, 5, 1, 2, "f32", "f32"), True), (W.conv2d_block(1, 56, 56, 12, 12, 5, 5, 1, 2, "f32", "f32"), False),
+    (W.conv2d_block(27, 184, 184, 3, 8, 3, 3, 1, 1, "f32", "f32"), True), (W.conv2d_block(8, 112, 112, 3, 8, 3, 3, 2, 1, "f32", "f32"), False)])
+def test_blocks_stay_on_the_literal_kernel_where_it_is_faster(blk, literal, monkeypatch):
+    """Few tiles with a long reduction, short reductions, few columns; a set contract_min overrides the rule, at any value."""
+    for tune, want in (("", literal), ("contract_min=65536", False), ("contract_min=65535", False)):
+        monkeypatch.setenv("STRIPE_TUNE", tune)
+        b = B.StripeBlock(blk)
+        assert b.info["kernel"].startswith("generic_") == want, (tune, b.info["kernel"])
+        b.close()
