@@ -622,15 +622,14 @@ hipError_t launch_t(const ContractLaunch& l, const ContractParams& p, const void
     case 4: return launch_modes<T, 1, 0>(l, p, a, b, o, bias, s);
     case 5: return launch_modes<T, 1, 1>(l, p, a, b, o, bias, s);
     case 6: return launch_modes<T, 1, 2>(l, p, a, b, o, bias, s);
-    case 7: return launch_modes<T, 1, 3>(l, p, a, b, o, bias, s);
     case 8: return launch_modes<T, 2, 0>(l, p, a, b, o, bias, s);
     case 9: return launch_modes<T, 2, 1>(l, p, a, b, o, bias, s);
     case 10: return launch_modes<T, 2, 2>(l, p, a, b, o, bias, s);
     case 11: return launch_modes<T, 2, 3>(l, p, a, b, o, bias, s);
     case 12: return launch_modes<T, 3, 0>(l, p, a, b, o, bias, s);
-    case 13: return launch_modes<T, 3, 1>(l, p, a, b, o, bias, s);
     case 14: return launch_modes<T, 3, 2>(l, p, a, b, o, bias, s);
-    default: return launch_modes<T, 3, 3>(l, p, a, b, o, bias, s);
+    case 15: return launch_modes<T, 3, 3>(l, p, a, b, o, bias, s);
+    default: return hipErrorInvalidValue;     // modes 1 and 3 exclude each other: both follow from the innermost reduction index's range
   }
 }
 
@@ -1061,9 +1060,6 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, Co
     k[0].range = padded;
     if (!fill_side(k, &p.k)) return false;
     p.K = (uint32_t)padded_K;
-    // the other operand's 16-byte vectors would cross the padding: they need a run of whole vectors, or none was padded
-    if (p.mode_a == 1) p.mode_a = 0;
-    if (p.mode_b == 1) p.mode_b = 0;
   }
   bool vec = n[0].o == 1 && n[0].range % 4 == 0 && p.o_base % 4 == 0 && !n[0].ob[0] && !n[0].ob[1];
   for (size_t j = 1; j < n.size(); ++j) vec = vec && n[j].o % 4 == 0;
