@@ -176,6 +176,60 @@ def test_rows_of_two_tiles_have_one_owner(dt, monkeypatch):
         assert np.array_equal(got.reshape(m, n)[:64].view(np.int32), clean.reshape(m, n)[:64].view(np.int32))
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("kind", ["convolution", "transposed", "both operands"])
+def test_non_finite_values_over_several_k_tiles(kind, dt, tile, monkeypatch):
+    """Infinities of both signs and NaN in both operands, a reduction of several K tiles that ends inside a vector, more rows and
+    columns than one part of a tile: the literal kernel's infinities, NaN and (to rounding) finite values."""
+    if kind == "convolution":
+        blk = W.conv2d_block(2, 13, 13, 13, 70, 5, 5, 1, 2, dt, "f32")
+    elif kind == "transposed":
+        bufs = [W.Buffer("I", "in", dt, (2, 9, 9, 36)), W.Buffer("F", "in", dt, (3, 3, 36, 20)), W.Buffer("O", "out", "f32", (2, 19, 19, 20))]
+        blk = W.flat_block(bufs, dict(n=2, y=9, x=9, i=3, j=3, c=36, k=20),
+                           [(["n", "y", "x", "c"], "assign"), (["i", "j", "c", "k"], "assign"), (["n", "2*y + i", "2*x + j", "k"], "add")])
+    else:
+        bufs = [W.Buffer("A", "in", dt, (70, 130)), W.Buffer("B", "in", dt, (68, 130)), W.Buffer("C", "out", "f32", (70, 68))]
+        blk = W.flat_block(bufs, dict(m=70, n=68, k=130), [(["m", "k"], "assign"), (["n", "k"], "assign"), (["m", "n"], "add")],
+                           constraints=["100 - k + m >= 0", "k + n - 20 >= 0"])
+    ins = [W.seeded_tensor(r.sizes, dt, i) for i, r in enumerate(blk.refs[:2])]
+    for i, t in enumerate(ins):
+        flat = t.view(-1)
+        for at, v in ((7, math.inf), (flat.numel() // 2, -math.inf), (flat.numel() // 2 + 3, math.inf), (flat.numel() - 2 - i, math.nan)):
+            flat[at] = v
+    monkeypatch.setenv("STRIPE_TUNE", f"contract_min=1,contract_tile={tile}")
+    got, sb = run_gpu(blk, ins, return_block=True)
+    assert sb.info["kernel"].startswith("contract_"), sb.info["kernel"]
+    want = run_gpu(blk, ins, "generic")
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
+    assert np.array_equal(np.isneginf(got), np.isneginf(want)) and np.isinf(want).any() and np.isnan(want).any()
+    fin = np.isfinite(want)
+    # sums of at most 325 products of order 1 in fp32: 325 * 2^-24 * sum |a b|
+    assert fin.any() and np.allclose(got[fin], want[fin], rtol=1e-5, atol=325 * 2.0 ** -24 * 325)
+
+
+def test_non_finite_values_do_not_stall(monkeypatch):
+    """One infinity in the image costs no multiple of the literal kernel's time (point by point it was 23 times that)."""
+    blk = W.conv2d_block(2, 8, 8, 256, 182, 5, 5, 1, 2, "f32", "f32")
+    ins = [W.seeded_tensor(r.sizes, "f32", i).cuda() for i, r in enumerate(blk.refs[:2])]
+    ins[0].view(-1)[12345] = math.inf
+    out, took = torch.zeros(W.output_extent(blk), device="cuda"), {}
+    for path in ("auto", "generic"):
+        sb = B.StripeBlock(blk, path)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        sb.run(ins, out)
+        ev[0].record()
+        for _ in range(5):
+            sb.run(ins, out)
+        ev[1].record()
+        torch.cuda.synchronize()
+        took[path] = ev[0].elapsed_time(ev[1])
+        kernel = sb.info["kernel"]
+        assert kernel.startswith("contract_" if path == "auto" else "generic_"), kernel
+        sb.close()
+    assert took["auto"] < 3 * took["generic"], took
+
+
 @pytest.mark.parametrize("in_dt,out_dt", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32")])
 @pytest.mark.parametrize("M,N,K", [(5, 33, 1024), (16, 16, 520), (17, 40, 512), (32, 130, 2064), (8, 1, 1040)])
 def test_few_rows(M, N, K, in_dt, out_dt):
