@@ -177,8 +177,10 @@ stripe_status_t stripe_block_create_for_path(const stripe_block_desc_t* desc, st
  * not enter the aggregation).  A block whose output elements are shared
  * between index tuples through different output indexes (O[x + i]) is run as
  * two launches: the aggregation's identity to every reached element, then an
- * atomic combine.  A statement list runs its statements in order on the
- * stream.
+ * atomic combine; sums of products over O[s*x + i] with x of one input and i of
+ * the other are rewritten to one owner per element instead, one launch that
+ * stores each element once.  A statement list runs its statements in order on
+ * the stream.
  * Workspace: temporaries of a statement list that are not fused away, and
  * the partial sums of a dense contraction whose reduction index is split
  * over workgroups (Section 2.1: aggregations are associative and commutative,

@@ -147,7 +147,7 @@ __device__ __forceinline__ uint32_t load_elem(__amdgpu_buffer_rsrc_t r, uint32_t
 
 // One operand's share of a K tile: ROWS x BKB bytes over 256 lanes, DW dwords each.  MODE: how it is fetched (see
 // ContractParams::mode_a); a template parameter, so that the loads of a K tile are straight-line code: with the three forms
-// behind branches the compiler waited for each load at the join (fp32 1000^3: 87 us, bf16 [k][m] x [k][n] 1000 x 1000 x 3000: 127 us).
+// behind branches the compiler waits for each load at the join.
 template <typename T, int ROWS, int BKB, bool SIDE_A, int MODE>
 struct Stager {
   static constexpr int E = sizeof(T), KP = Ct<T>::KP, V = Ct<T>::V;
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
   __shared__ int2 ob_m[BM], ob_n[BN];
   constexpr uint32_t BK = BKB / sizeof(T);
   // k's share of the addresses and range tests, for both operands: a K tile's entries are worked out once, one iteration
-  // before its loads, in a ring of three (decoded at each load, they were most of the kernel's time: bf16 [k][m] x [k][n] 1000 x 1000 x 3000 87 us)
+  // before its loads, in a ring of three (decoded at each load, they are most of the kernel's time)
   __shared__ i32x4 ks_a[3][BK], ks_b[3][BK];
   static_assert(BK <= 256, "one entry per lane");
 
@@ -760,9 +760,9 @@ static bool literal_is_faster(int dtype, const ContractParams& p, const LiteralS
   if (fused) return false;               // a launch and a temporary more: 33 x 33 x 1001 bf16 with bias and relu 12.0 us against 13.3
   if (lit.atomic) return false;          // two launches and atomic additions: 118 us against 10 for a transposed convolution
   if (lit.tiled) {
-    // Short reductions into few columns: 100000 x 3 x 5 fp32 7 us against 12 (20000 x 200 x 8 18 against 14).  Large images with few output channels fill a fraction of a tile's
-    // columns: 3x3, 3 -> 8 channels at 27 x 184 x 184 fp32 68 us against 164, 3 -> 4 bf16 40 against 71.  Products with a few
-    // columns whose first operand is contiguous along the rows: 300000 x 5 x 30 fp32 23 us against 31.
+    // Short reductions into few columns: 100000 x 3 x 5 fp32 7 us against 12 (20000 x 200 x 8 18 against 14).  Large images with few
+    // output channels fill a fraction of a tile's columns: 3x3, 3 -> 8 channels at 27 x 184 x 184 fp32 68 us against 164, 3 -> 4
+    // bf16 40 against 71.  Products with a few columns whose first operand is contiguous along the rows: 300000 x 5 x 30 fp32 23 us against 31.
     const uint32_t few = std::min(p.M, p.N);
     if (lit.chain <= 8 && few <= 40) return true;
     if (p.tested && lit.chain <= 32 && few <= (dtype == STRIPE_F32 ? 24u : 4u) && points >= ((__int128)1 << 26)) return true;
