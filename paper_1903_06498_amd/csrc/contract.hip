@@ -62,10 +62,16 @@ __device__ __forceinline__ void decode(const CtIndex& ix, uint32_t v, F f) {
 // The launch parameters, read again: what only the end of the kernel needs is not kept in scalar registers through the main
 // loop (the float kernels spilled up to 170 of them there; int8's spill few, and the reads would cost them 10 % where a workgroup
 // has one K tile).
-__device__ __forceinline__ const ContractParams& reread() {
-  auto at = __builtin_amdgcn_kernarg_segment_ptr();       // the first argument
+struct KernelArgs {
+  ContractParams p;
+  const void *a, *b;
+  void* o;
+  const float* bias;
+};
+__device__ __forceinline__ const KernelArgs& reread() {
+  auto at = __builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(at));
-  return *(const ContractParams*)at;
+  return *(const KernelArgs*)at;
 }
 
 struct KPart {
@@ -506,7 +512,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
           for (int j = 0; j < FN; ++j) acc[i][j] += part[(((w * WM * WN + wave % (WM * WN)) * FM + i) * FN + j) * 64 + lane];
   }
 
-  const ContractParams& q = sizeof(T) == 1 ? p : reread();
+  constexpr bool again = sizeof(T) > 1;
+  const KernelArgs& args = reread();
+  const ContractParams& q = again ? args.p : p;
+  void* const out = again ? args.o : O;
+  const float* const bias_n = again ? args.bias : bias;
   // A removed point contributes 0 * x, which is not 0 where x is an infinity or NaN: a tile that met one is summed again
   // (Definition 2: a removed point contributes nothing).  The operands are staged as before, in parts of at most 64 x 32 outputs;
   // 16 bytes of k at a time are summed, and only where such a sum is NaN are its points looked at one by one.  (Point by point from
@@ -533,8 +543,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
           __syncthreads();
           Stager<T, BM, BKB, true, MA> one_a;
           Stager<T, BN, BKB, false, MB> one_b;
-          one_a.load(q, __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)q.bytes_a, 0x00020000), rows_a, ks_a[0], kt * BK);
-          one_b.load(q, __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, (int)q.bytes_b, 0x00020000), rows_b, ks_b[0], kt * BK);
+          one_a.load(q, __builtin_amdgcn_make_buffer_rsrc((void*)args.a, 0, (int)q.bytes_a, 0x00020000), rows_a, ks_a[0], kt * BK);
+          one_b.load(q, __builtin_amdgcn_make_buffer_rsrc((void*)args.b, 0, (int)q.bytes_b, 0x00020000), rows_b, ks_b[0], kt * BK);
           one_a.store(q, lds, kt * BK, false);
           one_b.store(q, lds + BM * PITCH, kt * BK, false);
           __syncthreads();
@@ -573,7 +583,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
             const int mi = pm + 16 * i, ni = pn + 16 * j;
             const i32x4 rm = rows_a[mi], rn = rows_b[ni];
             if (rm[1] == kFar || rn[1] == kFar || ob_m[mi].x + ob_n[ni].x > q.ob[0] || ob_m[mi].y + ob_n[ni].y > q.ob[1]) continue;
-            put<S>(q, O, bias, o_base + rm[3] + rn[3], rn[3], (S)total[i][j]);
+            put<S>(q, out, bias_n, o_base + rm[3] + rn[3], rn[3], (S)total[i][j]);
           }
       }
       return;
@@ -598,7 +608,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
     if (q.epilogue >= 2) {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (n_in[e]) bs[e] = bias[n_off[e]];      // one column index of unit output stride
+        if (n_in[e]) bs[e] = bias_n[n_off[e]];      // one column index of unit output stride
     }
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
@@ -620,15 +630,15 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
       if (q.vec_out && n_in[0]) {
         if (om.x + on[0].x <= q.ob[0] && om.y + on[0].y <= q.ob[1]) {
           typedef S s4 __attribute__((ext_vector_type(4)));
-          if (half) *(bf16x4*)((uint16_t*)O + off + n_off[0]) = __builtin_convertvector((f32x4){(float)v[0], (float)v[1], (float)v[2], (float)v[3]}, bf16x4);
-          else *(s4*)((S*)O + off + n_off[0]) = (s4){v[0], v[1], v[2], v[3]};
+          if (half) *(bf16x4*)((uint16_t*)out + off + n_off[0]) = __builtin_convertvector((f32x4){(float)v[0], (float)v[1], (float)v[2], (float)v[3]}, bf16x4);
+          else *(s4*)((S*)out + off + n_off[0]) = (s4){v[0], v[1], v[2], v[3]};
         }
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if (n_in[e] && om.x + on[e].x <= q.ob[0] && om.y + on[e].y <= q.ob[1]) {
-            if (half) ((__bf16*)O)[off + n_off[e]] = (__bf16)(float)v[e];
-            else ((S*)O)[off + n_off[e]] = v[e];
+            if (half) ((__bf16*)out)[off + n_off[e]] = (__bf16)(float)v[e];
+            else ((S*)out)[off + n_off[e]] = v[e];
           }
       }
     }
@@ -1129,9 +1139,9 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, Co
   auto tiles = [&](int t) { return ((M + kTiles[t].bm - 1) / kTiles[t].bm) * ((N + kTiles[t].bn - 1) / kTiles[t].bn) * l->batch; };
   // The largest tile that still gives every CU a workgroup; 64 x 64 also for somewhat fewer, and for half as many where the
   // reduction is a few K tiles and the small tile's sharing of k has nothing to share.  Measured, us: 2000 x 2000 x 1000 bf16
-  // [k][m] 42 on 128 x 128, 54 on 64 x 64, 78 on 32 x 32; 3569 x 256 x 3264 bf16 (224 tiles of 64 x 64) 57 against 61 on 32 x 32;
-  // 500 x 1000 x 777 (128 tiles) 17 against 14; 596 x 715 x 64 (120 tiles) 8.6 against 9.3; a 3 -> 64-channel 5 x 5
-  // convolution at 135 x 135 (428 tiles of 128 x 64) 16 on those, 20 on 64 x 64.
+  // [k][m] 40 on 128 x 128, 53 on 64 x 64, 72 on 32 x 32; 3569 x 256 x 3264 bf16 (224 tiles of 64 x 64) 54 against 58 on 32 x 32;
+  // 500 x 1000 x 777 (128 tiles) 14 against 12; 238 x 2368 x 64 fp32 (148 tiles) 7.1 both; a 3 -> 64-channel 5 x 5
+  // convolution at 135 x 135 (428 tiles of 128 x 64) 16 on those, 17 on 64 x 64.
   int tile = tiles(0) >= 256 && M > 64 && N > 64               ? 0
              : tiles(3) >= 256                                  ? 3
              : tiles(1) >= 192 || (tiles(1) >= 96 && (int64_t)p.K * esize <= 512) ? 1
