@@ -190,7 +190,9 @@ stripe_status_t stripe_block_create_for_path(const stripe_block_desc_t* desc, st
  * with stripe_block_set_workspace(), run() uses it and never allocates;
  * otherwise the handle allocates it on its first run on a device (the only
  * allocation run() ever makes; that first call then is not purely
- * asynchronous) and frees it on destroy.  Either way two overlapping runs of
+ * asynchronous) and frees it on destroy.  A first run under graph capture
+ * cannot allocate: products with at most 32 rows are then recorded on a kernel
+ * that needs no workspace, anything else is to be run once before.  Either way two overlapping runs of
  * one handle race on the workspace.  Handles that report 0 bytes never
  * allocate.
  * Alignment: the specialised kernel families move 16 bytes per lane.

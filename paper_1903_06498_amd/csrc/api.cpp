@@ -44,9 +44,12 @@ struct stripe_block {
   // run on a device), else the library's static scratch array (run_static).
   std::vector<int64_t> temp_off, stage_ws_off;
   int64_t ws_bytes = 0;
-  // Where that is more than the static scratch holds, run_static takes the few-rows kernel for the split products it can run.
+  // Split products that the few-rows kernel can run without partial sums (and, fused with the second statement, without a
+  // temporary: alt_fused, as `fused`) are run there where that memory cannot be had: run_static where the static scratch is too
+  // small, and a first run under graph capture.
   RowsLaunch static_rows;
   int64_t static_ws_bytes = 0;
+  int alt_fused = 0;
   void* caller_ws = nullptr;
   size_t caller_ws_bytes = 0;
   void* owned_ws = nullptr;
@@ -284,12 +287,14 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
     const Plan& c = s0.blk->plan;
     const FlatBlock& e = s1.blk->plan.flat;
     // a split product is followed by a launch of its own for the second statement (about 3 us), the few-rows kernel stores through it
-    bool few_rows = s0.blk->rows.use && c.in_dtype == STRIPE_BF16;
+    bool few_rows = s0.blk->rows.use && c.in_dtype == STRIPE_BF16, alt = false;
     RowsLaunch rows = s0.blk->rows;
-    stripe_block_info_t rows_info = c.info;
-    if (!few_rows && path == STRIPE_PATH_AUTO && c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && s0.blk->gemm.split_k > 1)
+    stripe_block_info_t rows_info = c.info, unused = c.info;
+    if (!few_rows && path == STRIPE_PATH_AUTO && c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && s0.blk->gemm.split_k > 1) {
       few_rows = gemm_rows_select(c.gemm, c.in_dtype, gemm_few_rows_us(c.gemm, c.in_dtype, s0.blk->gemm) + 3.0, &rows, &rows_info);
-    bool ok = (few_rows || (c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && gemm_can_fuse_bias_relu(c.gemm, s0.blk->gemm))) &&
+      alt = !few_rows && gemm_rows_select(c.gemm, c.in_dtype, __builtin_huge_val(), &rows, &unused);
+    }
+    bool ok = (few_rows || alt || (c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && gemm_can_fuse_bias_relu(c.gemm, s0.blk->gemm))) &&
               root->refs[s0.dst].dir == STRIPE_TEMP && s1.n_in == 2 && s1.src[0] == s0.dst && !e.empty && e.intrinsic == STRIPE_INTR_ADD_RELU &&
               e.cons.empty() && e.n_refs == 3 && e.n_idx >= 2 && e.ref[0].dtype == STRIPE_F32 && e.ref[1].dtype == STRIPE_F32;
     if (ok) {
@@ -301,7 +306,7 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
         ok = rng[n] == c.gemm.N && rng[m] == c.gemm.M && ct[n] == 1 && cbias[n] == 1 && co[n] == 1 && ct[m] == c.gemm.c_m && cbias[m] == 0 &&
              co[m] >= c.gemm.N && e.ref[0].addr.k == c.gemm.c_base;
         if (ok) {
-          prog->fused = e.out_bf16 ? 4 : 3;
+          (alt ? prog->alt_fused : prog->fused) = e.out_bf16 ? 4 : 3;
           prog->plan.gemm = c.gemm;
           prog->gemm = s0.blk->gemm;
           prog->rows = rows;
@@ -311,7 +316,7 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
           prog->fuse_bias_off = e.ref[1].addr.k;
           prog->fuse_o_m = co[m];
           prog->fuse_o_base = e.ref[2].addr.k;
-          prog->temp_bytes[s0.dst] = 0;
+          if (!alt) prog->temp_bytes[s0.dst] = 0;
         }
       }
     }
@@ -424,10 +429,16 @@ stripe_status_t static_scratch_of(int dev, unsigned char** out) {
 
 // Where the handle's workspace lives for this run.  use_static: the GPU's static scratch array (no allocation
 // ever); otherwise the caller's workspace if one was set, else memory the handle allocates on its first run on a
-// device.  A handle that needs no workspace gets NULL.
-stripe_status_t resolve_workspace(stripe_block* blk, bool use_static, unsigned char** ws) {
+// device.  A handle that needs no workspace gets NULL.  *without: the run is to do without (see alt_fused).
+stripe_status_t resolve_workspace(stripe_block* blk, bool use_static, hipStream_t stream, unsigned char** ws, bool* without) {
   *ws = nullptr;
+  *without = false;
   if (blk->ws_bytes == 0) return STRIPE_OK;
+  const bool can_do_without = blk->alt_fused || (blk->stages.empty() && blk->static_rows.use);
+  if (use_static && can_do_without && blk->ws_bytes > (int64_t)STRIPE_STATIC_SCRATCH_BYTES) {
+    *without = true;
+    return STRIPE_OK;
+  }
   if (use_static && blk->static_ws_bytes > (int64_t)STRIPE_STATIC_SCRATCH_BYTES)
     return fail(STRIPE_ERR_NOMEM, "the block's workspace needs " + std::to_string((long long)blk->static_ws_bytes) + " bytes, the static scratch holds " +
                                       std::to_string((long long)STRIPE_STATIC_SCRATCH_BYTES));
@@ -440,6 +451,11 @@ stripe_status_t resolve_workspace(stripe_block* blk, bool use_static, unsigned c
   if (e != hipSuccess) return fail(STRIPE_ERR_HIP, hipGetErrorString(e));
   if (use_static) return static_scratch_of(dev, ws);
   if (dev != blk->owned_ws_dev) {   // first run (on this device)
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (can_do_without && stream && hipStreamIsCapturing(stream, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusActive) {
+      *without = true;
+      return STRIPE_OK;
+    }
     if (blk->owned_ws) (void)hipFree(blk->owned_ws);
     blk->owned_ws = nullptr;
     blk->owned_ws_dev = -1;
@@ -455,19 +471,20 @@ stripe_status_t resolve_workspace(stripe_block* blk, bool use_static, unsigned c
 
 stripe_status_t run_single(stripe_block* blk, const void* const* inputs, void* output, void* hip_stream, unsigned char* ws, bool static_rows);
 
-stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void* output, void* hip_stream, unsigned char* ws, bool static_rows) {
+stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void* output, void* hip_stream, unsigned char* ws, bool static_rows, bool without) {
   hipError_t e = hipSuccess;
   const int R = (int)prog->input_slot.size();
-  if (prog->fused) {
+  const int fused = prog->fused ? prog->fused : without ? prog->alt_fused : 0;
+  if (fused) {
     const Stage &s0 = prog->stages[0], &s1 = prog->stages[1];
     const float* bias = (const float*)inputs[prog->input_slot[s1.src[1]]] + prog->fuse_bias_off;
-    if (prog->fused >= 5) {
+    if (fused >= 5) {
       e = launch_contract(prog->contract, prog->plan.in_dtype, inputs[prog->input_slot[s0.src[0]]], inputs[prog->input_slot[s0.src[1]]], output, bias,
-                          prog->fused == 6, (hipStream_t)hip_stream);
+                          fused == 6, (hipStream_t)hip_stream);
       if (e != hipSuccess) return fail(STRIPE_ERR_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
       return STRIPE_OK;
     }
-    const bool conv = prog->fused < 3, out_bf16 = prog->fused == 2 || prog->fused == 4;
+    const bool conv = fused < 3, out_bf16 = fused == 2 || fused == 4;
     const bool any_align = prog->rows.use && prog->plan.info.path == STRIPE_PATH_GENERIC;    // generic path: any element alignment
     if (any_align) {
     } else if (((uintptr_t)inputs[prog->input_slot[s0.src[0]]] % 16) || ((uintptr_t)inputs[prog->input_slot[s0.src[1]]] % 16) ||
@@ -475,13 +492,13 @@ stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void*
       return fail(STRIPE_ERR_MISALIGNED, "the fused matrix-core kernel needs 16-byte aligned operands (convolution: also bias and output)");
     if (prog->rows.use)
       e = launch_gemm_rows(prog->plan.gemm, prog->plan.in_dtype, inputs[prog->input_slot[s0.src[0]]], inputs[prog->input_slot[s0.src[1]]], output,
-                           prog->fuse_o_m, prog->fuse_o_base, bias, prog->fused == 4, (hipStream_t)hip_stream);
-    else if (prog->fused >= 3)
+                           prog->fuse_o_m, prog->fuse_o_base, bias, fused == 4, (hipStream_t)hip_stream);
+    else if (fused >= 3)
       e = launch_gemm_bias_relu(prog->plan.gemm, prog->gemm, inputs[prog->input_slot[s0.src[0]]], inputs[prog->input_slot[s0.src[1]]], bias,
-                                output, prog->fuse_o_m, prog->fuse_o_base, prog->fused == 4, (hipStream_t)hip_stream);
+                                output, prog->fuse_o_m, prog->fuse_o_base, fused == 4, (hipStream_t)hip_stream);
     else
     e = launch_conv_bias_relu(prog->plan.conv, prog->conv, inputs[prog->input_slot[s0.src[0]]], inputs[prog->input_slot[s0.src[1]]], bias,
-                              output, prog->fused == 2, (hipStream_t)hip_stream);
+                              output, fused == 2, (hipStream_t)hip_stream);
     if (e != hipSuccess) return fail(STRIPE_ERR_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
     return STRIPE_OK;
   }
@@ -533,10 +550,11 @@ stripe_status_t run_any(stripe_block* blk, const void* const* inputs, void* outp
   for (int i = 0; i < blk->n_inputs; ++i)
     if (!inputs[i]) return fail(STRIPE_ERR_NULL, "an input pointer is NULL");
   unsigned char* ws = nullptr;
-  const stripe_status_t rc = resolve_workspace(blk, use_static, &ws);
+  bool without = false;
+  const stripe_status_t rc = resolve_workspace(blk, use_static, (hipStream_t)hip_stream, &ws, &without);
   if (rc != STRIPE_OK) return rc;
-  const bool static_rows = use_static && blk->ws_bytes > (int64_t)STRIPE_STATIC_SCRATCH_BYTES;
-  if (!blk->stages.empty()) return run_program(blk, inputs, output, hip_stream, ws, static_rows);
+  const bool static_rows = without || (use_static && blk->ws_bytes > (int64_t)STRIPE_STATIC_SCRATCH_BYTES);
+  if (!blk->stages.empty()) return run_program(blk, inputs, output, hip_stream, ws, static_rows, without);
   return run_single(blk, inputs, output, hip_stream, ws, static_rows);
 }
 

@@ -412,3 +412,33 @@ def test_captured_runs(kind, monkeypatch):
         torch.cuda.synchronize()
         assert torch.equal(out, eager) and out.any()
     sb.close()
+
+
+@pytest.mark.parametrize("fused", [False, True])
+def test_first_run_of_a_split_product_under_capture(fused):
+    """Few rows, few columns and a long reduction run as a split product with a workspace; a first run that is being captured,
+    where nothing can be allocated, is recorded on the kernel that needs none."""
+    M, N, K = 8, 256, 16384
+    blk = W.linear_bias_relu_program(M, N, K, "f32", b_transposed=True) if fused else matmul(M, N, K, "bf16", "nt")
+    ins = [W.seeded_tensor((M, K), "bf16", 0), W.seeded_tensor((N, K), "bf16", 1)] + ([W.seeded_tensor((N,), "f32", 2)] if fused else [])
+    want = ins[0].double() @ ins[1].double().t()
+    if fused:
+        want = torch.relu(want + ins[2].double())
+    tol = K * 2.0 ** -24 * (ins[0].double().abs() @ ins[1].double().abs().t()) + 1e-5
+    sb = B.StripeBlock(blk)
+    assert sb.info["workspace_bytes"] > 0 and "splitk" in sb.info["kernel"], sb.info
+    dins = [t.cuda() for t in ins]
+    out = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sb.run(dins, out)
+    eager = torch.zeros_like(out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert ((out.cpu().double() - want).abs() <= tol).all()
+        sb.run(dins, eager)          # allocates now, and runs split
+        torch.cuda.synchronize()
+        assert ((eager.cpu().double() - want).abs() <= tol).all()
+    sb.close()
