@@ -176,6 +176,24 @@ def test_rows_of_two_tiles_have_one_owner(dt, monkeypatch):
         assert np.array_equal(got.reshape(m, n)[:64].view(np.int32), clean.reshape(m, n)[:64].view(np.int32))
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("Ci", [3, 8])
+def test_infinities_on_the_tiled_literal_kernel(Ci, dt, monkeypatch):
+    """The kernel that few output channels over a large image stay on skips removed points too: infinite filter taps at the
+    image's border against the oracle."""
+    monkeypatch.setenv("STRIPE_TUNE", "generic_tiled=2")
+    blk = W.conv2d_block(1, 9, 8, Ci, 10, 3, 3, 1, 1, dt, "f32")
+    ins = [W.seeded_tensor((1, 9, 8, Ci), dt, 0).abs() + 0.5, W.seeded_tensor((3, 3, 10, Ci), dt, 1)]
+    ins[1][0, 1, 3, 2] = math.inf
+    ins[1][2, 2, 7, 0] = math.nan
+    got, sb = run_gpu(blk, ins, "generic", return_block=True)
+    assert sb.info["kernel"].startswith("generic_tiled_4x4"), sb.info
+    want = O.evaluate(blk, [W.to_numpy(t).ravel() for t in ins]).out
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want)) and np.isinf(want).any()
+    fin = np.isfinite(want)
+    assert np.allclose(got[fin], want[fin], rtol=1e-5, atol=1e-4)       # 72 products of order 1 in fp32
+
+
 @pytest.mark.parametrize("tile", [0, 1, 2, 3])
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("kind", ["convolution", "transposed", "both operands"])
