@@ -9,18 +9,21 @@
 // 2*i1 + i0 < R become range tests.  What the atomic form did in 117 us (stride-2 transposed 3x3, 8 x 28 x 28 x 32) then
 // is a product like any other.
 //
-// A workgroup of four wavefronts owns a BM x BN tile.  Operands are fetched through buffer loads: a point outside the
+// Operands are fetched through buffer loads: a point outside the
 // polyhedron or the tile's remainder gets an offset beyond the buffer's range and the load returns zero, so no select
 // follows.  The range is the operand's declared buffer: a constraint is tested for one operand (that suffices for the
 // sum, one factor is zero), so the other one may be fetched at a removed point, where its address is not the block's to
-// read.  It is then fetched element by element, and an element outside the buffer loads as zero.  Three ways to fetch, chosen per operand by the planner: 16 bytes along k; vectors along the row index, turned
-// to k order in registers; or element by element with neighbouring lanes on neighbouring k.  Tiles go registers -> LDS
-// (two buffers, one barrier per K tile) in rows of BKB bytes + 16, which spreads the 16 rows of a fragment read over all
-// banks; the loads of the next K tile are in flight during the matrix instructions.  A 16-byte fragment is one
+// read.  It is then fetched element by element, and an element outside the buffer loads as zero.  Ways to fetch, chosen per operand
+// by the planner: 16 or 8 bytes along k; vectors along the row index; or element by element with neighbouring lanes on
+// neighbouring k.  Tiles go registers -> LDS, k-contiguous operands as rows of k, the others as they lie in memory, lines of
+// rows that the transposing LDS reads turn (Stager, KMajor); a 16-byte fragment is one
 // 16x16x32 bf16 / 16x16x64 int8 instruction or four 16x16x4 fp32 ones; sums are fp32 / int32 throughout.
+// Two kernels: many tiles are shared by four wavefronts each (contract_kernel), few tiles by eight or sixteen that share the
+// reduction out (contract_waves_kernel); tile_us() has what each tile takes.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <type_traits>
 #include <vector>
@@ -79,14 +82,14 @@ struct KPart {
   int run;        // elements from here to the end of the innermost index's real range
 };
 
-template <bool SIDE_A>
-__device__ __forceinline__ KPart k_part(const ContractParams& p, uint32_t k) {
+// `side_a` may differ between lanes
+__device__ __forceinline__ KPart k_part(const ContractParams& p, uint32_t k, bool side_a) {
   KPart r = {0, 0, 0, 0};
   auto add = [&](int j, int v) {
     if (j == 0) r.run = p.k_run - v;
-    r.off += (SIDE_A ? p.k_a[j] : p.k_b[j]) * v;
-    r.t0 += (SIDE_A ? p.ka_t[0][j] : p.kb_t[0][j]) * v;
-    r.t1 += (SIDE_A ? p.ka_t[1][j] : p.kb_t[1][j]) * v;
+    r.off += (side_a ? p.k_a[j] : p.k_b[j]) * v;
+    r.t0 += (side_a ? p.ka_t[0][j] : p.kb_t[0][j]) * v;
+    r.t1 += (side_a ? p.ka_t[1][j] : p.kb_t[1][j]) * v;
   };
   if (p.k.n == 1) add(0, (int)k);
   else decode(p.k, k, add);
@@ -151,47 +154,110 @@ __device__ __forceinline__ uint32_t load_elem(__amdgpu_buffer_rsrc_t r, uint32_t
   else return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0);
 }
 
-// One operand's share of a K tile: ROWS x BKB bytes over 256 lanes, DW dwords each.  MODE: how it is fetched (see
-// ContractParams::mode_a); a template parameter, so that the loads of a K tile are straight-line code: with the three forms
+template <int E>
+struct Bits {
+  using type = typename std::conditional<E == 4, uint32_t, typename std::conditional<E == 2, uint16_t, uint8_t>::type>::type;
+};
+
+// How a tile lies in LDS.  Row-major operands: rows of BKB bytes of k whose 16-byte chunks are swizzled with the row, so that the
+// 16 rows of a fragment read cover all banks.
+template <int BKB>
+__device__ __forceinline__ constexpr uint32_t row_key(uint32_t row) {      // 16 chunks are one sweep over the banks
+  return BKB >= 256 ? row & 15 : BKB == 128 ? (row >> 1) & 7 : (row >> 2) & 3;
+}
+template <int BKB>
+__device__ __forceinline__ constexpr uint32_t row_at(uint32_t row, uint32_t chunk) {
+  return row * BKB + ((chunk ^ row_key<BKB>(row)) << 4);
+}
+// Operands fetched along their row index stay as they lie in memory, a line of ROWS elements per k; fragments are read with
+// the transposing LDS reads (fp32: element by element).  A half wavefront of such a read meets 8 (bf16), 4 (fp32) or 16 (int8)
+// values of k whose lines must fall on different banks: they differ in the bits of k listed here.  As many of them as a line
+// has groups of 16 rows are exclusive-ored onto the group, the others become the lowest bits of the line's number.
+template <typename T, int ROWS>
+struct KMajor {
+  static constexpr int E = sizeof(T), BITS = E == 2 ? 3 : E == 4 ? 2 : 4, STEP_BITS = E == 2 ? 5 : E == 4 ? 4 : 6;
+  static constexpr int LINE = ROWS * E, GROUPS = ROWS / 16, LG = GROUPS >= 8 ? 3 : GROUPS >= 4 ? 2 : GROUPS >= 2 ? 1 : 0;
+  static constexpr int LOW = BITS > LG ? BITS - LG : 0;
+  static __device__ __forceinline__ constexpr int bit(int t) { return E == 2 ? (t == 2 ? 3 : t) : E == 4 ? t + 2 : (t == 3 ? 4 : t); }
+  static __device__ __forceinline__ constexpr bool low(int b) {
+    for (int t = 0; t < LOW; ++t)
+      if (bit(t) == b) return true;
+    return false;
+  }
+  static __device__ __forceinline__ constexpr uint32_t line(uint32_t k) {       // k -> number of its line
+    uint32_t out = k >> STEP_BITS << STEP_BITS;
+    int pos = 0;
+    for (int t = 0; t < LOW; ++t) out |= (k >> bit(t) & 1) << pos++;
+    for (int b = 0; b < STEP_BITS; ++b)
+      if (!low(b)) out |= (k >> b & 1) << pos++;
+    return out;
+  }
+  static __device__ __forceinline__ constexpr uint32_t k_of(uint32_t line) {
+    uint32_t out = line >> STEP_BITS << STEP_BITS;
+    int pos = 0;
+    for (int t = 0; t < LOW; ++t) out |= (line >> pos++ & 1) << bit(t);
+    for (int b = 0; b < STEP_BITS; ++b)
+      if (!low(b)) out |= (line >> pos++ & 1) << b;
+    return out;
+  }
+  static __device__ __forceinline__ constexpr uint32_t key(uint32_t k) {
+    uint32_t out = 0;
+    for (int t = LOW; t < BITS; ++t) out |= (k >> bit(t) & 1) << (t - LOW);
+    return out;
+  }
+  static __device__ __forceinline__ constexpr uint32_t at(uint32_t k, uint32_t row) {
+    return line(k) * LINE + ((row / 16) ^ key(k)) * (16 * E) + row % 16 * E;
+  }
+};
+
+// One operand's share of a K tile: ROWS x BKB bytes over NT lanes, DW dwords each.  MODE: how it is fetched (see
+// ContractParams::mode_a); a template parameter, so that the loads of a K tile are straight-line code: with the forms
 // behind branches the compiler waits for each load at the join.
-template <typename T, int ROWS, int BKB, bool SIDE_A, int MODE>
+template <typename T, int NT, int ROWS, int BKB, bool SIDE_A, int MODE>
 struct Stager {
   static constexpr int E = sizeof(T), KP = Ct<T>::KP, V = Ct<T>::V;
-  static constexpr int DW = ROWS * BKB / 4 / 256;
-  static constexpr int PITCH = BKB + 16;
-  static_assert(MODE != 2 || DW % V == 0, "whole units of V rows per lane");
-  static constexpr int CH = BKB / 16, STEP1 = 256 / CH, VE = 16 / E;         // mode 1: vectors of VE along k
-  static constexpr int KD = BKB / 4, STEP0 = 256 / KD;                       // mode 0: dwords of KP along k
-  static constexpr int G = ROWS / V, GL = G < 8 ? G : 8;                     // mode 2: groups of V rows, GL on neighbouring lanes
-  static constexpr int CH3 = BKB / 8, STEP3 = 256 / CH3, VE3 = 8 / E;         // mode 3: vectors of 8 bytes along k
+  static constexpr int DW = ROWS * BKB / 4 / NT;
+  static constexpr int CH = BKB / 16, STEP1 = NT / CH, VE = 16 / E;          // mode 1: vectors of VE along k
+  static constexpr int KD = BKB / 4, STEP0 = NT / KD;                        // mode 0: dwords of KP along k
+  static constexpr int G = ROWS / V, STEP2 = NT / G, UD = V * E / 4;         // mode 2: groups of V rows, UD dwords each, neighbouring groups on neighbouring lanes
+  static constexpr int CH3 = BKB / 8, STEP3 = NT / CH3, VE3 = 8 / E;          // mode 3: vectors of 8 bytes along k
+  static_assert(DW % 4 == 0, "whole vectors per lane");
+  using L = KMajor<T, ROWS>;
+  static constexpr int SPAN = MODE == 1 ? VE : MODE == 3 ? VE3 : 1, ENTRIES = BKB / E / SPAN;   // k per table entry, entries of a K tile
+  static constexpr int NR = MODE == 1 ? DW / 4 : MODE == 3 ? DW / 2 : MODE == 2 ? 1 : 0;      // rows whose entries a lane keeps
   uint32_t r[DW];
   uint32_t back[MODE == 3 ? DW / 2 : 1];     // mode 3: bits a vector was fetched early (it would end behind the operand)
   uint64_t mask = 0;                         // mode 3: the vector's elements inside the innermost index's range
+
+  // the row entries a lane's loads need in every K tile
+  static __device__ __forceinline__ void keep(const i32x4* rows, i32x4* row, int tid) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) row[i] = rows[MODE == 1 ? tid / CH + i * STEP1 : MODE == 3 ? tid / CH3 + i * STEP3 : tid % G * V];
+  }
 
   static __device__ __forceinline__ uint32_t place(const ContractParams& p, const i32x4 row, const i32x4 k) {
     const bool ok = ((uint32_t)(row[1] + k[1]) <= (SIDE_A ? p.top_a[0] : p.top_b[0])) & ((uint32_t)(row[2] + k[2]) <= (SIDE_A ? p.top_a[1] : p.top_b[1]));
     return ok ? (uint32_t)(row[0] + k[0]) * E : kOutside;
   }
 
-  __device__ __forceinline__ void load(const ContractParams& p, __amdgpu_buffer_rsrc_t buf, const i32x4* rows, const i32x4* ks, uint32_t k0) {
-    const int tid = threadIdx.x;
+  __device__ __forceinline__ void load(const ContractParams& p, __amdgpu_buffer_rsrc_t buf, const i32x4* rows, const i32x4* row, const i32x4* ks, uint32_t k0, int tid) {
     if constexpr (MODE == 1) {
       const uint32_t k = k0 + (tid % CH) * VE;
-      i32x4 kp = ks[(tid % CH) * VE];
+      i32x4 kp = ks[tid % CH];
       if (k < p.K && k + VE > p.K) kp[0] -= (int)(k + VE - p.K);    // a row's last, partial vector is fetched from earlier on; store() shifts it down
 #pragma unroll
       for (int i = 0; i < DW / 4; ++i) {
-        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(buf, place(p, rows[tid / CH + i * STEP1], kp), 0, 0);
+        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(buf, place(p, row[i], kp), 0, 0);
 #pragma unroll
         for (int e = 0; e < 4; ++e) r[4 * i + e] = x[e];
       }
     } else if constexpr (MODE == 3) {
-      const i32x4 kp = ks[(tid % CH3) * VE3];
+      const i32x4 kp = ks[tid % CH3];
       const uint32_t last = (SIDE_A ? p.bytes_a : p.bytes_b) - 8;
       mask = kp[3] >= VE3 ? ~0ull : kp[3] <= 0 ? 0ull : (1ull << (8 * E * kp[3])) - 1;
 #pragma unroll
       for (int i = 0; i < DW / 2; ++i) {
-        const uint32_t off = place(p, rows[tid / CH3 + i * STEP3], kp);
+        const uint32_t off = place(p, row[i], kp);
         const bool late = off > last && off != kOutside;
         back[i] = late ? (off - last) * 8 : 0;
         const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(buf, late ? last : off, 0, 0);
@@ -199,24 +265,17 @@ struct Stager {
         r[2 * i + 1] = x[1];
       }
     } else if constexpr (MODE == 2) {
-      // V rows x KP steps of k per unit; lanes: GL row groups, then k, then the other row groups
 #pragma unroll
-      for (int i = 0; i < DW / V; ++i) {
-        const int u = tid + i * 256;
-        const int g = u % GL + u / (GL * KD) * GL, kd = u / GL % KD;
-        const i32x4 row = rows[g * V];
+      for (int i = 0; i < DW / UD; ++i) {
+        const uint32_t off = place(p, row[0], ks[L::k_of(tid / G + i * STEP2)]);
+        if constexpr (UD == 4) {
+          const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(buf, off, 0, 0);
 #pragma unroll
-        for (int q = 0; q < KP; ++q) {
-          const uint32_t off = place(p, row, ks[kd * KP + q]);
-          if constexpr (V * E == 16) {
-            const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(buf, off, 0, 0);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) r[V * i + 4 * q + e] = x[e];
-          } else {
-            const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(buf, off, 0, 0);
-            r[V * i + 2 * q] = x[0];
-            r[V * i + 2 * q + 1] = x[1];
-          }
+          for (int e = 0; e < 4; ++e) r[4 * i + e] = x[e];
+        } else {
+          const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(buf, off, 0, 0);
+          r[2 * i] = x[0];
+          r[2 * i + 1] = x[1];
         }
       }
     } else {
@@ -225,18 +284,46 @@ struct Stager {
       for (int q = 0; q < KP; ++q) kp[q] = ks[(tid % KD) * KP + q];
 #pragma unroll
       for (int i = 0; i < DW; ++i) {
-        const i32x4 row = rows[tid / KD + i * STEP0];
+        const i32x4 ri = rows[tid / KD + i * STEP0];
         uint32_t w = 0;
 #pragma unroll
-        for (int q = 0; q < KP; ++q) w |= load_elem<T>(buf, place(p, row, kp[q])) << (8 * E * q % 32);
+        for (int q = 0; q < KP; ++q) w |= load_elem<T>(buf, place(p, ri, kp[q])) << (8 * E * q % 32);
         r[i] = w;
       }
     }
   }
 
-  // -> LDS rows of k; returns whether every value is finite
-  __device__ __forceinline__ bool store(const ContractParams& p, unsigned char* lds, uint32_t k0, bool look) {
-    const int tid = threadIdx.x;
+  // The same for an operand with one row index, one reduction index and no tests (a plain product): row[i] holds the row's
+  // byte offset (beyond every buffer for a row past the end), step is the reduction index's stride in bytes.
+  __device__ __forceinline__ void load_plain(const ContractParams& p, __amdgpu_buffer_rsrc_t buf, const uint32_t* row, uint32_t step, uint32_t k0, int tid) {
+    static_assert(MODE == 1 || MODE == 2, "vectors along k or along the rows");
+    if constexpr (MODE == 1) {
+      const uint32_t k = k0 + (tid % CH) * VE, at = k + VE <= p.K ? k : p.K - VE;
+#pragma unroll
+      for (int i = 0; i < DW / 4; ++i) {
+        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(buf, k < p.K ? row[i] + at * E : kOutside, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[4 * i + e] = x[e];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < DW / UD; ++i) {
+        const uint32_t k = k0 + L::k_of(tid / G + i * STEP2), off = k < p.K ? row[0] + k * step : kOutside;
+        if constexpr (UD == 4) {
+          const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(buf, off, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) r[4 * i + e] = x[e];
+        } else {
+          const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(buf, off, 0, 0);
+          r[2 * i] = x[0];
+          r[2 * i + 1] = x[1];
+        }
+      }
+    }
+  }
+
+  // -> LDS; returns whether every value is finite
+  __device__ __forceinline__ bool store(const ContractParams& p, unsigned char* lds, uint32_t k0, bool look, int tid) {
     bool fin = true;
     if constexpr (MODE == 3) {
 #pragma unroll
@@ -266,37 +353,68 @@ struct Stager {
       }
 #pragma unroll
       for (int i = 0; i < DW / 4; ++i)
-        *(u32x4*)(lds + (tid / CH + i * STEP1) * PITCH + tid % CH * 16) = (u32x4){r[4 * i], r[4 * i + 1], r[4 * i + 2], r[4 * i + 3]};
+        *(u32x4*)(lds + row_at<BKB>(tid / CH + i * STEP1, tid % CH)) = (u32x4){r[4 * i], r[4 * i + 1], r[4 * i + 2], r[4 * i + 3]};
     } else if constexpr (MODE == 3) {
 #pragma unroll
-      for (int i = 0; i < DW / 2; ++i) *(u32x2*)(lds + (tid / CH3 + i * STEP3) * PITCH + tid % CH3 * 8) = (u32x2){r[2 * i], r[2 * i + 1]};
+      for (int i = 0; i < DW / 2; ++i) *(u32x2*)(lds + row_at<BKB>(tid / CH3 + i * STEP3, tid % CH3 / 2) + tid % 2 * 8) = (u32x2){r[2 * i], r[2 * i + 1]};
     } else if constexpr (MODE == 2) {
 #pragma unroll
-      for (int i = 0; i < DW / V; ++i) {
-        const int u = tid + i * 256;
-        const int g = u % GL + u / (GL * KD) * GL, kd = u / GL % KD;
-        unsigned char* at = lds + g * V * PITCH + kd * 4;
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-          uint32_t w;
-          if constexpr (KP == 1) {
-            w = r[V * i + v];
-          } else if constexpr (KP == 2) {   // row v: half v % 2 of dword v / 2 of the two k steps
-            const uint32_t x = r[V * i + v / 2], y = r[V * i + 4 + v / 2];
-            w = v % 2 ? (x >> 16) | (y & 0xffff0000u) : (x & 0xffffu) | (y << 16);
-          } else {
-            w = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) w |= ((r[V * i + 2 * q + v / 4] >> (8 * (v % 4))) & 0xffu) << (8 * q);
-          }
-          *(uint32_t*)(at + v * PITCH) = w;
-        }
+      for (int i = 0; i < DW / UD; ++i) {
+        unsigned char* at = lds + L::at(L::k_of(tid / G + i * STEP2), tid % G * V);
+        if constexpr (UD == 4) *(u32x4*)at = (u32x4){r[4 * i], r[4 * i + 1], r[4 * i + 2], r[4 * i + 3]};
+        else *(u32x2*)at = (u32x2){r[2 * i], r[2 * i + 1]};
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < DW; ++i) *(uint32_t*)(lds + (tid / KD + i * STEP0) * PITCH + tid % KD * 4) = r[i];
+      for (int i = 0; i < DW; ++i) *(uint32_t*)(lds + row_at<BKB>(tid / KD + i * STEP0, tid % KD / 4) + tid % 4 * 4) = r[i];
     }
     return fin;
+  }
+
+  // Fragment reads.  first(): a lane's address for the fragment of 16 rows from `row` on in step 0; fragment(): its 16 bytes of
+  // k in a 64-byte step.
+  static __device__ __forceinline__ uint32_t first(uint32_t row, int lane) {
+    if constexpr (MODE != 2) return row_at<BKB>(row + lane % 16, lane / 16);
+    else if constexpr (E == 4) return L::at(lane / 16 * 4, row + lane % 16);
+    else if constexpr (E == 2) return L::at(lane / 16 * 8 + lane % 16 / 4, row + lane % 4 * 4);
+    else return L::at(lane / 16 * 16 + lane % 16 / 2, row + lane % 2 * 8);
+  }
+  static __device__ __forceinline__ u32x4 fragment(const unsigned char* lds, uint32_t first, int step) {
+    if constexpr (MODE != 2) {
+      return *(const u32x4*)(lds + (first ^ (uint32_t)(step << 6)));
+    } else {
+      const unsigned char* at = lds + first + step * (64 / E * L::LINE);
+      if constexpr (E == 4) {
+        u32x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = *(const uint32_t*)(at + L::line(i) * L::LINE);
+        return v;
+      } else {
+        const u32x2 lo = transposed(at), hi = transposed(at + L::line(E == 2 ? 4 : 8) * L::LINE);
+        return (u32x4){lo[0], lo[1], hi[0], hi[1]};
+      }
+    }
+  }
+  // 16 lanes receive 16 columns of 4 (2-byte elements) or 8 (1-byte) lines: lane p gives the address of 8 bytes of line p / 4 (p / 2)
+  static __device__ __forceinline__ u32x2 transposed(const unsigned char* at) {
+    if constexpr (E == 2) {
+      typedef short s4 __attribute__((ext_vector_type(4)));
+      return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4*)at));
+    } else {
+      typedef int i2 __attribute__((ext_vector_type(2)));
+      return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) i2*)at));
+    }
+  }
+  // 16 bytes of one row's k from k = 16 / E * chunk on
+  static __device__ __forceinline__ u32x4 piece(const unsigned char* lds, uint32_t row, uint32_t chunk) {
+    if constexpr (MODE != 2) {
+      return *(const u32x4*)(lds + row_at<BKB>(row, chunk));
+    } else {
+      u32x4 v = {0, 0, 0, 0};
+#pragma unroll
+      for (int e = 0; e < VE; ++e) v[e * E / 4] |= (uint32_t)(*(const typename Bits<E>::type*)(lds + L::at(chunk * VE + e, row))) << (8 * E * e % 32);
+      return v;
+    }
   }
 };
 
@@ -313,59 +431,14 @@ __device__ __forceinline__ void put(const ContractParams& p, void* O, const floa
   ((S*)O)[off] = v;
 }
 
-// BM x BN tile, K tiles of BKB bytes per row; WM x WN wavefronts over the tile, the remaining factor WK of the four
-// wavefronts takes every WK-th 64-byte step of a K tile (small tiles) and their sums are added through LDS at the end.
-// PRECISE (float types): the products of one 64-byte step are summed from zero and join a total in double precision.  For blocks
-// whose literal kernel holds several sums per output (see wants_double): against it, fp32 totals had 1.1 to 1.5 times the error
-// in 64 bits (K of 64 to 33000), totals in double 0.7 to 0.99 times.  They cost up to 15 % (250 x 250 x 1001 nt fp32 20.1 -> 23.3
-// us, 1000 x 1000 x 3000 [k][m] bf16 50 -> 55), so other blocks, already more exact than before (1000^3 fp32: 5.6e-7 literal,
-// 1.5e-7 here), keep fp32 totals.
-template <typename T, int BM, int BN, int BKB, int WM, int WN, int MA, int MB, bool PRECISE>
-__global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 || PRECISE && BM == 64 ? 2 : 3) void contract_kernel(const ContractParams p, const T* __restrict__ A, const T* __restrict__ B,
-                                                       void* __restrict__ O, const float* __restrict__ bias) {
-  using Acc = typename Ct<T>::Acc;
-  using S = typename Ct<T>::S;
-  constexpr int WK = 4 / (WM * WN), STEPS = BKB / 64, FM = BM / WM / 16, FN = BN / WN / 16;
-  constexpr int PITCH = BKB + 16, BUF = (BM + BN) * PITCH;
-  static_assert(STEPS % WK == 0, "K steps are shared out evenly");
-  using Total = typename std::conditional<PRECISE, f64x4, Acc>::type;
-  static_assert(WK == 1 || (WK - 1) * BM * BN * (int)sizeof(Total) / 4 <= 2 * BUF, "partial sums fit the staging buffers");
-  __shared__ __align__(16) unsigned char lds[2 * BUF];
-  __shared__ i32x4 rows_a[BM], rows_b[BN];   // {input offset, range-test values, output offset}
-  __shared__ int2 ob_m[BM], ob_n[BN];
-  constexpr uint32_t BK = BKB / sizeof(T);
-  // k's share of the addresses and range tests, for both operands: a K tile's entries are worked out once, one iteration
-  // before its loads, in a ring of three (decoded at each load, they are most of the kernel's time)
-  __shared__ i32x4 ks_a[3][BK], ks_b[3][BK];
-  static_assert(BK <= 256, "one entry per lane");
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint32_t m0 = blockIdx.x / (uint32_t)p.tiles_n * BM, n0 = blockIdx.x % (uint32_t)p.tiles_n * BN;
-  int a_base = p.a_base, b_base = p.b_base, o_base = p.o_base;
-  {
-    uint32_t t = blockIdx.y;     // unused batch indexes: range 1
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int v = (int)(t % p.batch_range[j]);
-      t /= p.batch_range[j];
-      a_base += p.batch_a[j] * v;
-      b_base += p.batch_b[j] * v;
-      o_base += p.batch_o[j] * v;
-    }
-  }
-  auto fill_ks = [&](const ContractParams& c, uint32_t t, uint32_t slot) {       // A's entries on the first BK lanes, B's on the next (all lanes both where BK is 256)
-    const uint32_t at = (uint32_t)tid % BK;
-    if (2 * BK > 256 || (uint32_t)tid < BK) {
-      const KPart a = k_part<true>(c, t * BK + at);
-      ks_a[slot][at] = (i32x4){a.off, a.t0, a.t1, a.run};
-    }
-    if (2 * BK > 256 || ((uint32_t)tid >= BK && (uint32_t)tid < 2 * BK)) {
-      const KPart b = k_part<false>(c, t * BK + at);
-      ks_b[slot][at] = (i32x4){b.off, b.t0, b.t1, b.run};
-    }
-  };
-  for (uint32_t t = 0; t < 3; ++t) fill_ks(p, t, t);
-  for (int i = tid; i < BM + BN; i += 256) {
+// What every kernel below does first: the row tables of its tile.
+struct TileRows {
+  i32x4 *a, *b;      // {input offset, range-test values, output offset}
+  int2 *ob_m, *ob_n;
+};
+template <typename T, int NT, int BM, int BN, int MA, int MB>
+__device__ __forceinline__ void fill_rows(const ContractParams& p, uint32_t m0, uint32_t n0, int a_base, int b_base, const TileRows& rows) {
+  for (int i = threadIdx.x; i < BM + BN; i += NT) {
     const bool am = i < BM;
     uint32_t at = am ? m0 + i : n0 + i - BM;
     // Vectors along the row index: the operand's last, partial group of V rows starts V rows before its end instead.  The
@@ -382,227 +455,38 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
         ob.x += p.m_ob[0][j] * v; ob.y += p.m_ob[1][j] * v;
       });
       if (at >= p.M) e[1] = kFar;
-      rows_a[i] = e;
-      ob_m[i] = ob;
+      rows.a[i] = e;
+      rows.ob_m[i] = ob;
     } else {
       decode(p.n, at, [&](int j, int v) {
         e[0] += p.n_in[j] * v; e[1] += p.n_t[0][j] * v; e[2] += p.n_t[1][j] * v; e[3] += p.n_out[j] * v;
         ob.x += p.n_ob[0][j] * v; ob.y += p.n_ob[1][j] * v;
       });
       if (at >= p.N) e[1] = kFar;
-      rows_b[i - BM] = e;
-      ob_n[i - BM] = ob;
+      rows.b[i - BM] = e;
+      rows.ob_n[i - BM] = ob;
     }
   }
-  __syncthreads();
+}
 
-  const __amdgpu_buffer_rsrc_t buf_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)p.bytes_a, 0x00020000);
-  const __amdgpu_buffer_rsrc_t buf_b = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, (int)p.bytes_b, 0x00020000);
-  Stager<T, BM, BKB, true, MA> sa[2];      // K tiles t and t + 1 on their way
-  Stager<T, BN, BKB, false, MB> sb[2];
-  const uint32_t n_kt = (p.K + BK - 1) / BK;
-  const bool look = p.tested && std::is_same<S, float>::value;
-  bool fin = true;
-
-  const int wk = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+// Stores fragments (i, j) of the tile whose number is MINE modulo WK; m_at, n_at: the wavefront's place in the tile.
+template <typename T, int FM, int FN, int WK, typename Total>
+__device__ __forceinline__ void store_fragments(const ContractParams& q, void* out, const float* bias_n, int o_base, const TileRows& rows, int m_at, int n_at,
+                                                int wk, int lane, const Total (&acc)[FM][FN]) {
+  using S = typename Ct<T>::S;
   const int frag_row = lane & 15, frag_k = lane >> 4;
-  Total acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = (Total){0, 0, 0, 0};
-
-  // bf16 / fp32: partial sums over FLUSH K tiles start from zero and are added to the total, short chains of roundings
-  // instead of one long one (not on the largest tile, whose registers hold one set of sums at two wavefronts per SIMD)
-  constexpr uint32_t FLUSH = BM * BN > 8192 ? 0xffffffffu : std::is_same<T, float>::value ? 1 : std::is_same<T, uint16_t>::value ? 4 : 0xffffffffu;
-  Acc sum[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) sum[i][j] = (Acc){0, 0, 0, 0};
-  auto flush = [&]() {
-    if constexpr (!PRECISE) {
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          acc[i][j] += sum[i][j];
-          sum[i][j] = (Acc){0, 0, 0, 0};
-        }
-    }
-  };
-
-  // Two K tiles are in flight in registers (set t & 1 holds tile t): with one, few workgroups and long reductions spent an
-  // iteration waiting for memory.  The loop's loads are unconditional (a tile past the last one loads zeros); the last two tiles
-  // are peeled off without loads.
-  sa[0].load(p, buf_a, rows_a, ks_a[0], 0);
-  sb[0].load(p, buf_b, rows_b, ks_b[0], 0);
-  if (n_kt > 1) {
-    sa[1].load(p, buf_a, rows_a, ks_a[1], BK);
-    sb[1].load(p, buf_b, rows_b, ks_b[1], BK);
-  }
-  fin &= sa[0].store(p, lds, 0, look);
-  fin &= sb[0].store(p, lds + BM * PITCH, 0, look);
-  uint32_t slot = 2;             // of tile t + 2 in the ring
-  auto step = [&](uint32_t t, auto set, auto loads, auto stores) {
-    constexpr int S0 = decltype(set)::value;
-    __syncthreads();
-    if constexpr (decltype(loads)::value) {
-      sa[S0].load(p, buf_a, rows_a, ks_a[slot], (t + 2) * BK);
-      sb[S0].load(p, buf_b, rows_b, ks_b[slot], (t + 2) * BK);
-      slot = slot == 2 ? 0 : slot + 1;
-      fill_ks(p, t + 3, slot);        // over the entries of tile t, read two iterations ago
-    }
-    const unsigned char* base = lds + S0 * BUF + frag_k * 16;
-#pragma unroll
-    for (int s = 0; s < STEPS / WK; ++s) {
-      const unsigned char* at = base + (s * WK + wk) * 64;
-      u32x4 fa[FM], fb[FN];
-#pragma unroll
-      for (int i = 0; i < FM; ++i) fa[i] = *(const u32x4*)(at + (wm * (BM / WM) + i * 16 + frag_row) * PITCH);
-#pragma unroll
-      for (int j = 0; j < FN; ++j) fb[j] = *(const u32x4*)(at + (BM + wn * (BN / WN) + j * 16 + frag_row) * PITCH);
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {   // rows of the result: n
-          if constexpr (PRECISE) acc[i][j] += __builtin_convertvector(Ct<T>::step(fb[j], fa[i]), f64x4);
-          else sum[i][j] = Ct<T>::mma(fb[j], fa[i], sum[i][j]);
-        }
-    }
-    if ((t + 1) % FLUSH == 0) flush();
-    if constexpr (decltype(stores)::value) {
-      unsigned char* next = lds + (1 - S0) * BUF;
-      fin &= sa[1 - S0].store(p, next, (t + 1) * BK, look);
-      fin &= sb[1 - S0].store(p, next + BM * PITCH, (t + 1) * BK, look);
-    }
-  };
-  constexpr std::integral_constant<int, 0> even;
-  constexpr std::integral_constant<int, 1> odd;
-  constexpr std::true_type yes;
-  constexpr std::false_type no;
-  uint32_t t = 0;
-  for (; t + 2 < n_kt; t += 2) {
-    step(t, even, yes, yes);
-    step(t + 1, odd, yes, yes);
-  }
-  if (t + 1 < n_kt) {
-    step(t, even, no, yes);
-    step(t + 1, odd, no, no);
-  } else {
-    step(t, even, no, no);
-  }
-  flush();
-
-  if constexpr (WK > 1) {
-    __syncthreads();
-    Total* part = (Total*)lds;
-    if (wk > 0)
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) part[((((wk - 1) * WM * WN + wave % (WM * WN)) * FM + i) * FN + j) * 64 + lane] = acc[i][j];
-    __syncthreads();
-    if (wk == 0)
-#pragma unroll
-      for (int w = 0; w < WK - 1; ++w)
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) acc[i][j] += part[(((w * WM * WN + wave % (WM * WN)) * FM + i) * FN + j) * 64 + lane];
-  }
-
-  constexpr bool again = sizeof(T) > 1;
-  const KernelArgs& args = reread();
-  const ContractParams& q = again ? args.p : p;
-  void* const out = again ? args.o : O;
-  const float* const bias_n = again ? args.bias : bias;
-  // A removed point contributes 0 * x, which is not 0 where x is an infinity or NaN: a tile that met one is summed again
-  // (Definition 2: a removed point contributes nothing).  The operands are staged as before, in parts of at most 64 x 32 outputs;
-  // 16 bytes of k at a time are summed, and only where such a sum is NaN are its points looked at one by one.  (Point by point from
-  // memory, one infinity in the images of the 3 -> 64-channel 7x7 convolution at 8 x 224 x 224 made the call take 2456 us, with
-  // this 122; its literal kernel takes 215.)
-  if constexpr (std::is_same<S, float>::value) {
-    if (look && __syncthreads_or(!fin)) {
-      constexpr int SM = BM < 64 ? BM : 64, SN = 32, RM = SM / 16, RN = SN / 16, VE = 16 / sizeof(T);   // lanes: 16 x 16
-      const int lm = tid / 16, ln = tid % 16;
-      auto element = [](u32x4 v, int e) {
-        if constexpr (sizeof(T) == 2) return __uint_as_float(e % 2 ? v[e / 2] & 0xffff0000u : v[e / 2] << 16);
-        else return __uint_as_float(v[e]);
-      };
-      for (int part = 0; part < BM / SM * (BN / SN); ++part) {
-        const int pm = part / (BN / SN) * SM + lm, pn = part % (BN / SN) * SN + ln;
-        double total[RM][RN];
-#pragma unroll
-        for (int i = 0; i < RM; ++i)
-#pragma unroll
-          for (int j = 0; j < RN; ++j) total[i][j] = 0;
-        for (uint32_t kt = 0; kt < n_kt; ++kt) {
-          __syncthreads();
-          fill_ks(q, kt, 0);
-          __syncthreads();
-          Stager<T, BM, BKB, true, MA> one_a;
-          Stager<T, BN, BKB, false, MB> one_b;
-          one_a.load(q, __builtin_amdgcn_make_buffer_rsrc((void*)args.a, 0, (int)q.bytes_a, 0x00020000), rows_a, ks_a[0], kt * BK);
-          one_b.load(q, __builtin_amdgcn_make_buffer_rsrc((void*)args.b, 0, (int)q.bytes_b, 0x00020000), rows_b, ks_b[0], kt * BK);
-          one_a.store(q, lds, kt * BK, false);
-          one_b.store(q, lds + BM * PITCH, kt * BK, false);
-          __syncthreads();
-#pragma unroll 1
-          for (int c = 0; c < BKB / 16; ++c) {
-            u32x4 av[RM], bv[RN];
-#pragma unroll
-            for (int i = 0; i < RM; ++i) av[i] = *(const u32x4*)(lds + (pm + 16 * i) * PITCH + c * 16);
-#pragma unroll
-            for (int j = 0; j < RN; ++j) bv[j] = *(const u32x4*)(lds + (BM + pn + 16 * j) * PITCH + c * 16);
-#pragma unroll
-            for (int i = 0; i < RM; ++i)
-#pragma unroll
-              for (int j = 0; j < RN; ++j) {
-                float s = 0.f;
-#pragma unroll
-                for (int e = 0; e < VE; ++e) s = __builtin_fmaf(element(av[i], e), element(bv[j], e), s);
-                if (s != s) {
-                  const i32x4 rm = rows_a[pm + 16 * i], rn = rows_b[pn + 16 * j];
-                  s = 0.f;
-                  for (int e = 0; e < VE; ++e) {
-                    const i32x4 ka = ks_a[0][c * VE + e], kb = ks_b[0][c * VE + e];
-                    const bool in = ((uint32_t)(rm[1] + ka[1]) <= q.top_a[0]) & ((uint32_t)(rm[2] + ka[2]) <= q.top_a[1]) &
-                                    ((uint32_t)(rn[1] + kb[1]) <= q.top_b[0]) & ((uint32_t)(rn[2] + kb[2]) <= q.top_b[1]);
-                    if (in) s += element(av[i], e) * element(bv[j], e);
-                  }
-                }
-                total[i][j] += s;
-              }
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < RM; ++i)
-#pragma unroll
-          for (int j = 0; j < RN; ++j) {
-            const int mi = pm + 16 * i, ni = pn + 16 * j;
-            const i32x4 rm = rows_a[mi], rn = rows_b[ni];
-            if (rm[1] == kFar || rn[1] == kFar || ob_m[mi].x + ob_n[ni].x > q.ob[0] || ob_m[mi].y + ob_n[ni].y > q.ob[1]) continue;
-            put<S>(q, out, bias_n, o_base + rm[3] + rn[3], rn[3], (S)total[i][j]);
-          }
-      }
-      return;
-    }
-  }
-  if (WK > 1 && wk > 0) return;
-
 #pragma unroll
   for (int j = 0; j < FN; ++j) {
-    const int ni = wn * (BN / WN) + j * 16 + frag_k * 4;
+    const int ni = n_at + j * 16 + frag_k * 4;
     int n_off[4];
     bool n_in[4];
     int2 on[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const i32x4 rn = rows_b[ni + e];
+      const i32x4 rn = rows.b[ni + e];
       n_off[e] = rn[3];
       n_in[e] = rn[1] != kFar;
-      on[e] = ob_n[ni + e];
+      on[e] = rows.ob_n[ni + e];
     }
     float bs[4] = {0.f, 0.f, 0.f, 0.f};
     if (q.epilogue >= 2) {
@@ -612,11 +496,12 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
     }
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      const int mi = wm * (BM / WM) + i * 16 + frag_row;
-      const i32x4 rm = rows_a[mi];
+      if ((i * FN + j) % WK != wk) continue;
+      const int mi = m_at + i * 16 + frag_row;
+      const i32x4 rm = rows.a[mi];
       if (rm[1] == kFar) continue;
       const int off = o_base + rm[3];
-      const int2 om = ob_m[mi];
+      const int2 om = rows.ob_m[mi];
       S v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -645,6 +530,438 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
   }
 }
 
+// The block's batch indexes, from the grid's second dimension.
+__device__ __forceinline__ void batch_bases(const ContractParams& p, int* a_base, int* b_base, int* o_base) {
+  *a_base = p.a_base;
+  *b_base = p.b_base;
+  *o_base = p.o_base;
+  uint32_t t = blockIdx.y;     // unused batch indexes: range 1
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int v = (int)(t % p.batch_range[j]);
+    t /= p.batch_range[j];
+    *a_base += p.batch_a[j] * v;
+    *b_base += p.batch_b[j] * v;
+    *o_base += p.batch_o[j] * v;
+  }
+}
+
+// A removed point contributes 0 * x, which is not 0 where x is an infinity or NaN: a tile that met one is summed again
+// (Definition 2: a removed point contributes nothing).  The operands are staged as before, in parts of at most 64 x 32 outputs;
+// 16 bytes of k at a time are summed, and only where such a sum is NaN are its points looked at one by one.  (Point by point from
+// memory, one infinity in the images of the 3 -> 64-channel 7x7 convolution at 8 x 224 x 224 made the call take 2456 us, with
+// this 122; its literal kernel takes 215.)  All lanes of the workgroup; lds: (BM + BN) * BKB bytes and 16 bytes for each table entry.
+template <typename T, int NT, int BM, int BN, int BKB, int MA, int MB>
+__device__ __forceinline__ void sum_again(const KernelArgs& args, const TileRows& rows, int o_base, unsigned char* lds) {
+  using S = typename Ct<T>::S;
+  using SA = Stager<T, NT, BM, BKB, true, MA>;
+  using SB = Stager<T, NT, BN, BKB, false, MB>;
+  constexpr uint32_t BK = BKB / sizeof(T);
+  const ContractParams& q = args.p;
+  const int tid = threadIdx.x;
+  i32x4 *const ks_a = (i32x4*)(lds + (BM + BN) * BKB), *const ks_b = ks_a + SA::ENTRIES;
+  // lanes: 16 x 16 for a part, as many parts at a time as there are such sets of lanes
+  constexpr int SM = BM < 64 ? BM : 64, SN = BN < 32 ? BN : 32, RM = SM / 16, RN = SN / 16, VE = 16 / sizeof(T);
+  constexpr int PARTS = BM / SM * (BN / SN), AT_ONCE = NT / 256;
+  const int lm = tid / 16 % 16, ln = tid % 16;
+  auto element = [](u32x4 v, int e) {
+    if constexpr (sizeof(T) == 2) return __uint_as_float(e % 2 ? v[e / 2] & 0xffff0000u : v[e / 2] << 16);
+    else return __uint_as_float(v[e]);
+  };
+  const uint32_t n_kt = (q.K + BK - 1) / BK;
+  for (int part0 = 0; part0 < PARTS; part0 += AT_ONCE) {
+    const int part = part0 + tid / 256 < PARTS ? part0 + tid / 256 : PARTS - 1;      // a set without a part of its own repeats the last one
+    const int pm = part / (BN / SN) * SM + lm, pn = part % (BN / SN) * SN + ln;
+    double total[RM][RN];
+#pragma unroll
+    for (int i = 0; i < RM; ++i)
+#pragma unroll
+      for (int j = 0; j < RN; ++j) total[i][j] = 0;
+    for (uint32_t kt = 0; kt < n_kt; ++kt) {
+      __syncthreads();
+      for (int x = tid; x < SA::ENTRIES + SB::ENTRIES; x += NT) {
+        const bool a = x < SA::ENTRIES;
+        const KPart k = k_part(q, kt * BK + (a ? x * SA::SPAN : (x - SA::ENTRIES) * SB::SPAN), a);
+        ks_a[x] = (i32x4){k.off, k.t0, k.t1, k.run};
+      }
+      __syncthreads();
+      SA one_a;
+      SB one_b;
+      i32x4 row_a[SA::NR + 1], row_b[SB::NR + 1];
+      SA::keep(rows.a, row_a, tid);
+      SB::keep(rows.b, row_b, tid);
+      one_a.load(q, __builtin_amdgcn_make_buffer_rsrc((void*)args.a, 0, (int)q.bytes_a, 0x00020000), rows.a, row_a, ks_a, kt * BK, tid);
+      one_b.load(q, __builtin_amdgcn_make_buffer_rsrc((void*)args.b, 0, (int)q.bytes_b, 0x00020000), rows.b, row_b, ks_b, kt * BK, tid);
+      one_a.store(q, lds, kt * BK, false, tid);
+      one_b.store(q, lds + BM * BKB, kt * BK, false, tid);
+      __syncthreads();
+#pragma unroll 1
+      for (int c = 0; c < BKB / 16; ++c) {
+        u32x4 av[RM], bv[RN];
+#pragma unroll
+        for (int i = 0; i < RM; ++i) av[i] = SA::piece(lds, pm + 16 * i, c);
+#pragma unroll
+        for (int j = 0; j < RN; ++j) bv[j] = SB::piece(lds + BM * BKB, pn + 16 * j, c);
+#pragma unroll
+        for (int i = 0; i < RM; ++i)
+#pragma unroll
+          for (int j = 0; j < RN; ++j) {
+            float s = 0.f;
+#pragma unroll
+            for (int e = 0; e < VE; ++e) s = __builtin_fmaf(element(av[i], e), element(bv[j], e), s);
+            if (s != s) {
+              const i32x4 rm = rows.a[pm + 16 * i], rn = rows.b[pn + 16 * j];
+              s = 0.f;
+              for (int e = 0; e < VE; ++e) {
+                const i32x4 ka = ks_a[(c * VE + e) / SA::SPAN], kb = ks_b[(c * VE + e) / SB::SPAN];
+                const bool in = ((uint32_t)(rm[1] + ka[1]) <= q.top_a[0]) & ((uint32_t)(rm[2] + ka[2]) <= q.top_a[1]) &
+                                ((uint32_t)(rn[1] + kb[1]) <= q.top_b[0]) & ((uint32_t)(rn[2] + kb[2]) <= q.top_b[1]);
+                if (in) s += element(av[i], e) * element(bv[j], e);
+              }
+            }
+            total[i][j] += s;
+          }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < RM; ++i)
+#pragma unroll
+      for (int j = 0; j < RN; ++j) {
+        const int mi = pm + 16 * i, ni = pn + 16 * j;
+        const i32x4 rm = rows.a[mi], rn = rows.b[ni];
+        if (rm[1] == kFar || rn[1] == kFar || rows.ob_m[mi].x + rows.ob_n[ni].x > q.ob[0] || rows.ob_m[mi].y + rows.ob_n[ni].y > q.ob[1]) continue;
+        put<S>(q, args.o, args.bias, o_base + rm[3] + rn[3], rn[3], (S)total[i][j]);
+      }
+  }
+}
+
+// Many tiles: BM x BN tile shared by four wavefronts, K tiles of BKB bytes per row staged for all of them; WM x WN wavefronts
+// over the tile.
+// PRECISE (float types): the products of one 64-byte step are summed from zero and join a total in double precision.  For blocks
+// whose literal kernel holds several sums per output (see wants_double): against it, fp32 totals had 1.1 to 1.5 times the error
+// in 64 bits (K of 64 to 33000), totals in double 0.7 to 0.99 times.  They cost up to 15 % (250 x 250 x 1001 nt fp32 20.1 -> 23.3
+// us, 1000 x 1000 x 3000 [k][m] bf16 50 -> 55), so other blocks, already more exact than before (1000^3 fp32: 5.6e-7 literal,
+// 1.5e-7 here), keep fp32 totals.
+template <typename T, int BM, int BN, int BKB, int WM, int WN, int MA, int MB, bool PRECISE>
+__global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 || PRECISE ? 2 : 3) void contract_kernel(
+    const ContractParams p, const T* __restrict__ A, const T* __restrict__ B, void* __restrict__ O, const float* __restrict__ bias) {
+  using Acc = typename Ct<T>::Acc;
+  using S = typename Ct<T>::S;
+  using SA = Stager<T, 256, BM, BKB, true, MA>;
+  using SB = Stager<T, 256, BN, BKB, false, MB>;
+  static_assert(WM * WN == 4, "four wavefronts");
+  constexpr int STEPS = BKB / 64, FM = BM / WM / 16, FN = BN / WN / 16;
+  constexpr int BUF = (BM + BN) * BKB;
+  using Total = typename std::conditional<PRECISE, f64x4, Acc>::type;
+  __shared__ __align__(16) unsigned char lds[2 * BUF];
+  __shared__ i32x4 rows_a[BM], rows_b[BN];
+  __shared__ int2 ob_m[BM], ob_n[BN];
+  const TileRows rows = {rows_a, rows_b, ob_m, ob_n};
+  constexpr uint32_t BK = BKB / sizeof(T);
+  // k's share of the addresses and range tests, for both operands, one entry per vector of k: worked out for BATCH K tiles at a
+  // time on as many lanes, at least one iteration before the first of their loads, in a ring of two batches (decoded at each load,
+  // they are most of the kernel's time; a K tile's entries in each iteration a fifth of it)
+  constexpr uint32_t ENTRIES = SA::ENTRIES + SB::ENTRIES;
+  constexpr uint32_t BATCH = 8 * ENTRIES <= 256 ? 8 : 4 * ENTRIES <= 256 ? 4 : 2 * ENTRIES <= 256 ? 2 : 1;
+  __shared__ i32x4 ks_a[2 * BATCH][SA::ENTRIES], ks_b[2 * BATCH][SB::ENTRIES];
+  static_assert(2 * BUF >= BUF + (int)ENTRIES * 16, "room for the tables of sum_again");
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t m0 = blockIdx.x / (uint32_t)p.tiles_n * BM, n0 = blockIdx.x % (uint32_t)p.tiles_n * BN;
+  int a_base, b_base, o_base;
+  batch_bases(p, &a_base, &b_base, &o_base);
+  auto fill_ks = [&](uint32_t t) {       // K tiles t .. t + BATCH - 1, t a multiple of BATCH
+#pragma unroll
+    for (uint32_t x0 = 0; x0 < BATCH * ENTRIES; x0 += 256) {
+      const uint32_t x = x0 + tid;
+      if (x < BATCH * SA::ENTRIES) {
+        const uint32_t tile = t + x / SA::ENTRIES, e = x % SA::ENTRIES;
+        const KPart a = k_part(p, tile * BK + e * SA::SPAN, true);
+        ks_a[tile % (2 * BATCH)][e] = (i32x4){a.off, a.t0, a.t1, a.run};
+      } else if (x < BATCH * ENTRIES) {
+        const uint32_t y = x - BATCH * SA::ENTRIES, tile = t + y / SB::ENTRIES, e = y % SB::ENTRIES;
+        const KPart b = k_part(p, tile * BK + e * SB::SPAN, false);
+        ks_b[tile % (2 * BATCH)][e] = (i32x4){b.off, b.t0, b.t1, b.run};
+      }
+    }
+  };
+  fill_ks(0);
+  if (BATCH == 1) fill_ks(1);
+  fill_rows<T, 256, BM, BN, MA, MB>(p, m0, n0, a_base, b_base, rows);
+  __syncthreads();
+
+  const __amdgpu_buffer_rsrc_t buf_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)p.bytes_a, 0x00020000);
+  const __amdgpu_buffer_rsrc_t buf_b = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, (int)p.bytes_b, 0x00020000);
+  SA sa[2];      // K tiles t and t + 1 on their way
+  SB sb[2];
+  i32x4 row_a[SA::NR + 1], row_b[SB::NR + 1];
+  SA::keep(rows_a, row_a, tid);
+  SB::keep(rows_b, row_b, tid);
+  const uint32_t n_kt = (p.K + BK - 1) / BK;
+  const bool look = p.tested && std::is_same<S, float>::value;
+  bool fin = true;
+
+  const int wm = wave / WN, wn = wave % WN;
+  Total acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = (Total){0, 0, 0, 0};
+
+  // bf16 / fp32: partial sums over FLUSH K tiles start from zero and are added to the total, short chains of roundings
+  // instead of one long one (not on the largest tile, whose registers hold one set of sums at two wavefronts per SIMD)
+  constexpr uint32_t FLUSH = BM * BN > 8192 ? 0xffffffffu : std::is_same<T, float>::value ? 1 : std::is_same<T, uint16_t>::value ? 4 : 0xffffffffu;
+  Acc sum[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) sum[i][j] = (Acc){0, 0, 0, 0};
+  auto flush = [&]() {
+    if constexpr (!PRECISE) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          acc[i][j] += sum[i][j];
+          sum[i][j] = (Acc){0, 0, 0, 0};
+        }
+    }
+  };
+  uint32_t at_a[FM], at_b[FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i) at_a[i] = SA::first(wm * (BM / WM) + i * 16, lane);
+#pragma unroll
+  for (int j = 0; j < FN; ++j) at_b[j] = SB::first(wn * (BN / WN) + j * 16, lane);
+
+  // Two K tiles are in flight in registers (set t & 1 holds tile t): with one, few workgroups and long reductions spent an
+  // iteration waiting for memory.  The loop's loads are unconditional (a tile past the last one loads zeros); the last two tiles
+  // are peeled off without loads.
+  sa[0].load(p, buf_a, rows_a, row_a, ks_a[0], 0, tid);
+  sb[0].load(p, buf_b, rows_b, row_b, ks_b[0], 0, tid);
+  if (n_kt > 1) {
+    sa[1].load(p, buf_a, rows_a, row_a, ks_a[1], BK, tid);
+    sb[1].load(p, buf_b, rows_b, row_b, ks_b[1], BK, tid);
+  }
+  if (n_kt > 2 && BATCH <= 2) {
+    if (BATCH == 1) __syncthreads();      // over the entries of tile 0
+    fill_ks(2);
+  }
+  fin &= sa[0].store(p, lds, 0, look, tid);
+  fin &= sb[0].store(p, lds + BM * BKB, 0, look, tid);
+  auto step = [&](uint32_t t, auto set, auto loads, auto stores) {
+    constexpr int S0 = decltype(set)::value;
+    __syncthreads();
+    if constexpr (decltype(loads)::value) {
+      const uint32_t slot = (t + 2) % (2 * BATCH);
+      sa[S0].load(p, buf_a, rows_a, row_a, ks_a[slot], (t + 2) * BK, tid);
+      sb[S0].load(p, buf_b, rows_b, row_b, ks_b[slot], (t + 2) * BK, tid);
+      if ((t + 3) % BATCH == 0) fill_ks(t + 3);        // over the batch before tile t + 2's
+    }
+    const unsigned char *base_a = lds + S0 * BUF, *base_b = base_a + BM * BKB;
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      u32x4 fa[FM], fb[FN];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) fa[i] = SA::fragment(base_a, at_a[i], s);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) fb[j] = SB::fragment(base_b, at_b[j], s);
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {   // rows of the result: n
+          if constexpr (PRECISE) acc[i][j] += __builtin_convertvector(Ct<T>::step(fb[j], fa[i]), f64x4);
+          else sum[i][j] = Ct<T>::mma(fb[j], fa[i], sum[i][j]);
+        }
+    }
+    if ((t + 1) % FLUSH == 0) flush();
+    if constexpr (decltype(stores)::value) {
+      unsigned char* next = lds + (1 - S0) * BUF;
+      fin &= sa[1 - S0].store(p, next, (t + 1) * BK, look, tid);
+      fin &= sb[1 - S0].store(p, next + BM * BKB, (t + 1) * BK, look, tid);
+    }
+  };
+  constexpr std::integral_constant<int, 0> even;
+  constexpr std::integral_constant<int, 1> odd;
+  constexpr std::true_type yes;
+  constexpr std::false_type no;
+  uint32_t t = 0;
+  for (; t + 2 < n_kt; t += 2) {
+    step(t, even, yes, yes);
+    step(t + 1, odd, yes, yes);
+  }
+  if (t + 1 < n_kt) {
+    step(t, even, no, yes);
+    step(t + 1, odd, no, no);
+  } else {
+    step(t, even, no, no);
+  }
+  flush();
+
+  constexpr bool again = sizeof(T) > 1;
+  const KernelArgs& args = reread();
+  if constexpr (again) {
+    if (look && __syncthreads_or(!fin)) {
+      sum_again<T, 256, BM, BN, BKB, MA, MB>(args, rows, o_base, lds);
+      return;
+    }
+  }
+  store_fragments<T, FM, FN, 1>(again ? args.p : p, again ? args.o : O, again ? args.bias : bias, o_base, rows, wm * (BM / WM), wn * (BN / WN), 0, lane, acc);
+}
+
+// Few tiles: the tile's NW wavefronts share its reduction out.  Each stages its own K tiles, every NW-th, through its own part of
+// LDS and multiplies them into its own BM x BN sums, which meet at the end: no barrier inside the reduction, so that loads, LDS and
+// matrix instructions of different wavefronts overlap.  (Four wavefronts that stage K tiles for each other were bound by that
+// chain, barrier to barrier: without its loads or its matrix instructions their loop took the same time.)  A wavefront's LDS
+// instructions execute in order, so a K tile may be written over the one before without a wait.
+// PLAIN: a product with one index per side and no tests, whose addresses need no tables.
+// Measured, us (before: four wavefronts per tile): 56 x 64 x 4080 nt bf16 9.3 -> 5.4 (16 x 16), 400 x 500 x 3000 nt bf16 11.5 -> 8.3
+// and [k][m] 14.2 -> 10.9 (32 x 32), 1000 x 1000 x 3000 [k][m] bf16 48.5 -> 20, 1000^3 fp32 39 -> 25 (64 x 64).
+template <typename T, int NW, int BM, int BN, int BKB, int MA, int MB, bool PRECISE, bool PLAIN>
+__global__ __launch_bounds__(NW * 64, NW / 4) void contract_waves_kernel(const ContractParams p, const T* __restrict__ A, const T* __restrict__ B,
+                                                                        void* __restrict__ O, const float* __restrict__ bias) {
+  using Acc = typename Ct<T>::Acc;
+  using S = typename Ct<T>::S;
+  using SA = Stager<T, 64, BM, BKB, true, MA>;
+  using SB = Stager<T, 64, BN, BKB, false, MB>;
+  constexpr int NT = NW * 64, STEPS = BKB / 64, FM = BM / 16, FN = BN / 16, NF = FM * FN, STAGE = (BM + BN) * BKB;
+  constexpr uint32_t BK = BKB / sizeof(T);
+  using Total = typename std::conditional<PRECISE, f64x4, Acc>::type;
+  constexpr int PART = (NW - 1) * NF * 64 * (int)sizeof(Total);
+  // tables of a wavefront's next TABLES K tiles, one entry per vector of k
+  constexpr int ENTRIES = SA::ENTRIES + SB::ENTRIES, TABLES = 4 * ENTRIES <= 64 ? 4 : 2 * ENTRIES <= 64 ? 2 : 1;
+  constexpr int BKB_AGAIN = 16 * NT / BM, AGAIN = PLAIN || sizeof(T) == 1 ? 0 : (BM + BN) * BKB_AGAIN + 2 * BKB_AGAIN / (int)sizeof(T) * 16;
+  constexpr int NEED = NW * STAGE > PART ? NW * STAGE : PART, LDS = NEED > AGAIN ? NEED : AGAIN;
+  __shared__ __align__(16) unsigned char lds[LDS];
+  __shared__ i32x4 rows_a[BM], rows_b[BN];
+  __shared__ int2 ob_m[BM], ob_n[BN];
+  __shared__ i32x4 tables[PLAIN ? 1 : NW][PLAIN ? 1 : TABLES * ENTRIES];
+  const TileRows rows = {rows_a, rows_b, ob_m, ob_n};
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t m0 = blockIdx.x / (uint32_t)p.tiles_n * BM, n0 = blockIdx.x % (uint32_t)p.tiles_n * BN;
+  int a_base, b_base, o_base;
+  batch_bases(p, &a_base, &b_base, &o_base);
+  SA sa;
+  SB sb;
+  unsigned char *const mine_a = lds + wave * STAGE, *const mine_b = mine_a + BM * BKB;
+  const uint32_t n_kt = (p.K + BK - 1) / BK;
+  const bool look = !PLAIN && p.tested && std::is_same<S, float>::value;
+  bool fin = true;
+  uint32_t off_a[PLAIN ? SA::NR : 1], off_b[PLAIN ? SB::NR : 1], step_a = 0, step_b = 0;
+  i32x4 row_a[PLAIN ? 1 : SA::NR + 1], row_b[PLAIN ? 1 : SB::NR + 1];
+  auto load = [&](uint32_t t) {
+    // behind the last K tile nothing is fetched: the buffers are empty (a branch around the loads lets the compiler sink them)
+    const bool live = t < n_kt;
+    const __amdgpu_buffer_rsrc_t buf_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, live ? (int)p.bytes_a : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t buf_b = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, live ? (int)p.bytes_b : 0, 0x00020000);
+    if constexpr (PLAIN) {
+      sa.load_plain(p, buf_a, off_a, step_a, t * BK, lane);
+      sb.load_plain(p, buf_b, off_b, step_b, t * BK, lane);
+    } else {
+      const uint32_t it = t / NW % TABLES;
+      if (it == 0 && live) {
+#pragma unroll
+        for (int x0 = 0; x0 < TABLES * ENTRIES; x0 += 64) {
+          const int x = x0 + lane, y = x % ENTRIES;
+          const bool a = y < SA::ENTRIES;
+          const KPart k = k_part(p, (t + x / ENTRIES * NW) * BK + (a ? y * SA::SPAN : (y - SA::ENTRIES) * SB::SPAN), a);
+          if (x < TABLES * ENTRIES) tables[wave][x] = (i32x4){k.off, k.t0, k.t1, k.run};
+        }
+      }
+      const i32x4* ks = &tables[wave][it * ENTRIES];
+      sa.load(p, buf_a, rows_a, row_a, ks, t * BK, lane);
+      sb.load(p, buf_b, rows_b, row_b, ks + SA::ENTRIES, t * BK, lane);
+    }
+  };
+  if constexpr (PLAIN) {
+    auto offset = [](uint32_t at, uint32_t end, int stride, int base, int mode) {
+      constexpr uint32_t V = Ct<T>::V;
+      if (mode == 2 && at < end && at + V > end) at = end - V;
+      return at < end ? (uint32_t)(base + (int)at * stride) * (uint32_t)sizeof(T) : kOutside;
+    };
+#pragma unroll
+    for (int i = 0; i < SA::NR; ++i) off_a[i] = offset(m0 + (MA == 1 ? lane / SA::CH + i * SA::STEP1 : lane % SA::G * SA::V), p.M, p.m_in[0], a_base, MA);
+#pragma unroll
+    for (int i = 0; i < SB::NR; ++i) off_b[i] = offset(n0 + (MB == 1 ? lane / SB::CH + i * SB::STEP1 : lane % SB::G * SB::V), p.N, p.n_in[0], b_base, MB);
+    step_a = (uint32_t)p.k_a[0] * (uint32_t)sizeof(T);
+    step_b = (uint32_t)p.k_b[0] * (uint32_t)sizeof(T);
+    load(wave);
+  }
+  fill_rows<T, NT, BM, BN, MA, MB>(p, m0, n0, a_base, b_base, rows);      // PLAIN: read behind the barrier after the reduction
+  if constexpr (!PLAIN) {
+    __syncthreads();
+    SA::keep(rows_a, row_a, lane);
+    SB::keep(rows_b, row_b, lane);
+    load(wave);
+  }
+
+  Total acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = (Total){0, 0, 0, 0};
+  uint32_t at_a[FM], at_b[FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i) at_a[i] = SA::first(i * 16, lane);
+#pragma unroll
+  for (int j = 0; j < FN; ++j) at_b[j] = SB::first(j * 16, lane);
+  for (uint32_t t = wave; t < n_kt; t += NW) {
+    fin &= sa.store(p, mine_a, t * BK, look, lane);
+    fin &= sb.store(p, mine_b, t * BK, look, lane);
+    load(t + NW);
+    __builtin_amdgcn_sched_barrier(0);
+    u32x4 fa[STEPS][FM], fb[STEPS][FN];
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i) fa[s][i] = SA::fragment(mine_a, at_a[i], s);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) fb[s][j] = SB::fragment(mine_b, at_b[j], s);
+    }
+    // float types: sums that start from zero join the total, of 16 products (fp32) or of a K tile's 32 to 128 (bf16)
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {   // rows of the result: n
+        if constexpr (std::is_same<T, int8_t>::value) {
+#pragma unroll
+          for (int s = 0; s < STEPS; ++s) acc[i][j] = Ct<T>::mma(fb[s][j], fa[s][i], acc[i][j]);
+        } else if constexpr (PRECISE) {
+#pragma unroll
+          for (int s = 0; s < STEPS; ++s) acc[i][j] += __builtin_convertvector(Ct<T>::step(fb[s][j], fa[s][i]), f64x4);
+        } else if constexpr (std::is_same<T, float>::value) {
+#pragma unroll
+          for (int s = 0; s < STEPS; ++s) acc[i][j] += Ct<T>::mma(fb[s][j], fa[s][i], (Acc){0, 0, 0, 0});
+        } else {
+          Acc sum = (Acc){0, 0, 0, 0};
+#pragma unroll
+          for (int s = 0; s < STEPS; ++s) sum = Ct<T>::mma(fb[s][j], fa[s][i], sum);
+          acc[i][j] += sum;
+        }
+      }
+  }
+
+  const KernelArgs& args = reread();
+  if (__syncthreads_or(look && !fin)) {      // also: the staging buffers are free from here on
+    if constexpr (!PLAIN && sizeof(T) > 1) sum_again<T, NT, BM, BN, BKB_AGAIN, MA, MB>(args, rows, o_base, lds);
+    return;
+  }
+  // fragment f is stored by wavefront f % NW: the others' sums reach it through LDS and are added in the wavefronts' order
+  Total* part = (Total*)lds + lane;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const int owner = f % NW;
+    if (wave != owner) part[((wave < owner ? wave : wave - 1) * NF + f) * 64] = acc[f / FN][f % FN];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+    if (wave == f % NW) {
+#pragma unroll
+      for (int w = 0; w < NW - 1; ++w) acc[f / FN][f % FN] += part[(w * NF + f) * 64];
+    }
+  store_fragments<T, FM, FN, NW>(args.p, args.o, args.bias, o_base, rows, 0, 0, wave, lane, acc);
+}
+
 }  // namespace
 
 // one translation unit per element type compiles the kernels (CONTRACT_T); the planner is compiled with the last of them
@@ -656,23 +973,41 @@ namespace {
 
 template <typename T, int MA, int MB>
 hipError_t launch_modes(const ContractLaunch& l, const ContractParams& p, const void* a, const void* b, void* o, const float* bias, hipStream_t s) {
-  const dim3 g((unsigned)l.grid, (unsigned)l.batch), w(256);
-  auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, g, w, 0, s, p, (const T*)a, (const T*)b, o, bias);
+  const dim3 g((unsigned)l.grid, (unsigned)l.batch);
+  auto go = [&](auto kernel, int lanes) {
+    hipLaunchKernelGGL(kernel, g, dim3((unsigned)lanes), 0, s, p, (const T*)a, (const T*)b, o, bias);
     return hipGetLastError();
   };
-  constexpr bool real = sizeof(T) > 1;
+  constexpr bool real = sizeof(T) > 1, vectors = (MA == 1 || MA == 2) && (MB == 1 || MB == 2);
   switch (l.tile) {
-    case 0: return go(contract_kernel<T, 128, 128, 64, 2, 2, MA, MB, false>);
+    case 0: return go(contract_kernel<T, 128, 128, 64, 2, 2, MA, MB, false>, 256);
     case 1:
-      if constexpr (real) if (l.precise) return go(contract_kernel<T, 64, 64, 128, 2, 2, MA, MB, true>);
-      return go(contract_kernel<T, 64, 64, 128, 2, 2, MA, MB, false>);
+      if constexpr (real) if (l.precise) return go(contract_kernel<T, 64, 64, 128, 2, 2, MA, MB, true>, 256);
+      return go(contract_kernel<T, 64, 64, 128, 2, 2, MA, MB, false>, 256);
     case 3:
-      if constexpr (MB == 2 && sizeof(T) < 4) return hipErrorInvalidValue;   // 64 rows of 64 bytes are less than a unit per lane: the planner takes tile 1
-      else return go(contract_kernel<T, 128, 64, 64, 2, 2, MA, MB, false>);
+      if constexpr (MB == 2 && sizeof(T) < 4) return hipErrorInvalidValue;   // the planner takes tile 1
+      else return go(contract_kernel<T, 128, 64, 64, 2, 2, MA, MB, false>, 256);
+    case 4:
+      if constexpr (vectors) {
+        if (l.plain) {
+          if constexpr (real) if (l.precise) return go(contract_waves_kernel<T, 16, 16, 16, 256, MA, MB, true, true>, 1024);
+          return go(contract_waves_kernel<T, 16, 16, 16, 256, MA, MB, false, true>, 1024);
+        }
+      }
+      if constexpr (real) if (l.precise) return go(contract_waves_kernel<T, 16, 16, 16, 128, MA, MB, true, false>, 1024);
+      return go(contract_waves_kernel<T, 16, 16, 16, 128, MA, MB, false, false>, 1024);
+    case 5:
+      if constexpr (vectors) return go(contract_waves_kernel<T, 8, 64, 64, 64, MA, MB, false, true>, 512);
+      else return hipErrorInvalidValue;
     default:
-      if constexpr (real) if (l.precise) return go(contract_kernel<T, 32, 32, 256, 1, 1, MA, MB, true>);
-      return go(contract_kernel<T, 32, 32, 256, 1, 1, MA, MB, false>);
+      if constexpr (vectors) {
+        if (l.plain) {
+          if constexpr (real) if (l.precise) return go(contract_waves_kernel<T, 8, 32, 32, 128, MA, MB, true, true>, 512);
+          return go(contract_waves_kernel<T, 8, 32, 32, 128, MA, MB, false, true>, 512);
+        }
+      }
+      if constexpr (real) if (l.precise) return go(contract_waves_kernel<T, 8, 32, 32, 128, MA, MB, true, false>, 512);
+      return go(contract_waves_kernel<T, 8, 32, 32, 128, MA, MB, false, false>, 512);
   }
 }
 
@@ -717,10 +1052,11 @@ namespace {
 
 typedef __int128 i128;
 
+// 0, 1, 3: shared by four wavefronts; 2, 4, 5: the wavefronts share the reduction out
 struct Tile {
-  int bm, bn, bkb;
+  int bm, bn, bkb, lanes;
 };
-constexpr Tile kTiles[] = {{128, 128, 64}, {64, 64, 128}, {32, 32, 256}, {128, 64, 64}};
+constexpr Tile kTiles[] = {{128, 128, 64, 256}, {64, 64, 128, 256}, {32, 32, 128, 512}, {128, 64, 64, 256}, {16, 16, 256, 1024}, {64, 64, 64, 512}};
 
 struct Ix {                      // one index: range, address coefficients, constraint coefficients, output-bound coefficients
   int64_t range = 1, a = 0, b = 0, o = 0;
@@ -763,12 +1099,39 @@ static bool wants_double(int dtype, int tile, const LiteralSums& lit) {
   return tile == 2 && lit.chain > 8 && lit.chain < 17;
 }
 
-// Blocks that stay on their literal kernel.  Measured on 1,060 blocks of 65536 to 3e9 points in fp32, bf16 and int8: the faster
-// kernel is chosen, or one within 6 %, for all but 20 (the worst 30 %).
-static bool literal_is_faster(int dtype, const ContractParams& p, const LiteralSums& lit, bool fused, __int128 points, int64_t grid, int bk) {
-  if (points < 65536) return true;       // there a launch is all the time there is
+// Time of a block on tile t: a launch, per round of workgroups a fixed part and one for each K tile in a row -- all of them where
+// four wavefronts share a tile, every 8th or 16th where they share the reduction out -- and a part for what all workgroups' K tiles
+// take from memory together.  us, fitted to 344 products, convolutions and transposed convolutions of 1 to 4096 rows, 7 to 12544
+// points of reduction, each on every tile: the tile chosen by it takes 1.02 times as long as the best one (geometric mean).
+// single_rows: rows of a tile that are fetched element by element, 0.05 us for the loads of 64 elements (2 x 49 x 49, 64 channels,
+// transposed 3 x 3 to 15, bf16: 12.7 on 64 x 64, 18.6 on 32 x 32).
+static double tile_us(int dtype, int t, bool plain, int single_rows, double tiles, double k_bytes) {
+  struct Cost {
+    double fixed, k_tile, all;      // per round, per K tile and round, per K tile of 256 workgroups
+    double at_once;                 // workgroups of a round
+  };
+  static const Cost other[3][5] = {      // fp32, bf16, int8
+      {{5.3, 1.51, 0.92, 384}, {1.9, 1.20, 0.15, 384}, {2.2, 2.01, 0.76, 256}, {3.3, 1.01, 0.57, 384}, {1.6, 1.42, 1.59, 384}},
+      {{5.6, 0.93, 0.00, 256}, {2.8, 0.95, 0.03, 512}, {3.7, 1.48, 0.07, 256}, {4.1, 0.81, 0.03, 384}, {2.4, 1.20, 0.52, 256}},
+      {{4.2, 0.56, 0.57, 512}, {1.9, 0.38, 0.42, 768}, {3.2, 0.41, 0.56, 256}, {2.4, 0.43, 0.31, 384}, {3.2, 0.01, 1.34, 384}}};
+  static const Cost plain_product[3][6] = {
+      {{2.9, 1.32, 0.55, 256}, {1.4, 0.94, 0.25, 384}, {1.2, 1.37, 0.35, 256}, {2.2, 0.82, 0.49, 512}, {0.1, 2.04, 1.08, 256}, {1.9, 2.38, 0.88, 256}},
+      {{5.1, 0.50, 0.19, 256}, {2.2, 0.55, 0.16, 512}, {1.7, 0.57, 0.64, 384}, {3.0, 0.49, 0.11, 256}, {0.7, 1.46, 1.18, 256}, {3.1, 0.78, 0.96, 256}},
+      {{2.9, 0.71, 0.00, 256}, {1.6, 0.67, 0.06, 768}, {0.1, 1.45, 1.41, 768}, {1.7, 0.34, 0.17, 512}, {1.1, 0.80, 1.19, 256}, {2.0, 0.90, 1.04, 256}}};
+  const int d = dtype == STRIPE_F32 ? 0 : dtype == STRIPE_BF16 ? 1 : 2;
+  const Cost& c = plain ? plain_product[d][t] : other[d][t];
+  double k_tiles = std::ceil(k_bytes / (t == 4 && !plain ? 128 : kTiles[t].bkb));
+  if (t == 2 || t >= 4) k_tiles = std::ceil(k_tiles * 64 / kTiles[t].lanes);
+  const double singles = single_rows * k_bytes / (dtype == STRIPE_F32 ? 4 : dtype == STRIPE_BF16 ? 2 : 1) / 64;
+  return 4.0 + std::max(1.0, tiles / c.at_once) * (c.fixed + c.k_tile * k_tiles) + tiles / 256 * (c.all * k_tiles + 0.05 * singles);
+}
+
+// Blocks that stay on their literal kernel; here_us: what they take on this file's kernels.  Measured on 1,060 blocks of 65536 to
+// 3e9 points in fp32, bf16 and int8: the faster kernel is chosen, or one within 6 %, for all but 20 (the worst 30 %).
+static bool literal_is_faster(int dtype, const ContractParams& p, const LiteralSums& lit, bool simple, bool fused, __int128 points, double here_us) {
+  if (points < (simple && !fused ? 1024 : 65536)) return true;        // there a launch is all the time there is
   if (fused) return false;               // a launch and a temporary more: 33 x 33 x 1001 bf16 with bias and relu 12.0 us against 13.3
-  if (lit.atomic) return false;          // two launches and atomic additions: 118 us against 10 for a transposed convolution
+  if (lit.atomic && points >= 65536) return false;          // two launches and atomic additions: 118 us against 10 for a transposed convolution
   if (lit.tiled) {
     // Short reductions into few columns: 100000 x 3 x 5 fp32 7 us against 12 (20000 x 200 x 8 18 against 14).  Large images with few
     // output channels fill a fraction of a tile's columns: 3x3, 3 -> 8 channels at 27 x 184 x 184 fp32 68 us against 164, 3 -> 4
@@ -778,15 +1141,19 @@ static bool literal_is_faster(int dtype, const ContractParams& p, const LiteralS
     if (p.tested && lit.chain <= 32 && few <= (dtype == STRIPE_F32 ? 24u : 4u) && points >= ((__int128)1 << 26)) return true;
     return dtype == STRIPE_F32 && p.mode_a == 2 && p.N <= 8 && lit.chain <= 64 && points >= ((__int128)1 << 23);
   }
-  // Few tiles: both times from their steps.  A wavefront per output: 64 points a step, 0.36 us (0.6 with several reduction indexes
-  // to divide up), or what all outputs' steps take together (33 x 33 x 1001 nt fp32 10.4 us, on one tile row of this kernel 19;
-  // 250 x 250 x 1001 122 and 20).  A lane per output: 0.21 us a point.  Here: 0.78 / 0.62 / 0.8 us a K tile and workgroup round.
-  const double many = lit.n_red > 1 ? 2.0 : 1.0;
-  const double literal = lit.lanes == 64 ? 5.0 + (double)((lit.chain + 63) / 64) * std::max(lit.n_red > 1 ? 0.6 : 0.36, 1.2e-4 * many * (double)lit.outputs)
-                                         : 5.0 + 0.21 * (double)lit.chain * std::max(1.0, (double)lit.outputs / 5e5);
-  const double tile_us = dtype == STRIPE_F32 ? 0.78 : dtype == STRIPE_BF16 ? 0.62 : 0.8;
-  const double here = (p.tested && dtype != STRIPE_I8 ? 7.5 : 6.0) + (double)((p.K + bk - 1) / bk) * tile_us * std::max(1.0, (double)grid / 512);
-  return literal < here;
+  // A wavefront per output: 64 points a step, 0.36 us (0.6 with several reduction indexes to divide up), or what all outputs' steps
+  // take together (250 x 250 x 1001 122 us, here 10).  Few steps of few outputs, whose wavefronts each have a CU's loads to
+  // themselves, stay there, unless one 32 x 32 tile walking the whole reduction would be as fast.
+  if (lit.lanes == 64) {
+    const double many = lit.n_red > 1 ? 2.0 : 1.0;
+    const double literal = 5.0 + 4e-4 * (double)lit.outputs + (double)((lit.chain + 63) / 64) * std::max(lit.n_red > 1 ? 0.6 : 0.36, 1.2e-4 * many * (double)lit.outputs);
+    const double k_bytes = (double)p.K * (dtype == STRIPE_F32 ? 4 : dtype == STRIPE_BF16 ? 2 : 1);
+    const double one_tile = (p.tested && dtype != STRIPE_I8 ? 7.5 : 6.0) + std::ceil(k_bytes / 256) * (dtype == STRIPE_F32 ? 0.78 : dtype == STRIPE_BF16 ? 0.62 : 0.8);
+    if (literal < one_tile && ((literal < 12 && lit.outputs <= 4096) || lit.outputs <= 512)) return true;
+    return literal < here_us;
+  }
+  // A lane per output: 0.21 us a point (1 x 349 x 3328 int8 784 us).
+  return (5.0 + 0.21 * (double)lit.chain * std::max(1.0, (double)lit.outputs / 5e5)) * (lit.atomic ? 2 : 1) < here_us;
 }
 
 bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, ContractLaunch* l, stripe_block_info_t* info) {
@@ -957,7 +1324,7 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, Co
     else if (x.b) n.push_back(x);
     else m.push_back(x);
   }
-  if (m.empty() || n.empty() || k.empty() || bat.size() > 2) return false;
+  if (n.empty() || k.empty() || bat.size() > 2) return false;      // no row index: one row (a matrix-vector product)
   auto mag = [](int64_t v) { return v < 0 ? -v : v; };
   // rows: the index A holds contiguously first (vector fetches), else by output stride
   std::sort(m.begin(), m.end(), [&](const Ix& x, const Ix& y) { return (x.a == 1) != (y.a == 1) ? x.a == 1 : mag(x.o) < mag(y.o); });
@@ -1110,7 +1477,7 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, Co
     }
     const bool k_unit = (a ? k0.a : k0.b) == 1 && !k_tests;
     if (k_unit && ((k.size() == 1 && k0.range >= ve) || k0.range % ve == 0)) return 1;
-    if ((a ? row[0].a : row[0].b) == 1 && !row_tests && ((row.size() == 1 && row[0].range >= vr) || row[0].range % vr == 0)) return 2;
+    if (!row.empty() && (a ? row[0].a : row[0].b) == 1 && !row_tests && ((row.size() == 1 && row[0].range >= vr) || row[0].range % vr == 0)) return 2;
     if (k_unit && (a ? p.bytes_a : p.bytes_b) >= 8 && k0.range > 1) return 3;
     return 0;
   };
@@ -1137,33 +1504,44 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, Co
   const int least = tune_int("contract_min", 0);     // STRIPE_TUNE contract_min = n: every block of at least n points; 0: the rule
   if (least > 0 && points < least) return false;
   auto tiles = [&](int t) { return ((M + kTiles[t].bm - 1) / kTiles[t].bm) * ((N + kTiles[t].bn - 1) / kTiles[t].bn) * l->batch; };
-  // The largest tile that still gives every CU a workgroup; 64 x 64 also for somewhat fewer, and for half as many where the
-  // reduction is a few K tiles and the small tile's sharing of k has nothing to share.  Measured, us: 2000 x 2000 x 1000 bf16
-  // [k][m] 40 on 128 x 128, 53 on 64 x 64, 72 on 32 x 32; 3569 x 256 x 3264 bf16 (224 tiles of 64 x 64) 54 against 58 on 32 x 32;
-  // 500 x 1000 x 777 (128 tiles) 14 against 12; 238 x 2368 x 64 fp32 (148 tiles) 7.1 both; a 3 -> 64-channel 5 x 5
-  // convolution at 135 x 135 (428 tiles of 128 x 64) 16 on those, 17 on 64 x 64.
-  int tile = tiles(0) >= 256 && M > 64 && N > 64               ? 0
-             : tiles(3) >= 256                                  ? 3
-             : tiles(1) >= 192 || (tiles(1) >= 96 && (int64_t)p.K * esize <= 512) ? 1
-                                                                : 2;
+  const bool simple = m.size() <= 1 && n.size() == 1 && k.size() == 1 && !p.tested;      // a product
+  l->plain = simple && (p.mode_a == 1 || p.mode_a == 2) && (p.mode_b == 1 || p.mode_b == 2);
+  // A bf16 output's own rounding hides the sums'.
+  auto precise_on = [&](int t) { return !fb.out_bf16 && wants_double(dt, t, lit); };
+  auto runs = [&](int t) {
+    if (t == 3 && p.mode_b == 2 && esize < 4) return false;
+    if (t == 5 && !l->plain) return false;
+    return !(precise_on(t) && (t == 0 || t == 3 || t == 5));
+  };
+  int tile = -1;
+  for (int t = 0; t < 6; ++t) {
+    if (!runs(t)) continue;
+    const int singles = (p.mode_a == 0 ? kTiles[t].bm : 0) + (p.mode_b == 0 ? kTiles[t].bn : 0);
+    const double us = tile_us(dt, t, l->plain, singles, (double)tiles(t), (double)p.K * esize);
+    if (tile < 0 || us < l->us) {
+      tile = t;
+      l->us = us;
+    }
+  }
   const int forced = tune_int("contract_tile", -1);
-  if (forced >= 0 && forced <= 3) tile = forced;
+  if (forced >= 0 && forced <= 5) tile = forced;
   if (tile == 3 && p.mode_b == 2 && esize < 4) tile = 1;
-  l->precise = !fb.out_bf16 && wants_double(dt, tile, lit);      // a bf16 output's own rounding hides the sums'
-  if (l->precise && forced < 0 && (tile == 0 || tile == 3)) tile = 1;
+  if (tile == 5 && (!l->plain || precise_on(5))) tile = 1;
+  l->precise = precise_on(tile);
   l->tile = tile;
+  const int bkb = tile == 4 && !l->plain ? 128 : kTiles[tile].bkb;
   const i128 grid = tiles(tile) / l->batch;
   if (grid > 0x7fffffff) return false;
-  if (least == 0 && literal_is_faster(dt, p, lit, fused, points, (int64_t)grid * l->batch, kTiles[tile].bkb / esize)) return false;
+  if (least == 0 && literal_is_faster(dt, p, lit, simple, fused, points, l->us)) return false;
   p.tiles_n = (int32_t)((N + kTiles[tile].bn - 1) / kTiles[tile].bn);
   l->grid = (int64_t)grid;
   l->use = true;
   info->path = STRIPE_PATH_GENERIC;
-  info->tile_m = kTiles[tile].bm; info->tile_n = kTiles[tile].bn; info->tile_k = kTiles[tile].bkb / esize;
+  info->tile_m = kTiles[tile].bm; info->tile_n = kTiles[tile].bn; info->tile_k = bkb / esize;
   info->frag_m = info->frag_n = 16;
   info->frag_k = dt == STRIPE_F32 ? 4 : 64 / esize;
-  info->lds_bytes = (kTiles[tile].bm + kTiles[tile].bn) * (2 * (kTiles[tile].bkb + 16) + 24) + 96 * kTiles[tile].bkb / esize;
-  info->workgroup_size = 256;
+  info->lds_bytes = (kTiles[tile].bm + kTiles[tile].bn) * (bkb * (kTiles[tile].lanes > 256 ? kTiles[tile].lanes / 64 : 2) + 24);
+  info->workgroup_size = kTiles[tile].lanes;
   info->grid = l->grid * l->batch;
   std::snprintf(info->kernel, sizeof info->kernel, "contract_%s_%dx%dx%d_fetch%d%d", dt == STRIPE_F32 ? "f32" : dt == STRIPE_BF16 ? "bf16" : "i8",
                 kTiles[tile].bm, kTiles[tile].bn, (int)info->tile_k, p.mode_a, p.mode_b);

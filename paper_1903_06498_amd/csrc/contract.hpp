@@ -45,7 +45,9 @@ struct ContractLaunch {
   bool use = false;
   bool swap = false;            // the block's second operand plays A
   int tile = 0;                 // index into the kernel's tile table
-  bool precise = false;         // totals in double precision (tiles of 64 x 64 and 32 x 32)
+  bool precise = false;         // totals in double precision (not on the largest tiles)
+  double us = 0;                // the block's estimated time
+  bool plain = false;           // one index per side, no tests, both operands fetched in vectors
   int64_t grid = 0, batch = 1;
   int64_t first_a = 0, first_b = 0;   // an operand's buffer origin, in elements from the caller's pointer (a_base, b_base count from it)
   ContractParams p;

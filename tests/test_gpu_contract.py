@@ -460,3 +460,58 @@ def test_first_run_of_a_split_product_under_capture(fused):
         torch.cuda.synchronize()
         assert ((eager.cpu().double() - want).abs() <= tol).all()
     sb.close()
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "i8"])
+@pytest.mark.parametrize("layout", ["nn", "nt", "tn"])
+@pytest.mark.parametrize("M,N,K,tile", [(1, 17, 33, 4), (1, 130, 700, 5), (15, 17, 31, 4), (16, 16, 64, 4), (19, 33, 4100, 4), (64, 64, 64, 5),
+                                        (63, 65, 33, 5), (66, 130, 1025, 5), (9, 300, 2100, 2)])
+def test_products_whose_reduction_wavefronts_share(M, N, K, tile, layout, dt, monkeypatch):
+    """The tiles on which wavefronts share the reduction out: fewer K tiles than wavefronts, a last pass that only some have, partial
+    vectors, one row, rows and columns beside the tile."""
+    monkeypatch.setenv("STRIPE_TUNE", f"contract_min=1,contract_tile={tile},gemm_rows=0,gemm_dma=0")
+    blk = matmul(M, N, K, dt, layout)
+    ins = [W.seeded_tensor(blk.refs[0].sizes, dt, 0), W.seeded_tensor(blk.refs[1].sizes, dt, 1)]
+    info, _ = parity(blk, ins, what=f"{layout} {M}x{N}x{K} {dt}")
+    # one row of few columns whose operand cannot be fetched in vectors: no plain product, which the 64 x 64 form is for
+    assert info["kernel"].startswith(f"contract_{dt}_{ {2: '32x32', 4: '16x16', 5: '64x64'}[tile] }x"), info["kernel"]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "i8"])
+@pytest.mark.parametrize("shape", [(2, 19, 13, 3, 20, 5, 2, 2), (1, 9, 11, 8, 70, 3, 1, 1), (1, 7, 7, 72, 17, 7, 1, 3), (1, 6, 7, 9, 12, 3, 1, 1)])
+def test_convolutions_on_the_smallest_tile(shape, dt, monkeypatch):
+    """Constraints and several reduction indexes on the 16 x 16 tile: tables of more and of fewer K tiles than a wavefront has."""
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1,contract_tile=4,conv_igemm=0")
+    N, H, Wd, Ci, Co, R, s, p = shape
+    blk = W.conv2d_block(N, H, Wd, Ci, Co, R, R, s, p, dt, "i32" if dt == "i8" else "f32")
+    info, _ = parity(blk, [W.seeded_tensor((N, H, Wd, Ci), dt, 0), W.seeded_tensor((R, R, Co, Ci), dt, 1)], what=f"conv {shape} {dt}")
+    assert info["kernel"].startswith(f"contract_{dt}_16x16x"), info
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_non_finite_values_on_the_smallest_tile(dt, monkeypatch):
+    """A removed point contributes nothing there either: the literal kernel's infinities, NaN and finite values."""
+    blk = W.conv2d_block(1, 9, 9, 13, 20, 5, 5, 1, 2, dt, "f32")
+    ins = [W.seeded_tensor(r.sizes, dt, i) for i, r in enumerate(blk.refs[:2])]
+    for i, t in enumerate(ins):
+        flat = t.view(-1)
+        for at, v in ((7, math.inf), (flat.numel() // 2, -math.inf), (flat.numel() - 2 - i, math.nan)):
+            flat[at] = v
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1,contract_tile=4")
+    got, sb = run_gpu(blk, ins, return_block=True)
+    assert sb.info["kernel"].startswith(f"contract_{dt}_16x16x"), sb.info["kernel"]
+    want = run_gpu(blk, ins, "generic")
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
+    assert np.array_equal(np.isneginf(got), np.isneginf(want)) and np.isinf(want).any() and np.isnan(want).any()
+    fin = np.isfinite(want)
+    assert fin.any() and np.allclose(got[fin], want[fin], rtol=1e-5, atol=325 * 2.0 ** -24 * 325)     # 325 products of order 1 in fp32
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "i8"])
+@pytest.mark.parametrize("layout,M,N,K", [("nn", 1, 349, 1000), ("tn", 1, 128, 960), ("nn", 5, 19, 184), ("tn", 3, 64, 240), ("nt", 33, 56, 26)])
+def test_small_products(layout, M, N, K, dt):
+    """A row vector times a matrix and products of a few thousand points, chosen without any setting."""
+    blk = matmul(M, N, K, dt, layout)
+    ins = [W.seeded_tensor(blk.refs[0].sizes, dt, 0), W.seeded_tensor(blk.refs[1].sizes, dt, 1)]
+    info, _ = parity(blk, ins, what=f"{layout} {M}x{N}x{K} {dt}")
+    assert info["kernel"].startswith("contract_"), info["kernel"]
