@@ -57,6 +57,7 @@ struct stripe_block {
   // 1, 2: the two statements run as one convolution kernel with a bias+relu epilogue (fp32 / bf16 output);
   // 3, 4: the same with the dense-contraction kernel; 5, 6: with the general matrix-core contraction
   int fused = 0;
+  bool aligned_out = false;  // the convolution kernels would have fused the statements: bias and output 16-byte aligned
   int64_t fuse_bias_off = 0, fuse_o_m = 0, fuse_o_base = 0;
   ~stripe_block() {
     for (Stage& st : stages) delete st.blk;
@@ -272,7 +273,8 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
         ok = rng[k] == c.conv.Co && rng[px] == pixels && ct[k] == 1 && cbias[k] == 1 && co[k] == 1 && ct[px] == c.conv.Co && cbias[px] == 0 &&
              co[px] == c.conv.Co && e.ref[0].addr.k == 0 && e.ref[1].addr.k % 4 == 0 && e.ref[2].addr.k == 0;
       }
-      if (ok) {
+      prog->aligned_out = ok;
+      if (ok && !s0.blk->contract.use) {
         prog->fused = e.out_bf16 ? 2 : 1;
         prog->plan.conv = c.conv;
         prog->conv = s0.blk->conv;
@@ -290,11 +292,11 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
     bool few_rows = s0.blk->rows.use && c.in_dtype == STRIPE_BF16, alt = false;
     RowsLaunch rows = s0.blk->rows;
     stripe_block_info_t rows_info = c.info, unused = c.info;
-    if (!few_rows && path == STRIPE_PATH_AUTO && c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && s0.blk->gemm.split_k > 1) {
+    if (!few_rows && path == STRIPE_PATH_AUTO && !s0.blk->contract.use && c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && s0.blk->gemm.split_k > 1) {
       few_rows = gemm_rows_select(c.gemm, c.in_dtype, gemm_few_rows_us(c.gemm, c.in_dtype, s0.blk->gemm) + 3.0, &rows, &rows_info);
       alt = !few_rows && gemm_rows_select(c.gemm, c.in_dtype, __builtin_huge_val(), &rows, &unused);
     }
-    bool ok = (few_rows || alt || (c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && gemm_can_fuse_bias_relu(c.gemm, s0.blk->gemm))) &&
+    bool ok = (few_rows || alt || (c.info.path == STRIPE_PATH_MFMA_GEMM && !s0.blk->contract.use && c.in_dtype == STRIPE_BF16 && gemm_can_fuse_bias_relu(c.gemm, s0.blk->gemm))) &&
               root->refs[s0.dst].dir == STRIPE_TEMP && s1.n_in == 2 && s1.src[0] == s0.dst && !e.empty && e.intrinsic == STRIPE_INTR_ADD_RELU &&
               e.cons.empty() && e.n_refs == 3 && e.n_idx >= 2 && e.ref[0].dtype == STRIPE_F32 && e.ref[1].dtype == STRIPE_F32;
     if (ok) {
@@ -331,7 +333,7 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
     if (!ct.use && path == STRIPE_PATH_AUTO && c.info.path == STRIPE_PATH_GENERIC && !c.noop && !s0.blk->rows.use && c.in_dtype == STRIPE_BF16)
       contract_select(c.flat, literal_sums(c), true, &ct, &ct_info);
     const FlatBlock& e = s1.blk->plan.flat;
-    bool ok = c.info.path == STRIPE_PATH_GENERIC && ct.use && c.in_dtype == STRIPE_BF16 && ct.p.epilogue == 0 && !ct.p.n_ob_used && ct.batch == 1 &&
+    bool ok = (c.info.path == STRIPE_PATH_GENERIC || s0.blk->contract.use) && ct.use && c.in_dtype == STRIPE_BF16 && ct.p.epilogue == 0 && !ct.p.n_ob_used && ct.batch == 1 &&
               ct.p.n.n == 1 && ct.p.n_out[0] == 1 && root->refs[s0.dst].dir == STRIPE_TEMP && s1.n_in == 2 && s1.src[0] == s0.dst && !e.empty &&
               e.intrinsic == STRIPE_INTR_ADD_RELU && e.cons.empty() && e.n_refs == 3 && e.n_idx >= 2 && e.ref[0].dtype == STRIPE_F32 &&
               e.ref[1].dtype == STRIPE_F32;
@@ -357,6 +359,7 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
         prog->contract = ct;
         s0.blk->plan.info = ct_info;
         prog->plan.in_dtype = c.in_dtype;
+        prog->plan.info.path = c.info.path;
         prog->fuse_bias_off = e.ref[1].addr.k;
         prog->temp_bytes[s0.dst] = 0;
       }
@@ -479,6 +482,11 @@ stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void*
     const Stage &s0 = prog->stages[0], &s1 = prog->stages[1];
     const float* bias = (const float*)inputs[prog->input_slot[s1.src[1]]] + prog->fuse_bias_off;
     if (fused >= 5) {
+      // the family's pointer contract where the block is one of its
+      if (prog->plan.info.path != STRIPE_PATH_GENERIC &&
+          (((uintptr_t)inputs[prog->input_slot[s0.src[0]]] % 16) || ((uintptr_t)inputs[prog->input_slot[s0.src[1]]] % 16) ||
+           (prog->aligned_out && (((uintptr_t)bias % 16) || ((uintptr_t)output % 16)))))
+        return fail(STRIPE_ERR_MISALIGNED, "the fused matrix-core kernel needs 16-byte aligned operands (convolution: also bias and output)");
       e = launch_contract(prog->contract, prog->plan.in_dtype, inputs[prog->input_slot[s0.src[0]]], inputs[prog->input_slot[s0.src[1]]], output, bias,
                           fused == 6, (hipStream_t)hip_stream);
       if (e != hipSuccess) return fail(STRIPE_ERR_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
@@ -529,11 +537,14 @@ stripe_status_t run_single(stripe_block* blk, const void* const* inputs, void* o
                                        "dense contractions and the general convolution kernel, the output pointer) must be 16-byte aligned");
   switch (p.info.path) {
     case STRIPE_PATH_MFMA_GEMM:
-      if (blk->rows.use || (static_rows && blk->static_rows.use))
+      if (blk->contract.use) e = launch_contract(blk->contract, p.in_dtype, in0, in1, output, nullptr, false, s);
+      else if (blk->rows.use || (static_rows && blk->static_rows.use))
         e = launch_gemm_rows(p.gemm, p.in_dtype, in0, in1, output, p.gemm.c_m, p.gemm.c_base, nullptr, false, s);
       else e = launch_gemm(p.gemm, blk->gemm, in0, in1, output, ws, s);
       break;
-    case STRIPE_PATH_MFMA_CONV: e = launch_conv(p.conv, blk->conv, in0, in1, output, s); break;
+    case STRIPE_PATH_MFMA_CONV:
+      if (blk->contract.use) e = launch_contract(blk->contract, p.in_dtype, in0, in1, output, nullptr, false, s);
+      else e = launch_conv(p.conv, blk->conv, in0, in1, output, s); break;
     case STRIPE_PATH_POOL: e = launch_pool(p.pool, blk->pool, in0, in1, output, s); break;
     default:
       if (blk->rows.use) e = launch_gemm_rows(p.gemm, p.in_dtype, in0, in1, output, p.gemm.c_m, p.gemm.c_base, nullptr, false, s);
@@ -612,6 +623,24 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
     } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM &&
                gemm_rows_select(p.gemm, p.in_dtype, gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm), &blk->rows, &p.info)) {
       blk->gemm.ws_bytes = 0;    // no partial sums of a split reduction
+    }
+    // Products and convolutions with few tiles of their family's kernel and a long reduction, whose wavefronts then share the
+    // reduction out: on the general contraction where both estimates say so (6 x 1536 x 768 bf16 nn 21 us on one row of 256 x 256
+    // tiles, 7 here; 7 x 7, 256 -> 9 channels int8 over 3 x 42 x 42: 77 and 15).  Those families' pointer contract stays.
+    // (not under STRIPE_TUNE, which picks variants of those families, unless it says contract_over=1)
+    const bool igemm = p.info.path == STRIPE_PATH_MFMA_CONV && blk->conv.variant >= kConvIgemmVariant && blk->conv.variant < kConvGemmVariant;
+    if (!forced && picked && tune_int("contract_over", std::getenv("STRIPE_TUNE") == nullptr) && !blk->rows.use && (igemm || (p.info.path == STRIPE_PATH_MFMA_GEMM && (blk->gemm.split_k <= 1 || p.gemm.M <= 32)))) {
+      stripe_block_info_t other = p.info;
+      const double us = igemm ? conv_igemm_us(p.conv, blk->conv)
+                              : blk->gemm.split_k > 1 ? gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm) : gemm_us(p.gemm, p.in_dtype, blk->gemm);
+      const LiteralSums one_chain = {1, p.gen.red_total, p.gen.n_red, p.gen.n_outputs, false, false};      // those kernels hold one sum per output
+      if (us >= (igemm ? 25 : 13) && contract_select(p.flat, one_chain, true, &blk->contract, &other) && blk->contract.us < 0.8 * us) {
+        other.path = p.info.path;
+        p.info = other;
+        blk->gemm.ws_bytes = 0;    // no partial sums of a split reduction
+      } else {
+        blk->contract.use = false;
+      }
     }
     if (p.info.path == STRIPE_PATH_MFMA_GEMM && picked) blk->ws_bytes = blk->static_ws_bytes = blk->gemm.ws_bytes;
     stripe_block_info_t unused = p.info;

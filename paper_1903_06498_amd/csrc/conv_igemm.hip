@@ -372,6 +372,13 @@ __global__ __launch_bounds__(512, 1) void conv_igemm_kernel(const IgemmParams p,
 
 }  // namespace
 
+// One workgroup per CU and round: 64 bytes of a tap's channels at a time.  Fitted to convolutions of 49 to 70000 pixels, reductions
+// of 64 to 12544 (7 x 7, 256 channels int8 over 3 images of 42 x 42: 77 us on 21 workgroups).
+double conv_igemm_us(const Conv2dShape& c, const ConvLaunch& l) {
+  const double k_tiles = (double)(c.R * c.S * c.Ci) * (l.in_dtype == STRIPE_I8 ? 1 : 2) / 64, rounds = (double)((l.grid + 255) / 256);
+  return 4.0 + rounds * (2.0 + ((l.variant - kConvIgemmVariant) % 4 == 0 ? 0.25 : (l.variant - kConvIgemmVariant) % 4 == 1 ? 0.36 : 0.45) * k_tiles);
+}
+
 bool conv_igemm_select(const Conv2dShape& c, int in_dtype, bool out_bf16, ConvLaunch* l, stripe_block_info_t* info) {
   if (tune_int("conv_igemm", 1) == 0) return false;
   const bool i8 = in_dtype == STRIPE_I8;

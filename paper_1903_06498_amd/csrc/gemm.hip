@@ -1217,6 +1217,12 @@ double gemm_few_rows_us(const GemmShape& g, int in_dtype, const GemmLaunch& l) {
   return std::max(4.0 + rounds * (6.0 + 0.6 * k_tiles), bytes / 3.4e6);
 }
 
+// One workgroup per CU and round: 64 bytes of K at a time.  Fitted to products of 2 to 4096 rows, K of 128 to 4096.
+double gemm_us(const GemmShape& g, int in_dtype, const GemmLaunch& l) {
+  const double k_tiles = (double)g.K * (in_dtype == STRIPE_I8 ? 1 : 2) / 64, rounds = (double)((l.grid + 255) / 256);
+  return 4.0 + rounds * (l.variant >= 50 ? 1.0 + 0.28 * k_tiles : 4.0 + 0.62 * k_tiles);
+}
+
 bool gemm_select(const GemmShape& g, int in_dtype, GemmLaunch* l, stripe_block_info_t* info) {
   if (!gemm_select_one(g, in_dtype, l, info)) return false;
   l->split_k = choose_split_k(g, in_dtype, *l);

@@ -47,7 +47,9 @@ bool gemm_can_fuse_bias_relu(const GemmShape& g, const GemmLaunch& l);
 hipError_t launch_gemm_bias_relu(const GemmShape& g, const GemmLaunch& l, const void* a, const void* b, const void* bias, void* out,
                                  int64_t o_m, int64_t o_base, bool out_bf16, hipStream_t stream);
 
-// Estimated time, in us, of a product with few rows on the kernels gemm_select chose.
+// Estimated time, in us, of an unsplit product on the kernels gemm_select chose.
+double gemm_us(const GemmShape& g, int in_dtype, const GemmLaunch& l);
+// The same of a product with few rows, split or not.
 double gemm_few_rows_us(const GemmShape& g, int in_dtype, const GemmLaunch& l);
 // products with at most 32 rows and k-contiguous operands (gemm_rows.hip); bias != nullptr: O = relu(C + bias[n]).
 // other_us: what the product takes otherwise (infinite: unknown, slower).
@@ -78,6 +80,8 @@ hipError_t launch_conv_bias_relu(const Conv2dShape& c, const ConvLaunch& l, cons
                                  bool out_bf16, hipStream_t stream);
 // general convolution kernel (implicit contraction: any filter extent, stride, dilation, padding, image width;
 // bf16 with Ci % 32 == 0 or int8 with Ci % 64 == 0; channels contiguous); conv_select falls back to it
+// (its time in us, estimated)
+double conv_igemm_us(const Conv2dShape& c, const ConvLaunch& l);
 bool conv_igemm_select(const Conv2dShape& c, int in_dtype, bool out_bf16, ConvLaunch* l, stripe_block_info_t* info);
 // large bf16 convolutions (at least 128 tiles of 256 pixels x 256 channels, reduction a multiple of four 32-deep K tiles,
 // dense output, every pixel written) on the contraction kernel: pixels as rows of A, gathered per filter tap

@@ -515,3 +515,36 @@ def test_small_products(layout, M, N, K, dt):
     ins = [W.seeded_tensor(blk.refs[0].sizes, dt, 0), W.seeded_tensor(blk.refs[1].sizes, dt, 1)]
     info, _ = parity(blk, ins, what=f"{layout} {M}x{N}x{K} {dt}")
     assert info["kernel"].startswith("contract_"), info["kernel"]
+
+
+@pytest.mark.parametrize("kind", ["product", "convolution"])
+def test_family_blocks_on_the_contraction_keep_their_pointer_contract(kind):
+    """Few tiles and a long reduction: a product and a convolution of the matrix-core families run here, stay blocks of their family, and
+    refuse unaligned pointers as before; fused with bias + relu too."""
+    if kind == "product":
+        blk, prog = W.matmul_block(15, 64, 2432, "bf16", "f32"), None
+    else:
+        blk, prog = W.conv2d_block(3, 13, 13, 256, 64, 5, 5, 1, 2, "bf16", "f32"), W.conv_bias_relu_program(1, 13, 13, 256, 64, 5, 5, 1, 2, "bf16", "f32")
+    ins = [W.seeded_tensor(r.sizes, "bf16", i) for i, r in enumerate(blk.refs[:2])]
+    info, _ = parity(blk, ins, what=kind)
+    assert info["kernel"].startswith("contract_") and info["path_name"] == ("mfma_gemm" if kind == "product" else "mfma_conv"), info
+    sb = B.StripeBlock(blk)
+    out = torch.zeros(W.output_extent(blk), device="cuda")
+    with pytest.raises(B.StripeError) as e:
+        sb.run([unaligned(ins[0], 1), ins[1].cuda()], out)
+    assert e.value.status == 8, str(e.value)
+    sb.close()
+    if prog is not None:
+        sb = B.StripeBlock(prog)
+        assert sb.info["kernel"].startswith("contract_") and sb.info["kernel"].endswith("+bias_relu") and sb.info["workspace_bytes"] == 0, sb.info
+        held = [W.seeded_tensor(r.sizes, r.dtype, i).cuda() for i, r in enumerate(r for r in prog.refs if r.dir == "in")]
+        out = torch.zeros((1, 13, 13, 64), device="cuda")
+        with pytest.raises(B.StripeError) as e:
+            sb.run([held[0], held[1], unaligned(held[2].cpu(), 1)], out)
+        assert e.value.status == 8, str(e.value)
+        sb.run(held, out)
+        sb.close()
+        x, f, b = (t.double().cpu() for t in held)
+        want = torch.relu(torch.nn.functional.conv2d(x.permute(0, 3, 1, 2), f.permute(2, 3, 0, 1), padding=2) + b[:, None, None]).permute(0, 2, 3, 1)
+        err = (out.double().cpu() - want).abs().max()
+        assert err <= 6400 * 2.0 ** -24 * float((x.abs().max() * f.abs().max() * 6400).clamp(min=1)), float(err)     # 6400 fp32 additions
