@@ -941,8 +941,9 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_bf16_dma_kernel(const Gemm
 // ring of 32-deep K tiles, A rows swizzled by (row>>2)&3, B kept [k][n] in
 // 256-byte rows swizzled by 4*(k&3) and read with the transposing LDS read --
 // at half the bytes per tile (8 KB + 8 KB), so two workgroups fit on a CU.
-// M and N multiples of 128, K a multiple of 128 (256 for int8).  MODE as in the large-tile kernel: D_BT for a
-// transposed B (its tile then lies in LDS like A's), D_I8 for int8 operands with int32 accumulation.
+// K a multiple of 128 (256 for int8).  MODE as in the large-tile kernel: D_BT for a
+// transposed B (its tile then lies in LDS like A's), D_I8 for int8 operands with int32 accumulation, D_RAGGED for M and N that
+// are not multiples of 128 (2000 x 2048 x 2048 int8, 256 of these tiles instead of 64 large ones: 28.3 -> 15.1 us).
 // ---------------------------------------------------------------------------
 constexpr int T_BM = 128, T_BN = 128;
 constexpr int t128_lds_bytes(int kb) { return D_STAGES * (T_BM + T_BN) * kb; }   // 64 KB, or 128 KB with 128-byte K tile rows
@@ -981,31 +982,34 @@ __global__ __launch_bounds__(256 * (1 + W8), 1) void gemm_bf16_t128_kernel(const
   const unsigned tile = blockIdx.x - batch * tiles;
   const int tm = (int)(tile / (unsigned)p.tiles_n), tn = (int)(tile % (unsigned)p.tiles_n);
 
-  // loads: block wv (+ NW*u) of each operand's 8 blocks of 1 KB per K tile
-  const uint16_t* a_src;
-  const uint16_t* b_src;
-  {
-    const int row = RPB * wv + lane / LPR;              // + RPB*NW*u
+  // loads: block wv (+ NW*u) of each operand's 8 blocks of 1 KB per K tile; ragged: rows (or, for a row-major B, 8-column chunks)
+  // past the edge are redirected to the last valid one
+  const uint16_t* a_src[LPW];
+  const uint16_t* b_src[LPW];
+#pragma unroll
+  for (int u = 0; u < LPW; ++u) {
+    const int row = RPB * (wv + NW * u) + lane / LPR;
     const int chunk = (lane % LPR) ^ key(row);
-    a_src = A + p.a_base + ((int64_t)tm * T_BM + row) * p.a_m + chunk * 8;
+    int64_t gm = (int64_t)tm * T_BM + row, gn = (int64_t)tn * T_BN + row;
+    if ((MODE & D_RAGGED) && gm >= p.M) gm = p.M - 1;
+    if ((MODE & D_RAGGED) && gn >= p.N) gn = p.N - 1;
+    a_src[u] = A + p.a_base + gm * p.a_m + chunk * 8;
     if constexpr (MODE & D_BT) {
-      b_src = B + p.b_base + ((int64_t)tn * T_BN + row) * p.b_k + chunk * 8;
+      b_src[u] = B + p.b_base + gn * p.b_k + chunk * 8;
     } else {
-      const int k = 4 * wv + (lane >> 4);                 // + 4*NW*u ; k&3 == lane>>4
-      const int bchunk = (lane & 15) ^ (4 * (k & 3));
-      b_src = B + p.b_base + (int64_t)k * p.b_k + (int64_t)tn * T_BN + bchunk * 8;
+      const int k = 4 * (wv + NW * u) + (lane >> 4);      // k&3 == lane>>4
+      gn = (int64_t)tn * T_BN + ((lane & 15) ^ (4 * (k & 3))) * 8;
+      if ((MODE & D_RAGGED) && gn + 8 > p.N) gn = p.N - 8;
+      b_src[u] = B + p.b_base + (int64_t)k * p.b_k + gn;
     }
   }
-  const size_t a_step = (size_t)(RPB * NW) * p.a_m, b_step = (MODE & D_BT) ? (size_t)(RPB * NW) * p.b_k : (size_t)(4 * NW) * p.b_k,
-               b_kstep = (MODE & D_BT) ? (size_t)BKE : (size_t)BKE * p.b_k;
+  const size_t b_kstep = (MODE & D_BT) ? (size_t)BKE : (size_t)BKE * p.b_k;
   const unsigned wave_lds = wv * 1024;
   auto issue = [&](int stage, int kt) {
-    const uint16_t* a = a_src + (size_t)kt * BKE;
-    const uint16_t* b = b_src + (size_t)kt * b_kstep;
 #pragma unroll
-    for (int u = 0; u < LPW; ++u) d_load_lds16(a + u * a_step, stage * T_A_STAGE + u * (NW * 1024) + wave_lds);
+    for (int u = 0; u < LPW; ++u) d_load_lds16(a_src[u] + (size_t)kt * BKE, stage * T_A_STAGE + u * (NW * 1024) + wave_lds);
 #pragma unroll
-    for (int u = 0; u < LPW; ++u) d_load_lds16(b + u * b_step, T_B0 + stage * T_B_STAGE + u * (NW * 1024) + wave_lds);
+    for (int u = 0; u < LPW; ++u) d_load_lds16(b_src[u] + (size_t)kt * b_kstep, T_B0 + stage * T_B_STAGE + u * (NW * 1024) + wave_lds);
   };
   // fragment addresses
   const int fr = lane & 31, fh = lane >> 5;
@@ -1076,22 +1080,27 @@ __global__ __launch_bounds__(256 * (1 + W8), 1) void gemm_bf16_t128_kernel(const
     if (kt + 1 < k_tiles) iteration(kt + 1, af[1], bf[1], af[0], bf[0]);
   }
 
+  const int64_t m0 = (int64_t)tm * T_BM + wm * 64 * W8 + 4 * fh, n0 = (int64_t)tn * T_BN + wn * 32 + fr;
+  if ((MODE & D_RAGGED) && n0 >= p.N) return;
   if (!(MODE & D_I8) && p.epi) {   // fused relu(C + bias)
-    const int64_t off0 = p.c_base + ((int64_t)tm * T_BM + wm * 64 * W8 + 4 * fh) * p.c_m + (int64_t)tn * T_BN + wn * 32 + fr;
-    const float bn = p.bias[(int64_t)tn * T_BN + wn * 32 + fr];
+    const int64_t off0 = p.c_base + m0 * p.c_m + n0;
+    const float bn = p.bias[n0];
 #pragma unroll
     for (int q = 0; q < NF; ++q)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) epi_store(p, C, off0 + (int64_t)(32 * q + 8 * (v / 4) + (v % 4)) * p.c_m, acc[q][v], bn);
+      for (int v = 0; v < 16; ++v) {
+        const int r = 32 * q + 8 * (v / 4) + (v % 4);
+        if (!(MODE & D_RAGGED) || m0 + r < p.M) epi_store(p, C, off0 + (int64_t)r * p.c_m, acc[q][v], bn);
+      }
     return;
   }
-  float* c_g = C + p.c_base + ((int64_t)tm * T_BM + wm * 64 * W8 + 4 * fh) * p.c_m + (int64_t)tn * T_BN + wn * 32 + fr;
+  float* c_g = C + p.c_base + m0 * p.c_m + n0;
 #pragma unroll
   for (int q = 0; q < NF; ++q)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int r = 32 * q + 8 * (v / 4) + (v % 4);
-      __builtin_nontemporal_store(acc[q][v], c_g + (int64_t)r * p.c_m);
+      if (!(MODE & D_RAGGED) || m0 + r < p.M) __builtin_nontemporal_store(acc[q][v], c_g + (int64_t)r * p.c_m);
     }
 }
 
@@ -1264,6 +1273,9 @@ bool gemm_select(const GemmShape& g, int in_dtype, GemmLaunch* l, stripe_block_i
   return true;
 }
 
+// M and N that are not multiples of 128 on the 128-wide tiles; a STRIPE_TUNE that picks other variants leaves them to the large ones.
+static bool t128_takes_ragged() { return tune_int("gemm_t128_ragged", std::getenv("STRIPE_TUNE") == nullptr) && tune_int("gemm_t128_waves", 8) != 4; }
+
 static bool gemm_select_one(const GemmShape& g, int in_dtype, GemmLaunch* l, stripe_block_info_t* info) {
   if (in_dtype == STRIPE_I8) {
     // int8 x int8 -> int32 with both operands k-contiguous (C = A * B^T); K tiles of 64 bytes, four in flight
@@ -1273,18 +1285,19 @@ static bool gemm_select_one(const GemmShape& g, int in_dtype, GemmLaunch* l, str
     const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     if (tiles_m > 32767 || tiles_n > 32767) return false;
     const bool ragged = (g.M % BM || g.N % BN);
-    if (tiles_m * tiles_n * (g.batch > 1 ? g.batch : 1) <= 128 && g.M % T_BM == 0 && g.N % T_BN == 0 && tune_int("gemm_t128", 1) != 0 &&
-        g.M / T_BM <= 32767 && g.N / T_BN <= 32767) {
+    l->t128_ragged = g.M % T_BM || g.N % T_BN;
+    if (tiles_m * tiles_n * (g.batch > 1 ? g.batch : 1) <= 128 && (!l->t128_ragged || t128_takes_ragged()) && tune_int("gemm_t128", 1) != 0 &&
+        g.M / T_BM < 32767 && g.N / T_BN < 32767) {
       l->variant = 52;
       l->t128_waves = tune_int("gemm_t128_waves", 8) == 4 ? 4 : 8;
-      l->grid = (g.M / T_BM) * (g.N / T_BN);
+      l->grid = ((g.M + T_BM - 1) / T_BM) * ((g.N + T_BN - 1) / T_BN);
       info->path = STRIPE_PATH_MFMA_GEMM;
       info->tile_m = T_BM; info->tile_n = T_BN; info->tile_k = 64;
       info->frag_m = 32; info->frag_n = 32; info->frag_k = 32;
       info->lds_bytes = t128_lds_bytes(64);
       info->workgroup_size = 64 * l->t128_waves;
       info->grid = l->grid;
-      snprintf(info->kernel, sizeof info->kernel, "gemm_i8_128x128x64_mfma32x32x32_w%d_lds_direct_bt", l->t128_waves);
+      snprintf(info->kernel, sizeof info->kernel, "gemm_i8_128x128x64_mfma32x32x32_w%d_lds_direct_bt%s", l->t128_waves, l->t128_ragged ? "_ragged" : "");
       return true;
     }
     l->variant = 40 + (ragged ? D_RAGGED : 0);
@@ -1309,18 +1322,20 @@ static bool gemm_select_one(const GemmShape& g, int in_dtype, GemmLaunch* l, str
   const bool ragged = (g.M % BM || g.N % BN);
   // few large tiles: 128 x 128 tiles put four times as many workgroups on the chip
   const int64_t big_tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * (g.batch > 1 ? g.batch : 1);
-  if (dma_shape && big_tiles <= 128 && g.M % T_BM == 0 && g.N % T_BN == 0 && tune_int("gemm_t128", 1) != 0 &&
-      g.a_m % 8 == 0 && b_row % 8 == 0 && g.a_base % 8 == 0 && g.b_base % 8 == 0 && g.M / T_BM <= 32767 && g.N / T_BN <= 32767) {
+  l->t128_ragged = g.M % T_BM || g.N % T_BN;
+  if (dma_shape && big_tiles <= 128 && (!l->t128_ragged || (t128_takes_ragged() && g.N >= 8 && (bt || g.N % 8 == 0))) && tune_int("gemm_t128", 1) != 0 &&
+      g.a_m % 8 == 0 && b_row % 8 == 0 && g.a_base % 8 == 0 && g.b_base % 8 == 0 && g.M / T_BM < 32767 && g.N / T_BN < 32767) {
     l->variant = bt ? 51 : 50;
     l->t128_waves = tune_int("gemm_t128_waves", 8) == 4 ? 4 : 8;
-    l->grid = (g.M / T_BM) * (g.N / T_BN);
+    l->grid = ((g.M + T_BM - 1) / T_BM) * ((g.N + T_BN - 1) / T_BN);
     info->path = STRIPE_PATH_MFMA_GEMM;
     info->tile_m = T_BM; info->tile_n = T_BN; info->tile_k = D_BK;
     info->frag_m = 32; info->frag_n = 32; info->frag_k = 16;
     info->lds_bytes = t128_lds_bytes(64);
     info->workgroup_size = 64 * l->t128_waves;
     info->grid = l->grid;
-    snprintf(info->kernel, sizeof info->kernel, "gemm_bf16_128x128x32_mfma32x32x16_w%d_lds_direct%s", l->t128_waves, bt ? "_bt" : "");
+    snprintf(info->kernel, sizeof info->kernel, "gemm_bf16_128x128x32_mfma32x32x16_w%d_lds_direct%s%s", l->t128_waves, bt ? "_bt" : "",
+             l->t128_ragged ? "_ragged" : "");
     return true;
   }
   if (bt || ragged) {
@@ -1430,9 +1445,9 @@ static hipError_t launch_gemm_epi(const GemmShape& g, const GemmLaunch& l, const
     case 30 + D_BT: kernel = gemm_bf16_dma_kernel<4, 1, D_BT>; break;
     case 30 + D_RAGGED: kernel = gemm_bf16_dma_kernel<4, 1, D_RAGGED>; break;
     case 30 + D_BT + D_RAGGED: kernel = gemm_bf16_dma_kernel<4, 1, D_BT + D_RAGGED>; break;
-    case 50: kernel = t128_kb128 ? gemm_bf16_t128_kernel<0, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<0, 1> : gemm_bf16_t128_kernel<0, 0>; break;
-    case 51: kernel = t128_kb128 ? gemm_bf16_t128_kernel<D_BT, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<D_BT, 1> : gemm_bf16_t128_kernel<D_BT, 0>; break;
-    case 52: kernel = t128_kb128 ? gemm_bf16_t128_kernel<D_BT + D_I8, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<D_BT + D_I8, 1> : gemm_bf16_t128_kernel<D_BT + D_I8, 0>; break;
+    case 50: kernel = l.t128_ragged ? (t128_kb128 ? gemm_bf16_t128_kernel<D_RAGGED, 1, 128> : gemm_bf16_t128_kernel<D_RAGGED, 1>) : t128_kb128 ? gemm_bf16_t128_kernel<0, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<0, 1> : gemm_bf16_t128_kernel<0, 0>; break;
+    case 51: kernel = l.t128_ragged ? (t128_kb128 ? gemm_bf16_t128_kernel<D_BT + D_RAGGED, 1, 128> : gemm_bf16_t128_kernel<D_BT + D_RAGGED, 1>) : t128_kb128 ? gemm_bf16_t128_kernel<D_BT, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<D_BT, 1> : gemm_bf16_t128_kernel<D_BT, 0>; break;
+    case 52: kernel = l.t128_ragged ? (t128_kb128 ? gemm_bf16_t128_kernel<D_BT + D_I8 + D_RAGGED, 1, 128> : gemm_bf16_t128_kernel<D_BT + D_I8 + D_RAGGED, 1>) : t128_kb128 ? gemm_bf16_t128_kernel<D_BT + D_I8, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<D_BT + D_I8, 1> : gemm_bf16_t128_kernel<D_BT + D_I8, 0>; break;
     case 40: kernel = gemm_bf16_dma_kernel<4, 1, D_BT + D_I8>; break;
     case 40 + D_RAGGED: kernel = gemm_bf16_dma_kernel<4, 1, D_BT + D_RAGGED + D_I8>; break;
     case 10: kernel = gemm_bf16_w8_kernel<0>; break;
@@ -1456,8 +1471,8 @@ static hipError_t launch_gemm_epi(const GemmShape& g, const GemmLaunch& l, const
                  ? 1
                  : 0;
   if (l.variant >= 50) {
-    pk.tiles_m = (int)(g.M / T_BM);
-    pk.tiles_n = (int)(g.N / T_BN);
+    pk.tiles_m = (int)((g.M + T_BM - 1) / T_BM);
+    pk.tiles_n = (int)((g.N + T_BN - 1) / T_BN);
   }
   // more than 64 KB of dynamic LDS has to be enabled once per device
   int dev = -1;

@@ -548,3 +548,38 @@ def test_family_blocks_on_the_contraction_keep_their_pointer_contract(kind):
         want = torch.relu(torch.nn.functional.conv2d(x.permute(0, 3, 1, 2), f.permute(2, 3, 0, 1), padding=2) + b[:, None, None]).permute(0, 2, 3, 1)
         err = (out.double().cpu() - want).abs().max()
         assert err <= 6400 * 2.0 ** -24 * float((x.abs().max() * f.abs().max() * 6400).clamp(min=1)), float(err)     # 6400 fp32 additions
+
+
+@pytest.mark.parametrize("M,N,K,dt,layout", [(130, 136, 128, "bf16", "nn"), (127, 264, 384, "bf16", "nn"), (129, 333, 256, "bf16", "nt"), (33, 9, 128, "bf16", "nt"),
+                                             (300, 257, 1024, "i8", "nt"), (2, 8, 256, "i8", "nt"), (1000, 520, 256, "i8", "nt")])
+@pytest.mark.parametrize("kb", [64, 128])
+def test_ragged_products_on_the_128_wide_tiles(M, N, K, dt, layout, kb, monkeypatch):
+    """Rows and columns beside the tile: nothing of them is read past the operand or stored, position-sensitive operands exactly."""
+    monkeypatch.setenv("STRIPE_TUNE", f"gemm_t128_ragged=1,gemm_t128_kb={kb},gemm_rows=0,gemm_splitk=0")
+    blk = matmul(M, N, K, dt, layout)
+    a = ((torch.arange(M)[:, None] * 7 + torch.arange(K)[None, :] * 3) % 251 - 125).to(torch.int8 if dt == "i8" else torch.bfloat16)
+    sel = (torch.arange(N) + 37) % K
+    b = torch.zeros((K, N), dtype=a.dtype)
+    b[sel, torch.arange(N)] = 1
+    gpu, sb = run_gpu(blk, [a, b.t().contiguous() if layout == "nt" else b], return_block=True)
+    assert "_128x128x" in sb.info["kernel"] and sb.info["kernel"].endswith("_ragged"), sb.info["kernel"]
+    assert np.array_equal(gpu.reshape(M, N), a.float()[:, sel].numpy())
+    ins = [W.seeded_tensor(blk.refs[0].sizes, dt, 0), W.seeded_tensor(blk.refs[1].sizes, dt, 1)]
+    parity(blk, ins, what=f"ragged {M}x{N}x{K} {dt}")
+
+
+def test_ragged_fused_product_on_the_128_wide_tiles(monkeypatch):
+    monkeypatch.setenv("STRIPE_TUNE", "gemm_t128_ragged=1,gemm_rows=0,gemm_splitk=0")
+    for M, N, out_dt in ((130, 333, "bf16"), (70, 129, "f32")):
+        prog = W.linear_bias_relu_program(M, N, 256, out_dt, b_transposed=True)
+        sb = B.StripeBlock(prog)
+        assert "_128x128x" in sb.info["kernel"] and "_ragged+bias_relu" in sb.info["kernel"], sb.info["kernel"]
+        held = [W.seeded_tensor(r.sizes, r.dtype, i).cuda() for i, r in enumerate(r for r in prog.refs if r.dir == "in")]
+        out = torch.full((M, N), -7.0, dtype=torch.bfloat16 if out_dt == "bf16" else torch.float32, device="cuda")
+        sb.run(held, out)
+        sb.close()
+        x, w, b = (t.double().cpu() for t in held)
+        want = torch.relu(x @ w.t() + b)
+        # 256 products of order up to |x||w| in fp32, then half a step of the output type
+        tol = 256 * 2.0 ** -24 * (x.abs() @ w.abs().t() + b.abs()) + (2.0 ** -8 * want if out_dt == "bf16" else 0)
+        assert bool(((out.double().cpu() - want).abs() <= tol).all())
