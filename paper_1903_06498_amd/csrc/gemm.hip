@@ -1274,7 +1274,8 @@ bool gemm_select(const GemmShape& g, int in_dtype, GemmLaunch* l, stripe_block_i
 }
 
 // M and N that are not multiples of 128 on the 128-wide tiles; a STRIPE_TUNE that picks other variants leaves them to the large ones.
-static bool t128_takes_ragged() { return tune_int("gemm_t128_ragged", std::getenv("STRIPE_TUNE") == nullptr) && tune_int("gemm_t128_waves", 8) != 4; }
+// Not at the few rows (M <= 32) that the few-rows kernel is priced against: three quarters of the tile would be padding.
+static bool t128_takes_ragged(const GemmShape& g) { return g.M > 32 && tune_int("gemm_t128_ragged", std::getenv("STRIPE_TUNE") == nullptr) && tune_int("gemm_t128_waves", 8) != 4; }
 
 static bool gemm_select_one(const GemmShape& g, int in_dtype, GemmLaunch* l, stripe_block_info_t* info) {
   if (in_dtype == STRIPE_I8) {
@@ -1286,7 +1287,7 @@ static bool gemm_select_one(const GemmShape& g, int in_dtype, GemmLaunch* l, str
     if (tiles_m > 32767 || tiles_n > 32767) return false;
     const bool ragged = (g.M % BM || g.N % BN);
     l->t128_ragged = g.M % T_BM || g.N % T_BN;
-    if (tiles_m * tiles_n * (g.batch > 1 ? g.batch : 1) <= 128 && (!l->t128_ragged || t128_takes_ragged()) && tune_int("gemm_t128", 1) != 0 &&
+    if (tiles_m * tiles_n * (g.batch > 1 ? g.batch : 1) <= 128 && (!l->t128_ragged || t128_takes_ragged(g)) && tune_int("gemm_t128", 1) != 0 &&
         g.M / T_BM < 32767 && g.N / T_BN < 32767) {
       l->variant = 52;
       l->t128_waves = tune_int("gemm_t128_waves", 8) == 4 ? 4 : 8;
@@ -1323,7 +1324,7 @@ static bool gemm_select_one(const GemmShape& g, int in_dtype, GemmLaunch* l, str
   // few large tiles: 128 x 128 tiles put four times as many workgroups on the chip
   const int64_t big_tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * (g.batch > 1 ? g.batch : 1);
   l->t128_ragged = g.M % T_BM || g.N % T_BN;
-  if (dma_shape && big_tiles <= 128 && (!l->t128_ragged || (t128_takes_ragged() && g.N >= 8 && (bt || g.N % 8 == 0))) && tune_int("gemm_t128", 1) != 0 &&
+  if (dma_shape && big_tiles <= 128 && (!l->t128_ragged || (t128_takes_ragged(g) && g.N >= 8 && (bt || g.N % 8 == 0))) && tune_int("gemm_t128", 1) != 0 &&
       g.a_m % 8 == 0 && b_row % 8 == 0 && g.a_base % 8 == 0 && g.b_base % 8 == 0 && g.M / T_BM < 32767 && g.N / T_BN < 32767) {
     l->variant = bt ? 51 : 50;
     l->t128_waves = tune_int("gemm_t128_waves", 8) == 4 ? 4 : 8;

@@ -551,7 +551,7 @@ def test_family_blocks_on_the_contraction_keep_their_pointer_contract(kind):
 
 
 @pytest.mark.parametrize("M,N,K,dt,layout", [(130, 136, 128, "bf16", "nn"), (127, 264, 384, "bf16", "nn"), (129, 333, 256, "bf16", "nt"), (33, 9, 128, "bf16", "nt"),
-                                             (300, 257, 1024, "i8", "nt"), (2, 8, 256, "i8", "nt"), (1000, 520, 256, "i8", "nt")])
+                                             (300, 257, 1024, "i8", "nt"), (33, 8, 256, "i8", "nt"), (1000, 520, 256, "i8", "nt")])
 @pytest.mark.parametrize("kb", [64, 128])
 def test_ragged_products_on_the_128_wide_tiles(M, N, K, dt, layout, kb, monkeypatch):
     """Rows and columns beside the tile: nothing of them is read past the operand or stored, position-sensitive operands exactly."""
