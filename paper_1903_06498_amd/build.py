@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libstripe_hip.so")
-SOURCES = ["api.cpp", "plan.cpp", "tiling.cpp", "generic.hip", "generic_tiled.hip", "contract.hip:4", "contract.hip:2", "contract.hip:1", "pool.hip", "gemm.hip", "gemm_rows.hip", "conv.hip", "conv_i8.hip", "conv_igemm.hip"]
+SOURCES = ["api.cpp", "plan.cpp", "tiling.cpp", "generic.hip", "generic_tiled.hip", "contract.hip:4", "contract.hip:2", "contract.hip:1", "pool.hip", "gemm.hip", "gemm_rows.hip", "conv.hip", "conv_i8.hip", "conv_igemm.hip", "conv_few.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
          # the LDS-direct load helpers name M0 in their clobber lists on purpose (see their comments); the compiler

@@ -31,6 +31,7 @@ struct stripe_block {
   ConvLaunch conv;
   PoolLaunch pool;
   RowsLaunch rows;           // products with few rows (the GEMM or the generic path's pointer contract)
+  FewLaunch few;             // blocks of the generic path that are convolutions with at most four input channels
   ContractLaunch contract;   // blocks of the generic path that the general matrix-core contraction takes
   int n_inputs = 0;
   // statement lists (empty for a single block): stages in order, and per root refinement either the caller's
@@ -55,7 +56,7 @@ struct stripe_block {
   void* owned_ws = nullptr;
   int owned_ws_dev = -1;
   // 1, 2: the two statements run as one convolution kernel with a bias+relu epilogue (fp32 / bf16 output);
-  // 3, 4: the same with the dense-contraction kernel; 5, 6: with the general matrix-core contraction
+  // 3, 4: the same with the dense-contraction kernel; 5, 6: with the general matrix-core contraction; 7, 8: with the few-channels convolution
   int fused = 0;
   bool aligned_out = false;  // the convolution kernels would have fused the statements: bias and output 16-byte aligned
   int64_t fuse_bias_off = 0, fuse_o_m = 0, fuse_o_base = 0;
@@ -330,8 +331,14 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
     const Plan& c = s0.blk->plan;
     ContractLaunch ct = s0.blk->contract;
     stripe_block_info_t ct_info = c.info;
-    if (!ct.use && path == STRIPE_PATH_AUTO && c.info.path == STRIPE_PATH_GENERIC && !c.noop && !s0.blk->rows.use && c.in_dtype == STRIPE_BF16)
-      contract_select(c.flat, literal_sums(c), true, &ct, &ct_info);
+    FewLaunch few = s0.blk->few;
+    if (path == STRIPE_PATH_AUTO && c.info.path == STRIPE_PATH_GENERIC && !c.noop && !s0.blk->rows.use && c.in_dtype == STRIPE_BF16) {
+      if (!ct.use) contract_select(c.flat, literal_sums(c), true, &ct, &ct_info);      // (also where few.use: its checks below)
+      // the few-channels convolution where the contraction would fuse (the checks of the second statement are the same); below 2048
+      // output pixels both take less than a call costs its caller (3.5 and 5 us)
+      if (few.use) ct_info = c.info;
+      else if (ct.use && c.is_conv && c.conv.N * c.conv.Ho * c.conv.Wo >= 2048 && (root->refs[R - 1].dtype == STRIPE_BF16 || tune_int("conv_few", 1) == 2)) conv_few_select(c.conv, c.in_dtype, &few, &ct_info);
+    }
     const FlatBlock& e = s1.blk->plan.flat;
     bool ok = (c.info.path == STRIPE_PATH_GENERIC || s0.blk->contract.use) && ct.use && c.in_dtype == STRIPE_BF16 && ct.p.epilogue == 0 && !ct.p.n_ob_used && ct.batch == 1 &&
               ct.p.n.n == 1 && ct.p.n_out[0] == 1 && root->refs[s0.dst].dir == STRIPE_TEMP && s1.n_in == 2 && s1.src[0] == s0.dst && !e.empty &&
@@ -355,8 +362,10 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
         }
       }
       if (ok) {
-        prog->fused = e.out_bf16 ? 6 : 5;
+        prog->fused = (few.use ? 7 : 5) + (e.out_bf16 ? 1 : 0);
         prog->contract = ct;
+        prog->few = few;
+        prog->plan.conv = c.conv;
         s0.blk->plan.info = ct_info;
         prog->plan.in_dtype = c.in_dtype;
         prog->plan.info.path = c.info.path;
@@ -384,7 +393,7 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
       for (int d = 0; d < root->refs[r].ndim; ++d) n *= root->refs[r].sizes[d];
       info.algorithmic_bytes += n * (root->refs[r].dtype == STRIPE_I8 ? 1 : root->refs[r].dtype == STRIPE_BF16 ? 2 : 4);
     }
-  if (prog->fused) names = std::string(prog->stages[0].blk->plan.info.kernel) + (prog->fused == 2 || prog->fused == 6 ? "+bias_relu_bf16" : "+bias_relu");
+  if (prog->fused) names = std::string(prog->stages[0].blk->plan.info.kernel) + (prog->fused == 2 || prog->fused == 6 || prog->fused == 8 ? "+bias_relu_bf16" : "+bias_relu");
   std::snprintf(info.kernel, sizeof info.kernel, "%s", names.c_str());
   // workspace layout: temporaries that were not scalarised away, then what each stage's own launches need
   prog->temp_off.assign(R, 0);
@@ -487,8 +496,9 @@ stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void*
           (((uintptr_t)inputs[prog->input_slot[s0.src[0]]] % 16) || ((uintptr_t)inputs[prog->input_slot[s0.src[1]]] % 16) ||
            (prog->aligned_out && (((uintptr_t)bias % 16) || ((uintptr_t)output % 16)))))
         return fail(STRIPE_ERR_MISALIGNED, "the fused matrix-core kernel needs 16-byte aligned operands (convolution: also bias and output)");
-      e = launch_contract(prog->contract, prog->plan.in_dtype, inputs[prog->input_slot[s0.src[0]]], inputs[prog->input_slot[s0.src[1]]], output, bias,
-                          fused == 6, (hipStream_t)hip_stream);
+      const void *in = inputs[prog->input_slot[s0.src[0]]], *flt = inputs[prog->input_slot[s0.src[1]]];
+      e = fused >= 7 ? launch_conv_few(prog->plan.conv, prog->few, prog->plan.in_dtype, in, flt, output, bias, fused == 8, (hipStream_t)hip_stream)
+                     : launch_contract(prog->contract, prog->plan.in_dtype, in, flt, output, bias, fused == 6, (hipStream_t)hip_stream);
       if (e != hipSuccess) return fail(STRIPE_ERR_HIP, std::string("kernel launch failed: ") + hipGetErrorString(e));
       return STRIPE_OK;
     }
@@ -548,6 +558,7 @@ stripe_status_t run_single(stripe_block* blk, const void* const* inputs, void* o
     case STRIPE_PATH_POOL: e = launch_pool(p.pool, blk->pool, in0, in1, output, s); break;
     default:
       if (blk->rows.use) e = launch_gemm_rows(p.gemm, p.in_dtype, in0, in1, output, p.gemm.c_m, p.gemm.c_base, nullptr, false, s);
+      else if (blk->few.use) e = launch_conv_few(p.conv, blk->few, p.in_dtype, in0, in1, output, nullptr, false, s);
       else if (blk->contract.use) e = launch_contract(blk->contract, p.in_dtype, in0, in1, output, nullptr, false, s);
       else e = launch_generic(p, in0, in1, output, s);
       break;
@@ -619,6 +630,9 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
       // without a forced path, sum-of-products blocks of the generic path run on the matrix cores where that is faster
       if (!forced && !(p.is_gemm && gemm_rows_select(p.gemm, p.in_dtype, __builtin_huge_val(), &blk->rows, &p.info))) {
         contract_select(p.flat, literal_sums(p), false, &blk->contract, &p.info);
+        // Few input channels: faster than the general contraction (7x7 stride 2, 3 -> 64, bf16, 8 x 224 x 224: 34 us there), with fp32
+        // chains as long as its own: not where the literal kernel holds 64 sums per output and the contraction totals in double precision.
+        if (blk->contract.use && p.is_conv && (!blk->contract.precise || tune_int("conv_few", 1) == 2) && conv_few_select(p.conv, p.in_dtype, &blk->few, &p.info)) blk->contract.use = false;
       }
     } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM &&
                gemm_rows_select(p.gemm, p.in_dtype, gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm), &blk->rows, &p.info)) {
@@ -629,7 +643,9 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
     // tiles, 7 here; 7 x 7, 256 -> 9 channels int8 over 3 x 42 x 42: 77 and 15).  Those families' pointer contract stays.
     // (not under STRIPE_TUNE, which picks variants of those families, unless it says contract_over=1)
     const bool igemm = p.info.path == STRIPE_PATH_MFMA_CONV && blk->conv.variant >= kConvIgemmVariant && blk->conv.variant < kConvGemmVariant;
-    if (!forced && picked && tune_int("contract_over", std::getenv("STRIPE_TUNE") == nullptr) && !blk->rows.use && (igemm || (p.info.path == STRIPE_PATH_MFMA_GEMM && (blk->gemm.split_k <= 1 || p.gemm.M <= 32)))) {
+    // (nor where full tiles fill half the chip: the estimates would be made for nothing, 60 us of a 4096^3 product's creation)
+    const bool full = p.info.path == STRIPE_PATH_MFMA_GEMM && p.info.grid >= 128 && p.gemm.M >= 256 && p.gemm.N >= 256;
+    if (!forced && picked && tune_int("contract_over", std::getenv("STRIPE_TUNE") == nullptr) && !blk->rows.use && !full && (igemm || (p.info.path == STRIPE_PATH_MFMA_GEMM && (blk->gemm.split_k <= 1 || p.gemm.M <= 32)))) {
       stripe_block_info_t other = p.info;
       const double us = igemm ? conv_igemm_us(p.conv, blk->conv)
                               : blk->gemm.split_k > 1 ? gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm) : gemm_us(p.gemm, p.in_dtype, blk->gemm);

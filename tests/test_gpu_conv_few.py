@@ -1,0 +1,89 @@
+"""Convolutions with at most four input channels on their own kernel, against the oracle: ragged pixel groups and channel tiles, strides,
+filters whose taps do not fill a chunk, rows of several workgroups, windows of larger tensors, non-finite values, the fused form."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1903_06498_amd import binding as B
+from paper_1903_06498_amd import workloads as W
+from tests.util import parity, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32", "i8"])
+@pytest.mark.parametrize("shape", [(2, 19, 18, 3, 64, 7, 7, 2, 3), (1, 9, 33, 3, 20, 3, 3, 1, 1), (3, 12, 11, 2, 70, 5, 5, 2, 2), (1, 8, 17, 4, 16, 1, 4, 1, 0),
+                                   (1, 21, 40, 2, 33, 5, 3, 3, 1), (2, 7, 7, 3, 129, 7, 7, 1, 3), (1, 3, 3, 3, 5, 2, 2, 1, 0)])
+@pytest.mark.parametrize("ty", [0, 1, 3])
+def test_few_channels(shape, dt, ty, monkeypatch):
+    monkeypatch.setenv("STRIPE_TUNE", f"contract_min=1,conv_few=1,conv_few_ty={ty}")
+    N, H, Wd, Ci, Co, R, S, s, p = shape
+    blk = W.conv2d_block(N, H, Wd, Ci, Co, R, S, s, p, dt, "i32" if dt == "i8" else "f32")
+    sb = B.StripeBlock(blk)
+    name = sb.info["kernel"]
+    sb.close()
+    if name.startswith("contract_"):      # fp32 and bf16 blocks whose literal kernel holds 64 sums per output
+        monkeypatch.setenv("STRIPE_TUNE", f"contract_min=1,conv_few=2,conv_few_ty={ty}")
+    info, _ = parity(blk, [W.seeded_tensor((N, H, Wd, Ci), dt, 0), W.seeded_tensor((R, S, Co, Ci), dt, 1)], what=f"few {shape} {dt}", threads=8)
+    assert info["kernel"].startswith(f"conv_few_{dt}_c{Ci}"), info["kernel"]
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_non_finite_values(dt, monkeypatch):
+    """Infinities and NaN at the border of the image and of the filter: what a constraint removes contributes nothing."""
+    blk = W.conv2d_block(1, 13, 20, 3, 20, 5, 5, 2, 2, dt, "f32")
+    ins = [W.seeded_tensor(r.sizes, dt, i) for i, r in enumerate(blk.refs[:2])]
+    ins[0][0, 0, 0, 1] = math.inf
+    ins[0][0, 6, 19, 2] = -math.inf
+    ins[1][0, 0, 3, 0] = math.inf
+    ins[1][4, 4, 18, 2] = math.nan
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1,conv_few=2")
+    got, sb = run_gpu(blk, ins, return_block=True)
+    assert sb.info["kernel"].startswith("conv_few_"), sb.info["kernel"]
+    want = run_gpu(blk, ins, "generic")
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
+    assert np.array_equal(np.isneginf(got), np.isneginf(want)) and np.isinf(want).any() and np.isnan(want).any()
+    fin = np.isfinite(want)
+    assert fin.any() and np.allclose(got[fin], want[fin], rtol=1e-5, atol=75 * 2.0 ** -24 * 75)      # 75 products of order 1 in fp32
+
+
+@pytest.mark.parametrize("out_dt", ["bf16", "f32"])
+@pytest.mark.parametrize("Co", [64, 18])
+def test_fused_bias_relu(out_dt, Co, monkeypatch):
+    """The following statement in the store, inputs and bias behind unaligned addresses, an output with and without whole vectors."""
+    monkeypatch.setenv("STRIPE_TUNE", "conv_few=2")
+    prog = W.conv_bias_relu_program(2, 30, 26, 3, Co, 7, 7, 2, 3, "bf16", out_dt)
+    sb = B.StripeBlock(prog)
+    assert sb.info["kernel"].startswith("conv_few_") and "+bias_relu" in sb.info["kernel"] and sb.info["workspace_bytes"] == 0, sb.info
+    host = [W.seeded_tensor(r.sizes, r.dtype, i) for i, r in enumerate(r for r in prog.refs if r.dir == "in")]
+    held = []
+    for t in host:
+        big = torch.zeros(t.numel() + 1, dtype=t.dtype, device="cuda")
+        big[1:] = t.reshape(-1).cuda()
+        held.append(big[1:])
+    out = torch.full((2, 15, 13, Co), -7.0, dtype=torch.bfloat16 if out_dt == "bf16" else torch.float32, device="cuda")
+    sb.run(held, out)
+    sb.close()
+    x, f, b = (t.double() for t in host)
+    pre = torch.nn.functional.conv2d(x.permute(0, 3, 1, 2), f.permute(2, 3, 0, 1), stride=2, padding=3) + b[:, None, None]
+    want = torch.relu(pre).permute(0, 2, 3, 1)
+    mag = torch.nn.functional.conv2d(x.abs().permute(0, 3, 1, 2), f.abs().permute(2, 3, 0, 1), stride=2, padding=3).permute(0, 2, 3, 1) + b.abs()
+    tol = 148 * 2.0 ** -24 * mag + (2.0 ** -8 * want if out_dt == "bf16" else 0)      # 147 products and the bias in fp32, half a step of bf16
+    assert bool(((out.double().cpu() - want).abs() <= tol).all())
+
+
+def test_window_of_a_larger_image(monkeypatch):
+    """An input whose pixels are four channels apart and whose rows are longer: the last pixel's load ends with the operand."""
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1,conv_few=2")
+    for dt in ("bf16", "i8", "f32"):
+        blk = W.conv2d_block(2, 11, 12, 3, 24, 3, 3, 1, 1, dt, "i32" if dt == "i8" else "f32")
+        dense = [W.seeded_tensor((2, 11, 12, 3), dt, 0), W.seeded_tensor((3, 3, 24, 3), dt, 1)]
+        want = run_gpu(blk, dense, "generic")
+        got, sb = run_gpu(blk, dense, return_block=True)
+        assert sb.info["kernel"].startswith("conv_few_"), sb.info["kernel"]
+        if dt == "i8":
+            assert np.array_equal(got, want)
+        else:
+            assert np.allclose(got, want, rtol=1e-5, atol=27 * 2.0 ** -24 * 27)
