@@ -710,20 +710,25 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
 
   // bf16 / fp32: partial sums over FLUSH K tiles start from zero and are added to the total, short chains of roundings
   // instead of one long one (not on the largest tile, whose registers hold one set of sums at two wavefronts per SIMD)
+  // fp32 on the 64 x 64 tile: a sum for the even steps and one for the odd ones, 16 products each (one sum: 1.2 times the error of
+  // 32 x 32 tiles at 29 x 29, 64 -> 64, transposed 2x2, 0.8 times now, for 2 % of the time).  Where the fetch by elements holds the registers, one:
+  // 6 x 49 x 49, 11 -> 72, 5x5 took 36 us instead of 27.
+  constexpr int SUMS = std::is_same<T, float>::value && BM * BN <= 4096 && MA != 3 && MB != 3 ? 2 : 1;
   constexpr uint32_t FLUSH = BM * BN > 8192 ? 0xffffffffu : std::is_same<T, float>::value ? 1 : std::is_same<T, uint16_t>::value ? 4 : 0xffffffffu;
-  Acc sum[FM][FN];
+  Acc sum[SUMS][FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) sum[i][j] = (Acc){0, 0, 0, 0};
+    for (int j = 0; j < FN; ++j) sum[0][i][j] = sum[SUMS - 1][i][j] = (Acc){0, 0, 0, 0};
   auto flush = [&]() {
     if constexpr (!PRECISE) {
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-          acc[i][j] += sum[i][j];
-          sum[i][j] = (Acc){0, 0, 0, 0};
+          if constexpr (SUMS == 1) acc[i][j] += sum[0][i][j];
+          else acc[i][j] += sum[0][i][j] + sum[1][i][j];
+          sum[0][i][j] = sum[SUMS - 1][i][j] = (Acc){0, 0, 0, 0};
         }
     }
   };
@@ -770,7 +775,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
 #pragma unroll
         for (int j = 0; j < FN; ++j) {   // rows of the result: n
           if constexpr (PRECISE) acc[i][j] += __builtin_convertvector(Ct<T>::step(fb[j], fa[i]), f64x4);
-          else sum[i][j] = Ct<T>::mma(fb[j], fa[i], sum[i][j]);
+          else sum[s % SUMS][i][j] = Ct<T>::mma(fb[j], fa[i], sum[s % SUMS][i][j]);
         }
     }
     if ((t + 1) % FLUSH == 0) flush();
@@ -945,7 +950,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void contract_waves_kernel(const C
     if constexpr (!PLAIN && sizeof(T) > 1) sum_again<T, NT, BM, BN, BKB_AGAIN, MA, MB>(args, rows, o_base, lds);
     return;
   }
-  // fragment f is stored by wavefront f % NW: the others' sums reach it through LDS and are added in the wavefronts' order
+  // fragment f is stored by wavefront f % NW: the others' sums reach it through LDS and are added in pairs
+  // (one after the other: 1.2 times the error at 5 x 88 x 1520 bf16)
   Total* part = (Total*)lds + lane;
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
@@ -956,8 +962,15 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void contract_waves_kernel(const C
 #pragma unroll
   for (int f = 0; f < NF; ++f)
     if (wave == f % NW) {
+      Total sums[NW];
 #pragma unroll
-      for (int w = 0; w < NW - 1; ++w) acc[f / FN][f % FN] += part[(w * NF + f) * 64];
+      for (int w = 0; w < NW - 1; ++w) sums[w] = part[(w * NF + f) * 64];
+      sums[NW - 1] = acc[f / FN][f % FN];
+#pragma unroll
+      for (int h = NW / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int w = 0; w < h; ++w) sums[w] += sums[w + h];
+      acc[f / FN][f % FN] = sums[0];
     }
   store_fragments<T, FM, FN, NW>(args.p, args.o, args.bias, o_base, rows, 0, 0, wave, lane, acc);
 }
