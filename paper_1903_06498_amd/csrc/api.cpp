@@ -643,7 +643,7 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
     // tiles, 7 here; 7 x 7, 256 -> 9 channels int8 over 3 x 42 x 42: 77 and 15).  Those families' pointer contract stays.
     // (not under STRIPE_TUNE, which picks variants of those families, unless it says contract_over=1)
     const bool igemm = p.info.path == STRIPE_PATH_MFMA_CONV && blk->conv.variant >= kConvIgemmVariant && blk->conv.variant < kConvGemmVariant;
-    // (nor where full tiles fill half the chip: the estimates would be made for nothing, 60 us of a 4096^3 product's creation)
+    // (nor where full tiles fill half the chip: the contraction has no idle CUs to win back there, so its estimates are not made)
     const bool full = p.info.path == STRIPE_PATH_MFMA_GEMM && p.info.grid >= 128 && p.gemm.M >= 256 && p.gemm.N >= 256;
     if (!forced && picked && tune_int("contract_over", std::getenv("STRIPE_TUNE") == nullptr) && !blk->rows.use && !full && (igemm || (p.info.path == STRIPE_PATH_MFMA_GEMM && (blk->gemm.split_k <= 1 || p.gemm.M <= 32)))) {
       stripe_block_info_t other = p.info;
