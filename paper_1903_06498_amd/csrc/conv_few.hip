@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kLanes, 2) void conv_few_kernel(const FewParams p, 
   for (int r = wave; r < p.rows; r += kWaves) {
     const int y = y0 * p.sy - p.py + r;
     const bool row_in = y >= 0 && y < p.H;
-    const int base = p.i_base + n * p.i_n + y * p.i_y;
+    const int base = row_in ? p.i_base + n * p.i_n + y * p.i_y : 0;
     for (int c0 = 0; c0 < p.cols; c0 += 64 * BATCH) {
       Pixel<T> v[BATCH];
 #pragma unroll
@@ -297,21 +297,38 @@ __global__ __launch_bounds__(kLanes, 2) void conv_few_kernel(const FewParams p, 
 
 int chunks_of(const Conv2dShape& c, int esize) { return (int)((c.S * 4 * esize + 15) / 16); }
 
+// What lies in LDS, in 64 bits: strides of up to 2^20 make rows that no 32-bit product of them holds.
+struct FewLds {
+  int64_t rows, cols, groups, row_bytes, filter_bytes;
+  int64_t bytes() const { return filter_bytes + rows * row_bytes; }
+};
+FewLds few_lds(const Conv2dShape& c, int esize, const FewLaunch& l) {
+  FewLds f;
+  f.rows = (l.ty - 1) * c.stride_y + c.R;
+  f.groups = (c.Wo + 15) / 16;
+  f.cols = (f.groups * 16 - 1) * c.stride_x + chunks_of(c, esize) * (4 / esize);      // the taps of the last pixel's last chunk included
+  f.row_bytes = (f.cols * 4 * esize + 15) / 16 * 16;
+  f.filter_bytes = (int64_t)l.steps * 4 * 16 * l.fn * 16;
+  return f;
+}
+
+// (for shapes that conv_few_select took: everything fits)
 FewParams make_params(const Conv2dShape& c, int esize, const FewLaunch& l) {
   FewParams p = {};
+  const FewLds lds = few_lds(c, esize, l);
   p.Ho = (int)c.Ho; p.Wo = (int)c.Wo; p.H = (int)c.H; p.W = (int)c.W; p.Co = (int)c.Co; p.Ci = (int)c.Ci;
   p.R = (int)c.R; p.S = (int)c.S; p.sy = (int)c.stride_y; p.sx = (int)c.stride_x; p.py = (int)c.pad_y; p.px = (int)c.pad_x;
   p.ty = l.ty;
   p.strips = (int)((c.Ho + l.ty - 1) / l.ty);
   p.chunks_per_row = chunks_of(c, esize);
-  p.rows = (l.ty - 1) * p.sy + p.R;
-  p.groups = (int)((c.Wo + 15) / 16);
-  p.cols = (p.groups * 16 - 1) * p.sx + p.chunks_per_row * (4 / esize);      // the taps of the last pixel's last chunk included
+  p.rows = (int)lds.rows;
+  p.groups = (int)lds.groups;
+  p.cols = (int)lds.cols;
   auto magic = [](int d) { return d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
   p.chunks_mul = magic(p.chunks_per_row);
   p.groups_mul = magic(p.groups);
-  p.row_bytes = (p.cols * 4 * esize + 15) / 16 * 16;
-  p.filter_bytes = l.steps * 4 * 16 * l.fn * 16;
+  p.row_bytes = (int)lds.row_bytes;
+  p.filter_bytes = (int)lds.filter_bytes;
   p.co_tiles = (int)((c.Co + 16 * l.fn - 1) / (16 * l.fn));
   p.co_split = l.co_split;
   p.i_n = (int)(c.i_n * esize); p.i_y = (int)(c.i_y * esize); p.i_x = (int)(c.i_x * esize);
@@ -322,8 +339,6 @@ FewParams make_params(const Conv2dShape& c, int esize, const FewLaunch& l) {
   p.o_n = c.o_n; p.o_y = c.o_y; p.o_x = c.o_x; p.o_base = c.o_base;
   return p;
 }
-
-int lds_bytes(const FewParams& p) { return p.filter_bytes + p.rows * p.row_bytes; }
 
 }  // namespace
 
@@ -360,22 +375,22 @@ bool conv_few_select(const Conv2dShape& c, int in_dtype, FewLaunch* l, stripe_bl
   l->ty = 1;
   while (l->ty < 8 && l->ty < c.Ho && c.N * ((c.Ho + l->ty - 1) / l->ty) * std::min(co_tiles, 2) > 256) {
     ++l->ty;
-    if (lds_bytes(make_params(c, esize, *l)) > 80 * 1024) {
+    if (few_lds(c, esize, *l).bytes() > 80 * 1024) {
       --l->ty;
       break;
     }
   }
   const int forced = tune_int("conv_few_ty", 0);
   if (forced > 0 && forced <= 64) l->ty = forced;
-  const FewParams p = make_params(c, esize, *l);
-  if (lds_bytes(p) > kMaxLds || l->ty * p.groups > 65535) return false;
-  const int64_t strips = c.N * p.strips;
+  const FewLds lds = few_lds(c, esize, *l);
+  if (lds.bytes() > kMaxLds || l->ty * lds.groups > 65535) return false;
+  const int64_t strips = c.N * ((c.Ho + l->ty - 1) / l->ty);
   while (l->co_split < co_tiles && strips * (l->co_split + 1) <= 256) ++l->co_split;
   if (strips > 0x7fffffff) return false;
-  l->lds = lds_bytes(p);
+  l->lds = (int)lds.bytes();
   l->grid = strips;
   l->use = true;
-  info->tile_m = l->ty * 16 * p.groups; info->tile_n = 16 * l->fn; info->tile_k = 64 / esize;
+  info->tile_m = (int)(l->ty * 16 * lds.groups); info->tile_n = 16 * l->fn; info->tile_k = 64 / esize;
   info->frag_m = info->frag_n = 16;
   info->frag_k = esize == 4 ? 4 : 64 / esize;
   info->lds_bytes = l->lds;

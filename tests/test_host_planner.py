@@ -304,3 +304,20 @@ def test_blocks_stay_on_the_literal_kernel_where_it_is_faster(blk, literal, monk
         b = B.StripeBlock(blk)
         assert b.info["kernel"].startswith("generic_") == want, (tune, b.info["kernel"])
         b.close()
+
+
+def strided_conv(R, S, stride_x, Ho, Wo, Ci, Co, dt):
+    """A convolution whose image is as large as its taps reach: stride 1 along y, stride_x along x."""
+    H, Wd = Ho + R - 1, stride_x * (Wo - 1) + S
+    bufs = [W.Buffer("I", "in", dt, (1, H, Wd, Ci)), W.Buffer("F", "in", dt, (R, S, Co, Ci)), W.Buffer("O", "out", "i32" if dt == "i8" else "f32", (1, Ho, Wo, Co))]
+    return W.flat_block(bufs, dict(n=1, y=Ho, x=Wo, i=R, j=S, c=Ci, k=Co),
+                        [(["n", "y + i", f"{stride_x}*x + j", "c"], "assign"), (["i", "j", "k", "c"], "assign"), (["n", "y", "x", "k"], "add")])
+
+
+@pytest.mark.parametrize("R,stride_x,dt", [(26, 600000, "f32"), (26, 688300, "f32"), (28, 800000, "bf16")])
+def test_image_rows_that_no_lds_holds(R, stride_x, dt):
+    """Few input channels, rows of image of gigabytes between the taps: sizes that 32-bit products wrap into a plausible range.  The
+    general contraction's, which holds no image rows; what is planned fits the 160 KB of LDS."""
+    b = B.StripeBlock(strided_conv(R, 2, stride_x, 40, 2, 2, 4096, dt))
+    assert not b.info["kernel"].startswith("conv_few_") and 0 <= b.info["lds_bytes"] <= 160 * 1024, (b.info["kernel"], b.info["lds_bytes"])
+    b.close()
