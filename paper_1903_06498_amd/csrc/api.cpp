@@ -32,7 +32,8 @@ struct stripe_block {
   PoolLaunch pool;
   RowsLaunch rows;           // products with few rows (the GEMM or the generic path's pointer contract)
   FewLaunch few;             // blocks of the generic path that are convolutions with at most four input channels
-  ContractLaunch contract;   // blocks of the generic path that the general matrix-core contraction takes
+  ContractLaunch contract;   // blocks of the generic path that the general matrix-core contraction takes, and those it takes from their family
+  stripe_block_info_t family_info = {};      // the latter: what their family's kernel was to be
   int n_inputs = 0;
   // statement lists (empty for a single block): stages in order, and per root refinement either the caller's
   // input number, or the size of a temporary the handle owns (allocated on the first run, per device)
@@ -256,7 +257,9 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
 
   // Fusion and scalarisation (Section 2.3): a convolution into a temporary followed by O = relu(T + bias[k]) over
   // the same dense image runs as one kernel whose accumulators are the temporary, which then needs no memory.
-  if (prog->stages.size() == 2 && tune_int("fuse", 1)) {
+  // check: only notes whether the convolution kernels would have fused them.
+  const bool may_fuse = prog->stages.size() == 2 && tune_int("fuse", 1);
+  auto fuse_conv = [&](bool check) {
     const Stage &s0 = prog->stages[0], &s1 = prog->stages[1];
     const Plan& c = s0.blk->plan;
     const FlatBlock& e = s1.blk->plan.flat;
@@ -275,7 +278,7 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
              co[px] == c.conv.Co && e.ref[0].addr.k == 0 && e.ref[1].addr.k % 4 == 0 && e.ref[2].addr.k == 0;
       }
       prog->aligned_out = ok;
-      if (ok && !s0.blk->contract.use) {
+      if (ok && !check) {
         prog->fused = e.out_bf16 ? 2 : 1;
         prog->plan.conv = c.conv;
         prog->conv = s0.blk->conv;
@@ -283,9 +286,9 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
         prog->temp_bytes[s0.dst] = 0;               // scalarised away
       }
     }
-  }
+  };
   // The same for a dense contraction C = A * B (or A * B^T) followed by O[m,n] = relu(C[m,n] + bias[n]).
-  if (!prog->fused && prog->stages.size() == 2 && tune_int("fuse", 1)) {
+  auto fuse_gemm = [&]() {
     const Stage &s0 = prog->stages[0], &s1 = prog->stages[1];
     const Plan& c = s0.blk->plan;
     const FlatBlock& e = s1.blk->plan.flat;
@@ -293,11 +296,11 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
     bool few_rows = s0.blk->rows.use && c.in_dtype == STRIPE_BF16, alt = false;
     RowsLaunch rows = s0.blk->rows;
     stripe_block_info_t rows_info = c.info, unused = c.info;
-    if (!few_rows && path == STRIPE_PATH_AUTO && !s0.blk->contract.use && c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && s0.blk->gemm.split_k > 1) {
+    if (!few_rows && path == STRIPE_PATH_AUTO && c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && s0.blk->gemm.split_k > 1) {
       few_rows = gemm_rows_select(c.gemm, c.in_dtype, gemm_few_rows_us(c.gemm, c.in_dtype, s0.blk->gemm) + 3.0, &rows, &rows_info);
       alt = !few_rows && gemm_rows_select(c.gemm, c.in_dtype, __builtin_huge_val(), &rows, &unused);
     }
-    bool ok = (few_rows || alt || (c.info.path == STRIPE_PATH_MFMA_GEMM && !s0.blk->contract.use && c.in_dtype == STRIPE_BF16 && gemm_can_fuse_bias_relu(c.gemm, s0.blk->gemm))) &&
+    bool ok = (few_rows || alt || (c.info.path == STRIPE_PATH_MFMA_GEMM && c.in_dtype == STRIPE_BF16 && gemm_can_fuse_bias_relu(c.gemm, s0.blk->gemm))) &&
               root->refs[s0.dst].dir == STRIPE_TEMP && s1.n_in == 2 && s1.src[0] == s0.dst && !e.empty && e.intrinsic == STRIPE_INTR_ADD_RELU &&
               e.cons.empty() && e.n_refs == 3 && e.n_idx >= 2 && e.ref[0].dtype == STRIPE_F32 && e.ref[1].dtype == STRIPE_F32;
     if (ok) {
@@ -323,10 +326,10 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
         }
       }
     }
-  }
+  };
   // And for the general matrix-core contraction: the second statement reads T and writes O through one map, over the
   // product's output and nothing else, with a bias along the product's single column index.
-  if (!prog->fused && prog->stages.size() == 2 && tune_int("fuse", 1)) {
+  auto fuse_contract = [&]() {
     const Stage &s0 = prog->stages[0], &s1 = prog->stages[1];
     const Plan& c = s0.blk->plan;
     ContractLaunch ct = s0.blk->contract;
@@ -373,6 +376,28 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
         prog->temp_bytes[s0.dst] = 0;
       }
     }
+  };
+  if (may_fuse) {
+    stripe_block* first = prog->stages[0].blk;
+    const bool over = first->contract.use && first->plan.info.path != STRIPE_PATH_GENERIC;      // a family's block on the contraction
+    if (over) {
+      fuse_conv(true);
+      fuse_contract();
+      // Not in one launch there (an output laid out unlike the temporary): the family's kernel where it fuses them, as its second
+      // launch and the temporary's way through memory cost more than the contraction gains (3 us at least).
+      if (!prog->fused) {
+        std::swap(first->plan.info, first->family_info);
+        first->contract.use = false;
+      }
+    }
+    if (!prog->fused) fuse_conv(false);
+    if (!prog->fused) fuse_gemm();
+    if (!prog->fused && over) {
+      std::swap(first->plan.info, first->family_info);
+      first->contract.use = true;
+      prog->alt_fused = 0;
+    }
+    if (!prog->fused && !over) fuse_contract();
   }
   // what the program as a whole looks like from outside
   stripe_block_info_t& info = prog->plan.info;
@@ -652,6 +677,7 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
       const LiteralSums one_chain = {1, p.gen.red_total, p.gen.n_red, p.gen.n_outputs, false, false};      // those kernels hold one sum per output
       if (us >= (igemm ? 25 : 13) && contract_select(p.flat, one_chain, true, &blk->contract, &other) && blk->contract.us < 0.8 * us) {
         other.path = p.info.path;
+        blk->family_info = p.info;
         p.info = other;
         blk->gemm.ws_bytes = 0;    // no partial sums of a split reduction
       } else {

@@ -321,3 +321,16 @@ def test_image_rows_that_no_lds_holds(R, stride_x, dt):
     b = B.StripeBlock(strided_conv(R, 2, stride_x, 40, 2, 2, 4096, dt))
     assert not b.info["kernel"].startswith("conv_few_") and 0 <= b.info["lds_bytes"] <= 160 * 1024, (b.info["kernel"], b.info["lds_bytes"])
     b.close()
+
+
+@pytest.mark.parametrize("M,N,K,out_dt,b_transposed", [(64, 136, 1536, "f32", True), (33, 64, 1024, "bf16", False), (15, 320, 8192, "bf16", True),
+                                                       (100, 24, 1536, "f32", False), (2, 24, 1536, "f32", False)])
+def test_an_output_laid_out_unlike_the_temporary_is_fused(M, N, K, out_dt, b_transposed):
+    """Products of few tiles, which the general contraction takes where it can store through the second statement: where it cannot (rows
+    of the output further apart than the temporary's), their family's kernel does, in one launch and without a temporary."""
+    prog = W.linear_bias_relu_program(M, N, K, out_dt, b_transposed=b_transposed)
+    prog.refs[-1].strides = [N + 8, 1]
+    prog.child.next.refs[-1].strides = [N + 8, 1]
+    b = B.StripeBlock(prog)
+    assert "+bias_relu" in b.info["kernel"] and b.info["workspace_bytes"] == 0, b.info
+    b.close()
