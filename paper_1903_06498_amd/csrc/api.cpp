@@ -517,9 +517,11 @@ stripe_status_t run_program(stripe_block* prog, const void* const* inputs, void*
     const float* bias = (const float*)inputs[prog->input_slot[s1.src[1]]] + prog->fuse_bias_off;
     if (fused >= 5) {
       // the family's pointer contract where the block is one of its
+      const uintptr_t bias_align = prog->aligned_out ? 16 : prog->plan.info.path == STRIPE_PATH_MFMA_GEMM ? 4 : 1;
+      const uintptr_t out_align = bias_align == 4 && fused == 6 ? 2 : bias_align;
       if (prog->plan.info.path != STRIPE_PATH_GENERIC &&
           (((uintptr_t)inputs[prog->input_slot[s0.src[0]]] % 16) || ((uintptr_t)inputs[prog->input_slot[s0.src[1]]] % 16) ||
-           (prog->aligned_out && (((uintptr_t)bias % 16) || ((uintptr_t)output % 16)))))
+           (uintptr_t)bias % bias_align || (uintptr_t)output % out_align))
         return fail(STRIPE_ERR_MISALIGNED, "the fused matrix-core kernel needs 16-byte aligned operands (convolution: also bias and output)");
       const void *in = inputs[prog->input_slot[s0.src[0]]], *flt = inputs[prog->input_slot[s0.src[1]]];
       e = fused >= 7 ? launch_conv_few(prog->plan.conv, prog->few, prog->plan.in_dtype, in, flt, output, bias, fused == 8, (hipStream_t)hip_stream)

@@ -334,3 +334,16 @@ def test_an_output_laid_out_unlike_the_temporary_is_fused(M, N, K, out_dt, b_tra
     b = B.StripeBlock(prog)
     assert "+bias_relu" in b.info["kernel"] and b.info["workspace_bytes"] == 0, b.info
     b.close()
+
+
+def test_a_fused_product_on_the_contraction_refuses_what_its_family_refuses():
+    """Inputs at 16 bytes, the bias at 4, the output at its element: refused before anything is launched, so without a GPU too."""
+    for out_dt, esize in (("f32", 4), ("bf16", 2)):
+        b = B.StripeBlock(W.linear_bias_relu_program(64, 136, 1536, out_dt))
+        assert b.info["kernel"].startswith("contract_") and b.info["path_name"] == "mfma_gemm", b.info
+        x, w, bias, out = (1 << 20 << i for i in range(4))      # never touched
+        for ptrs in ((x + 2, w, bias, out), (x, w + 8, bias, out), (x, w, bias + 2, out), (x, w, bias, out + esize // 2)):
+            with pytest.raises(B.StripeError) as e:
+                b.run(ptrs[:3], ptrs[3], stream=0)
+            assert e.value.status == 8, (ptrs, str(e.value))
+        b.close()
