@@ -1556,8 +1556,8 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, Co
   info->lds_bytes = (kTiles[tile].bm + kTiles[tile].bn) * (bkb * (kTiles[tile].lanes > 256 ? kTiles[tile].lanes / 64 : 2) + 24);
   info->workgroup_size = kTiles[tile].lanes;
   info->grid = l->grid * l->batch;
-  std::snprintf(info->kernel, sizeof info->kernel, "contract_%s_%dx%dx%d_fetch%d%d", dt == STRIPE_F32 ? "f32" : dt == STRIPE_BF16 ? "bf16" : "i8",
-                kTiles[tile].bm, kTiles[tile].bn, (int)info->tile_k, p.mode_a, p.mode_b);
+  std::snprintf(info->kernel, sizeof info->kernel, "contract_%s_%dx%dx%d_fetch%d%d%s", dt == STRIPE_F32 ? "f32" : dt == STRIPE_BF16 ? "bf16" : "i8",
+                kTiles[tile].bm, kTiles[tile].bn, (int)info->tile_k, p.mode_a, p.mode_b, l->precise ? "_f64" : "");
   return true;
 }
 

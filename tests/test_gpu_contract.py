@@ -583,3 +583,19 @@ def test_ragged_fused_product_on_the_128_wide_tiles(monkeypatch):
         # 256 products of order up to |x||w| in fp32, then half a step of the output type
         tol = 256 * 2.0 ** -24 * (x.abs() @ w.abs().t() + b.abs()) + (2.0 ** -8 * want if out_dt == "bf16" else 0)
         assert bool(((out.double().cpu() - want).abs() <= tol).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(12, 323, 8192), (20, 1000, 8192), (2, 16, 8192)])
+def test_few_rows_with_an_fp32_output(M, N, K):
+    """relu(X W^T + b) in fp32 where the general contraction replaces the few-rows kernel: totals in double precision, so what is left is
+    chains of at most 32 products and one rounding of the total."""
+    prog = W.linear_bias_relu_program(M, N, K, "f32")
+    sb = B.StripeBlock(prog)
+    held = [W.seeded_tensor(r.sizes, r.dtype, i).cuda() for i, r in enumerate(r for r in prog.refs if r.dir == "in")]
+    out = torch.full((M, N), -7.0, device="cuda")
+    sb.run(held, out)
+    sb.close()
+    x, w, b = (t.double().cpu() for t in held)
+    want = torch.relu(x @ w.t() + b)
+    tol = 64 * 2.0 ** -24 * (x.abs() @ w.abs().t()) + 2.0 ** -23 * (want.abs() + b.abs())
+    assert bool(((out.double().cpu() - want).abs() <= tol).all())

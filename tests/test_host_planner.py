@@ -347,3 +347,13 @@ def test_a_fused_product_on_the_contraction_refuses_what_its_family_refuses():
                 b.run(ptrs[:3], ptrs[3], stream=0)
             assert e.value.status == 8, (ptrs, str(e.value))
         b.close()
+
+
+@pytest.mark.parametrize("M,N,K", [(8, 64, 8192), (12, 320, 8192), (16, 128, 8192), (20, 1000, 8192), (8, 4096, 4096)])
+def test_few_rows_with_an_fp32_output_keep_totals_in_double(M, N, K):
+    """A Linear layer with bias and relu at few rows: the few-rows kernel's totals are in double precision, and those of the general
+    contraction where it takes its place (its name says so)."""
+    b = B.StripeBlock(W.linear_bias_relu_program(M, N, K, "f32"))
+    assert b.info["kernel"].startswith("gemm_rows_") or "_f64" in b.info["kernel"], b.info["kernel"]
+    assert b.info["kernel"].endswith("+bias_relu") and b.info["path_name"] == "mfma_gemm", b.info
+    b.close()
