@@ -10,8 +10,9 @@
 // four 16x16x4 fp32 instructions -- and the filter's fragments stay in registers.  Filter rows end with zero weights where the
 // taps do not fill a chunk (7 taps of bf16: 8), a fourth channel is zero in both operands.
 // The filter's rows are laid out so that a lane ends up with 4 * FN consecutive output channels of its pixel, which leave
-// as 16-byte stores without a pass through LDS.
-// What bounds it at that size (34.7 us before, 13.6 to 18.2 here, by where the output lies in memory): the rows' arrival, then the
+// in stores of four of them (fp32, int32: 16 bytes, bf16: 8) without a pass through LDS; ordinary ones, since a line of the output
+// is written by several of them, which meet in L2 (past it, 24 x 94 x 94, 3 -> 64, 3x3, int8 took 68.1 us instead of 25.4).
+// What bounds it at that size (34.7 us before, 12.2 here; 13.6 to 18.2, by where the output lay in memory, with stores past L2): the rows' arrival, then the
 // write of the output (12.8 MB in bf16, 2.3 us), one after the other in the one workgroup that a CU has (up to 200 registers of filter
 // and sums).  The same layer in int8 at 13 x 61 x 61, 7x7 to 32 channels: 11.7 and 5.8; in fp32 at 3 x 75 x 75, 7x7 to 64: 21.6 and 12.0.
 #include <hip/hip_runtime.h>
@@ -280,8 +281,8 @@ __global__ __launch_bounds__(kLanes, 2) void conv_few_kernel(const FewParams p, 
         const int k = k0 + 4 * j;
         if (p.vec && k + 4 <= p.Co) {
           if (std::is_same<S, float>::value && p.epilogue == 3)
-            __builtin_nontemporal_store(__builtin_convertvector((f32x4){(float)v[0], (float)v[1], (float)v[2], (float)v[3]}, bf16x4), (bf16x4*)((uint16_t*)O + off + 4 * j));
-          else __builtin_nontemporal_store(v, (s4*)((S*)O + off + 4 * j));
+            *(bf16x4*)((uint16_t*)O + off + 4 * j) = __builtin_convertvector((f32x4){(float)v[0], (float)v[1], (float)v[2], (float)v[3]}, bf16x4);
+          else *(s4*)((S*)O + off + 4 * j) = v;
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
