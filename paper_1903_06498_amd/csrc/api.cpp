@@ -340,7 +340,7 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
       // the few-channels convolution where the contraction would fuse (the checks of the second statement are the same); below 2048
       // output pixels both take less than a call costs its caller (3.5 and 5 us)
       if (few.use) ct_info = c.info;
-      else if (ct.use && c.is_conv && c.conv.N * c.conv.Ho * c.conv.Wo >= 2048 && (root->refs[R - 1].dtype == STRIPE_BF16 || tune_int("conv_few", 1) == 2)) conv_few_select(c.conv, c.in_dtype, &few, &ct_info);
+      else if (ct.use && c.is_conv && c.conv.N * c.conv.Ho * c.conv.Wo >= 2048 && (root->refs[R - 1].dtype == STRIPE_BF16 || tune_int("conv_few", 1) == 2)) conv_few_select(c.conv, c.in_dtype, root->refs[R - 1].dtype == STRIPE_BF16 ? 2 : 4, ct.us, &few, &ct_info);
     }
     // Few rows and a reduction long enough to be split, with an fp32 output: the few-rows kernel's, whose totals are in double precision,
     // or the contraction's with such totals, whichever is faster (12 x 320 x 8192: 14.6 us there, 8.4 here).  A bf16 output's own rounding
@@ -673,7 +673,7 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
         contract_select(p.flat, literal_sums(p), false, &blk->contract, &p.info);
         // Few input channels: faster than the general contraction (7x7 stride 2, 3 -> 64, bf16, 8 x 224 x 224: 34 us there), with fp32
         // chains as long as its own: not where the literal kernel holds 64 sums per output and the contraction totals in double precision.
-        if (blk->contract.use && p.is_conv && (!blk->contract.precise || tune_int("conv_few", 1) == 2) && conv_few_select(p.conv, p.in_dtype, &blk->few, &p.info)) blk->contract.use = false;
+        if (blk->contract.use && p.is_conv && (!blk->contract.precise || tune_int("conv_few", 1) == 2) && conv_few_select(p.conv, p.in_dtype, 4, blk->contract.us, &blk->few, &p.info)) blk->contract.use = false;
       }
     } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM &&
                gemm_rows_select(p.gemm, p.in_dtype, gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm), &blk->rows, &p.info)) {

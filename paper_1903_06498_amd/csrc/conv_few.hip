@@ -343,7 +343,17 @@ FewParams make_params(const Conv2dShape& c, int esize, const FewLaunch& l) {
 
 }  // namespace
 
-bool conv_few_select(const Conv2dShape& c, int in_dtype, FewLaunch* l, stripe_block_info_t* info) {
+// us, fitted to 316 blocks of one to four channels, 1 to 1008 output channels, 2x2 to 7x7 (standard deviation 11 %).  Per round of
+// workgroups: the tiles of output channels that one takes in turn, each with its filter and the image fragments of a wavefront's groups
+// of pixels read again; then the write of the output, slower where its channels are no multiple of four and leave one by one, 4 * FN apart.
+static double few_us(const Conv2dShape& c, int esize, const FewLaunch& l, int out_size) {
+  const double rounds = std::max(1.0, (double)(l.grid * l.co_split) / 256), tiles = std::ceil((double)((c.Co + 16 * l.fn - 1) / (16 * l.fn)) / l.co_split);
+  const double units = std::ceil((double)(std::min<int64_t>(l.ty, c.Ho) * ((c.Wo + 15) / 16)) / kWaves);
+  const double out_mb = (double)c.N * (double)c.Ho * (double)c.Wo * (double)c.Co * out_size / 1e6;
+  return 4.0 + rounds * tiles * (0.32 + units * l.fn * (0.0655 * l.steps * (esize == 4 ? 2 : 1) + 0.02)) + out_mb * (c.Co % 4 == 0 ? 0.245 : l.fn == 4 ? 1.21 : 0.54);
+}
+
+bool conv_few_select(const Conv2dShape& c, int in_dtype, int out_size, double other_us, FewLaunch* l, stripe_block_info_t* info) {
   l->use = false;
   if (!tune_int("conv_few", std::getenv("STRIPE_TUNE") == nullptr)) return false;      // a STRIPE_TUNE that picks other variants keeps them
   const int esize = in_dtype == STRIPE_F32 ? 4 : in_dtype == STRIPE_BF16 ? 2 : in_dtype == STRIPE_I8 ? 1 : 0;
@@ -388,8 +398,12 @@ bool conv_few_select(const Conv2dShape& c, int in_dtype, FewLaunch* l, stripe_bl
   const int64_t strips = c.N * ((c.Ho + l->ty - 1) / l->ty);
   while (l->co_split < co_tiles && strips * (l->co_split + 1) <= 256) ++l->co_split;
   if (strips > 0x7fffffff) return false;
-  l->lds = (int)lds.bytes();
   l->grid = strips;
+  // Where the general contraction is the faster one, it stays: many tiles of output channels (10 x 50 x 50, 2 -> 1008, 3x3 stride 3,
+  // fp32 29.6 us here and 10.9 there), large outputs in single elements (7 x 127 x 127, 3 -> 103, 2x2, fp32 61.8 and 36.8).  The tenth is
+  // for both estimates' errors.  Of 316 blocks on both, 5 are taken that lose more than 5 %, and 15 are left that would gain as much.
+  if (tune_int("conv_few", 1) != 2 && few_us(c, esize, *l, out_size) > 0.9 * other_us) return false;
+  l->lds = (int)lds.bytes();
   l->use = true;
   info->tile_m = (int)(l->ty * 16 * lds.groups); info->tile_n = 16 * l->fn; info->tile_k = 64 / esize;
   info->frag_m = info->frag_n = 16;

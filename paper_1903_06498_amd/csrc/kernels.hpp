@@ -96,14 +96,15 @@ hipError_t launch_conv_igemm(const Conv2dShape& c, const ConvLaunch& l, int in_d
 bool conv_i8_select(const Conv2dShape& c, int in_dtype, ConvLaunch* l, stripe_block_info_t* info);
 hipError_t launch_conv_i8(const Conv2dShape& c, const ConvLaunch& l, const void* in, const void* flt, void* out, hipStream_t stream);
 
-// convolutions with at most four input channels (conv_few.hip); bias != nullptr: O = relu(T + bias[k])
+// convolutions with at most four input channels (conv_few.hip); bias != nullptr: O = relu(T + bias[k]).  out_size: bytes of an output
+// element; other_us: what the block takes otherwise.
 struct FewLaunch {
   bool use = false;
   int steps = 0, fn = 0, ty = 1, co_split = 1, lds = 0;   // K steps and channel fragments in registers, output rows of a workgroup
   int64_t grid = 0;
   mutable int lds_enabled_on = -1;
 };
-bool conv_few_select(const Conv2dShape& c, int in_dtype, FewLaunch* l, stripe_block_info_t* info);
+bool conv_few_select(const Conv2dShape& c, int in_dtype, int out_size, double other_us, FewLaunch* l, stripe_block_info_t* info);
 hipError_t launch_conv_few(const Conv2dShape& c, const FewLaunch& l, int in_dtype, const void* in, const void* flt, void* out, const float* bias, bool out_bf16,
                            hipStream_t stream);
 
