@@ -59,8 +59,9 @@ struct Few;
 template <>
 struct Few<uint16_t> {
   using Acc = f32x4;
-  static __device__ __forceinline__ Acc mma(u32x4 a, u32x4 b, Acc c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  template <bool>
+  static __device__ __forceinline__ void add(u32x4 a, u32x4 b, Acc& c) {
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   }
   static __device__ __forceinline__ float widen(const unsigned char* p) { return __uint_as_float((uint32_t)*(const uint16_t*)p << 16); }
   static __device__ __forceinline__ bool finite(uint32_t w) { return ((w & 0x7f80u) != 0x7f80u) & ((w & 0x7f800000u) != 0x7f800000u); }
@@ -68,11 +69,14 @@ struct Few<uint16_t> {
 template <>
 struct Few<float> {
   using Acc = f32x4;
-  static __device__ __forceinline__ Acc mma(u32x4 a, u32x4 b, Acc c) {
+  // 16 products in one chain that starts from zero; the few of a short filter as two chains of eight
+  template <bool SHORT>
+  static __device__ __forceinline__ void add(u32x4 a, u32x4 b, Acc& c) {
     const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+    Acc s[2] = {(Acc){0, 0, 0, 0}, (Acc){0, 0, 0, 0}};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[i], c, 0, 0, 0);
-    return c;
+    for (int i = 0; i < 4; ++i) s[SHORT ? i / 2 : 0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[i], s[SHORT ? i / 2 : 0], 0, 0, 0);
+    c += SHORT ? s[0] + s[1] : s[0];
   }
   static __device__ __forceinline__ float widen(const unsigned char* p) { return *(const float*)p; }
   static __device__ __forceinline__ bool finite(uint32_t w) { return (w & 0x7f800000u) != 0x7f800000u; }
@@ -80,8 +84,9 @@ struct Few<float> {
 template <>
 struct Few<int8_t> {
   using Acc = i32x4;
-  static __device__ __forceinline__ Acc mma(u32x4 a, u32x4 b, Acc c) {
-    return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0, 0);
+  template <bool>
+  static __device__ __forceinline__ void add(u32x4 a, u32x4 b, Acc& c) {
+    c = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), c, 0, 0, 0);
   }
   static __device__ __forceinline__ float widen(const unsigned char* p) { return (float)*(const int8_t*)p; }
   static __device__ __forceinline__ bool finite(uint32_t) { return true; }
@@ -250,17 +255,16 @@ __global__ __launch_bounds__(kLanes, 2) void conv_few_kernel(const FewParams p, 
         u32x4 fa[STEPS];
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) fa[t] = *(const u32x4_at4*)(at + slot_at[t]);
-        Acc acc[FN];
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          acc[j] = (Acc){0, 0, 0, 0};
+        for (int j = 0; j < FN; ++j) {      // rows of the result: output channels; floats: K step t joins sum t % SUMS
+          constexpr int SUMS = sizeof(T) == 1 ? 1 : STEPS >= 7 ? 4 : 2;
+          Acc acc[4] = {(Acc){0, 0, 0, 0}, (Acc){0, 0, 0, 0}, (Acc){0, 0, 0, 0}, (Acc){0, 0, 0, 0}};
 #pragma unroll
-          for (int t = 0; t < STEPS; ++t) {      // rows of the result: output channels; fp32: a step's 16 products start from zero
-            if constexpr (sizeof(T) == 4) acc[j] += Few<T>::mma(fb[t][j], fa[t], (Acc){0, 0, 0, 0});
-            else acc[j] = Few<T>::mma(fb[t][j], fa[t], acc[j]);
-          }
+          for (int t = 0; t < STEPS; ++t) Few<T>::template add<STEPS == 2>(fb[t][j], fa[t], acc[t % SUMS]);
+          if (SUMS == 4) acc[0] += acc[2], acc[1] += acc[3];
+          if (SUMS >= 2) acc[0] += acc[1];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sum[j][e] = acc[j][e];
+          for (int e = 0; e < 4; ++e) sum[j][e] = acc[0][e];
         }
       }
       if (x >= p.Wo) continue;
