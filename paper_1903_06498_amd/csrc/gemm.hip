@@ -30,7 +30,8 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 
 struct GemmParams {
-  int32_t tiles_m, tiles_n, k_tiles, pad_;
+  int32_t tiles_m, tiles_n, k_tiles;
+  int32_t chain;              // K tiles whose products are summed from zero before they join the total (128 x 128 tiles, ragged floats; 0: all)
   int32_t M, N;               // used by the variants that accept M, N that are not multiples of the tile
   int64_t a_m, b_k, c_m;      // row strides in elements (a_k = b_n = c_n = 1); for a transposed B ([n][k], k contiguous) b_k holds its row stride
   int64_t a_base, b_base, c_base;
@@ -959,7 +960,10 @@ __device__ __forceinline__ void t_wait_loads() {   // until at most N of the wav
 // KB: bytes of a K tile row of A (and of a transposed B): 64, or 128 -- K tiles of 64 instead of 32 deep, half as
 // many barriers per matrix instruction, whole 128-byte lines per row -- where one workgroup per CU covers the
 // product anyway (the ring then takes 128 KB).
-template <int MODE, int W8 = 0, int KB = 64>
+// CHAINS (ragged floats): sums of p.chain K tiles start from zero and join a total where these products were split into more slices on
+// the 256-wide tiles (chain_of_large_tiles); four such totals join another one, so that they are no long chain either.  3905 x 640 x
+// 3072: 26.0 -> 27.1 us, 1.9e-7 instead of 3.4e-7 off.
+template <int MODE, int W8 = 0, int KB = 64, bool CHAINS = false>
 __global__ __launch_bounds__(256 * (1 + W8), 1) void gemm_bf16_t128_kernel(const GemmParams p, const uint16_t* __restrict__ A,
                                                                          const uint16_t* __restrict__ B, float* __restrict__ C) {
   static_assert(KB == 64 || KB == 128, "K tile rows");
@@ -1075,9 +1079,39 @@ __global__ __launch_bounds__(256 * (1 + W8), 1) void gemm_bf16_t128_kernel(const
     if (kt + 4 < k_tiles) issue(kt & 3, kt + 4);
     D_FENCE();
   };
+  const int join = CHAINS ? p.chain : 1;
+  int next = join, fours = 4 * join;
+  f32x16 total[2][CHAINS ? NF : 1];
+#pragma unroll
+  for (int q = 0; q < (CHAINS ? NF : 1); ++q)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) total[0][q][v] = total[1][q][v] = 0.f;
+  auto add_to = [&](f32x16* to, f32x16* from) {
+#pragma unroll
+    for (int q = 0; q < (CHAINS ? NF : 1); ++q)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        to[q][v] += from[q][v];
+        from[q][v] = 0.f;
+      }
+  };
   for (int kt = 0; kt < k_tiles; kt += 2) {
     iteration(kt, af[0], bf[0], af[1], bf[1]);
     if (kt + 1 < k_tiles) iteration(kt + 1, af[1], bf[1], af[0], bf[0]);
+    if constexpr (CHAINS) {
+      if (kt + 2 == next) {
+        next += join;
+        add_to(total[0], acc);
+        if (kt + 2 == fours) {
+          fours += 4 * join;
+          add_to(total[1], total[0]);
+        }
+      }
+    }
+  }
+  if constexpr (CHAINS) {
+    add_to(total[0], total[1]);
+    add_to(acc, total[0]);
   }
 
   const int64_t m0 = (int64_t)tm * T_BM + wm * 64 * W8 + 4 * fh, n0 = (int64_t)tn * T_BN + wn * 32 + fr;
@@ -1158,7 +1192,7 @@ GemmParams make_params(const GemmShape& g, bool i8 = false) {
   p.M = (int)g.M;
   p.N = (int)g.N;
   p.k_tiles = (int)(g.K / BK);
-  p.pad_ = 0;
+  p.chain = 0;
   p.a_m = g.a_m; p.c_m = g.c_m;
   p.b_k = (g.b_k == 1 && g.b_n != 1) ? g.b_n : g.b_k;   // row stride of B as stored: [n][k] (transposed) or [k][n]
   if (i8) {   // int8 operands seen as 16-bit matrices of half the width (see D_I8)
@@ -1216,6 +1250,17 @@ static int choose_split_k(const GemmShape& g, int in_dtype, const GemmLaunch& l)
   return (int)best;
 }
 
+// The 128-wide tiles need half as many slices as the 256-wide ones to fill the chip, which would double the chains of roundings: 401 x
+// 320 x 2560 bf16 is 1.01e-7 off in the 2-norm in 10 slices there, 1.33e-7 in 5 here, and 3905 x 640 x 3072 1.9e-7 in 3 and 3.4e-7
+// whole.  How many products in a row to sum from zero for chains as short as there; 0: the slices are.
+static int64_t chain_of_large_tiles(const GemmShape& g, const GemmLaunch& l) {
+  GemmLaunch large = l;
+  large.variant = 30;
+  large.grid = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  const int64_t slices = choose_split_k(g, STRIPE_BF16, large);
+  return slices > l.split_k ? g.K / slices : 0;
+}
+
 // A product with few rows on these kernels, fitted to 250 products of 2 to 32 rows, 16 to 120000 columns, K of 512 to 32768 (13 to
 // 150 us, bf16 and int8).  Split: two launches, the K tiles of one workgroup, partial sums out and back, the operands once.
 // Not split: rounds of workgroups, or the operands from memory.
@@ -1236,6 +1281,7 @@ bool gemm_select(const GemmShape& g, int in_dtype, GemmLaunch* l, stripe_block_i
   if (!gemm_select_one(g, in_dtype, l, info)) return false;
   l->split_k = choose_split_k(g, in_dtype, *l);
   l->ws_bytes = 0;
+  l->t128_chain = l->variant >= 50 && l->t128_ragged && in_dtype == STRIPE_BF16 ? chain_of_large_tiles(g, *l) : 0;
   l->t128_kb = 64;
   if (l->variant >= 50 && l->t128_waves == 8) {
     // 128-byte K tile rows (a 128 KB ring: one workgroup per CU) where one round of workgroups covers the product anyway
@@ -1446,8 +1492,8 @@ static hipError_t launch_gemm_epi(const GemmShape& g, const GemmLaunch& l, const
     case 30 + D_BT: kernel = gemm_bf16_dma_kernel<4, 1, D_BT>; break;
     case 30 + D_RAGGED: kernel = gemm_bf16_dma_kernel<4, 1, D_RAGGED>; break;
     case 30 + D_BT + D_RAGGED: kernel = gemm_bf16_dma_kernel<4, 1, D_BT + D_RAGGED>; break;
-    case 50: kernel = l.t128_ragged ? (t128_kb128 ? gemm_bf16_t128_kernel<D_RAGGED, 1, 128> : gemm_bf16_t128_kernel<D_RAGGED, 1>) : t128_kb128 ? gemm_bf16_t128_kernel<0, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<0, 1> : gemm_bf16_t128_kernel<0, 0>; break;
-    case 51: kernel = l.t128_ragged ? (t128_kb128 ? gemm_bf16_t128_kernel<D_BT + D_RAGGED, 1, 128> : gemm_bf16_t128_kernel<D_BT + D_RAGGED, 1>) : t128_kb128 ? gemm_bf16_t128_kernel<D_BT, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<D_BT, 1> : gemm_bf16_t128_kernel<D_BT, 0>; break;
+    case 50: kernel = l.t128_chain ? (t128_kb128 ? gemm_bf16_t128_kernel<D_RAGGED, 1, 128, true> : gemm_bf16_t128_kernel<D_RAGGED, 1, 64, true>) : l.t128_ragged ? (t128_kb128 ? gemm_bf16_t128_kernel<D_RAGGED, 1, 128> : gemm_bf16_t128_kernel<D_RAGGED, 1>) : t128_kb128 ? gemm_bf16_t128_kernel<0, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<0, 1> : gemm_bf16_t128_kernel<0, 0>; break;
+    case 51: kernel = l.t128_chain ? (t128_kb128 ? gemm_bf16_t128_kernel<D_BT + D_RAGGED, 1, 128, true> : gemm_bf16_t128_kernel<D_BT + D_RAGGED, 1, 64, true>) : l.t128_ragged ? (t128_kb128 ? gemm_bf16_t128_kernel<D_BT + D_RAGGED, 1, 128> : gemm_bf16_t128_kernel<D_BT + D_RAGGED, 1>) : t128_kb128 ? gemm_bf16_t128_kernel<D_BT, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<D_BT, 1> : gemm_bf16_t128_kernel<D_BT, 0>; break;
     case 52: kernel = l.t128_ragged ? (t128_kb128 ? gemm_bf16_t128_kernel<D_BT + D_I8 + D_RAGGED, 1, 128> : gemm_bf16_t128_kernel<D_BT + D_I8 + D_RAGGED, 1>) : t128_kb128 ? gemm_bf16_t128_kernel<D_BT + D_I8, 1, 128> : t128_w8 ? gemm_bf16_t128_kernel<D_BT + D_I8, 1> : gemm_bf16_t128_kernel<D_BT + D_I8, 0>; break;
     case 40: kernel = gemm_bf16_dma_kernel<4, 1, D_BT + D_I8>; break;
     case 40 + D_RAGGED: kernel = gemm_bf16_dma_kernel<4, 1, D_BT + D_RAGGED + D_I8>; break;
@@ -1472,6 +1518,7 @@ static hipError_t launch_gemm_epi(const GemmShape& g, const GemmLaunch& l, const
                  ? 1
                  : 0;
   if (l.variant >= 50) {
+    pk.chain = (int)(l.t128_chain / (D_BK * (t128_kb128 ? 2 : 1)));
     pk.tiles_m = (int)((g.M + T_BM - 1) / T_BM);
     pk.tiles_n = (int)((g.N + T_BN - 1) / T_BN);
   }

@@ -34,6 +34,7 @@ struct GemmLaunch {
   int t128_waves = 4;   // wavefronts of the 128 x 128-tile kernel: 4 or 8
   int t128_kb = 64;     // bytes of its K tile rows: 64, or 128 where one workgroup per CU covers the product
   bool t128_ragged = false;   // M or N is no multiple of its tile
+  int64_t t128_chain = 0;     // products it sums from zero before they join the total (a multiple of 128); 0: all
   int64_t grid = 0;
   int split_k = 1;       // slices of the reduction index, each run as one product of a batch into the workspace
   int64_t ws_bytes = 0;  // workspace launch_gemm needs: split_k images of M x N partial sums

@@ -599,3 +599,19 @@ def test_few_rows_with_an_fp32_output(M, N, K):
     want = torch.relu(x @ w.t() + b)
     tol = 64 * 2.0 ** -24 * (x.abs() @ w.abs().t()) + 2.0 ** -23 * (want.abs() + b.abs())
     assert bool(((out.double().cpu() - want).abs() <= tol).all())
+
+
+@pytest.mark.parametrize("M,N,K,layout,most", [(401, 320, 2560, "nn", 1.15e-7), (537, 264, 2560, "nt", 1.15e-7), (1905, 640, 3072, "nn", 1.8e-7)])
+def test_ragged_products_sum_in_short_chains(M, N, K, layout, most):
+    """128-wide tiles need fewer slices of the reduction than 256-wide ones, which must not lengthen the chains of roundings: 256, 256 and
+    768 products from zero (1.0e-7, 1.0e-7 and 1.6e-7 off in the 2-norm; in one chain per slice 1.3e-7, 1.3e-7 and 3.4e-7)."""
+    g = torch.Generator().manual_seed(7)
+    a, b = (torch.randn(s, generator=g).to(torch.bfloat16).cuda() for s in ((M, K), (N, K) if layout == "nt" else (K, N)))
+    sb = B.StripeBlock(W.matmul_block(M, N, K, "bf16", "f32", b_transposed=layout == "nt"))
+    assert "128x128" in sb.info["kernel"] and "_ragged" in sb.info["kernel"], sb.info["kernel"]
+    out = torch.zeros((M, N), device="cuda")
+    sb.run([a, b], out)
+    sb.close()
+    want = a.double() @ (b.double().t() if layout == "nt" else b.double()).contiguous()
+    err = float((out.double() - want).norm() / want.norm())
+    assert err <= most, err
