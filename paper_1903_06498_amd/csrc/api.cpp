@@ -682,11 +682,11 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
     // Products and convolutions with few tiles of their family's kernel and a long reduction, whose wavefronts then share the
     // reduction out: on the general contraction where both estimates say so (6 x 1536 x 768 bf16 nn 21 us on one row of 256 x 256
     // tiles, 7 here; 7 x 7, 256 -> 9 channels int8 over 3 x 42 x 42: 77 and 15).  Those families' pointer contract stays.
-    // (not under STRIPE_TUNE, which picks variants of those families, unless it says contract_over=1)
+    // (not where STRIPE_TUNE picks variants of those families, unless it says contract_over=1)
     const bool igemm = p.info.path == STRIPE_PATH_MFMA_CONV && blk->conv.variant >= kConvIgemmVariant && blk->conv.variant < kConvGemmVariant;
     // (nor where full tiles fill half the chip: the contraction has no idle CUs to win back there, so its estimates are not made)
     const bool full = p.info.path == STRIPE_PATH_MFMA_GEMM && p.info.grid >= 128 && p.gemm.M >= 256 && p.gemm.N >= 256;
-    if (!forced && picked && tune_int("contract_over", std::getenv("STRIPE_TUNE") == nullptr) && !blk->rows.use && !full && (igemm || (p.info.path == STRIPE_PATH_MFMA_GEMM && (blk->gemm.split_k <= 1 || p.gemm.M <= 32)))) {
+    if (!forced && picked && tune_int("contract_over", !tune_sets("gemm_") && !tune_sets("conv_") && !tune_sets("contract_")) && !blk->rows.use && !full && (igemm || (p.info.path == STRIPE_PATH_MFMA_GEMM && (blk->gemm.split_k <= 1 || p.gemm.M <= 32)))) {
       stripe_block_info_t other = p.info;
       const double us = igemm ? conv_igemm_us(p.conv, blk->conv)
                               : blk->gemm.split_k > 1 ? gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm) : gemm_us(p.gemm, p.in_dtype, blk->gemm);

@@ -359,7 +359,7 @@ static double few_us(const Conv2dShape& c, int esize, const FewLaunch& l, int ou
 
 bool conv_few_select(const Conv2dShape& c, int in_dtype, int out_size, double other_us, FewLaunch* l, stripe_block_info_t* info) {
   l->use = false;
-  if (!tune_int("conv_few", std::getenv("STRIPE_TUNE") == nullptr)) return false;      // a STRIPE_TUNE that picks other variants keeps them
+  if (!tune_int("conv_few", !tune_sets("conv_") && !tune_sets("contract_"))) return false;
   const int esize = in_dtype == STRIPE_F32 ? 4 : in_dtype == STRIPE_BF16 ? 2 : in_dtype == STRIPE_I8 ? 1 : 0;
   if (!esize || c.Ci < 1 || c.Ci > 4 || c.i_c != 1 || c.f_c != 1 || c.o_k != 1 || c.R * c.S < 2) return false;
   if (c.dil_x != 1 || c.dil_y != 1 || c.stride_x < 1 || c.stride_y < 1 || c.pad_x < 0 || c.pad_y < 0) return false;

@@ -1319,9 +1319,9 @@ bool gemm_select(const GemmShape& g, int in_dtype, GemmLaunch* l, stripe_block_i
   return true;
 }
 
-// M and N that are not multiples of 128 on the 128-wide tiles; a STRIPE_TUNE that picks other variants leaves them to the large ones.
+// M and N that are not multiples of 128 on the 128-wide tiles.
 // Not at the few rows (M <= 32) that the few-rows kernel is priced against: three quarters of the tile would be padding.
-static bool t128_takes_ragged(const GemmShape& g) { return g.M > 32 && tune_int("gemm_t128_ragged", std::getenv("STRIPE_TUNE") == nullptr) && tune_int("gemm_t128_waves", 8) != 4; }
+static bool t128_takes_ragged(const GemmShape& g) { return g.M > 32 && tune_int("gemm_t128_ragged", !tune_sets("gemm_")) && tune_int("gemm_t128_waves", 8) != 4; }
 
 static bool gemm_select_one(const GemmShape& g, int in_dtype, GemmLaunch* l, stripe_block_info_t* info) {
   if (in_dtype == STRIPE_I8) {

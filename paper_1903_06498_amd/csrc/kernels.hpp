@@ -22,6 +22,16 @@ inline int tune_int(const char* key, int dflt) {
     if ((f == s || f[-1] == ',') && f[n] == '=') return std::atoi(f + n + 1);
   return dflt;
 }
+// Whether it sets a knob of that family of kernels (a key that begins so).  Rules that take a family's blocks elsewhere are off by
+// default where it does, so that the variants it picks run.
+inline bool tune_sets(const char* family) {
+  const size_t n = std::strlen(family);
+  for (const char* f = std::getenv("STRIPE_TUNE"); f; f = std::strchr(f, ',')) {
+    if (*f == ',') ++f;
+    if (std::strncmp(f, family, n) == 0) return true;
+  }
+  return false;
+}
 
 // ---- generic affine-index contraction (any legal block) -------------------
 hipError_t launch_generic(const Plan& plan, const void* in0, const void* in1, void* out, hipStream_t stream);

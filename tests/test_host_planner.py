@@ -368,3 +368,15 @@ def test_few_input_channels_where_their_kernel_is_the_faster_one(N, H, Ci, Co, R
     b = B.StripeBlock(W.conv2d_block(N, H, H, Ci, Co, R, R, stride, 0 if R == 2 else R // 2, dt, "i32" if dt == "i8" else "f32"))
     assert b.info["kernel"].startswith("conv_few_" if few else "contract_"), b.info["kernel"]
     b.close()
+
+
+@pytest.mark.parametrize("tune", ["", "pool_ty=2", "pool_nt=1,generic_i64=0", "fuse=1"])
+def test_a_knob_of_one_family_leaves_the_others_alone(tune, monkeypatch):
+    """A ragged product on 128-wide tiles, a first layer of an image network, a product and a convolution of few tiles on the contraction."""
+    blocks = [W.matmul_block(2000, 2048, 2048, "i8", "i32", b_transposed=True), W.conv2d_block(8, 224, 224, 3, 64, 7, 7, 2, 3, "bf16", "f32"),
+              W.matmul_block(6, 1536, 768, "bf16", "f32"), W.conv2d_block(3, 42, 42, 256, 9, 7, 7, 1, 3, "i8", "i32")]
+    monkeypatch.delenv("STRIPE_TUNE", raising=False)
+    want = [B.StripeBlock(b).info["kernel"] for b in blocks]
+    assert [w.split("_")[0] for w in want] == ["gemm", "conv", "contract", "contract"] and "128x128" in want[0] and "conv_few" in want[1], want
+    monkeypatch.setenv("STRIPE_TUNE", tune)
+    assert [B.StripeBlock(b).info["kernel"] for b in blocks] == want
