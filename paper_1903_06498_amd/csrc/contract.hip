@@ -813,11 +813,18 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
   store_fragments<T, FM, FN, 1>(again ? args.p : p, again ? args.o : O, again ? args.bias : bias, o_base, rows, wm * (BM / WM), wn * (BN / WN), 0, lane, acc);
 }
 
+// Order of a wavefront's memory accesses, for the compiler: no instruction.
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Few tiles: the tile's NW wavefronts share its reduction out.  Each stages its own K tiles, every NW-th, through its own part of
 // LDS and multiplies them into its own BM x BN sums, which meet at the end: no barrier inside the reduction, so that loads, LDS and
 // matrix instructions of different wavefronts overlap.  (Four wavefronts that stage K tiles for each other were bound by that
 // chain, barrier to barrier: without its loads or its matrix instructions their loop took the same time.)  A wavefront's LDS
-// instructions execute in order, so a K tile may be written over the one before without a wait.
+// instructions execute in order, so a K tile may be written over the one before without a wait; wave_order() keeps the compiler,
+// which looks at one lane at a time, from moving a lane's reads and writes across each other.
 // PLAIN: a product with one index per side and no tests, whose addresses need no tables.
 // Measured, us (before: four wavefronts per tile): 56 x 64 x 4080 nt bf16 9.3 -> 5.4 (16 x 16), 400 x 500 x 3000 nt bf16 11.5 -> 8.3
 // and [k][m] 14.2 -> 10.9 (32 x 32), 1000 x 1000 x 3000 [k][m] bf16 48.5 -> 20, 1000^3 fp32 39 -> 25 (64 x 64).
@@ -871,6 +878,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void contract_waves_kernel(const C
           const KPart k = k_part(p, (t + x / ENTRIES * NW) * BK + (a ? y * SA::SPAN : (y - SA::ENTRIES) * SB::SPAN), a);
           if (x < TABLES * ENTRIES) tables[wave][x] = (i32x4){k.off, k.t0, k.t1, k.run};
         }
+        wave_order();
       }
       const i32x4* ks = &tables[wave][it * ENTRIES];
       sa.load(p, buf_a, rows_a, row_a, ks, t * BK, lane);
@@ -910,9 +918,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void contract_waves_kernel(const C
 #pragma unroll
   for (int j = 0; j < FN; ++j) at_b[j] = SB::first(j * 16, lane);
   for (uint32_t t = wave; t < n_kt; t += NW) {
+    wave_order();      // the fragments of the K tile before are read
     fin &= sa.store(p, mine_a, t * BK, look, lane);
     fin &= sb.store(p, mine_b, t * BK, look, lane);
     load(t + NW);
+    wave_order();
     __builtin_amdgcn_sched_barrier(0);
     u32x4 fa[STEPS][FM], fb[STEPS][FN];
 #pragma unroll
