@@ -8,7 +8,7 @@ import torch
 
 from paper_1903_06498_amd import binding as B
 from paper_1903_06498_amd import workloads as W
-from tests.util import parity, run_gpu
+from tests.util import SENTINEL_F, SENTINEL_I, parity, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -104,3 +104,54 @@ def test_sums_are_short_chains(shape, dt, most, monkeypatch):
     want = torch.nn.functional.conv2d(x.double().permute(0, 3, 1, 2), f.double().permute(2, 3, 0, 1), stride=s, padding=p).permute(0, 2, 3, 1).numpy()
     err = np.linalg.norm(got.reshape(want.shape) - want) / np.linalg.norm(want)
     assert err <= most, err
+
+
+@pytest.mark.parametrize("dt", ["bf16", "i8", "f32"])
+@pytest.mark.parametrize("Ci,extra", [(3, 1), (2, 0), (2, 3), (4, 3)])
+def test_windows_of_larger_tensors(Ci, extra, dt, monkeypatch):
+    """Image, filter and output as windows: pixels `extra` channels further apart, longer rows, origins and ends inside the parents.
+    What lies beside the windows (NaN; int8: 127) is read by no sum, what lies beside the output stays: the same bits as from dense
+    tensors, which the oracle is asked about too."""
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1,conv_few=2")
+    odt = "i32" if dt == "i8" else "f32"
+    N, H, Wd, Co, R, S = 2, 11, 21, 22, 3, 5
+    dense_ins = [W.seeded_tensor((N, H, Wd, Ci), dt, 0), W.seeded_tensor((R, S, Co, Ci), dt, 1)]
+    dense = W.conv2d_block(N, H, Wd, Ci, Co, R, S, 2, 1, dt, odt)
+    info, _ = parity(dense, dense_ins, what=f"dense {Ci} {dt}")
+    want, sb = run_gpu(dense, dense_ins, return_block=True)
+    sb.close()
+    block = W.conv2d_block(N, H, Wd, Ci, Co, R, S, 2, 1, dt, odt)
+    osz = block.refs[2].sizes
+    parents = [(N + 1, H + 3, Wd + 5, Ci + extra), (R + 1, S + 2, Co + 3, Ci + extra), (N + 1, osz[1] + 2, osz[2] + 1, Co + 6)]
+    W.embed(block, [(1, 2, 3, extra // 2), (1, 1, 2, extra // 2), (0, 1, 1, 4)], parents)
+    ins = []
+    for r, t, sizes in zip(block.refs, dense_ins, parents):
+        big = torch.full(sizes, 127 if dt == "i8" else math.nan, dtype=t.dtype)
+        big[tuple(slice(c, c + n) for c, n in zip(r.access_const, r.sizes))] = t
+        ins.append(big)
+    got, sb = run_gpu(block, ins, return_block=True)
+    assert sb.info["kernel"] == info["kernel"] and sb.info["kernel"].startswith("conv_few_"), (sb.info["kernel"], info["kernel"])
+    sb.close()
+    image = np.full(int(np.prod(parents[2])), SENTINEL_I if odt == "i32" else np.float32(SENTINEL_F), dtype=got.dtype)
+    image[:got.size] = got
+    image = image.reshape(parents[2])
+    inside = tuple(slice(c, c + n) for c, n in zip((0, 1, 1, 4), osz))
+    assert np.array_equal(image[inside], want.reshape(osz))
+    image[inside] = SENTINEL_I if odt == "i32" else np.float32(SENTINEL_F)
+    assert (image == (SENTINEL_I if odt == "i32" else np.float32(SENTINEL_F))).all()
+
+
+@pytest.mark.parametrize("dt", ["bf16", "i8", "f32"])
+@pytest.mark.parametrize("sy,sx,py,px,R,S", [(1, 3, 2, 0, 5, 3), (3, 1, 0, 3, 2, 7), (2, 1, 1, 2, 3, 4)])
+def test_asymmetric_strides_and_pads(sy, sx, py, px, R, S, dt, monkeypatch):
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1,conv_few=2")
+    N, H, Wd, Ci, Co = 2, 17, 35, 3, 37
+    Ho, Wo = (H + 2 * py - R) // sy + 1, (Wd + 2 * px - S) // sx + 1
+    bufs = [W.Buffer("I", "in", dt, (N, H, Wd, Ci)), W.Buffer("F", "in", dt, (R, S, Co, Ci)),
+            W.Buffer("O", "out", "i32" if dt == "i8" else "f32", (N, Ho, Wo, Co))]
+    ya, xa = f"{sy}*y + i - {py}", f"{sx}*x + j - {px}"
+    blk = W.flat_block(bufs, dict(n=N, y=Ho, x=Wo, i=R, j=S, c=Ci, k=Co),
+                       [(["n", ya, xa, "c"], "assign"), (["i", "j", "k", "c"], "assign"), (["n", "y", "x", "k"], "add")],
+                       constraints=[f"{ya} >= 0", f"{H - 1 + py} - {sy}*y - i >= 0", f"{xa} >= 0", f"{Wd - 1 + px} - {sx}*x - j >= 0"])
+    info, _ = parity(blk, [W.seeded_tensor((N, H, Wd, Ci), dt, 0), W.seeded_tensor((R, S, Co, Ci), dt, 1)], what=f"{sy} {sx} {py} {px} {dt}")
+    assert info["kernel"].startswith(f"conv_few_{dt}_c3"), info["kernel"]
