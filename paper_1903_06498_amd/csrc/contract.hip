@@ -1114,12 +1114,14 @@ bool fill_side(const std::vector<Ix>& v, CtIndex* c) {
 // where that kernel sums an output's points in one chain (here chains of at most 32 fp32 products, 17 on the 32 x 32 tile, and
 // fp32 totals), also where such chains meet in atomic additions, if they are as long as this kernel's (transposed 3x3, 32
 // channels, fp32: 1.08e-7 both; 8 channels: 6.6e-8 and 1.0e-7).  bf16 sums run through chains of up to 256 products.
-static bool wants_double(int dtype, int tile, const LiteralSums& lit) {
+// few: fewer than 96 tiles of 64 x 64.  There fp32 reductions of 9 to 16, one step of 16 products, run as the two chains of eight of
+// the form with totals in double on every tile, as on the 32 x 32 one: half the roundings in a row for no time (a launch is most of it).
+static bool wants_double(int dtype, int tile, bool few, const LiteralSums& lit) {
   if (dtype == STRIPE_I8) return false;
   if (lit.lanes == 64) return true;
   if (dtype == STRIPE_BF16) return lit.atomic;
   if (lit.atomic) return tile == 0 || tile == 3 || lit.chain < (tile == 1 ? 32 : 17);
-  return tile == 2 && lit.chain > 8 && lit.chain < 17;
+  return (tile == 2 || few) && lit.chain > 8 && lit.chain < 17;
 }
 
 // Time of a block on tile t: a launch, per round of workgroups a fixed part and one for each K tile in a row -- all of them where
@@ -1530,7 +1532,7 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, Co
   const bool simple = m.size() <= 1 && n.size() == 1 && k.size() == 1 && !p.tested;      // a product
   l->plain = simple && (p.mode_a == 1 || p.mode_a == 2) && (p.mode_b == 1 || p.mode_b == 2);
   // A bf16 output's own rounding hides the sums'.
-  auto precise_on = [&](int t) { return !fb.out_bf16 && wants_double(dt, t, lit); };
+  auto precise_on = [&](int t) { return !fb.out_bf16 && wants_double(dt, t, tiles(1) < 96, lit); };
   auto runs = [&](int t) {
     if (t == 3 && p.mode_b == 2 && esize < 4) return false;
     if (t == 5 && !l->plain) return false;

@@ -615,3 +615,33 @@ def test_ragged_products_sum_in_short_chains(M, N, K, layout, most):
     want = a.double() @ (b.double().t() if layout == "nt" else b.double()).contiguous()
     err = float((out.double() - want).norm() / want.norm())
     assert err <= most, err
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "i8"])
+@pytest.mark.parametrize("M,N,K,tile,lanes", [(129, 2100, 289, 5, 512), (70, 4100, 1025, 5, 512), (63, 65, 33, 5, 512), (9, 300, 2100, 2, 512), (19, 33, 4100, 4, 1024)])
+def test_long_products_whose_reduction_wavefronts_share(M, N, K, tile, lanes, dt, monkeypatch):
+    """Both operands k-contiguous, K tiles beyond one per wavefront and a partial last one, on the kernel whose wavefronts stage for
+    themselves (its workgroup tells it from the one whose four wavefronts share a K tile)."""
+    monkeypatch.setenv("STRIPE_TUNE", f"contract_min=1,contract_tile={tile},gemm_rows=0,gemm_dma=0")
+    blk = matmul(M, N, K, dt, "nt")
+    info, _ = parity(blk, [W.seeded_tensor((M, K), dt, 0), W.seeded_tensor((N, K), dt, 1)], what=f"{M}x{N}x{K} {dt}", threads=8)
+    assert info["kernel"].startswith(f"contract_{dt}_") and info["workgroup_size"] == lanes, info
+
+
+@pytest.mark.parametrize("layout,M,N,K,dt,most", [("nt", 200, 300, 16, "f32", 6.7e-8), ("nn", 500, 200, 12, "f32", 5.9e-8), ("tn", 300, 700, 9, "f32", 5.3e-8)])
+def test_short_fp32_reductions_are_two_chains(layout, M, N, K, dt, most):
+    """9 to 16 fp32 products in one chain are 7.3e-8, 6.4e-8 and 5.6e-8 off in the 2-norm at these sizes, as two chains of eight
+    6.0e-8, 5.4e-8 and 5.0e-8."""
+    error_at_most(layout, M, N, K, dt, most)
+
+
+def error_at_most(layout, M, N, K, dt, most):
+    g = torch.Generator().manual_seed(5)
+    a, b = (torch.randn(n, generator=g).to(torch.bfloat16 if dt == "bf16" else torch.float32) for n in ((M, K), (K, N)))
+    ins = [a.t().contiguous() if layout == "tn" else a, b.t().contiguous() if layout == "nt" else b]
+    got, sb = run_gpu(matmul(M, N, K, dt, layout), ins, return_block=True)
+    assert sb.info["kernel"].startswith("contract_"), sb.info["kernel"]
+    sb.close()
+    want = (a.double() @ b.double()).numpy()
+    err = np.linalg.norm(got.reshape(want.shape) - want) / np.linalg.norm(want)
+    assert err <= most, (err, most)
