@@ -431,6 +431,19 @@ __device__ __forceinline__ void put(const ContractParams& p, void* O, const floa
   ((S*)O)[off] = v;
 }
 
+// LDS of a workgroup in bytes, as the two kernels below declare it: staging buffers, row tables, k tables.
+constexpr int k_entries(int esize, int bkb, int mode) { return bkb / (mode == 1 ? 16 : mode == 3 ? 8 : esize); }
+constexpr int shared_lds_bytes(int esize, int bm, int bn, int bkb, int mode_a, int mode_b) {
+  const int entries = k_entries(esize, bkb, mode_a) + k_entries(esize, bkb, mode_b), batch = 8 * entries <= 256 ? 8 : 4 * entries <= 256 ? 4 : 2 * entries <= 256 ? 2 : 1;
+  return (bm + bn) * (2 * bkb + 24) + 2 * batch * entries * 16;
+}
+constexpr int waves_lds_bytes(int esize, int waves, int bm, int bn, int bkb, int mode_a, int mode_b, bool precise, bool plain) {
+  const int stage = waves * (bm + bn) * bkb, part = (waves - 1) * bm * bn * (precise ? 8 : 4), bkb_again = 16 * 64 * waves / bm;
+  const int again = plain || esize == 1 ? 0 : (bm + bn) * bkb_again + 2 * bkb_again / esize * 16, most = stage > part ? stage : part;
+  const int entries = k_entries(esize, bkb, mode_a) + k_entries(esize, bkb, mode_b), tables = 4 * entries <= 64 ? 4 : 2 * entries <= 64 ? 2 : 1;
+  return (most > again ? most : again) + (bm + bn) * 24 + (plain ? 0 : waves * tables * entries * 16);
+}
+
 // What every kernel below does first: the row tables of its tile.
 struct TileRows {
   i32x4 *a, *b;      // {input offset, range-test values, output offset}
@@ -665,6 +678,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
   constexpr uint32_t BATCH = 8 * ENTRIES <= 256 ? 8 : 4 * ENTRIES <= 256 ? 4 : 2 * ENTRIES <= 256 ? 2 : 1;
   __shared__ i32x4 ks_a[2 * BATCH][SA::ENTRIES], ks_b[2 * BATCH][SB::ENTRIES];
   static_assert(2 * BUF >= BUF + (int)ENTRIES * 16, "room for the tables of sum_again");
+  static_assert(sizeof lds + sizeof rows_a + sizeof rows_b + sizeof ob_m + sizeof ob_n + sizeof ks_a + sizeof ks_b == shared_lds_bytes(sizeof(T), BM, BN, BKB, MA, MB), "LDS");
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint32_t m0 = blockIdx.x / (uint32_t)p.tiles_n * BM, n0 = blockIdx.x % (uint32_t)p.tiles_n * BN;
@@ -847,6 +861,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void contract_waves_kernel(const C
   __shared__ i32x4 rows_a[BM], rows_b[BN];
   __shared__ int2 ob_m[BM], ob_n[BN];
   __shared__ i32x4 tables[PLAIN ? 1 : NW][PLAIN ? 1 : TABLES * ENTRIES];
+  static_assert(LDS + sizeof rows_a + sizeof rows_b + sizeof ob_m + sizeof ob_n + (PLAIN ? 0 : sizeof tables) == waves_lds_bytes(sizeof(T), NW, BM, BN, BKB, MA, MB, PRECISE, PLAIN), "LDS");
   const TileRows rows = {rows_a, rows_b, ob_m, ob_n};
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t m0 = blockIdx.x / (uint32_t)p.tiles_n * BM, n0 = blockIdx.x % (uint32_t)p.tiles_n * BN;
@@ -1565,7 +1580,9 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, Co
   info->tile_m = kTiles[tile].bm; info->tile_n = kTiles[tile].bn; info->tile_k = bkb / esize;
   info->frag_m = info->frag_n = 16;
   info->frag_k = dt == STRIPE_F32 ? 4 : 64 / esize;
-  info->lds_bytes = (kTiles[tile].bm + kTiles[tile].bn) * (bkb * (kTiles[tile].lanes > 256 ? kTiles[tile].lanes / 64 : 2) + 24);
+  const Tile& kt = kTiles[tile];
+  info->lds_bytes = kt.lanes > 256 ? waves_lds_bytes(esize, kt.lanes / 64, kt.bm, kt.bn, bkb, p.mode_a, p.mode_b, l->precise, l->plain)
+                                   : shared_lds_bytes(esize, kt.bm, kt.bn, bkb, p.mode_a, p.mode_b);
   info->workgroup_size = kTiles[tile].lanes;
   info->grid = l->grid * l->batch;
   std::snprintf(info->kernel, sizeof info->kernel, "contract_%s_%dx%dx%d_fetch%d%d%s", dt == STRIPE_F32 ? "f32" : dt == STRIPE_BF16 ? "bf16" : "i8",

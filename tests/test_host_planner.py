@@ -380,3 +380,14 @@ def test_a_knob_of_one_family_leaves_the_others_alone(tune, monkeypatch):
     assert [w.split("_")[0] for w in want] == ["gemm", "conv", "contract", "contract"] and "128x128" in want[0] and "conv_few" in want[1], want
     monkeypatch.setenv("STRIPE_TUNE", tune)
     assert [B.StripeBlock(b).info["kernel"] for b in blocks] == want
+
+
+@pytest.mark.parametrize("M,N,K,dt,layout,lds", [(1000, 1000, 3000, "bf16", "tn", 7 * 64 * 64 * 4 + 128 * 24),       # the sums on their way to each other are the most
+                                                 (56, 64, 4080, "bf16", "nt", 16 * 32 * 256 + 32 * 24)])             # K tiles of 16 wavefronts
+def test_lds_of_the_general_contraction(M, N, K, dt, layout, lds):
+    """What its kernels declare: it decides how many workgroups a CU holds."""
+    bufs = [W.Buffer("A", "in", dt, (K, M) if layout == "tn" else (M, K)), W.Buffer("B", "in", dt, (N, K) if layout == "nt" else (K, N)), W.Buffer("C", "out", "f32", (M, N))]
+    b = B.StripeBlock(W.flat_block(bufs, dict(m=M, n=N, k=K), [(["k", "m"] if layout == "tn" else ["m", "k"], "assign"),
+                                                               (["n", "k"] if layout == "nt" else ["k", "n"], "assign"), (["m", "n"], "add")]))
+    assert b.info["kernel"].startswith("contract_") and b.info["lds_bytes"] == lds, b.info
+    b.close()
