@@ -724,10 +724,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
 
   // bf16 / fp32: partial sums over FLUSH K tiles start from zero and are added to the total, short chains of roundings
   // instead of one long one (not on the largest tile, whose registers hold one set of sums at two wavefronts per SIMD)
-  // fp32 on the 64 x 64 tile: a sum for the even steps and one for the odd ones, 16 products each (one sum: 1.2 times the error of
+  // On the 64 x 64 tile a sum for the even steps and one for the odd ones, 16 (fp32) or 32 (bf16) products each (fp32, one sum: 1.2 times the error of
   // 32 x 32 tiles at 29 x 29, 64 -> 64, transposed 2x2, 0.8 times now, for 2 % of the time).  Where the fetch by elements holds the registers, one:
-  // 6 x 49 x 49, 11 -> 72, 5x5 took 36 us instead of 27.
-  constexpr int SUMS = std::is_same<T, float>::value && BM * BN <= 4096 && MA != 3 && MB != 3 ? 2 : 1;
+  // 6 x 49 x 49, 11 -> 72, 5x5 took 36 us instead of 27.  So do two bf16 operands along their rows: 1501 x 832 x 598 [k][m] 14.9 us instead of 13.0.
+  constexpr int SUMS = sizeof(T) > 1 && STEPS > 1 && BM * BN <= 4096 && MA != 3 && MB != 3 && !(sizeof(T) == 2 && MA == 2 && MB == 2) ? 2 : 1;
   constexpr uint32_t FLUSH = BM * BN > 8192 ? 0xffffffffu : std::is_same<T, float>::value ? 1 : std::is_same<T, uint16_t>::value ? 4 : 0xffffffffu;
   Acc sum[SUMS][FM][FN];
 #pragma unroll
@@ -947,7 +947,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void contract_waves_kernel(const C
 #pragma unroll
       for (int j = 0; j < FN; ++j) fb[s][j] = SB::fragment(mine_b, at_b[j], s);
     }
-    // float types: sums that start from zero join the total, of 16 products (fp32) or of a K tile's 32 to 128 (bf16)
+    // float types: sums that start from zero join the total, of 16 products (fp32) or of 32, the K tile's one to four in pairs (bf16)
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -962,10 +962,14 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void contract_waves_kernel(const C
 #pragma unroll
           for (int s = 0; s < STEPS; ++s) acc[i][j] += Ct<T>::mma(fb[s][j], fa[s][i], (Acc){0, 0, 0, 0});
         } else {
-          Acc sum = (Acc){0, 0, 0, 0};
+          Acc sum[STEPS];
 #pragma unroll
-          for (int s = 0; s < STEPS; ++s) sum = Ct<T>::mma(fb[s][j], fa[s][i], sum);
-          acc[i][j] += sum;
+          for (int s = 0; s < STEPS; ++s) sum[s] = Ct<T>::mma(fb[s][j], fa[s][i], (Acc){0, 0, 0, 0});
+#pragma unroll
+          for (int h = STEPS / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int s = 0; s < h; ++s) sum[s] += sum[s + h];
+          acc[i][j] += sum[0];
         }
       }
   }
