@@ -672,8 +672,9 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
       if (!forced && !(p.is_gemm && gemm_rows_select(p.gemm, p.in_dtype, __builtin_huge_val(), &blk->rows, &p.info))) {
         contract_select(p.flat, literal_sums(p), false, &blk->contract, &p.info);
         // Few input channels: faster than the general contraction (7x7 stride 2, 3 -> 64, bf16, 8 x 224 x 224: 34 us there), with fp32
-        // chains as long as its own: not where the literal kernel holds 64 sums per output and the contraction totals in double precision.
-        if (blk->contract.use && p.is_conv && (!blk->contract.precise || tune_int("conv_few", 1) == 2) && conv_few_select(p.conv, p.in_dtype, 4, blk->contract.us, &blk->few, &p.info)) blk->contract.use = false;
+        // chains as short as its own (two of eight for 9 to 16 products): not where the literal kernel holds 64 sums per output, for which the
+        // contraction totals in double precision.
+        if (blk->contract.use && p.is_conv && (!blk->contract.precise || literal_sums(p).lanes < 64 || tune_int("conv_few", 1) == 2) && conv_few_select(p.conv, p.in_dtype, 4, blk->contract.us, &blk->few, &p.info)) blk->contract.use = false;
       }
     } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM &&
                gemm_rows_select(p.gemm, p.in_dtype, gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm), &blk->rows, &p.info)) {

@@ -391,3 +391,11 @@ def test_lds_of_the_general_contraction(M, N, K, dt, layout, lds):
                                                                (["n", "k"] if layout == "nt" else ["k", "n"], "assign"), (["m", "n"], "add")]))
     assert b.info["kernel"].startswith("contract_") and b.info["lds_bytes"] == lds, b.info
     b.close()
+
+
+@pytest.mark.parametrize("N,H,Ci,Co,R,stride", [(1, 20, 4, 16, 2, 1), (2, 35, 3, 32, 2, 1), (4, 35, 4, 64, 2, 2), (2, 49, 3, 64, 3, 1), (7, 19, 3, 48, 3, 2)])
+def test_few_input_channels_and_a_short_fp32_reduction(N, H, Ci, Co, R, stride):
+    """12 or 16 products, which both kernels sum as two chains of eight, and 27: on the one for few input channels."""
+    b = B.StripeBlock(W.conv2d_block(N, H, H, Ci, Co, R, R, stride, 0 if R == 2 else R // 2, "f32", "f32"))
+    assert b.info["kernel"].startswith("conv_few_"), b.info["kernel"]
+    b.close()
