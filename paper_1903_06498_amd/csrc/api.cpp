@@ -97,6 +97,10 @@ LiteralSums literal_sums(const Plan& p) {
   return {p.tiled.use ? 1 : p.gen.lanes, p.gen.red_total, p.gen.n_red, p.gen.n_outputs, p.gen.atomic != 0, p.tiled.use != 0};
 }
 
+// What the few-channels convolution is compared with.  Its line was drawn against estimates of the contraction that lie a microsecond
+// above its time at short reductions; those of tile 6 do not (2 x 49 x 49, 3 -> 64, 3x3, fp32: 6.4 us there, 7.9 on that tile).
+double us_for_few(const ContractLaunch& c) { return c.us + (c.tile == 6 ? 1.0 : 0.0); }
+
 // A root block with a statement list (Section 3.2: statements execute as if in serial): every statement is planned
 // as a block of its own over the root buffers it names; temporaries of the root live in memory the handle owns.
 stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t path, stripe_block_t** out) {
@@ -340,7 +344,7 @@ stripe_status_t create_program(const stripe_block_desc_t* root, stripe_path_t pa
       // the few-channels convolution where the contraction would fuse (the checks of the second statement are the same); below 2048
       // output pixels both take less than a call costs its caller (3.5 and 5 us)
       if (few.use) ct_info = c.info;
-      else if (ct.use && c.is_conv && c.conv.N * c.conv.Ho * c.conv.Wo >= 2048 && (root->refs[R - 1].dtype == STRIPE_BF16 || tune_int("conv_few", 1) == 2)) conv_few_select(c.conv, c.in_dtype, root->refs[R - 1].dtype == STRIPE_BF16 ? 2 : 4, ct.us, &few, &ct_info);
+      else if (ct.use && c.is_conv && c.conv.N * c.conv.Ho * c.conv.Wo >= 2048 && (root->refs[R - 1].dtype == STRIPE_BF16 || tune_int("conv_few", 1) == 2)) conv_few_select(c.conv, c.in_dtype, root->refs[R - 1].dtype == STRIPE_BF16 ? 2 : 4, us_for_few(ct), &few, &ct_info);
     }
     // Few rows and a reduction long enough to be split, with an fp32 output: the few-rows kernel's, whose totals are in double precision,
     // or the contraction's with such totals, whichever is faster (12 x 320 x 8192: 14.6 us there, 8.4 here).  A bf16 output's own rounding
@@ -674,7 +678,7 @@ stripe_status_t create_single(const stripe_block_desc_t* desc, stripe_path_t pat
         // Few input channels: faster than the general contraction (7x7 stride 2, 3 -> 64, bf16, 8 x 224 x 224: 34 us there), with fp32
         // chains as short as its own (two of eight for 9 to 16 products): not where the literal kernel holds 64 sums per output, for which the
         // contraction totals in double precision.
-        if (blk->contract.use && p.is_conv && (!blk->contract.precise || literal_sums(p).lanes < 64 || tune_int("conv_few", 1) == 2) && conv_few_select(p.conv, p.in_dtype, 4, blk->contract.us, &blk->few, &p.info)) blk->contract.use = false;
+        if (blk->contract.use && p.is_conv && (!blk->contract.precise || literal_sums(p).lanes < 64 || tune_int("conv_few", 1) == 2) && conv_few_select(p.conv, p.in_dtype, 4, us_for_few(blk->contract), &blk->few, &p.info)) blk->contract.use = false;
       }
     } else if (!forced && p.info.path == STRIPE_PATH_MFMA_GEMM &&
                gemm_rows_select(p.gemm, p.in_dtype, gemm_few_rows_us(p.gemm, p.in_dtype, blk->gemm), &blk->rows, &p.info)) {

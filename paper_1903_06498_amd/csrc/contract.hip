@@ -648,8 +648,35 @@ __device__ __forceinline__ void sum_again(const KernelArgs& args, const TileRows
   }
 }
 
+// The sums of NW wavefronts that share a tile's reduction out: fragment f is stored by wavefront f % NW, the others' sums reach it
+// through LDS and are added in pairs (one after the other: 1.2 times the error at 5 x 88 x 1520 bf16).
+template <int NW, int FM, int FN, typename Total>
+__device__ __forceinline__ void meet(Total (&acc)[FM][FN], unsigned char* lds, int wave, int lane) {
+  constexpr int NF = FM * FN;
+  Total* part = (Total*)lds + lane;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const int owner = f % NW;
+    if (wave != owner) part[((wave < owner ? wave : wave - 1) * NF + f) * 64] = acc[f / FN][f % FN];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+    if (wave == f % NW) {
+      Total sums[NW];
+#pragma unroll
+      for (int w = 0; w < NW - 1; ++w) sums[w] = part[(w * NF + f) * 64];
+      sums[NW - 1] = acc[f / FN][f % FN];
+#pragma unroll
+      for (int h = NW / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int w = 0; w < h; ++w) sums[w] += sums[w + h];
+      acc[f / FN][f % FN] = sums[0];
+    }
+}
+
 // Many tiles: BM x BN tile shared by four wavefronts, K tiles of BKB bytes per row staged for all of them; WM x WN wavefronts
-// over the tile.
+// over the tile, or (32 x 32) all four over the tile and every fourth 64-byte step of a K tile, their sums meeting at the end.
 // PRECISE (float types): the products of one 64-byte step are summed from zero and join a total in double precision.  For blocks
 // whose literal kernel holds several sums per output (see wants_double): against it, fp32 totals had 1.1 to 1.5 times the error
 // in 64 bits (K of 64 to 33000), totals in double 0.7 to 0.99 times.  They cost up to 15 % (250 x 250 x 1001 nt fp32 20.1 -> 23.3
@@ -662,8 +689,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
   using S = typename Ct<T>::S;
   using SA = Stager<T, 256, BM, BKB, true, MA>;
   using SB = Stager<T, 256, BN, BKB, false, MB>;
-  static_assert(WM * WN == 4, "four wavefronts");
-  constexpr int STEPS = BKB / 64, FM = BM / WM / 16, FN = BN / WN / 16;
+  constexpr int WK = 4 / (WM * WN), STEPS = BKB / 64 / WK, FM = BM / WM / 16, FN = BN / WN / 16;
   constexpr int BUF = (BM + BN) * BKB;
   using Total = typename std::conditional<PRECISE, f64x4, Acc>::type;
   __shared__ __align__(16) unsigned char lds[2 * BUF];
@@ -715,12 +741,17 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
   const bool look = p.tested && std::is_same<S, float>::value;
   bool fin = true;
 
-  const int wm = wave / WN, wn = wave % WN;
-  Total acc[FM][FN];
+  static_assert(WM * WN * WK == 4 && (WK == 1 || WK == 4) && STEPS * WK * 64 == BKB, "four wavefronts, over the tile or over a K tile");
+  const int wk = WK == 1 ? 0 : wave, wm = WK == 1 ? wave / WN : 0, wn = WK == 1 ? wave % WN : 0;
+  // Where the wavefronts share a K tile, one total for the even ones and one for the odd ones: chains of totals half as long, as short
+  // as with eight wavefronts that stage for themselves (4 x 32 x 32, 128 -> 192, 3x3, fp32: 1.05e-7 off with one, 9.4e-8 there).
+  constexpr int TOTALS = WK > 1 && !PRECISE && sizeof(T) > 1 ? 2 : 1;
+  Total totals[TOTALS][FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = (Total){0, 0, 0, 0};
+    for (int j = 0; j < FN; ++j) totals[0][i][j] = totals[TOTALS - 1][i][j] = (Total){0, 0, 0, 0};
+  Total(&acc)[FM][FN] = totals[0];
 
   // bf16 / fp32: partial sums over FLUSH K tiles start from zero and are added to the total, short chains of roundings
   // instead of one long one (not on the largest tile, whose registers hold one set of sums at two wavefronts per SIMD)
@@ -728,20 +759,20 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
   // 32 x 32 tiles at 29 x 29, 64 -> 64, transposed 2x2, 0.8 times now, for 2 % of the time).  Where the fetch by elements holds the registers, one:
   // 6 x 49 x 49, 11 -> 72, 5x5 took 36 us instead of 27.  So do two bf16 operands along their rows: 1501 x 832 x 598 [k][m] 14.9 us instead of 13.0.
   constexpr int SUMS = sizeof(T) > 1 && STEPS > 1 && BM * BN <= 4096 && MA != 3 && MB != 3 && !(sizeof(T) == 2 && MA == 2 && MB == 2) ? 2 : 1;
-  constexpr uint32_t FLUSH = BM * BN > 8192 ? 0xffffffffu : std::is_same<T, float>::value ? 1 : std::is_same<T, uint16_t>::value ? 4 : 0xffffffffu;
+  constexpr uint32_t FLUSH = BM * BN > 8192 ? 0xffffffffu : std::is_same<T, float>::value || TOTALS == 2 ? 1 : std::is_same<T, uint16_t>::value ? 4 : 0xffffffffu;
   Acc sum[SUMS][FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j) sum[0][i][j] = sum[SUMS - 1][i][j] = (Acc){0, 0, 0, 0};
-  auto flush = [&]() {
+  auto flush = [&](Total (&to)[FM][FN]) {
     if constexpr (!PRECISE) {
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-          if constexpr (SUMS == 1) acc[i][j] += sum[0][i][j];
-          else acc[i][j] += sum[0][i][j] + sum[1][i][j];
+          if constexpr (SUMS == 1) to[i][j] += sum[0][i][j];
+          else to[i][j] += sum[0][i][j] + sum[1][i][j];
           sum[0][i][j] = sum[SUMS - 1][i][j] = (Acc){0, 0, 0, 0};
         }
     }
@@ -781,9 +812,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
     for (int s = 0; s < STEPS; ++s) {
       u32x4 fa[FM], fb[FN];
 #pragma unroll
-      for (int i = 0; i < FM; ++i) fa[i] = SA::fragment(base_a, at_a[i], s);
+      for (int i = 0; i < FM; ++i) fa[i] = SA::fragment(base_a, at_a[i], s * WK + wk);
 #pragma unroll
-      for (int j = 0; j < FN; ++j) fb[j] = SB::fragment(base_b, at_b[j], s);
+      for (int j = 0; j < FN; ++j) fb[j] = SB::fragment(base_b, at_b[j], s * WK + wk);
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -792,7 +823,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
           else sum[s % SUMS][i][j] = Ct<T>::mma(fb[j], fa[i], sum[s % SUMS][i][j]);
         }
     }
-    if ((t + 1) % FLUSH == 0) flush();
+    if ((t + 1) % FLUSH == 0) flush(totals[TOTALS == 2 ? S0 : 0]);
     if constexpr (decltype(stores)::value) {
       unsigned char* next = lds + (1 - S0) * BUF;
       fin &= sa[1 - S0].store(p, next, (t + 1) * BK, look, tid);
@@ -814,7 +845,13 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
   } else {
     step(t, even, no, no);
   }
-  flush();
+  flush(acc);
+  if constexpr (TOTALS == 2) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] += totals[1][i][j];
+  }
 
   constexpr bool again = sizeof(T) > 1;
   const KernelArgs& args = reread();
@@ -824,7 +861,12 @@ __global__ __launch_bounds__(256, sizeof(T) == 1 ? 1 : BM == 128 && BN == 128 ||
       return;
     }
   }
-  store_fragments<T, FM, FN, 1>(again ? args.p : p, again ? args.o : O, again ? args.bias : bias, o_base, rows, wm * (BM / WM), wn * (BN / WN), 0, lane, acc);
+  if constexpr (WK > 1) {
+    static_assert((WK - 1) * FM * FN * 64 * (int)sizeof(Total) <= 2 * BUF, "partial sums fit the staging buffers");
+    __syncthreads();
+    meet<WK>(acc, lds, wave, lane);
+  }
+  store_fragments<T, FM, FN, WK>(again ? args.p : p, again ? args.o : O, again ? args.bias : bias, o_base, rows, wm * (BM / WM), wn * (BN / WN), wk, lane, acc);
 }
 
 // Order of a wavefront's memory accesses, for the compiler: no instruction.
@@ -979,28 +1021,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void contract_waves_kernel(const C
     if constexpr (!PLAIN && sizeof(T) > 1) sum_again<T, NT, BM, BN, BKB_AGAIN, MA, MB>(args, rows, o_base, lds);
     return;
   }
-  // fragment f is stored by wavefront f % NW: the others' sums reach it through LDS and are added in pairs
-  // (one after the other: 1.2 times the error at 5 x 88 x 1520 bf16)
-  Total* part = (Total*)lds + lane;
-#pragma unroll
-  for (int f = 0; f < NF; ++f) {
-    const int owner = f % NW;
-    if (wave != owner) part[((wave < owner ? wave : wave - 1) * NF + f) * 64] = acc[f / FN][f % FN];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int f = 0; f < NF; ++f)
-    if (wave == f % NW) {
-      Total sums[NW];
-#pragma unroll
-      for (int w = 0; w < NW - 1; ++w) sums[w] = part[(w * NF + f) * 64];
-      sums[NW - 1] = acc[f / FN][f % FN];
-#pragma unroll
-      for (int h = NW / 2; h > 0; h /= 2)
-#pragma unroll
-        for (int w = 0; w < h; ++w) sums[w] += sums[w + h];
-      acc[f / FN][f % FN] = sums[0];
-    }
+  meet<NW>(acc, lds, wave, lane);
   store_fragments<T, FM, FN, NW>(args.p, args.o, args.bias, o_base, rows, 0, 0, wave, lane, acc);
 }
 
@@ -1041,6 +1062,9 @@ hipError_t launch_modes(const ContractLaunch& l, const ContractParams& p, const 
     case 5:
       if constexpr (vectors) return go(contract_waves_kernel<T, 8, 64, 64, 64, MA, MB, false, true>, 512);
       else return hipErrorInvalidValue;
+    case 6:
+      if constexpr (real) if (l.precise) return go(contract_kernel<T, 32, 32, 256, 1, 1, MA, MB, true>, 256);
+      return go(contract_kernel<T, 32, 32, 256, 1, 1, MA, MB, false>, 256);
     default:
       if constexpr (vectors) {
         if (l.plain) {
@@ -1094,11 +1118,11 @@ namespace {
 
 typedef __int128 i128;
 
-// 0, 1, 3: shared by four wavefronts; 2, 4, 5: the wavefronts share the reduction out
+// 0, 1, 3, 6: staged for four wavefronts; 2, 4, 5: the wavefronts share the reduction out and stage for themselves
 struct Tile {
   int bm, bn, bkb, lanes;
 };
-constexpr Tile kTiles[] = {{128, 128, 64, 256}, {64, 64, 128, 256}, {32, 32, 128, 512}, {128, 64, 64, 256}, {16, 16, 256, 1024}, {64, 64, 64, 512}};
+constexpr Tile kTiles[] = {{128, 128, 64, 256}, {64, 64, 128, 256}, {32, 32, 128, 512}, {128, 64, 64, 256}, {16, 16, 256, 1024}, {64, 64, 64, 512}, {32, 32, 256, 256}};
 
 struct Ix {                      // one index: range, address coefficients, constraint coefficients, output-bound coefficients
   int64_t range = 1, a = 0, b = 0, o = 0;
@@ -1130,17 +1154,17 @@ bool fill_side(const std::vector<Ix>& v, CtIndex* c) {
 }  // namespace
 
 // Whether totals in double precision are needed for an error no larger than the literal kernel's.  It is not larger anyway
-// where that kernel sums an output's points in one chain (here chains of at most 32 fp32 products, 17 on the 32 x 32 tile, and
+// where that kernel sums an output's points in one chain (here chains of at most 32 fp32 products, 17 on the 32 x 32 tiles, and
 // fp32 totals), also where such chains meet in atomic additions, if they are as long as this kernel's (transposed 3x3, 32
 // channels, fp32: 1.08e-7 both; 8 channels: 6.6e-8 and 1.0e-7).  bf16 sums run through chains of up to 256 products.
 // few: fewer than 96 tiles of 64 x 64.  There fp32 reductions of 9 to 16, one step of 16 products, run as the two chains of eight of
-// the form with totals in double on every tile, as on the 32 x 32 one: half the roundings in a row for no time (a launch is most of it).
+// the form with totals in double on every tile, as on the 32 x 32 ones: half the roundings in a row for no time (a launch is most of it).
 static bool wants_double(int dtype, int tile, bool few, const LiteralSums& lit) {
   if (dtype == STRIPE_I8) return false;
   if (lit.lanes == 64) return true;
   if (dtype == STRIPE_BF16) return lit.atomic;
   if (lit.atomic) return tile == 0 || tile == 3 || lit.chain < (tile == 1 ? 32 : 17);
-  return (tile == 2 || few) && lit.chain > 8 && lit.chain < 17;
+  return (tile == 2 || tile == 6 || few) && lit.chain > 8 && lit.chain < 17;
 }
 
 // Time of a block on tile t: a launch, per round of workgroups a fixed part and one for each K tile in a row -- all of them where
@@ -1148,26 +1172,35 @@ static bool wants_double(int dtype, int tile, bool few, const LiteralSums& lit) 
 // take from memory together.  us, fitted to 344 products, convolutions and transposed convolutions of 1 to 4096 rows, 7 to 12544
 // points of reduction, each on every tile: the tile chosen by it takes 1.02 times as long as the best one (geometric mean).
 // single_rows: rows of a tile that are fetched element by element, 0.05 us for the loads of 64 elements (2 x 49 x 49, 64 channels,
-// transposed 3 x 3 to 15, bf16: 12.7 on 64 x 64, 18.6 on 32 x 32).
-static double tile_us(int dtype, int t, bool plain, int single_rows, double tiles, double k_bytes) {
+// transposed 3 x 3 to 15, bf16: 12.8 on 64 x 64, 17.7 on 32 x 32 where each wavefront stages for itself, 11.0 where four share a K tile).
+// The last, tile 6 (no products: plain ones are never the fastest there): chosen to lose least on 330 convolutions and transposed
+// ones, half of them on tiles 1, 2, 4 and 6 (0.5 % over the fastest, 5 % with tiles 0 to 4 alone: 3x3, 64 -> 115 at 2 x 55 x 55, fp32 25.7 -> 19.6).
+// Its operands fetched along their rows cost it more than the others.
+static double tile_us(int dtype, int t, bool plain, int single_rows, int along_rows, double tiles, double k_bytes) {
   struct Cost {
     double fixed, k_tile, all;      // per round, per K tile and round, per K tile of 256 workgroups
     double at_once;                 // workgroups of a round
   };
-  static const Cost other[3][5] = {      // fp32, bf16, int8
-      {{5.3, 1.51, 0.92, 384}, {1.9, 1.20, 0.15, 384}, {2.2, 2.01, 0.76, 256}, {3.3, 1.01, 0.57, 384}, {1.6, 1.42, 1.59, 384}},
-      {{5.6, 0.93, 0.00, 256}, {2.8, 0.95, 0.03, 512}, {3.7, 1.48, 0.07, 256}, {4.1, 0.81, 0.03, 384}, {2.4, 1.20, 0.52, 256}},
-      {{4.2, 0.56, 0.57, 512}, {1.9, 0.38, 0.42, 768}, {3.2, 0.41, 0.56, 256}, {2.4, 0.43, 0.31, 384}, {3.2, 0.01, 1.34, 384}}};
+  static const Cost other[3][7] = {      // fp32, bf16, int8
+      {{5.3, 1.51, 0.92, 384}, {1.9, 1.20, 0.15, 384}, {2.2, 2.01, 0.76, 256}, {3.3, 1.01, 0.57, 384}, {1.6, 1.42, 1.59, 384}, {}, {1.7, 1.07, 0.00, 384}},
+      {{5.6, 0.93, 0.00, 256}, {2.8, 0.95, 0.03, 512}, {3.7, 1.48, 0.07, 256}, {4.1, 0.81, 0.03, 384}, {2.4, 1.20, 0.52, 256}, {}, {3.7, 0.59, 0.17, 512}},
+      {{4.2, 0.56, 0.57, 512}, {1.9, 0.38, 0.42, 768}, {3.2, 0.41, 0.56, 256}, {2.4, 0.43, 0.31, 384}, {3.2, 0.01, 1.34, 384}, {}, {2.6, 0.57, 0.13, 512}}};
   static const Cost plain_product[3][6] = {
       {{2.9, 1.32, 0.55, 256}, {1.4, 0.94, 0.25, 384}, {1.2, 1.37, 0.35, 256}, {2.2, 0.82, 0.49, 512}, {0.1, 2.04, 1.08, 256}, {1.9, 2.38, 0.88, 256}},
       {{5.1, 0.50, 0.19, 256}, {2.2, 0.55, 0.16, 512}, {1.7, 0.57, 0.64, 384}, {3.0, 0.49, 0.11, 256}, {0.7, 1.46, 1.18, 256}, {3.1, 0.78, 0.96, 256}},
       {{2.9, 0.71, 0.00, 256}, {1.6, 0.67, 0.06, 768}, {0.1, 1.45, 1.41, 768}, {1.7, 0.34, 0.17, 512}, {1.1, 0.80, 1.19, 256}, {2.0, 0.90, 1.04, 256}}};
   const int d = dtype == STRIPE_F32 ? 0 : dtype == STRIPE_BF16 ? 1 : 2;
-  const Cost& c = plain ? plain_product[d][t] : other[d][t];
+  Cost c = plain ? plain_product[d][t] : other[d][t];
+  double single_us = 0.05;
+  if (t == 6) {
+    static const double along_rows_us[3] = {1.55, 0.4, 0.3}, singles_us[3] = {0.045, 0.03, 0.025};
+    c.fixed += along_rows * along_rows_us[d];
+    single_us = singles_us[d];
+  }
   double k_tiles = std::ceil(k_bytes / (t == 4 && !plain ? 128 : kTiles[t].bkb));
-  if (t == 2 || t >= 4) k_tiles = std::ceil(k_tiles * 64 / kTiles[t].lanes);
+  if (t == 2 || t == 4 || t == 5) k_tiles = std::ceil(k_tiles * 64 / kTiles[t].lanes);
   const double singles = single_rows * k_bytes / (dtype == STRIPE_F32 ? 4 : dtype == STRIPE_BF16 ? 2 : 1) / 64;
-  return 4.0 + std::max(1.0, tiles / c.at_once) * (c.fixed + c.k_tile * k_tiles) + tiles / 256 * (c.all * k_tiles + 0.05 * singles);
+  return 4.0 + std::max(1.0, tiles / c.at_once) * (c.fixed + c.k_tile * k_tiles) + tiles / 256 * (c.all * k_tiles + single_us * singles);
 }
 
 // Blocks that stay on their literal kernel; here_us: what they take on this file's kernels.  Measured on 1,060 blocks of 65536 to
@@ -1196,7 +1229,9 @@ static bool literal_is_faster(int dtype, const ContractParams& p, const LiteralS
     if (literal < one_tile && ((literal < 12 && lit.outputs <= 4096) || lit.outputs <= 512)) return true;
     return literal < here_us;
   }
-  // A lane per output: 0.21 us a point (1 x 349 x 3328 int8 784 us).
+  // A lane per output: 0.21 us a point (1 x 349 x 3328 int8 784 us).  Reductions of a K tile or two take 1.5 us less here than their
+  // estimate says (transposed 2x2, 12 -> 11 at 4 x 36 x 36, bf16: 8.6 us there).
+  if (lit.outputs >= 100000) here_us -= 1.5;
   return (5.0 + 0.21 * (double)lit.chain * std::max(1.0, (double)lit.outputs / 5e5)) * (lit.atomic ? 2 : 1) < here_us;
 }
 
@@ -1555,20 +1590,21 @@ bool contract_select(const FlatBlock& fb, const LiteralSums& lit, bool fused, Co
   auto runs = [&](int t) {
     if (t == 3 && p.mode_b == 2 && esize < 4) return false;
     if (t == 5 && !l->plain) return false;
+    if (t == 6 && l->plain) return false;
     return !(precise_on(t) && (t == 0 || t == 3 || t == 5));
   };
   int tile = -1;
-  for (int t = 0; t < 6; ++t) {
+  for (int t = 0; t < 7; ++t) {
     if (!runs(t)) continue;
     const int singles = (p.mode_a == 0 ? kTiles[t].bm : 0) + (p.mode_b == 0 ? kTiles[t].bn : 0);
-    const double us = tile_us(dt, t, l->plain, singles, (double)tiles(t), (double)p.K * esize);
+    const double us = tile_us(dt, t, l->plain, singles, (p.mode_a == 2) + (p.mode_b == 2), (double)tiles(t), (double)p.K * esize);
     if (tile < 0 || us < l->us) {
       tile = t;
       l->us = us;
     }
   }
   const int forced = tune_int("contract_tile", -1);
-  if (forced >= 0 && forced <= 5) tile = forced;
+  if (forced >= 0 && forced <= 6) tile = forced;
   if (tile == 3 && p.mode_b == 2 && esize < 4) tile = 1;
   if (tile == 5 && (!l->plain || precise_on(5))) tile = 1;
   l->precise = precise_on(tile);

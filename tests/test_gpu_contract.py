@@ -647,6 +647,66 @@ def error_at_most(layout, M, N, K, dt, most):
     assert err <= most, (err, most)
 
 
+# ------------------------------------------------------------------ 32 x 32 tiles whose K tile four wavefronts share (tile 6)
+@pytest.mark.parametrize("dt", ["f32", "bf16", "i8"])
+@pytest.mark.parametrize("kind", ["nn", "nt", "tn", "conv3", "conv5", "upconv", "upconv2"])
+def test_tiles_whose_k_tile_wavefronts_share(kind, dt, monkeypatch):
+    """Every way to fetch, one and several K tiles with remainders, tables of a batch and of one K tile, constraints."""
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1,contract_tile=6,gemm_rows=0,gemm_dma=0,conv_igemm=0")
+    if kind in ("nn", "nt", "tn"):
+        for M, N, K in ((33, 68, 129), (1, 17, 300), (70, 40, 1037)):
+            blk = matmul(M, N, K, dt, kind)
+            info, _ = parity(blk, [W.seeded_tensor(r.sizes, dt, i) for i, r in enumerate(blk.refs[:2])], what=f"{kind} {M}x{N}x{K} {dt}")
+            assert info["kernel"].startswith(f"contract_{dt}_32x32x") and info["workgroup_size"] == 256, info
+        return
+    if kind.startswith("conv"):
+        N, H, Wd, Ci, Co, R, s, p = (1, 9, 11, 8, 70, 3, 1, 1) if kind == "conv3" else (2, 13, 12, 11, 37, 5, 2, 2)
+        blk = W.conv2d_block(N, H, Wd, Ci, Co, R, R, s, p, dt, "i32" if dt == "i8" else "f32")
+    else:
+        R, Ci, Co, H = (3, 36, 20, 9) if kind == "upconv" else (2, 19, 33, 7)
+        Ho = 2 * (H - 1) + R
+        bufs = [W.Buffer("I", "in", dt, (2, H, H, Ci)), W.Buffer("F", "in", dt, (R, R, Ci, Co)), W.Buffer("O", "out", "i32" if dt == "i8" else "f32", (2, Ho, Ho, Co))]
+        blk = W.flat_block(bufs, dict(n=2, y=H, x=H, i=R, j=R, c=Ci, k=Co),
+                           [(["n", "y", "x", "c"], "assign"), (["i", "j", "c", "k"], "assign"), (["n", "2*y + i", "2*x + j", "k"], "add")])
+    info, _ = parity(blk, [W.seeded_tensor(r.sizes, dt, i) for i, r in enumerate(blk.refs[:2])], what=f"{kind} {dt}")
+    assert info["kernel"].startswith(f"contract_{dt}_32x32x") and info["workgroup_size"] == 256, info
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("Ci,Co", [(13, 20), (8, 40)])
+def test_non_finite_values_where_wavefronts_share_a_k_tile(Ci, Co, dt, monkeypatch):
+    """A removed point contributes nothing there either: the literal kernel's infinities, NaN and finite values."""
+    blk = W.conv2d_block(1, 9, 9, Ci, Co, 5, 5, 1, 2, dt, "f32")
+    ins = [W.seeded_tensor(r.sizes, dt, i) for i, r in enumerate(blk.refs[:2])]
+    for i, t in enumerate(ins):
+        flat = t.view(-1)
+        for at, v in ((7, math.inf), (flat.numel() // 2, -math.inf), (flat.numel() - 2 - i, math.nan)):
+            flat[at] = v
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1,contract_tile=6")
+    got, sb = run_gpu(blk, ins, return_block=True)
+    assert sb.info["kernel"].startswith(f"contract_{dt}_32x32x") and sb.info["workgroup_size"] == 256, sb.info
+    want = run_gpu(blk, ins, "generic")
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want))
+    assert np.array_equal(np.isneginf(got), np.isneginf(want)) and np.isinf(want).any() and np.isnan(want).any()
+    fin = np.isfinite(want)
+    assert fin.any() and np.allclose(got[fin], want[fin], rtol=1e-5, atol=325 * 2.0 ** -24 * 325)     # 325 products of order 1 in fp32
+
+
+@pytest.mark.parametrize("seed", range(0, 64, 3))
+def test_random_blocks_where_wavefronts_share_a_k_tile(seed, monkeypatch):
+    monkeypatch.setenv("STRIPE_TUNE", "contract_min=1,contract_tile=6")
+    blk = random_block(seed)
+    nrng = np.random.default_rng(seed)
+    ins = [torch.from_numpy(nrng.integers(-3, 4, size=int(np.prod(r.sizes)), dtype=np.int8)) for r in blk.refs[:-1]]
+    try:
+        gpu, sb = run_gpu(blk, ins, return_block=True)
+    except B.StripeError as e:
+        assert e.status == 5, str(e)
+        pytest.skip(f"rejected at create: {e}")
+    res = O.evaluate(blk, [W.to_numpy(t) for t in ins], out=np.full(W.output_extent(blk), SENTINEL_I, np.int64))
+    assert np.array_equal(gpu.astype(np.int64), res.out), sb.info["kernel"]
+
+
 @pytest.mark.parametrize("layout,M,N,K,most", [("nn", 49, 2304, 64, 4.0e-8), ("tn", 164, 856, 64, 4.05e-8), ("nn", 381, 960, 64, 4.05e-8), ("tn", 14, 384, 384, 6.7e-8)])
 def test_bf16_sums_of_a_k_tile_are_short(layout, M, N, K, most):
     """64 products in one chain are 4.2e-8 off in the 2-norm, 128 at a time 7.0e-8 at K = 384; as sums of 32 that meet in pairs
