@@ -1199,8 +1199,11 @@ static double tile_us(int dtype, int t, bool plain, int single_rows, int along_r
   }
   double k_tiles = std::ceil(k_bytes / (t == 4 && !plain ? 128 : kTiles[t].bkb));
   if (t == 2 || t == 4 || t == 5) k_tiles = std::ceil(k_tiles * 64 / kTiles[t].lanes);
+  // int8 products of one K tile on many 64 x 64 tiles, an operand along its rows: start and end of every workgroup (4096 x 4096 x 64 nn 25.7 us
+  // there, 16.8 on 128 x 128; 1500 x 2500 x 100 10.9 and 9.2; below 512 tiles and with two K tiles 64 x 64 is the faster one).
+  const double one_k_tile = plain && d == 2 && t == 1 && along_rows && k_tiles == 1 && tiles > 512 ? 0.75 * (tiles - 512) / 256 : 0.0;
   const double singles = single_rows * k_bytes / (dtype == STRIPE_F32 ? 4 : dtype == STRIPE_BF16 ? 2 : 1) / 64;
-  return 4.0 + std::max(1.0, tiles / c.at_once) * (c.fixed + c.k_tile * k_tiles) + tiles / 256 * (c.all * k_tiles + single_us * singles);
+  return 4.0 + std::max(1.0, tiles / c.at_once) * (c.fixed + c.k_tile * k_tiles) + tiles / 256 * (c.all * k_tiles + single_us * singles) + one_k_tile;
 }
 
 // Blocks that stay on their literal kernel; here_us: what they take on this file's kernels.  Measured on 1,060 blocks of 65536 to

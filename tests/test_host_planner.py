@@ -416,3 +416,11 @@ def test_convolutions_on_the_tile_whose_k_tile_wavefronts_share(N, H, Ci, Co, dt
     b = B.StripeBlock(blk)
     assert b.info["kernel"].startswith(f"contract_{dt}_32x32x") and b.info["workgroup_size"] == 256, b.info
     b.close()
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(1857, 3136, 64, "128x128"), (4096, 4096, 64, "128x128"), (2500, 1300, 64, "128x128"), (1024, 3000, 40, "64x64"), (3000, 3000, 200, "64x64")])
+def test_int8_products_of_one_k_tile(M, N, K, tile):
+    """Many outputs and a short reduction on large tiles (10.6 and 12.4 us, 16.8 and 25.7, 8.8 and 10.6 on 64 x 64), not with few tiles or a longer one."""
+    b = B.StripeBlock(W.matmul_block(M, N, K, "i8", "i32"))
+    assert b.info["kernel"].startswith(f"contract_i8_{tile}x"), b.info["kernel"]
+    b.close()
